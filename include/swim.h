@@ -124,16 +124,14 @@ int swim_version(void);
  *                    addition theorem), taken by FP64 Gauss-Legendre
  *                    quadrature, with H1 = M/r^2 - g, H2 = (g - 2M/r^2)/r^2,
  *                    M = int_0^r s g ds, and g(0) in closed form from the
- *                    sine and cosine integrals.  FP32 runs read it from the
- *                    per-system tables, built once per launch by one sweep
- *                    over the table's 2113 nodes in increasing r (prefix
- *                    and suffix sums of the two integrals over the gaps
- *                    between nodes, a far-field expansion beyond
- *                    alpha r = 40); FP64
- *                    evaluates the quadrature per pair, a few hundred
- *                    times the cost of the closed forms (a reference mode
- *                    for small systems).  It applies to every velocity and
- *                    pressure evaluation, including the pressure's blob
+ *                    sine and cosine integrals.  Runs read it from per-system
+ *                    tables, built once per launch by one sweep over the
+ *                    table's 704 intervals in increasing r (prefix and suffix
+ *                    sums of the two integrals, a far-field expansion beyond
+ *                    alpha r = 40): cubic pieces in FP32, degree-8 pieces
+ *                    (about 1e-15) in FP64; pairs beyond the table
+ *                    (r > 2^21 eps) are evaluated directly, in FP64 by the
+ *                    quadrature.  It applies to every velocity and pressure evaluation, including the pressure's blob
  *                    mass (1 - eps^3/R^3).
  * Read-only counters (swim_get_option): SWIM_OPT_GRAPH_LAUNCHES (graph
  * replays and first launches so far), SWIM_OPT_GRAPH_CAPTURES.
@@ -216,7 +214,7 @@ int swim_pair_velocity(swim_ctx *ctx, int32_t dtype, int64_t n_sys, const int64_
  * Limits: n_sys <= 64 systems and at most 4160 pair-kernel blocks (256
  * targets each: about 1M points in all); beyond either, SWIM_EINVAL with a
  * message and nothing launched.  Each GPU holds one copy of the array
- * (about 1.7 MB, kept until the process ends; its address is taken by
+ * (about 6.6 MB, kept until the process ends; its address is taken by
  * swim_create for the context's device, else SWIM_ESTATE).  Every call on
  * a GPU uses that GPU's one array: calls that overlap on one GPU (several
  * streams or contexts, host threads) race and must be serialized by the
@@ -237,13 +235,11 @@ int swim_pair_velocity_noalloc(swim_ctx *ctx, int32_t dtype, int64_t n_sys, cons
  * (with SWIM_BLOB_PAPER: m = 1 - eps^3/R^3 for every alpha).
  * x, y, fx, fy device dtype[n]; tx, ty device dtype[nt]; u, v, p device
  * dtype[nt] (written).  alpha >= 0, eps > 0, alpha*eps <= 1.  Sums are
- * accumulated in FP64.  FP32 reads the pair kernel from the system's table
- * (as the forward runs do; built on the device at each call, for the
- * paper's blob at alpha > 0 from its quadrature), with the direct FP32
- * evaluation beyond it; FP64 evaluates it directly (the paper's blob at
- * alpha > 0: quadrature per pair).  The pressure weight m/(2 pi r^2):
+ *accumulated in FP64.  The pair kernel is read from the system's table (as
+ * in the forward runs; built on the device at each call), with the direct
+ * evaluation beyond it.  The pressure weight m/(2 pi r^2):
  * FP32 from a second per-call table on the same intervals, FP64 directly.
- * Sums are FP64 either way.  Asynchronous. */
+ * Asynchronous. */
 int swim_flow_field(swim_ctx *ctx, int32_t dtype, int64_t n, const void *x, const void *y, const void *fx,
                     const void *fy, double alpha, double eps, int64_t nt, const void *tx, const void *ty,
                     void *u, void *v, void *p, void *stream);

@@ -86,7 +86,7 @@ constexpr int64_t MLP_NPARAM = 207393;
 // Workspace of swim_pair_velocity_noalloc: a fixed device array in place of
 // the context's allocations.  Sections (256-byte aligned): system offsets,
 // alpha, eps, the block list (system, first target) of the pair kernel, the
-// per-system constants (in the working type and in FP64) and the FP32 kernel
+// per-system constants (in the working type and in FP64) and the kernel
 // tables.  Every section is written by the call before its kernels read it,
 // so nothing needs clearing between calls.
 constexpr int64_t NOALLOC_MAX_SYS = 64;      // systems per call
@@ -100,7 +100,8 @@ constexpr size_t NA_BLKF = na_align(NA_BLKS + NOALLOC_MAX_BLOCKS * 8);
 constexpr size_t NA_SYSC = na_align(NA_BLKF + NOALLOC_MAX_BLOCKS * 8);  // end of the staged host data
 constexpr size_t NA_SYSC64 = na_align(NA_SYSC + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
 constexpr size_t NA_TAB = na_align(NA_SYSC64 + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
-constexpr size_t NA_BYTES = na_align(NA_TAB + NOALLOC_MAX_SYS * sizeof(TabSys));  // ~1.7 MB
+constexpr size_t NA_BYTES = na_align(NA_TAB + NOALLOC_MAX_SYS * sizeof(TabSys64));  // ~6.6 MB (FP32 tables share it)
+static_assert(sizeof(TabSys) <= sizeof(TabSys64), "FP32 tables share the FP64 slots");
 
 static_assert(sizeof(SysConst<float>) <= sizeof(SysConst<double>), "FP32 constants share the FP64 slots");
 static __device__ __align__(256) unsigned char scratch[NA_BYTES];
@@ -392,6 +393,26 @@ int sysconst_buffers(swim_ctx* c, int32_t dtype, int64_t n_sys, void** sysc, voi
     return SWIM_OK;
 }
 
+// the systems' kernel tables from their FP64 constants (an FP64 run's own)
+hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, void* sysc64, void* tab, hipStream_t st)
+{
+    return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, c->opt_blob, st);
+}
+
+// FP64 calls keep one kernel table of 99 KB per system in HBM: larger
+// batches run in chunks of this many systems (1.6 GB), fewer when the
+// allocation fails, so that tables never decide whether a call fits
+constexpr int64_t TAB64_CHUNK = 16384;
+int64_t tab64_chunk(swim_ctx* c, int64_t n_sys)
+{
+    int64_t m = std::min(n_sys, TAB64_CHUNK);
+    while (m > 1 && ensure(c, B_TAB, (size_t)m * table_bytes(SWIM_F64)) == SWIM_ENOMEM) {
+        (void)hipGetLastError();
+        m = (m + 1) / 2;
+    }
+    return m;
+}
+
 // ------------------------------------------------------------------------
 // forward run (shared by swim_forward and abc_step)
 // ------------------------------------------------------------------------
@@ -515,7 +536,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     TRY(ensure(c, B_QUEUE, 8 * 4));
-    if (dtype == SWIM_F32) TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes()));
+    TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     Batch b;
     b.n_sys = n_sys;
     b.pt_off = (const int64_t*)c->buf[B_OFF].p;
@@ -525,7 +546,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     b.params = params_dev;
     b.sysc = sysc;
     b.sysc64 = sysc64;
-    b.tab = dtype == SWIM_F32 ? c->buf[B_TAB].p : nullptr;
+    b.tab = c->buf[B_TAB].p;
     // launch shapes of the persistent buckets (and their LDS limits, set
     // here: nothing inside a stream capture may change them)
     struct Bucket {
@@ -541,8 +562,10 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         // untuned default: 16 waves, except FP32 systems of 65..128 points,
         // which take 8 (16 offsets of the pair schedule per wave instead of 8
         // halves the per-wave share of each step's fixed work; two systems
-        // per CU either way)
-        const int wps_default = (dtype == SWIM_F32 && q.tpl == 2) ? 8 : 16;
+        // per CU either way), and FP64 runs, which take 8 (222 VGPRs; 16
+        // waves have 128 and spill 239 of them: 7.3 against 3.8 us per step
+        // at N = 64)
+        const int wps_default = (dtype == SWIM_F64 || q.tpl == 2) ? 8 : 16;
         q.wps = c->opt_wps ? c->opt_wps : (c->tuned_wps[dtype][q.tpl] ? c->tuned_wps[dtype][q.tpl] : wps_default);
         // at most FWD_MAX_WINDOWS point windows per lane: fewer waves are not
         // built (their one-wave instantiations exceed 256 VGPRs and spill to
@@ -622,7 +645,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         hipError_t e = launch_sysconst_batch(dtype, n_sys, (const int64_t*)c->buf[B_SWOFF].p,
                                              (const int32_t*)c->buf[B_NPT].p, params_dev, run.eps_over_ds, sysc,
                                              sysc64, status, c->opt_blob, st);
-        if (e == hipSuccess && dtype == SWIM_F32) e = launch_table_build(0, n_sys, sysc64, c->buf[B_TAB].p, c->opt_blob, st);
+        if (e == hipSuccess) e = build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st);
         if (e == hipSuccess) e = launch_fill_i32((int32_t*)c->buf[B_QUEUE].p, 0, 8, st);
         if (e == hipSuccess && c->opt_time) e = hipEventRecord(c->time_ev[0], st);
         // Buckets (and the large systems) are independent: with more than
@@ -766,21 +789,23 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
 }
 
 
-// FP32 runs keep one kernel table per system in HBM (12 KB each), so very
-// large batches run in chunks of FWD_CHUNK systems; the systems are
-// independent and their order within a batch does not change any result.
+// Runs keep one kernel table per system in HBM (FP32 24.8 KB, FP64 99 KB),
+// so very large batches run in chunks of FWD_CHUNK (FP64: tab64_chunk)
+// systems; the systems are independent and their order within a batch does
+// not change any result.
 constexpr int64_t FWD_CHUNK = 262144;
 
 int forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim,
                  const double* params_dev, const Run& run, void* obs, void* speed, int32_t* status,
                  int32_t* steps_done, hipStream_t st)
 {
-    if (dtype != SWIM_F32 || n_sys <= FWD_CHUNK)
+    const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
+    if (n_sys <= chunk)
         return forward_chunk(c, dtype, n_sys, N, nswim, params_dev, run, obs, speed, status, steps_done, st);
-    const size_t es = 4;
+    const size_t es = dtype == SWIM_F32 ? 4 : 8;
     int64_t f0 = 0;  // first filament of the chunk
-    for (int64_t s0 = 0; s0 < n_sys; s0 += FWD_CHUNK) {
-        const int64_t m = std::min(FWD_CHUNK, n_sys - s0);
+    for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
+        const int64_t m = std::min(chunk, n_sys - s0);
         int64_t nf = 0;
         for (int64_t s = s0; s < s0 + m; ++s) nf += nswim ? nswim[s] : 1;
         TRY(forward_chunk(c, dtype, m, N + s0, nswim ? nswim + s0 : nullptr, params_dev + f0 * SWIM_NPARAM, run,
@@ -1019,25 +1044,11 @@ int swim_get_option(swim_ctx* c, int32_t key, int32_t* value)
     return SWIM_OK;
 }
 
-int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t* sys_off, const double* alpha,
-                       const double* eps, const void* x, const void* y, const void* fx, const void* fy, void* ux,
-                       void* uy, void* stream)
+// one evaluation of the velocity sum (arguments checked by the caller)
+static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t* sys_off, const double* alpha,
+                               const double* eps, const void* x, const void* y, const void* fx, const void* fy,
+                               void* ux, void* uy, hipStream_t st)
 {
-    TRY(check_ctx(c));
-    TRY(check_dtype(dtype));
-    if (n_sys < 0) return fail(SWIM_EINVAL, "n_sys < 0");
-    if (n_sys == 0) return SWIM_OK;
-    if (!sys_off || !alpha || !eps) return fail(SWIM_EINVAL, "sys_off/alpha/eps must be host arrays");
-    if (sys_off[0] != 0) return fail(SWIM_EINVAL, "sys_off[0] must be 0");
-    for (int64_t s = 0; s < n_sys; ++s) {
-        if (sys_off[s + 1] < sys_off[s]) return fail(SWIM_EINVAL, "sys_off must be non-decreasing (system %lld)", (long long)s);
-        if (!(std::isfinite(alpha[s]) && alpha[s] >= 0)) return fail(SWIM_EINVAL, "alpha[%lld] must be finite and >= 0", (long long)s);
-        if (!(std::isfinite(eps[s]) && eps[s] > 0)) return fail(SWIM_EINVAL, "eps[%lld] must be finite and > 0", (long long)s);
-        if (alpha[s] * eps[s] > 1.0) return fail(SWIM_EINVAL, "alpha*eps > 1 for system %lld", (long long)s);
-    }
-    const int64_t npts = sys_off[n_sys];
-    if (npts > 0 && (!x || !y || !fx || !fy || !ux || !uy)) return fail(SWIM_EINVAL, "null data pointer");
-    hipStream_t st = pick(c, stream);
     int64_t maxn = 0;
     for (int64_t s = 0; s < n_sys; ++s) maxn = std::max(maxn, sys_off[s + 1] - sys_off[s]);
     const int tpl = maxn >= 2048 ? 2 : 1;
@@ -1058,15 +1069,44 @@ int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t*
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     HIPCHK(launch_sysconst(dtype, n_sys, (const double*)c->buf[B_ALPHA].p, (const double*)c->buf[B_EPS].p, sysc,
                            sysc64, c->opt_blob, st));
-    void* tab = nullptr;
-    if (dtype == SWIM_F32) {
-        TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes()));
-        HIPCHK(launch_table_build(0, n_sys, sysc64, c->buf[B_TAB].p, c->opt_blob, st));
-        tab = c->buf[B_TAB].p;
-    }
+    TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
+    void* tab = c->buf[B_TAB].p;
+    HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
     HIPCHK(launch_pair_velocity(dtype, tpl, (int64_t)bs.size(), (const int64_t*)c->buf[B_BLKS].p,
                                 (const int64_t*)c->buf[B_BLKF].p, (const int64_t*)c->buf[B_OFF].p, sysc, tab, x, y,
                                 fx, fy, ux, uy, st));
+    return SWIM_OK;
+}
+
+int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t* sys_off, const double* alpha,
+                       const double* eps, const void* x, const void* y, const void* fx, const void* fy, void* ux,
+                       void* uy, void* stream)
+{
+    TRY(check_ctx(c));
+    TRY(check_dtype(dtype));
+    if (n_sys < 0) return fail(SWIM_EINVAL, "n_sys < 0");
+    if (n_sys == 0) return SWIM_OK;
+    if (!sys_off || !alpha || !eps) return fail(SWIM_EINVAL, "sys_off/alpha/eps must be host arrays");
+    if (sys_off[0] != 0) return fail(SWIM_EINVAL, "sys_off[0] must be 0");
+    for (int64_t s = 0; s < n_sys; ++s) {
+        if (sys_off[s + 1] < sys_off[s]) return fail(SWIM_EINVAL, "sys_off must be non-decreasing (system %lld)", (long long)s);
+        if (!(std::isfinite(alpha[s]) && alpha[s] >= 0)) return fail(SWIM_EINVAL, "alpha[%lld] must be finite and >= 0", (long long)s);
+        if (!(std::isfinite(eps[s]) && eps[s] > 0)) return fail(SWIM_EINVAL, "eps[%lld] must be finite and > 0", (long long)s);
+        if (alpha[s] * eps[s] > 1.0) return fail(SWIM_EINVAL, "alpha*eps > 1 for system %lld", (long long)s);
+    }
+    const int64_t npts = sys_off[n_sys];
+    if (npts > 0 && (!x || !y || !fx || !fy || !ux || !uy)) return fail(SWIM_EINVAL, "null data pointer");
+    hipStream_t st = pick(c, stream);
+    const int64_t chunk = dtype == SWIM_F32 ? n_sys : tab64_chunk(c, n_sys);
+    if (n_sys <= chunk) return pair_velocity_chunk(c, dtype, n_sys, sys_off, alpha, eps, x, y, fx, fy, ux, uy, st);
+    std::vector<int64_t> off(chunk + 1);
+    for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
+        const int64_t m = std::min(chunk, n_sys - s0);
+        for (int64_t s = 0; s <= m; ++s) off[s] = sys_off[s0 + s] - sys_off[s0];
+        const size_t o = (size_t)sys_off[s0] * 8;
+        TRY(pair_velocity_chunk(c, dtype, m, off.data(), alpha + s0, eps + s0, (const char*)x + o, (const char*)y + o,
+                                (const char*)fx + o, (const char*)fy + o, (char*)ux + o, (char*)uy + o, st));
+    }
     return SWIM_OK;
 }
 
@@ -1123,11 +1163,8 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     void* sysc64 = dtype == SWIM_F32 ? (void*)(ws + NA_SYSC64) : nullptr;
     HIPCHK(launch_sysconst(dtype, n_sys, (const double*)(ws + NA_ALPHA), (const double*)(ws + NA_EPS), sysc, sysc64,
                            c->opt_blob, st));
-    void* tab = nullptr;
-    if (dtype == SWIM_F32) {
-        tab = ws + NA_TAB;
-        HIPCHK(launch_table_build(0, n_sys, sysc64, tab, c->opt_blob, st));
-    }
+    void* tab = ws + NA_TAB;
+    HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
     HIPCHK(launch_pair_velocity(dtype, tpl, nb, (const int64_t*)(ws + NA_BLKS), (const int64_t*)(ws + NA_BLKF),
                                 (const int64_t*)(ws + NA_OFF), sysc, tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
@@ -1176,23 +1213,21 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
             fc.ser[k] = fc.inv_e2 * (2.0 * (k + 1) * gam[k + 1] - 0.5 * z0 * z0 * gam[k] / (k + 1));
     }
     hipStream_t st = pick(c, stream);
-    const void* tab = nullptr;
+    // the pair kernel from the system's table, as in the forward runs (built
+    // on the device from the FP64 kernel functions)
+    TRY(begin_uploads(c, 16));
+    TRY(stage(c, &alpha, 8, B_ALPHA, st));
+    TRY(stage(c, &eps, 8, B_EPS, st));
+    TRY(end_uploads(c, st));
+    void *sysc, *sysc64;
+    TRY(sysconst_buffers(c, dtype, 1, &sysc, &sysc64));
+    HIPCHK(launch_sysconst(dtype, 1, (const double*)c->buf[B_ALPHA].p, (const double*)c->buf[B_EPS].p, sysc, sysc64,
+                           c->opt_blob, st));
+    TRY(ensure(c, B_TAB, table_bytes(dtype)));
+    const void* tab = c->buf[B_TAB].p;
+    HIPCHK(build_tables(c, dtype, 1, sysc, sysc64, c->buf[B_TAB].p, st));
     void* wtab = nullptr;
     if (dtype == SWIM_F32) {
-        // FP32: the pair kernel from the system's table, as in the forward
-        // runs (built on the device from the FP64 kernel functions; for the
-        // paper's blob at alpha > 0 from its quadrature)
-        TRY(begin_uploads(c, 16));
-        TRY(stage(c, &alpha, 8, B_ALPHA, st));
-        TRY(stage(c, &eps, 8, B_EPS, st));
-        TRY(end_uploads(c, st));
-        void *sysc, *sysc64;
-        TRY(sysconst_buffers(c, SWIM_F32, 1, &sysc, &sysc64));
-        HIPCHK(launch_sysconst(SWIM_F32, 1, (const double*)c->buf[B_ALPHA].p, (const double*)c->buf[B_EPS].p, sysc,
-                               sysc64, c->opt_blob, st));
-        TRY(ensure(c, B_TAB, table_bytes()));
-        HIPCHK(launch_table_build(0, 1, sysc64, c->buf[B_TAB].p, c->opt_blob, st));
-        tab = c->buf[B_TAB].p;
         // and the pressure weight's table on the same intervals
         TRY(ensure(c, B_WTAB, (size_t)TAB_N * 16));
         wtab = c->buf[B_WTAB].p;
@@ -1321,6 +1356,19 @@ int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_spe
                        int32_t obs_every, void* head, void* tail, int32_t* status, hipStream_t st)
 {
     if (n_sys == 0) return SWIM_OK;
+    if (dtype == SWIM_F64) {
+        const int64_t chunk = tab64_chunk(c, n_sys);
+        const int64_t nobs1 = (obs_every > 0 ? steps / obs_every : 0) + 1;
+        if (chunk < n_sys) {
+            for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
+                const size_t o = (size_t)s0 * sh.n_swim * nobs1 * 2 * 8;
+                TRY(sperm_forward_impl(c, dtype, std::min(chunk, n_sys - s0), sh, sys_params + SWIM_SP_NPARAM * s0,
+                                       swim_params + (size_t)3 * sh.n_swim * s0, steps, dt, obs_every,
+                                       (char*)head + o, (char*)tail + o, status + s0, st));
+            }
+            return SWIM_OK;
+        }
+    }
     const SpermShape g = sperm_geometry(sh);
     SpermRun r{};
     r.n_sys = n_sys;
@@ -1342,16 +1390,16 @@ int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_spe
     if (c->opt_wps == 2 || c->opt_wps == 4 || c->opt_wps == 8) wps = c->opt_wps;
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
-    if (dtype == SWIM_F32) TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes()));
+    TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     TRY(ensure(c, B_QUEUE, 8 * 4));
     HIPCHK(prepare_sperm(dtype, tpl, wps));
     const int per_cu = sperm_blocks_per_cu(dtype, tpl, wps);
     const int nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(n_sys, (int64_t)per_cu * c->num_cu));
     HIPCHK(launch_sperm_setup(dtype, n_sys, sh.n_swim, sh.eps, sys_params, swim_params, sysc, sysc64, status,
                               c->opt_blob, st));
-    if (dtype == SWIM_F32) HIPCHK(launch_table_build(0, n_sys, sysc64, c->buf[B_TAB].p, c->opt_blob, st));
+    HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st));
     HIPCHK(launch_fill_i32((int32_t*)c->buf[B_QUEUE].p, 0, 8, st));
-    HIPCHK(launch_sperm_forward(dtype, tpl, wps, nblocks, g, r, sysc, dtype == SWIM_F32 ? c->buf[B_TAB].p : nullptr,
+    HIPCHK(launch_sperm_forward(dtype, tpl, wps, nblocks, g, r, sysc, c->buf[B_TAB].p,
                                 (int32_t*)c->buf[B_QUEUE].p, head, tail, status, st));
     return SWIM_OK;
 }
@@ -1645,11 +1693,11 @@ int swim_kernel_eval_host(int32_t dtype, double alpha, double eps, int32_t blob,
         std::vector<TabE> tab(TAB_N + 1);
         if (C64.paper == 2.0) {
             // the paper's blob at alpha > 0: the nodes from the sweep
-            std::vector<double> fh(PB_NODES), fg(PB_NODES);
-            pb_table_nodes_host(C64, fh.data(), fg.data());
+            std::vector<double> fh(7 * TAB_N), fg(7 * TAB_N);
+            pb_table_host<7>(C64, fh.data(), fg.data());
             for (int i = 0; i < TAB_N; ++i) {
-                const double h4[4] = {fh[3 * i], fh[3 * i + 1], fh[3 * i + 2], fh[3 * i + 3]};
-                const double g4[4] = {fg[3 * i], fg[3 * i + 1], fg[3 * i + 2], fg[3 * i + 3]};
+                const double *h = &fh[7 * i], *g = &fg[7 * i];
+                const double h4[4] = {h[0], h[2], h[4], h[6]}, g4[4] = {g[0], g[2], g[4], g[6]};
                 tab_assemble(C64, h4, g4, tab[i], nullptr);
             }
             tab_interval(C64, TAB_N, tab[TAB_N], nullptr);

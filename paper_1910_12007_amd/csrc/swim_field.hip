@@ -12,8 +12,8 @@
 // series in delta whose coefficients the host computes per call.
 //
 // One thread per target; the sources pass through LDS in tiles; every sum is
-// accumulated in FP64.  The pair kernel: FP32 from the system's table (as in
-// the forward runs), FP64 by direct evaluation.
+// accumulated in FP64.  The pair kernel comes from the system's table, as in
+// the forward runs.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -66,12 +66,12 @@ __global__ __launch_bounds__(256) void k_weight_table(FieldConst fc, float4* wt)
     wt[i] = make_float4(c[0], c[1], c[2], c[3]);
 }
 
-// tab (FP32 only): the system's kernel table, used for every pair inside it;
-// beyond it the direct evaluation (FP64: the direct evaluation throughout)
+// tab: the system's kernel table (TabSys, TabSys64), used for every pair
+// inside it; beyond it the direct evaluation
 template <typename T>
 __global__ __launch_bounds__(256) void k_flow_field(int64_t n, const T* x, const T* y, const T* fx, const T* fy,
                                                     FieldConst fc, int64_t nt, const T* tx, const T* ty, T* u, T* v,
-                                                    T* p, const TabSys* tab, const float4* wtab)
+                                                    T* p, const void* tab_g, const float4* wtab)
 {
     __shared__ Src4<T> tile[FIELD_TILE];
     const SysConst<T> C = *reinterpret_cast<const SysConst<T>*>(sizeof(T) == 4 ? (const void*)&fc.c32
@@ -102,17 +102,25 @@ __global__ __launch_bounds__(256) void k_flow_field(int64_t n, const T* x, const
             const T t2 = fma_t(dx, dx, dy * dy);
             bool direct = true;
             if constexpr (sizeof(T) == 4) {
-                if (tab) {
-                    const uint32_t bits = tab_bits(t2, C.ts);
-                    const uint32_t id = bits >> TAB_SHIFT;
-                    if (id < TAB_END) {
-                        tab_eval(tab->e[id - TAB_BIAS], tab_u(bits), Ht, H2);
-                        H2 *= C.ts;  // the table holds H2 / sigma
-                        direct = false;
-                    }
+                const uint32_t bits = tab_bits(t2, C.ts);
+                const uint32_t id = bits >> TAB_SHIFT;
+                if (id < TAB_END) {
+                    tab_eval(((const TabSys*)tab_g)->e[id - TAB_BIAS], tab_u(bits), Ht, H2);
+                    H2 *= C.ts;  // the table holds H2 / sigma
+                    direct = false;
+                }
+            } else {
+                direct = tab64_lookup(tab_g, t2, C.ts, Ht, H2);
+            }
+            if (direct) {
+                if constexpr (sizeof(T) == 8) {
+                    const V2<T> v = kernel_far64(C, t2);
+                    Ht = v.x;
+                    H2 = v.y;
+                } else {
+                    kernel_eval<T>(C, t2, Ht, H2);
                 }
             }
-            if (direct) kernel_eval<T>(C, t2, Ht, H2);
             const T fd = fma_t(s.fx, dx, s.fy * dy);
             su += (double)fma_t(Ht, s.fx, H2 * fd * dx);
             sv += (double)fma_t(Ht, s.fy, H2 * fd * dy);
@@ -156,12 +164,11 @@ hipError_t launch_flow_field(int dtype, int64_t n, const void* x, const void* y,
     if (dtype == 0)
         hipLaunchKernelGGL(k_flow_field<float>, dim3(nb), dim3(256), 0, st, n, (const float*)x, (const float*)y,
                            (const float*)fx, (const float*)fy, fc, nt, (const float*)tx, (const float*)ty, (float*)u,
-                           (float*)v, (float*)p, (const TabSys*)tab, (const float4*)wtab);
+                           (float*)v, (float*)p, tab, (const float4*)wtab);
     else
         hipLaunchKernelGGL(k_flow_field<double>, dim3(nb), dim3(256), 0, st, n, (const double*)x, (const double*)y,
                            (const double*)fx, (const double*)fy, fc, nt, (const double*)tx, (const double*)ty,
-                           (double*)u, (double*)v, (double*)p, (const TabSys*)nullptr,
-                           (const float4*)nullptr);
+                           (double*)u, (double*)v, (double*)p, tab, (const float4*)nullptr);
     return hipGetLastError();
 }
 

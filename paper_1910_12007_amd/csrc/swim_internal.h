@@ -23,7 +23,7 @@ struct Batch {
     const double* params;    // [n_filaments][9]
     const void* sysc;        // SysConst<T>[n_sys]
     const void* sysc64;      // SysConst<double>[n_sys] (FP32 runs: builds the kernel tables)
-    const void* tab;         // FP32 runs: TabE[n_sys][TAB_N] kernel tables
+    const void* tab;         // kernel tables: TabSys[n_sys] (FP32), TabSys64[n_sys] (FP64)
 };
 
 struct Run {
@@ -54,10 +54,10 @@ hipError_t launch_pair_velocity(int dtype, int tpl, int64_t n_blocks, const int6
                                 const int64_t* blk_first, const int64_t* pt_off, const void* sysc,
                                 const void* tab, const void* x, const void* y, const void* fx,
                                 const void* fy, void* ux, void* uy, hipStream_t st);
-// bytes of one system's FP32 kernel table
-size_t table_bytes();
-// FP32 kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s]
-hipError_t launch_table_build(int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st);
+// bytes of one system's kernel table (TabSys, TabSys64)
+size_t table_bytes(int dtype);
+// kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s]
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st);
 hipError_t launch_forces(int dtype, int64_t n_fil, const int64_t* fil_off, const int32_t* npt,
                          const double* params, double t, const void* x, const void* y, void* fx,
                          void* fy, hipStream_t st);

@@ -140,7 +140,8 @@ __device__ __forceinline__ void point_force(const Seg& seg, int p, const FilP<T>
 
 // Accumulate the velocity sum of eq. (BrV) over sources src[0..n) for the
 // TPL targets (xi, yi) of this lane, with H1 taken relative to H1(0), in
-// FP64 by direct evaluation (FP32 lanes use pair_accumulate_x).  The
+// FP64 (FP32 lanes use pair_accumulate_x): kernel values from the system's
+// FP64 table, pairs beyond it by direct evaluation in a second pass.  The
 // constant part H1(0) sum_j F_j is the caller's: the velocity kernel for
 // given forces adds it once per target; in a forward run the forces are the
 // elastic forces of a translation-invariant energy (Appendix EFT, EFB), whose
@@ -148,22 +149,39 @@ __device__ __forceinline__ void point_force(const Seg& seg, int p, const FilP<T>
 // and is not evaluated (its floating-point value is only rounding noise of
 // the cancelling forces).
 template <typename T, int TPL>
-__device__ __forceinline__ void pair_accumulate(const SysConst<T>& C, const Src4<T>* src, int n,
+__device__ __forceinline__ void pair_accumulate(const SysConst<T>& C, const TabSys64* tab, const Src4<T>* src, int n,
                                                 const T (&xi)[TPL], const T (&yi)[TPL],
                                                 T (&ax)[TPL], T (&ay)[TPL])
 {
     static_assert(sizeof(T) == 8, "FP64 only");
+    auto add = [&](const Src4<T>& s, int k, T dx, T dy, T Ht, T H2) {
+        const T h2fd = H2 * fma_t(s.fx, dx, s.fy * dy);
+        ax[k] = fma_t(Ht, s.fx, fma_t(h2fd, dx, ax[k]));
+        ay[k] = fma_t(Ht, s.fy, fma_t(h2fd, dy, ay[k]));
+    };
+    bool far = false;
     for (int j = 0; j < n; ++j) {
         const Src4<T> s = src[j];
 #pragma unroll
         for (int k = 0; k < TPL; ++k) {
             const T dx = xi[k] - s.x, dy = yi[k] - s.y;
-            const T t = fma_t(dx, dx, dy * dy);
             T Ht, H2;
-            kernel_eval<T>(C, t, Ht, H2);
-            const T h2fd = H2 * fma_t(s.fx, dx, s.fy * dy);
-            ax[k] = fma_t(Ht, s.fx, fma_t(h2fd, dx, ax[k]));
-            ay[k] = fma_t(Ht, s.fy, fma_t(h2fd, dy, ay[k]));
+            far = tab64_lookup(tab, fma_t(dx, dx, dy * dy), C.ts, Ht, H2) || far;
+            add(s, k, dx, dy, Ht, H2);
+        }
+    }
+    if (__any(far)) {
+        for (int j = 0; j < n; ++j) {
+            const Src4<T> s = src[j];
+#pragma unroll
+            for (int k = 0; k < TPL; ++k) {
+                const T dx = xi[k] - s.x, dy = yi[k] - s.y;
+                const T t = fma_t(dx, dx, dy * dy);
+                if (tab64_index(fma_t(t, C.ts, (T)1)) >= (uint32_t)TAB_N) {
+                    const V2<T> v = kernel_far64(C, t);
+                    add(s, k, dx, dy, v.x, v.y);
+                }
+            }
         }
     }
 }
@@ -227,31 +245,30 @@ __device__ __forceinline__ void pair_accumulate_x(const SysConst<float>& C, cons
 // set-up
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_sysconst(int64_t n, const double* alpha, const double* eps, SysConst<T>* out,
-                           SysConst<double>* out64, int blob)
+__global__ __launch_bounds__(64) void k_sysconst(const double* alpha, const double* eps, SysConst<T>* out,
+                                                 SysConst<double>* out64, int blob)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    sysconst_compute2<T>(alpha[i], eps[i], out + i, out64 ? out64 + i : nullptr, blob);
+    const int64_t i = blockIdx.x;  // one wave per system
+    sysconst_wave<T>(alpha[i], eps[i], out + i, out64 ? out64 + i : nullptr, blob, threadIdx.x);
 }
 
 // per-system constants of a forward batch; systems whose parameters leave
 // the kernel's domain (alpha < 0, alpha*eps > 1, non-finite rows) are
 // flagged SWIM_ST_BADPARAM_ and skipped by the run kernels.
 template <typename T>
-__global__ void k_sysconst_batch(int64_t n, const int64_t* sw_off, const int32_t* npt, const double* params,
-                                 double eps_over_ds, SysConst<T>* out, SysConst<double>* out64, int32_t* status,
-                                 int blob)
+__global__ __launch_bounds__(64) void k_sysconst_batch(const int64_t* sw_off, const int32_t* npt, const double* params,
+                                                       double eps_over_ds, SysConst<T>* out, SysConst<double>* out64,
+                                                       int32_t* status, int blob)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
+    const int64_t s = blockIdx.x;  // one wave per system
+    const int lane = threadIdx.x;
     const double alpha = params[9 * sw_off[s]];
     const double eps = eps_over_ds / (double)(npt[s] - 1);
     bool ok = isfinite(alpha) && alpha >= 0.0 && alpha * eps <= 1.0;
-    for (int64_t f = sw_off[s]; f < sw_off[s + 1]; ++f)
-        for (int c = 0; c < 9; ++c) ok = ok && isfinite(params[9 * f + c]);
-    status[s] = ok ? 0 : SWIM_ST_BADPARAM_;
-    sysconst_compute2<T>(ok ? alpha : 0.0, eps, out + s, out64 ? out64 + s : nullptr, blob);
+    for (int64_t k = 9 * sw_off[s] + lane; k < 9 * sw_off[s + 1]; k += 64) ok = ok && isfinite(params[k]);
+    ok = __all(ok);
+    if (lane == 0) status[s] = ok ? 0 : SWIM_ST_BADPARAM_;
+    sysconst_wave<T>(ok ? alpha : 0.0, eps, out + s, out64 ? out64 + s : nullptr, blob, lane);
 }
 
 // FP32 kernel tables of systems [s0, s0 + n), one thread per interval; the
@@ -293,131 +310,118 @@ __global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const
     tab_assemble(sysc64[s], h, g, tab[s].e[i], &tab[s].h0lo[i]);
 }
 
-// FP32 kernel tables with the paper's blob (eq. eqnblob): one workgroup of
-// PB_BLOCK threads per system.  A system at alpha > 0 (paper == 2) takes the
-// sweep of pb_table_nodes_host, split over the workgroup:
-//  1. thread tid of the first PB_SWEEP threads integrates a contiguous run
-//     of the gaps [1, kL] and leaves the gap integrals in LDS (slot k of
-//     three node arrays); the last wave meanwhile takes the tail integral
-//     beyond r_kL, one panel per lane;
-//  2. exclusive prefix sums of A and Cq and the suffix sum of B over the
-//     per-thread totals (a wave scan, then the waves in order);
-//  3. each thread turns its own slots into A(r_k), B(r_k), Cq(r_k) and then
-//     into the node values of the sweep;
-//  4. the nodes outside the sweep (and every node of a system at alpha = 0,
-//     closed forms) are spread over the threads;
-//  5. the entries are assembled from the node values as in k_table_build.
-constexpr int PB_BLOCK = 512;
-constexpr int PB_SWEEP = PB_BLOCK - 64;  // threads of the gap quadratures
+// Kernel tables by the interval sweep (pb_iv_*), one workgroup of TAB_N
+// threads per system, one interval per thread: FP32 tables with the paper's
+// blob (K = 7 nodes), and FP64 tables of any blob (K = 9).  A system at
+// alpha > 0 with the paper's blob (paper == 2):
+//  1. each thread evaluates the Bessel functions at its interval's nodes
+//     and totals the integrands of A and B;
+//  2. exclusive prefix sums of A and suffix sums of B over the intervals;
+//  3. the flux G at the nodes, totals of the integrands of g - g(0) and I2,
+//     and their prefix sums;
+//  4. the node values; intervals outside the sweep take the near-contact
+//     series or the far field.
+// Other systems evaluate their closed forms at the nodes.  Bound by the FP64
+// Bessel functions (one set per node, ~250 operations); with one quadrature
+// rule per gap between nodes instead (three 6-point rules per interval, a
+// Bessel set at every point) 4096 FP32 tables took 1.2 ms and one 60 us.
+constexpr int PB_BLOCK = TAB_N;
+static_assert(PB_BLOCK % 64 == 0 && PB_BLOCK <= 1024, "one interval per thread");
 
-// exclusive scan of v over the workgroup in thread order (REV: from the last
-// thread down), plus its total; red holds PB_BLOCK / 64 values
-template <bool REV> __device__ double pb_block_scan(double v, double* red, double* total)
+// exclusive scans over the workgroup in thread order: a forward, b forward
+// or (REVB) from the last thread down; red holds 2 PB_BLOCK / 64 values
+template <bool REVB> __device__ void pb_block_scan2(double& a, double& b, double* red)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = PB_BLOCK / 64;
-    const int l = REV ? 63 - lane : lane;
-    double inc = v;  // inclusive scan within the wave, in order of l
+    const int l = REVB ? 63 - lane : lane;
+    double ia = a, ib = b;  // inclusive within the wave
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const double u = __shfl(inc, REV ? min(lane + o, 63) : max(lane - o, 0), 64);
-        if (l >= o) inc += u;
+        const double ua = __shfl(ia, max(lane - o, 0), 64);
+        const double ub = __shfl(ib, REVB ? min(lane + o, 63) : max(lane - o, 0), 64);
+        if (lane >= o) ia += ua;
+        if (l >= o) ib += ub;
     }
-    if (l == 63) red[wave] = inc;
+    __syncthreads();  // the previous scan's totals are read
+    if (lane == 63) red[wave] = ia;
+    if (l == 63) red[NW + wave] = ib;
     __syncthreads();
-    double before = 0.0, all = 0.0;
+    double ba = 0.0, bb = 0.0;
     for (int w = 0; w < NW; ++w) {
-        const int ww = REV ? NW - 1 - w : w;
-        if (REV ? ww > wave : ww < wave) before += red[ww];
-        all += red[ww];
+        if (w < wave) ba += red[w];
+        const int ww = REVB ? NW - 1 - w : w;
+        if (REVB ? ww > wave : ww < wave) bb += red[NW + ww];
     }
-    __syncthreads();
-    *total = all;
-    return before + inc - v;
+    a = ba + ia - a;
+    b = bb + ib - b;
 }
 
+template <int K>
 __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const SysConst<double>* __restrict__ sysc64,
-                                                             TabSys* __restrict__ tab)
+                                                             void* __restrict__ tab)
 {
-    __shared__ double s_fh[PB_NODES], s_fg[PB_NODES], s_c[PB_NODES];
-    __shared__ double s_red[PB_BLOCK / 64];
-    __shared__ double s_tail;
-    const int tid = threadIdx.x;
+    __shared__ double s_red[2 * PB_BLOCK / 64];
+    __shared__ double s_sh[PB_NSER - 1], s_sg[PB_NSER - 1];
+    const int i = threadIdx.x;  // the interval
     const int64_t s = s0 + blockIdx.x;
     // read in place (uniform loads), not copied into per-lane registers
     const SysConst<double>& C = sysc64[s];
     const bool sweep = C.paper == 2.0;
-    int kS = PB_NODES, kL = -1;
-    if (sweep) pb_sweep_range(C, kS, kL);
-    if (kL >= kS) {  // uniform over the workgroup
-        const double alpha = sqrt(C.a2), eps = C.eps;
-        const int per = (kL + PB_SWEEP - 1) / PB_SWEEP;
-        const int k0 = tid < PB_SWEEP ? 1 + tid * per : kL + 1, k1 = min(kL + 1, k0 + per);
-        double ta = 0.0, tb = 0.0, tc = 0.0;
-        double ulo = (k0 > 1 && k0 <= kL) ? asinh(sqrt(pb_node_t(C.its, k0 - 1)) / eps) : 0.0;
-        for (int k = k0; k < k1; ++k) {
-            const double r = sqrt(pb_node_t(C.its, k));
-            const double uhi = asinh(r / eps);
-            double ga, gb, gc;
-            pb_gap(alpha, eps, ulo, uhi, k > kS, alpha * r <= 2.0, &ga, &gb, &gc);
-            ulo = uhi;
-            s_fh[k] = ga;
-            s_fg[k] = gb;
-            s_c[k] = gc;
-            ta += ga;
-            tb += gb;
-            tc += gc;
+    double fh[K], fg[K];
+    int iS = TAB_N;
+    if (sweep) {  // uniform over the workgroup
+        const PbRange R = pb_range(C);
+        iS = R.iS;
+        const double alpha = sqrt(C.a2);
+        const bool in = i >= R.iS && i < R.iE;
+        double fa[K], fb[K], p[K], q[K];
+        double A = 0.0, B = 0.0;
+        if (i == TAB_N - 1) pb_series(C, s_sh, s_sg);
+        if (in) {
+            pb_iv_nodes<K, true>(C, alpha, i, fa, fb, p, q);
+            A = lob_total<K>(fa);
+            B = lob_total<K>(fb);
+        } else if (i < R.iS) {
+            pb_iv_nodes<K, false>(C, alpha, i, fa, fb, p, q);
+            A = lob_total<K>(fa);
         }
-        // B(r_L), the integral beyond the sweep's last node: the last wave
-        // takes one panel of pb_tail_panel per lane
-        if (tid >= PB_SWEEP) {
-            const double rL = sqrt(pb_node_t(C.its, kL));
-            const double v = wave_total(pb_tail_panel(alpha, eps, rL, tid - PB_SWEEP, 64));
-            if (tid == PB_SWEEP) s_tail = v;
+        pb_block_scan2<true>(A, B, s_red);
+        const bool own = in && i < R.iF;
+        double D = 0.0, I2 = 0.0;
+        if (own) {
+            pb_iv_flux<K>(C, i, A, B, fa, fb, p, q);
+            D = lob_total<K>(fa);
+            I2 = lob_total<K>(fb);
         }
-        double tot;
-        double A = pb_block_scan<false>(ta, s_red, &tot);
-        double Cq = pb_block_scan<false>(tc, s_red, &tot);
-        double B = pb_block_scan<true>(tb, s_red, &tot) + s_tail;
-        for (int k = k0; k < k1; ++k) {
-            A += s_fh[k];
-            Cq += s_c[k];
-            s_fh[k] = A;
-            s_c[k] = Cq;
+        pb_block_scan2<false>(D, I2, s_red);
+        if (own) {
+            // start values of the sweep from the series
+            double v0, hv, h0, g0;
+            tab_span(R.iS, v0, hv);
+            const double t0 = (v0 - 1.0) * C.its;
+            pb_series_eval(s_sh, s_sg, t0 * C.inv_e2, h0, g0);
+            pb_iv_values<K>(C, i, D + (-2.0 * h0 - t0 * g0), I2 + t0 * t0 * g0, fa, fb, fh, fg);
+        } else {
+            pb_iv_outside<K>(C, i, true, iS, s_sh, s_sg, fh, fg);
         }
-        for (int k = k1 - 1; k >= k0; --k) {
-            const double gb = s_fg[k];
-            s_fg[k] = B;
-            B += gb;
-        }
-        for (int k = max(k0, kS); k < k1; ++k) {
-            double fh, fg;
-            pb_node_sweep(alpha, eps, pb_node_t(C.its, k), s_fh[k], s_fg[k], s_c[k], C.h1c, fh, fg);
-            s_fh[k] = fh;
-            s_fg[k] = fg;
-        }
+    } else {
+        pb_iv_outside<K>(C, i, false, iS, s_sh, s_sg, fh, fg);
     }
-    __syncthreads();
-    for (int k = tid; k < PB_NODES; k += PB_BLOCK) {
-        if (k >= kS && k <= kL) continue;
-        double fh, fg;
-        if (sweep)
-            pb_node_outside(C, k, kS, fh, fg);
-        else
-            kernel_paper_stokes<double>(C, pb_node_t(C.its, k), fh, fg);  // alpha = 0: closed forms
-        s_fh[k] = fh;
-        s_fg[k] = fg;
-    }
-    __syncthreads();
-    TabSys& T = tab[s];
-    for (int i = tid; i <= TAB_N; i += PB_BLOCK) {
-        if (i == TAB_N) {
-            tab_interval(C, i, T.e[i], &T.h0lo[i]);  // the zero entry
-            continue;
-        }
-        const double fh[4] = {s_fh[3 * i], s_fh[3 * i + 1], s_fh[3 * i + 2], s_fh[3 * i + 3]};
-        const double fg[4] = {s_fg[3 * i], s_fg[3 * i + 1], s_fg[3 * i + 2], s_fg[3 * i + 3]};
-        tab_assemble(C, fh, fg, T.e[i], &T.h0lo[i]);
+    if constexpr (K == 7) {
+        TabSys& T = reinterpret_cast<TabSys*>(tab)[s];
+        const double h4[4] = {fh[0], fh[2], fh[4], fh[6]}, g4[4] = {fg[0], fg[2], fg[4], fg[6]};
+        tab_assemble(C, h4, g4, T.e[i], &T.h0lo[i]);
+        if (i == 0) tab_interval(C, TAB_N, T.e[TAB_N], &T.h0lo[TAB_N]);  // the zero entry
+    } else {
+        TabE64& e = reinterpret_cast<TabSys64*>(tab)[s].e[i];
+        double c[9];
+        tab64_poly(fh, c);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) e.h[k] = c[k];
+        tab64_poly(fg, c);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) e.g[k] = c[k];
     }
 }
 
@@ -435,7 +439,7 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n)
 template <typename T, int TPL>
 __global__ __launch_bounds__(256) void k_pair_velocity(const int64_t* blk_sys, const int64_t* blk_first,
                                                         const int64_t* pt_off, const SysConst<T>* sysc,
-                                                        const TabSys* tabs, const T* x, const T* y, const T* fx,
+                                                        const void* tabs, const T* x, const T* y, const T* fx,
                                                         const T* fy, T* ux, T* uy)
 {
     __shared__ Src4<T> tile[256];
@@ -447,8 +451,8 @@ __global__ __launch_bounds__(256) void k_pair_velocity(const int64_t* blk_sys, c
     const int64_t first = blk_first[blockIdx.x];
     const int64_t p0 = pt_off[s];
     const int64_t n = pt_off[s + 1] - p0;
-    const SysConst<T> C = sysc[s];
-    if constexpr (sizeof(T) == 4) tab_load(tabs + s, tab, tid, 256);
+    const SysConst<T>& C = sysc[s];
+    if constexpr (sizeof(T) == 4) tab_load((const TabSys*)tabs + s, tab, tid, 256);
     // FP32 accumulates in FP64 (pair_accumulate_x); FP64 in FP64
     T xi[TPL], yi[TPL], ax[TPL], ay[TPL];
     double axd[TPL], ayd[TPL];
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(256) void k_pair_velocity(const int64_t* blk_sys, c
         if constexpr (sizeof(T) == 4)
             pair_accumulate_x<TPL>(C, tab, tile, m, xi, yi, axd, ayd);
         else
-            pair_accumulate<T, TPL>(C, tile, m, xi, yi, ax, ay);
+            pair_accumulate<T, TPL>(C, (const TabSys64*)tabs + s, tile, m, xi, yi, ax, ay);
     }
     sfx = wave_sum(sfx);
     sfy = wave_sum(sfy);
@@ -733,7 +737,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         __syncthreads();
         return;
     }
-    const SysConst<T> C = ((const SysConst<T>*)b.sysc)[s];
+    const SysConst<T>& C = ((const SysConst<T>*)b.sysc)[s];
     const double dsd = 1.0 / (double)(N - 1);
     constexpr bool WIN = fwd_window(COMP ? 0 : 1, TPL, WPS);
     if constexpr (WIN)
@@ -847,11 +851,13 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
             // 1 + (r/eps)^2 < 2^44, inside the table (the initial positions
             // are the caller's: a run placed beyond the bound reads zeros
             // for its far pairs in its first step and stops)
+            // (FP64 reads its table from HBM and tests every pair)
             T ax[TPL], ay[TPL];
+            const void* tab = COMP ? (const void*)L.tab : (const void*)((const TabSys64*)b.tab + s);
             if (one_seg)
-                pair_phase_seg<T, TPL, false, WIN>(C, L.tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
+                pair_phase_seg<T, TPL, !COMP, WIN>(C, tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
             else
-                pair_phase_sym<T, TPL, WPS, false, WIN>(C, L.tab, L.src, n, wave, lane, ax, ay);
+                pair_phase_sym<T, TPL, WPS, !COMP, WIN>(C, tab, L.src, n, wave, lane, ax, ay);
 #pragma unroll
             for (int c = 0; c < TPL; ++c) {
                 if (c < nblk64) {
@@ -1144,7 +1150,7 @@ __global__ __launch_bounds__(256) void k_big_step(const int64_t* blk_sys, const 
     const T* xl = (const T*)S.xl[cur] + p0;
     const T* yl = (const T*)S.yl[cur] + p0;
     const T t = (T)((double)step * r.dt);
-    const SysConst<T> C = ((const SysConst<T>*)b.sysc)[s];
+    const SysConst<T>& C = ((const SysConst<T>*)b.sysc)[s];
     // FP32 sums whole large systems per lane: FP64 accumulation
     // (pair_accumulate_x); FP64 runs accumulate in FP64 anyway
     T xi[TPL], yi[TPL], ax[TPL], ay[TPL];
@@ -1168,7 +1174,7 @@ __global__ __launch_bounds__(256) void k_big_step(const int64_t* blk_sys, const 
         if constexpr (COMP)
             pair_accumulate_x<TPL>(C, tab, src, m_t, xi, yi, axd, ayd);
         else
-            pair_accumulate<T, TPL>(C, src, m_t, xi, yi, ax, ay);
+            pair_accumulate<T, TPL>(C, (const TabSys64*)b.tab + s, src, m_t, xi, yi, ax, ay);
     }
 #pragma unroll
     for (int k = 0; k < TPL; ++k) {
@@ -1552,11 +1558,11 @@ hipError_t launch_sysconst_batch(int dtype, int64_t n_sys, const int64_t* sw_off
 {
     if (n_sys <= 0) return hipSuccess;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_sysconst_batch<float>, dim3(nblk(n_sys, 64)), dim3(64), 0, st, n_sys, sw_off, npt,
-                           params, eps_over_ds, (SysConst<float>*)sysc, (SysConst<double>*)sysc64, status, blob);
+        hipLaunchKernelGGL(k_sysconst_batch<float>, dim3((unsigned)n_sys), dim3(64), 0, st, sw_off, npt, params,
+                           eps_over_ds, (SysConst<float>*)sysc, (SysConst<double>*)sysc64, status, blob);
     else
-        hipLaunchKernelGGL(k_sysconst_batch<double>, dim3(nblk(n_sys, 64)), dim3(64), 0, st, n_sys, sw_off, npt,
-                           params, eps_over_ds, (SysConst<double>*)sysc, (SysConst<double>*)nullptr, status, blob);
+        hipLaunchKernelGGL(k_sysconst_batch<double>, dim3((unsigned)n_sys), dim3(64), 0, st, sw_off, npt, params,
+                           eps_over_ds, (SysConst<double>*)sysc, (SysConst<double>*)nullptr, status, blob);
     return hipGetLastError();
 }
 
@@ -1565,22 +1571,25 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
 {
     if (n_sys <= 0) return hipSuccess;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_sysconst<float>, dim3(nblk(n_sys, 64)), dim3(64), 0, st, n_sys, alpha, eps,
+        hipLaunchKernelGGL(k_sysconst<float>, dim3((unsigned)n_sys), dim3(64), 0, st, alpha, eps,
                            (SysConst<float>*)sysc, (SysConst<double>*)sysc64, blob);
     else
-        hipLaunchKernelGGL(k_sysconst<double>, dim3(nblk(n_sys, 64)), dim3(64), 0, st, n_sys, alpha, eps,
+        hipLaunchKernelGGL(k_sysconst<double>, dim3((unsigned)n_sys), dim3(64), 0, st, alpha, eps,
                            (SysConst<double>*)sysc, (SysConst<double>*)nullptr, blob);
     return hipGetLastError();
 }
 
-size_t table_bytes() { return sizeof(TabSys); }
+size_t table_bytes(int dtype) { return dtype == 0 ? sizeof(TabSys) : sizeof(TabSys64); }
 
-hipError_t launch_table_build(int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st)
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (blob == 1)
-        hipLaunchKernelGGL(k_table_build_pb, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, (TabSys*)tab);
+    if (dtype == 1)
+        hipLaunchKernelGGL(k_table_build_pb<9>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
+                           (const SysConst<double>*)sysc64, tab);
+    else if (blob == 1)
+        hipLaunchKernelGGL(k_table_build_pb<7>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
+                           (const SysConst<double>*)sysc64, tab);
     else
         hipLaunchKernelGGL(k_table_build, dim3((unsigned)(n * TAB_WAVES)), dim3(64), 0, st, s0, n,
                            (const SysConst<double>*)sysc64, (TabSys*)tab);
@@ -1600,7 +1609,7 @@ static void pair_launch(int64_t nb, const int64_t* bs, const int64_t* bf, const 
                         void* uy, hipStream_t st)
 {
     hipLaunchKernelGGL((k_pair_velocity<T, TPL>), dim3((unsigned)nb), dim3(256), 0, st, bs, bf, off,
-                       (const SysConst<T>*)sysc, (const TabSys*)tab, (const T*)x, (const T*)y, (const T*)fx,
+                       (const SysConst<T>*)sysc, tab, (const T*)x, (const T*)y, (const T*)fx,
                        (const T*)fy, (T*)ux, (T*)uy);
 }
 
@@ -1747,7 +1756,7 @@ hipError_t launch_big_init(int dtype, const int64_t* list, int64_t n_list, const
 size_t big_step_lds_bytes(int dtype, int32_t max_pts)
 {
     (void)max_pts;  // sources are tiled: any system size
-    return (dtype == 0 ? table_bytes() : 0) + (size_t)BIG_TILE * 4 * (dtype == 0 ? sizeof(float) : sizeof(double));
+    return (dtype == 0 ? table_bytes(0) : 0) + (size_t)BIG_TILE * 4 * (dtype == 0 ? sizeof(float) : sizeof(double));
 }
 
 template <typename T, int TPL>

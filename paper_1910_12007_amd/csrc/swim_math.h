@@ -35,6 +35,7 @@
 #include <stdint.h>
 
 #include "swim_kfit.h"
+#include "swim_pbrule.h"
 
 #define SWIM_HD __host__ __device__ __forceinline__
 
@@ -119,6 +120,23 @@ SWIM_HD double ifit(int nu, double x)
     }
     const double c0 = nu ? swim_ifit_i1_f64[0] : swim_ifit_i0_f64[0];
     return fma(u, b1, c0 - b2);
+}
+// both orders of a fit at once, its first NF terms (two independent chains)
+template <int NF>
+SWIM_HD void fit01(const double* c0, const double* c1, double x, double& f0, double& f1)
+{
+    const double u = 2.0 * x - 1.0, u2 = 2.0 * u;
+    double a1 = 0.0, a2 = 0.0, b1 = 0.0, b2 = 0.0;
+#pragma unroll
+    for (int j = NF - 1; j >= 1; --j) {
+        const double a0 = fma(u2, a1, c0[j] - a2), b0 = fma(u2, b1, c1[j] - b2);
+        a2 = a1;
+        a1 = a0;
+        b2 = b1;
+        b1 = b0;
+    }
+    f0 = fma(u, a1, c0[0] - a2);
+    f1 = fma(u, b1, c1[0] - b2);
 }
 
 // Ascending series of fixed length in y = z^2/4 (A&S 9.6.10, 9.6.13),
@@ -288,8 +306,8 @@ SWIM_HD double taylor_at(const double* p, int M, int n, double w0)
 //   gam_{n+1} = eps^2 (phi_n + alpha^2 gam_n) / (4 (n+1)^2),
 //   phi_n = 3/(2 pi eps^2) C(-5/2, n).
 // All of this runs in FP64 and costs ~1e3 Bessel evaluations per kernel
-// value: it builds the FP32 tables once per system and is the direct FP64
-// evaluation.
+// value: the direct FP64 evaluation (the tables' sweep, at the end of this
+// file, takes all nodes of a system together).
 // ---------------------------------------------------------------------------
 constexpr double GL10_X[5] = {0.14887433898163122, 0.4333953941292472, 0.6794095682990244,
                               0.8650633666889845, 0.9739065285171717};
@@ -365,26 +383,19 @@ SWIM_HD double pb_i0x(double x, double z, double enz)
     return ifit(0, SWIM_IFIT_IS / x) * exp(x - z) / sqrt(x);
 }
 
-// Panel rule: widest panel in u and the cut-off exponent.  The direct FP64
-// evaluation takes (1/2, 42): ~1e-15 relative.  The FP32 tables, whose
-// cubic pieces are good to ~1e-7, are built with (3/2, 26): 10-point rules
-// on panels 3/4 wide in half-width against poles pi/2 off the axis leave
-// ~1e-13, the cut-off e^-26 ~5e-12, at about a third of the panels.
-struct PbRule {
-    double du, cut;
-};
-constexpr PbRule PB_EXACT = {0.5, 42.0};
-constexpr PbRule PB_TABLE = {1.5, 26.0};
+// panel rule of the direct evaluation: widest panel in u and the cut-off
+// exponent (~1e-15 relative)
+constexpr double PB_DU = 0.5, PB_CUT = 42.0;
 
 // exp(alpha r) int_{u0}^inf (3/2pi) sinh u/cosh^4 u K0(alpha eps sinh u) du
-SWIM_HD double pb_outer(double alpha, double eps, double r, double u0, PbRule q = PB_EXACT)
+SWIM_HD double pb_outer(double alpha, double eps, double r, double u0)
 {
     const double z = alpha * r, ez = exp(fmin(z, SWIM_KFIT_ZS));
     double b = 0.0, ul = u0;
     for (int p = 0; p < 400; ++p) {
         const double sl = eps * sinh(ul), x = alpha * (sl - r);
-        if (x + 3.0 * (ul - u0) > q.cut) break;
-        const double uh = fmin(ul + q.du, asinh((sl + (1.0 + 0.25 * x) / alpha) / eps));
+        if (x + 3.0 * (ul - u0) > PB_CUT) break;
+        const double uh = fmin(ul + PB_DU, asinh((sl + (1.0 + 0.25 * x) / alpha) / eps));
         const double hm = 0.5 * (uh - ul), ct = 0.5 * (uh + ul);
         for (int i = 0; i < 10; ++i) {
             const double u = i < 5 ? ct - hm * GL10_X[4 - i] : ct + hm * GL10_X[i - 5];
@@ -445,7 +456,7 @@ SWIM_HD double pb_g0_closed(double a)
 }
 
 // g(r) and M(r) for delta >= 1/4
-SWIM_HD void pb_gM(double alpha, double eps, double t, double* g, double* M, PbRule q = PB_EXACT)
+SWIM_HD void pb_gM(double alpha, double eps, double t, double* g, double* M)
 {
     const double r = sqrt(t), z = alpha * r, ur = asinh(r / eps);
     const bool small = z <= 2.0;
@@ -453,9 +464,9 @@ SWIM_HD void pb_gM(double alpha, double eps, double t, double* g, double* M, PbR
     double as = 0.0, cq = 0.0, uh = ur;
     for (int p = 0; p < 400 && uh > 0.0; ++p) {
         const double sh = eps * sinh(uh), x = alpha * (r - sh);
-        if (x - 3.0 * (ur - uh) > q.cut) break;
+        if (x - 3.0 * (ur - uh) > PB_CUT) break;
         const double sl = sh - (1.0 + 0.25 * x) / alpha;
-        const double ul = fmax(fmax(uh - q.du, 0.0), sl > 0.0 ? asinh(sl / eps) : 0.0);
+        const double ul = fmax(fmax(uh - PB_DU, 0.0), sl > 0.0 ? asinh(sl / eps) : 0.0);
         const double hm = 0.5 * (uh - ul), ct = 0.5 * (uh + ul);
         for (int i = 0; i < 10; ++i) {
             const double u = i < 5 ? ct - hm * GL10_X[4 - i] : ct + hm * GL10_X[i - 5];
@@ -471,7 +482,7 @@ SWIM_HD void pb_gM(double alpha, double eps, double t, double* g, double* M, PbR
         }
         uh = ul;
     }
-    const double bs = pb_outer(alpha, eps, r, ur, q);
+    const double bs = pb_outer(alpha, eps, r, ur);
     double k0e, k1e, i0e, i1e;
     bessel_k01e_f64(z, &k0e, &k1e);
     bessel_i01e_f64(z, &i0e, &i1e);
@@ -489,8 +500,9 @@ SWIM_HD void pb_gM(double alpha, double eps, double t, double* g, double* M, PbR
 }
 
 // Constants of the closed forms: the reading's blob (blob 0) for every
-// alpha, the paper's blob (blob 1) at alpha = 0.
-template <typename T> SWIM_HD void sysconst_base(double alpha, double eps, SysConst<T>* out, int blob)
+// alpha, the paper's blob (blob 1) at alpha = 0; without the polynomials U, V
+// (zeros).
+template <typename T> SWIM_HD void sysconst_scalars(double alpha, double eps, SysConst<T>* out, int blob)
 {
     const double a2 = alpha * alpha, e2 = eps * eps, w0 = a2 * e2;
     SysConst<T> C;
@@ -529,6 +541,15 @@ template <typename T> SWIM_HD void sysconst_base(double alpha, double eps, SysCo
     C.K0z0 = (T)K0;
     C.q0 = (T)Q0;
     C.h1c = (T)(c * K0 / (4.0 * PI));
+    *out = C;
+}
+
+template <typename T> SWIM_HD void sysconst_base(double alpha, double eps, SysConst<T>* out, int blob)
+{
+    sysconst_scalars<T>(alpha, eps, out, blob);
+    if (alpha == 0.0) return;
+    SysConst<T>& C = *out;
+    const double a2 = alpha * alpha, w0 = a2 * (eps * eps);
     const double* pI0 = SETUP_SERIES.I0;
     const double* pP0 = SETUP_SERIES.P0;
     const double* pA = SETUP_SERIES.A;
@@ -548,7 +569,6 @@ template <typename T> SWIM_HD void sysconst_base(double alpha, double eps, SysCo
         C.V[n - 2] = (T)(v * a2m);
         a2m *= a2;
     }
-    *out = C;
 }
 
 // the paper's blob at alpha > 0, given g(0)
@@ -595,10 +615,11 @@ template <typename T> SWIM_HD void sysconst_compute(double alpha, double eps, Sy
         sysconst_base<T>(alpha, eps, out, blob);
 }
 
-// FP64 constants rounded to T field by field (what sysconst_base<T> forms)
-template <typename T> SWIM_HD void sysconst_cast(const SysConst<double>& D, SysConst<T>* out)
+// FP64 constants rounded to T field by field (what sysconst_base<T> forms),
+// without the polynomials U, V
+template <typename T> SWIM_HD void sysconst_cast_scalars(const SysConst<double>& D, SysConst<T>* out)
 {
-    SysConst<T> C;
+    SysConst<T>& C = *out;
     C.a2 = (T)D.a2;
     C.e2 = (T)D.e2;
     C.inv_e2 = (T)D.inv_e2;
@@ -615,31 +636,7 @@ template <typename T> SWIM_HD void sysconst_cast(const SysConst<double>& D, SysC
     C.its = (T)D.its;
     C.tr = (T)D.tr;
     C.eps = (T)D.eps;
-    for (int n = 0; n < NT_MAX; ++n) {
-        C.U[n] = (T)D.U[n];
-        C.V[n] = (T)D.V[n];
-    }
     C.hoff = (T)D.hoff;
-    *out = C;
-}
-
-// the constants in T and, if out64 is not null, in FP64 (one FP64 pass for
-// both; g(0) of the paper's blob integrated once)
-template <typename T>
-SWIM_HD void sysconst_compute2(double alpha, double eps, SysConst<T>* out, SysConst<double>* out64, int blob)
-{
-    if (blob == 1 && alpha > 0.0) {
-        const double g0 = pb_g0_closed(alpha * eps);
-        sysconst_paper<T>(alpha, eps, g0, out);
-        if (out64) sysconst_paper<double>(alpha, eps, g0, out64);
-        return;
-    }
-    if (out64) {
-        sysconst_base<double>(alpha, eps, out64, blob);
-        sysconst_cast<T>(*out64, out);
-    } else {
-        sysconst_base<T>(alpha, eps, out, blob);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -804,8 +801,7 @@ SWIM_HD void kernel_paper_stokes(const SysConst<T>& C, T t, T& Ht, T& H2)
 // H1 = M/r^2 - g, H2 = (g - 2M/r^2)/r^2 from the quadrature.  Not inlined:
 // it is large and only systems of this blob call it.
 __host__ __device__ __attribute__((noinline)) inline void kernel_paper_brinkman(const SysConst<double>& C, double t,
-                                                                              double& Ht, double& H2,
-                                                                              PbRule q = PB_EXACT)
+                                                                              double& Ht, double& H2)
 {
     const double delta = t * C.inv_e2;
     if (delta < 0.25) {
@@ -822,22 +818,18 @@ __host__ __device__ __attribute__((noinline)) inline void kernel_paper_brinkman(
         return;
     }
     double g, M;
-    pb_gM(sqrt(C.a2), C.eps, t, &g, &M, q);
+    pb_gM(sqrt(C.a2), C.eps, t, &g, &M);
     const double Mt = M / t;
     H2 = (g - 2.0 * Mt) / t;
     Ht = Mt - g - C.h1c;
 }
 
+// systems with closed forms: the reading's blob, the paper's blob at
+// alpha = 0, and (FP32 constants) its stand-in beyond the table
 template <typename T>
-SWIM_HD void kernel_eval(const SysConst<T>& C, T t, T& Ht, T& H2)
+SWIM_HD void kernel_eval_closed(const SysConst<T>& C, T t, T& Ht, T& H2)
 {
     if (C.paper != (T)0) {
-        if constexpr (sizeof(T) == 8) {
-            if (C.paper != 1.0) {
-                kernel_paper_brinkman(C, t, Ht, H2);
-                return;
-            }
-        }
         kernel_paper_stokes<T>(C, t, Ht, H2);
         return;
     }
@@ -847,6 +839,18 @@ SWIM_HD void kernel_eval(const SysConst<T>& C, T t, T& Ht, T& H2)
     else
         kernel_large_z<T>(C, t, w, Ht, H2);
     if constexpr (sizeof(T) == 4) Ht += C.hoff;
+}
+
+template <typename T>
+SWIM_HD void kernel_eval(const SysConst<T>& C, T t, T& Ht, T& H2)
+{
+    if constexpr (sizeof(T) == 8) {
+        if (C.paper == 2.0) {
+            kernel_paper_brinkman(C, t, Ht, H2);
+            return;
+        }
+    }
+    kernel_eval_closed<T>(C, t, Ht, H2);
 }
 
 // ---------------------------------------------------------------------------
@@ -860,7 +864,7 @@ SWIM_HD void kernel_eval(const SysConst<T>& C, T t, T& Ht, T& H2)
 // On each interval both functions are the cubic through their values at the
 // Chebyshev-Lobatto nodes 0, 1/4, 3/4, 1 of the interval, evaluated once per
 // system in FP64 by kernel_eval<double> (for the paper's blob at alpha > 0
-// by its quadrature with the table's panel rule).  The relative width 1/16 of an
+// by the sweep over all intervals at the end of this file).  The relative width 1/16 of an
 // interval bounds the interpolation error by about 4e-3 (1/16)^4 max|f''''|
 // in units of the function's own scale (about 1e-7 for the log and 1/t
 // behaviour of these kernels); rounding the coefficients to FP32 adds one
@@ -929,10 +933,7 @@ SWIM_HD void tab_node(const SysConst<double>& C, int i, int k, double& fh, doubl
     const double v0 = a * (1.0 + (double)j / (double)(1 << TAB_M)), hv = a / (double)(1 << TAB_M);
     const double un = k == 0 ? 0.0 : k == 1 ? 0.25 : k == 2 ? 0.75 : 1.0;
     const double t = fmax((v0 - 1.0 + hv * un) * C.its, 1e-300);
-    if (C.paper == 2.0)
-        kernel_paper_brinkman(C, t, fh, fg, PB_TABLE);
-    else
-        kernel_eval<double>(C, t, fh, fg);
+    kernel_eval<double>(C, t, fh, fg);
 }
 
 // the table entry from its four node values; h0lo, if not null: the FP32
@@ -973,125 +974,256 @@ SWIM_HD void tab_eval(const TabE& e, float u, float& Ht, float& H2s)
 }
 
 // ---------------------------------------------------------------------------
-// The paper's blob at alpha > 0: all table nodes of one system in one sweep.
+// The paper's blob at alpha > 0: all table intervals of one system in one sweep.
 //
-// The nodes of the FP32 table (node k: interval k/3 at coordinate 0, 1/4,
-// 3/4; node 3 TAB_N the end of the last interval) have increasing r.  With
-// A, B and Cq the integrals of pb_gM, each node needs
-//   A(r_k) = sum of the integrals of phi I0(alpha s) s over the gaps
-//            [r_{m-1}, r_m], m <= k (a prefix sum from s = 0),
-//   Cq(r_k) likewise (only where alpha r_k <= 2),
-//   B(r_k) = B(r_L) + the gaps m > k up to the last node L of the sweep
-//            (a suffix sum; B(r_L) is one tail integral, pb_outer),
-// and then g and M follow exactly as in pb_gM.  The gaps are narrow (at
-// most 1/64 in u beyond the first octave), so a 6-point Gauss-Legendre rule
-// per gap is exact to rounding for the blob's density (poles pi/2 off the
-// axis) and for the Bessel factors up to alpha r = PB_ZF (they change by at
-// most exp(PB_ZF/64) over a gap).  The sweep covers the nodes with
-// delta = t/eps^2 >= 1/4 and alpha r <= PB_ZF; below, g is the near-contact
-// series of kernel_paper_brinkman; beyond, the far-field expansion of
-// pb_node_far.  Every node value is one gap quadrature and one set of Bessel
-// functions instead of a panel quadrature of its own.
+// Interval i covers v in [v0, v0 + hv] (v = 1 + sigma t, t = r^2); a function
+// on it is held by its values at K Chebyshev-Lobatto nodes (swim_pbrule.h),
+// which integrate and interpolate it together.  With the blob measure
+// phi s ds = phi dt / 2 the sweep carries four running integrals:
+//   A(r) = int_0^r phi I0(alpha s) s ds         (prefix sum over intervals),
+//   B(r) = int_r^inf phi K0(alpha s) s ds       (suffix sum, up to
+//          alpha r = PB_ZB, beyond which K0 has fallen by e^-40 or more),
+//   G = r g'(r) = z [K1(z) A - I1(z) B], z = alpha r (> 0),
+//   g(r) - g(0) = int_0^r G / s ds,   I2(r) = int_0^r s G ds,
+// and H2 = I2 / r^4, Ht = -(g - g(0) + I2 / r^2) / 2 (M = r^2 g/2 - I2/2
+// by parts): every integrand is positive, so no difference of nearly equal
+// numbers is formed.  Each node costs one set of Bessel functions; the
+// interval totals go through four scans.  The sweep starts at the first
+// interval with delta = t/eps^2 >= 1/4 (below, and for its start values,
+// the near-contact series) and ends at alpha r = PB_ZF (beyond, the
+// far-field expansion of pb_node_far).  On an interval of relative width
+// 1/16 the integrands' singularities (t = 0 and t = -eps^2) are at least 9
+// half-widths away: K = 7 (FP32 tables) leaves ~1e-10 and K = 9 (FP64
+// tables) ~1e-15 of the node values.
 // ---------------------------------------------------------------------------
-constexpr int PB_NODES = 3 * TAB_N + 1;  // table nodes of one system
-constexpr double PB_ZF = 40.0;           // alpha r beyond which the far-field expansion serves
-constexpr int PB_NA = 14;                // terms of the far-field expansion
-constexpr double GL6_X[3] = {0.23861918608319693, 0.66120938646626448, 0.93246951420315205};
-constexpr double GL6_W[3] = {0.46791393457269137, 0.36076157304813894, 0.17132449237916975};
+constexpr double PB_ZF = 40.0;  // alpha r beyond which the far-field expansion serves
+constexpr double PB_ZB = 80.0;  // alpha r at which B's integral is cut
+constexpr int PB_NA = 14, PB_NY = 5;  // far-field expansion: terms in w, powers of y kept
 
-// t = r^2 of table node k (the t of tab_node: node k % 3 of interval k / 3)
-SWIM_HD double pb_node_t(double its, int k)
+template <int K> SWIM_HD constexpr double lob_xi(int k) { return K == 7 ? LOB7_XI[k] : LOB9_XI[k]; }
+template <int K> SWIM_HD constexpr double lob_q(int k, int m) { return K == 7 ? LOB7_Q[k][m] : LOB9_Q[k][m]; }
+
+// start and width of interval i in v
+SWIM_HD void tab_span(int i, double& v0, double& hv)
 {
-    const int i = k / 3, kk = k - 3 * i;
     const int e = i >> TAB_M, j = i & ((1 << TAB_M) - 1);
-    const double a = ldexp(1.0, e);
-    const double v0 = a * (1.0 + (double)j / (double)(1 << TAB_M)), hv = a / (double)(1 << TAB_M);
-    const double un = kk == 0 ? 0.0 : kk == 1 ? 0.25 : 0.75;
-    return fmax((v0 - 1.0 + hv * un) * its, 1e-300);
+    hv = ldexp(1.0, e - TAB_M);
+    v0 = hv * (double)((1 << TAB_M) + j);
 }
 
-// integrals over the gap [ulo, uhi] in u = asinh(s/eps) of the blob measure
-// phi s ds = (3/2pi) sinh u/cosh^4 u du times I0(alpha s) (ga), K0(alpha s)
-// (gb, if wantB) and (I0(alpha s) - 1)/alpha^2 (gc, if wantC)
-SWIM_HD void pb_gap(double alpha, double eps, double ulo, double uhi, bool wantB, bool wantC, double* ga, double* gb,
-                    double* gc)
+// first interval that starts at t >= thr (TAB_N if none does)
+SWIM_HD int tab_first(double ts, double thr)
 {
-    const double hm = 0.5 * (uhi - ulo), ct = 0.5 * (uhi + ulo);
-    double A = 0.0, B = 0.0, Cq = 0.0;
-#pragma unroll 1
-    for (int i = 0; i < 6; ++i) {
-        const double u = i < 3 ? ct - hm * GL6_X[2 - i] : ct + hm * GL6_X[i - 3];
-        double sh, dens;
-        pb_point(u, &sh, &dens);
-        const double wd = hm * (i < 3 ? GL6_W[2 - i] : GL6_W[i - 3]) * dens;
-        const double s = eps * sh, xs = alpha * s;
-        A += wd * pb_i0x(xs, 0.0, 1.0);
-        if (wantB) B += wd * pb_k0x(xs, 0.0, 1.0);
-        if (wantC) {
-            // (I0(xs) - 1)/alpha^2 = (s^2/4) sum_k (xs^2/4)^k / ((k+1)!)^2
-            Cq += wd * 0.25 * s * s * horner(BSER.iq, 0.25 * xs * xs);
+    const double v = 1.0 + thr * ts;
+    const int i = (int)(__builtin_bit_cast(uint64_t, v) >> (52 - TAB_M)) - (1023 << TAB_M);
+    if (i >= TAB_N) return TAB_N;
+    double v0, hv;
+    tab_span(i, v0, hv);
+    return v0 >= v ? i : i + 1;
+}
+
+// sweep ranges of a system: intervals [iS, iF) from the sweep, B's integral
+// over [iS, iE)
+struct PbRange {
+    int iS, iF, iE;
+};
+SWIM_HD PbRange pb_range(const SysConst<double>& C)
+{
+    PbRange r;
+    r.iS = tab_first(C.ts, 0.25 * C.e2);
+    r.iF = tab_first(C.ts, PB_ZF * PB_ZF * C.inv_a2);
+    r.iE = tab_first(C.ts, PB_ZB * PB_ZB * C.inv_a2);
+    return r;
+}
+
+// near-contact series (delta < 1/4 and a little beyond): coefficients of
+//   Ht = delta sum_n sh[n] delta^n,   H2 = sum_n sg[n] delta^n,
+// from gam_{n+1} = eps^2 (phi_n + alpha^2 gam_n) / (4 (n+1)^2)
+struct PbSeries {
+    double sh[PB_NSER - 1], sg[PB_NSER - 1];
+};
+SWIM_HD void pb_series(const SysConst<double>& C, double* sh, double* sg)
+{
+    double gam = C.K0z0, phin = 1.5 / PI * C.inv_e2;
+    for (int n = 0; n + 1 < PB_NSER; ++n) {
+        const double rn = PB_RECIP.lin[n], rn1 = PB_RECIP.lin[n + 1];  // 1/(n+1), 1/(n+2)
+        gam = C.e2 * (phin + C.a2 * gam) * (0.25 * rn * rn);           // gam_{n+1}
+        phin *= (-2.5 - n) * rn;
+        sg[n] = gam * (double)(n + 1) * rn1 * C.inv_e2;
+        sh[n] = -0.5 * gam * (double)(2 * n + 3) * rn1;
+    }
+}
+SWIM_HD void pb_series_eval(const double* sh, const double* sg, double delta, double& Ht, double& H2)
+{
+    double h = sh[PB_NSER - 2], g = sg[PB_NSER - 2];
+    for (int n = PB_NSER - 3; n >= 0; --n) {
+        h = fma(h, delta, sh[n]);
+        g = fma(g, delta, sg[n]);
+    }
+    Ht = h * delta;
+    H2 = g;
+}
+
+// 1/x and 1/sqrt(x) of normal positive x to about one rounding: on the
+// device the hardware estimate (a little better than 2^-24) and two Newton
+// steps, a third of the instructions of the correctly rounded forms
+SWIM_HD double rcp_nr(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+#else
+    return 1.0 / x;
+#endif
+}
+SWIM_HD double rsqrt_nr(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+#else
+    return 1.0 / sqrt(x);
+#endif
+}
+
+// I0(z), and with WITHK: z I1(z), K0(z), z K1(z) (z > 0); NF terms of the
+// large-argument fits (14: 1e-12, the FP32 tables; 27: all)
+template <bool WITHK, int NF> SWIM_HD void pb_bessel(double z, double& I0, double& zI1, double& K0, double& zK1)
+{
+    if (z <= SWIM_KFIT_ZS) {
+        const double y = 0.25 * z * z;
+        double i0 = 0.0, i1 = 0.0;
+#pragma unroll
+        for (int k = NSER_K - 1; k >= 0; --k) {
+            i0 = fma(i0, y, BSER.i0[k]);
+            if constexpr (WITHK) i1 = fma(i1, y, BSER.i1[k]);
+        }
+        I0 = i0;
+        if constexpr (WITHK) {
+            zI1 = 2.0 * y * i1;
+            // the ascending series in w = z^2 (A&S 9.6.13, 9.6.11)
+            const double w = z * z, L = log(0.25 * w);
+            double P0 = 0, A = 0, B = 0;
+#pragma unroll
+            for (int k = NSER_K - 1; k >= 0; --k) {
+                P0 = fma(P0, w, SETUP_SERIES.P0[k]);
+                A = fma(A, w, SETUP_SERIES.A[k]);
+                B = fma(B, w, SETUP_SERIES.B[k]);
+            }
+            K0 = -0.5 * L * I0 + P0;
+            zK1 = 1.0 + (0.5 * L * A - B);
+        }
+        return;
+    }
+    const double e = exp(z), rs = rsqrt_nr(z), rz = rs * rs;
+    if (z <= SWIM_IFIT_IS) {
+        const double y = 0.25 * z * z;
+        double i0 = 0.0, i1 = 0.0;
+#pragma unroll
+        for (int k = NSER_I - 1; k >= 0; --k) {
+            i0 = fma(i0, y, BSER.i0[k]);
+            if constexpr (WITHK) i1 = fma(i1, y, BSER.i1[k]);
+        }
+        I0 = i0;
+        if constexpr (WITHK) zI1 = 2.0 * y * i1;
+    } else {
+        double f0, f1;
+        fit01<NF>(swim_ifit_i0_f64, swim_ifit_i1_f64, SWIM_IFIT_IS * rz, f0, f1);
+        const double c = e * rs;
+        I0 = c * f0;
+        if constexpr (WITHK) zI1 = z * (c * f1);
+    }
+    if constexpr (WITHK) {
+        double f0, f1;
+        fit01<NF>(swim_kfit_k0_f64, swim_kfit_k1_f64, SWIM_KFIT_ZS * rz, f0, f1);
+        const double c = rcp_nr(e) * rs;
+        K0 = c * f0;
+        zK1 = z * (c * f1);
+    }
+}
+
+// node values of interval i: fa = phi I0 dt/2, fb = phi K0 dt/2 (dt/2 per
+// unit of the rule's x), p = z K1, q = z I1; without WITHK (intervals below
+// the sweep) fa only
+template <int K, bool WITHK>
+SWIM_HD void pb_iv_nodes(const SysConst<double>& C, double alpha, int i, double (&fa)[K], double (&fb)[K],
+                         double (&p)[K], double (&q)[K])
+{
+    double v0, hv;
+    tab_span(i, v0, hv);
+    const double w = 0.25 * hv * C.its * (1.5 / PI) * C.eps * C.e2;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double t = fmax((v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, 1e-300);
+        const double rR = rsqrt_nr(t + C.e2), rR2 = rR * rR, f = w * (rR2 * rR2 * rR);
+        const double z = alpha * (t * rsqrt_nr(t));
+        double I0, zI1, K0, zK1;
+        pb_bessel<WITHK, K == 7 ? 14 : 27>(z, I0, zI1, K0, zK1);
+        fa[k] = f * I0;
+        if constexpr (WITHK) {
+            fb[k] = f * K0;
+            p[k] = zK1;
+            q[k] = zI1;
         }
     }
-    *ga = A;
-    *gb = B;
-    *gc = Cq;
+}
+template <int K> SWIM_HD double lob_total(const double (&f)[K])
+{
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) s = fma(lob_q<K>(K - 1, k), f[k], s);
+    return s;
 }
 
-// The tail B(r) = int_r^inf phi K0(alpha s) s ds beyond the sweep's last
-// node, as np panels in d = u - u(r): panel p of [0, dmax] by 10-point
-// Gauss-Legendre.  Its integrand falls like exp(-x - 3 d) with
-// x = alpha (s - r), so dmax is where x + 3 d reaches 44 (at most 15): the
-// neglected remainder is below e^-44 of the integrand at s = r, and a panel
-// of dmax/np (np = 64) changes the exponent by at most (alpha r + 3) dmax/np.
-SWIM_HD double pb_tail_dmax(double alpha, double eps, double r)
+// G at the nodes from A at the interval's start and B at its end, left in fa
+// as G dt / (2 t) (the integrand of g - g(0)) and in fb as G dt / 2 (I2's)
+template <int K>
+SWIM_HD void pb_iv_flux(const SysConst<double>& C, int i, double A0, double B1, double (&fa)[K], double (&fb)[K],
+                        const double (&p)[K], const double (&q)[K])
 {
-    const double u0 = asinh(r / eps);
-    double lo = 0.0, hi = 15.0;
-    for (int it = 0; it < 24; ++it) {
-        const double d = 0.5 * (lo + hi);
-        const double x = alpha * (eps * sinh(u0 + d) - r);
-        if (x + 3.0 * d > 44.0) hi = d;
-        else lo = d;
+    double v0, hv;
+    tab_span(i, v0, hv);
+    const double w = 0.25 * hv * C.its;
+    double G[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        double A = 0.0, B = 0.0;  // from the start; to the end (the rule mirrored)
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            A = fma(lob_q<K>(k, m), fa[m], A);
+            B = fma(lob_q<K>(K - 1 - k, K - 1 - m), fb[m], B);
+        }
+        G[k] = p[k] * (A0 + A) - q[k] * (B1 + B);
     }
-    return hi;
-}
-SWIM_HD double pb_tail_panel(double alpha, double eps, double r, int p, int np)
-{
-    const double u0 = asinh(r / eps), dmax = pb_tail_dmax(alpha, eps, r);
-    const double ul = u0 + dmax * p / np, uh = u0 + dmax * (p + 1) / np;
-    const double hm = 0.5 * (uh - ul), ct = 0.5 * (uh + ul);
-    double b = 0.0;
-#pragma unroll 1
-    for (int i = 0; i < 10; ++i) {
-        const double u = i < 5 ? ct - hm * GL10_X[4 - i] : ct + hm * GL10_X[i - 5];
-        double sh, dens;
-        pb_point(u, &sh, &dens);
-        b += hm * (i < 5 ? GL10_W[4 - i] : GL10_W[i - 5]) * dens * pb_k0x(alpha * eps * sh, 0.0, 1.0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double t = (v0 - 1.0 + hv * lob_xi<K>(k)) * C.its;
+        fb[k] = w * G[k];
+        fa[k] = fb[k] * rcp_nr(t);
     }
-    return b;
 }
 
-// node values Ht, H2 from A(r), B(r), Cq(r) (the formulas of pb_gM)
-SWIM_HD void pb_node_sweep(double alpha, double eps, double t, double A, double B, double Cq, double h1c, double& fh,
-                           double& fg)
+// Ht, H2 at the nodes from g - g(0) and I2 at the interval's start
+template <int K>
+SWIM_HD void pb_iv_values(const SysConst<double>& C, int i, double D0, double I20, const double (&fa)[K],
+                          const double (&fb)[K], double (&fh)[K], double (&fg)[K])
 {
-    const double r = sqrt(t), z = alpha * r;
-    double K0, K1, Q, i0e, i1e;
-    bessel_k01_q_f64(z, &K0, &K1, &Q);
-    bessel_i01e_f64(z, &i0e, &i1e);
-    const double ez = exp(z), I0 = i0e * ez, I1 = i1e * ez;
-    const double g = -(K0 * A + I0 * B);
-    double M;
-    if (z <= 2.0) {
-        M = Cq + t * (Q / (z * z)) * A - t * (I1 / z) * B;
-    } else {
-        const double R = sqrt(t + eps * eps);
-        const double m = 1.0 - eps * eps * eps / (R * R * R);
-        M = (z * (K1 * A - I1 * B) - m / (2.0 * PI)) / (alpha * alpha);
+    double v0, hv;
+    tab_span(i, v0, hv);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        double D = 0.0, I2 = 0.0;
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            D = fma(lob_q<K>(k, m), fa[m], D);
+            I2 = fma(lob_q<K>(k, m), fb[m], I2);
+        }
+        const double t = (v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, rt = rcp_nr(t), I2t = (I20 + I2) * rt;
+        fg[k] = I2t * rt;
+        fh[k] = -0.5 * (D0 + D + I2t);
     }
-    const double Mt = M / t;
-    fg = (g - 2.0 * Mt) / t;
-    fh = Mt - g - h1c;
 }
 
 // Far field (alpha r > PB_ZF).  There g is the decaying particular solution
@@ -1128,106 +1260,193 @@ struct PbAsym {
 };
 static constexpr PbAsym PB_ASYM{};
 
+// Here y < 1/(PB_ZF)^2 (alpha eps <= 1) and g itself is below 2e-5 of M/r^2,
+// so PB_NY powers of y carry every term; the double sum is unrolled, its
+// coefficients literals (as a loop over a table of them in memory it was the
+// longest chain of a table build; not inlined, or the literals are hoisted
+// out of the caller's loop over nodes into registers it does not have).  Beyond alpha r = 316 (w < 1e-5) five
+// terms in w do.
+struct PbFar {
+    double sg, sr;
+};
+template <int NA> __host__ __device__ __attribute__((noinline)) PbFar pb_far_sums(double w, double y)
+{
+    double sg = 0.0, sr = 0.0;
+#pragma unroll
+    for (int n = NA - 1; n >= 0; --n) {
+        double pg = 0.0, pr = 0.0;
+#pragma unroll
+        for (int j = PB_NY - 1; j >= 0; --j)
+            if (j <= n) {
+                pg = fma(pg, y, PB_ASYM.d[n][j]);
+                pr = fma(pr, y, PB_ASYM.e[n][j]);
+            }
+        sg = fma(sg, w, pg);
+        sr = fma(sr, w, pr);
+    }
+    return PbFar{sg, sr};
+}
+
 SWIM_HD void pb_node_far(double alpha, double eps, double t, double h1c, double& fh, double& fg)
 {
-    const double e2 = eps * eps, R2 = t + e2, R = sqrt(R2), a2 = alpha * alpha;
-    const double w = 1.0 / (a2 * R2), y = e2 / R2;
-    double sg = 0.0, sr = 0.0, wn = 1.0;
-#pragma unroll 1
-    for (int n = 0; n < PB_NA; ++n) {
-        double pg = PB_ASYM.d[n][n], pr = PB_ASYM.e[n][n];
-#pragma unroll 1
-        for (int j = n - 1; j >= 0; --j) {
-            pg = pg * y + PB_ASYM.d[n][j];
-            pr = pr * y + PB_ASYM.e[n][j];
-        }
-        sg += wn * pg;
-        sr += wn * pr;
-        wn *= w;
-    }
-    const double pre = 3.0 * e2 * eps / (2.0 * PI * a2 * R2 * R2 * R);
-    const double g = -pre * sg;
-    const double rg = -pre * (t / R2) * sr;
-    const double m = 1.0 - y * (eps / R);
-    const double M = (rg - m / (2.0 * PI)) / a2;
-    const double Mt = M / t;
-    fg = (g - 2.0 * Mt) / t;
+    const double e2 = eps * eps, R2 = t + e2, rR = rsqrt_nr(R2), rR2 = rR * rR, ra2 = rcp_nr(alpha * alpha);
+    const double w = ra2 * rR2, y = e2 * rR2;
+    const PbFar F = w < 1e-5 ? pb_far_sums<5>(w, y) : pb_far_sums<PB_NA>(w, y);
+    const double pre = (1.5 / PI) * e2 * eps * ra2 * (rR2 * rR2 * rR);
+    const double g = -pre * F.sg;
+    const double rg = -pre * (t * rR2) * F.sr;
+    const double m = 1.0 - y * (eps * rR);
+    const double M = (rg - m * (0.5 / PI)) * ra2;
+    const double rt = rcp_nr(t), Mt = M * rt;
+    fg = (g - 2.0 * Mt) * rt;
     fh = Mt - g - h1c;
 }
 
-// the sweep's node range of a system: nodes [kS, kL] take pb_node_sweep
-// (delta >= 1/4 and alpha r <= PB_ZF); below kS the near-contact series,
-// beyond kL the far field
-SWIM_HD void pb_sweep_range(const SysConst<double>& C, int& kS, int& kL)
+// Ht, H2 at the nodes of an interval outside the sweep: the near-contact
+// series below it, the far field beyond; systems without a sweep (alpha = 0,
+// or the reading's blob): the closed forms
+template <int K>
+SWIM_HD void pb_iv_outside(const SysConst<double>& C, int i, bool sweep, int iS, const double* sh, const double* sg,
+                           double (&fh)[K], double (&fg)[K])
 {
+    double v0, hv;
+    tab_span(i, v0, hv);
     const double alpha = sqrt(C.a2);
-    int lo = 0, hi = PB_NODES;  // first node with delta >= 1/4
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        if (pb_node_t(C.its, mid) * C.inv_e2 >= 0.25) hi = mid;
-        else lo = mid + 1;
+#pragma unroll 1
+    for (int k = 0; k < K; k += K == 7 ? 2 : 1) {  // K = 7: the cubic's nodes 0, 1/4, 3/4, 1 alone
+        const double t = fmax((v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, 1e-300);
+        double h, g;
+        if (!sweep)
+            kernel_eval_closed<double>(C, t, h, g);
+        else if (i < iS)
+            pb_series_eval(sh, sg, t * C.inv_e2, h, g);
+        else
+            pb_node_far(alpha, C.eps, t, C.h1c, h, g);
+#pragma unroll
+        for (int m = 0; m < K; ++m)
+            if (m == k) {
+                fh[m] = h;
+                fg[m] = g;
+            }
     }
-    kS = lo;
-    lo = 0;
-    hi = PB_NODES;  // first node with alpha r > PB_ZF
-    while (lo < hi) {
-        const int mid = (lo + hi) / 2;
-        if (alpha * sqrt(pb_node_t(C.its, mid)) > PB_ZF) hi = mid;
-        else lo = mid + 1;
-    }
-    kL = lo - 1;
 }
 
-// the node values of a system outside the sweep (k < kS or k > kL)
-SWIM_HD void pb_node_outside(const SysConst<double>& C, int k, int kS, double& fh, double& fg)
+// FP64 kernel tables: on the same intervals, Ht and H2 as polynomials of
+// degree 8 in x in [-1, 1) through the K = 9 nodes (error ~1e-17 of the
+// function's scale: the singularities lie 33 half-widths away), about one
+// rounding beyond the node values.  Interval and x come exactly from the bits
+// of the double v.
+struct alignas(16) TabE64 {
+    double h[9], g[9];
+};
+struct alignas(16) TabSys64 {
+    TabE64 e[TAB_N];
+};
+static_assert(sizeof(TabE64) == 144, "FP64 table entries are nine 16-byte pieces");
+
+// monomial coefficients of the polynomial through the node values f: by way
+// of the Chebyshev coefficients of f - f[4], whose magnitudes fall by 66 per
+// degree, so that neither transform amplifies rounding
+SWIM_HD void tab64_poly(const double (&f)[9], double (&c)[9])
 {
-    const double t = pb_node_t(C.its, k);
-    if (k < kS)
-        kernel_paper_brinkman(C, t, fh, fg);  // delta < 1/4: the series
-    else
-        pb_node_far(sqrt(C.a2), C.eps, t, C.h1c, fh, fg);
+    double a[9];
+#pragma unroll
+    for (int n = 0; n < 9; ++n) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s = fma(LOB9_A[n][k], f[k] - f[4], s);
+        a[n] = s;
+    }
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int n = 8; n >= 0; --n)
+            if (n >= j && (n - j) % 2 == 0) s = fma(LOB9_T[n][j], a[n], s);
+        c[j] = s;
+    }
+    c[0] += f[4];
 }
 
-// Host form of the sweep (the device kernel splits the same sums over a
-// workgroup): FP64 values Ht, H2 of every table node of a system with the
-// paper's blob at alpha > 0 (C.paper == 2).
-inline void pb_table_nodes_host(const SysConst<double>& C, double* fh, double* fg)
+// interval of v = 1 + sigma t (>= TAB_N: beyond the table, NaN included) and
+// the coordinate x in [-1, 1) on it
+SWIM_HD uint32_t tab64_index(double v)
 {
-    const double alpha = sqrt(C.a2), eps = C.eps;
-    int kS, kL;
-    pb_sweep_range(C, kS, kL);
-    for (int k = 0; k < PB_NODES; ++k)
-        if (k < kS || k > kL) pb_node_outside(C, k, kS, fh[k], fg[k]);
-    if (kL < kS) return;
-    const int ng = kL + 1;
-    double* ga = new double[ng];
-    double* gb = new double[ng];
-    double* gc = new double[ng];
-    double ulo = 0.0;
-    for (int k = 1; k <= kL; ++k) {
-        const double t = pb_node_t(C.its, k);
-        const double uhi = asinh(sqrt(t) / eps);
-        pb_gap(alpha, eps, ulo, uhi, k > kS, alpha * sqrt(t) <= 2.0, &ga[k], &gb[k], &gc[k]);
-        ulo = uhi;
+    return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32 >> (20 - TAB_M)) - (1023u << TAB_M);
+}
+SWIM_HD double tab64_x(double v)
+{
+    const uint64_t m = (__builtin_bit_cast(uint64_t, v) << TAB_M) & 0x000FFFFFFFFFFFFFull;
+    return fma(2.0, __builtin_bit_cast(double, m | 0x3FF0000000000000ull), -3.0);
+}
+SWIM_HD void tab64_eval(const TabE64& e, double x, double& Ht, double& H2)
+{
+    double h = e.h[8], g = e.g[8];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) {
+        h = fma(h, x, e.h[k]);
+        g = fma(g, x, e.g[k]);
     }
-    const double rL = sqrt(pb_node_t(C.its, kL));
-    double B = 0.0;
-    for (int p = 0; p < 64; ++p) B += pb_tail_panel(alpha, eps, rL, p, 64);
-    double* Bk = new double[ng];
-    for (int k = kL; k >= kS; --k) {
-        Bk[k] = B;
-        if (k > kS) B += gb[k];
+    Ht = h;
+    H2 = g;
+}
+
+// Host form of the sweep (the device kernel splits the same intervals over a
+// workgroup): node values Ht, H2 of every table interval at the K nodes,
+// fh[i K + k], for any system (C.paper == 2: the sweep).  K = 7 fills the
+// cubic's nodes 0, 2, 4, 6 outside the sweep.
+template <int K> inline void pb_table_host(const SysConst<double>& C, double* fh, double* fg)
+{
+    const bool sweep = C.paper == 2.0;
+    const double alpha = sqrt(C.a2);
+    PbRange R{TAB_N, TAB_N, TAB_N};
+    PbSeries S{};
+    if (sweep) {
+        R = pb_range(C);
+        pb_series(C, S.sh, S.sg);
     }
-    double A = 0.0, Cq = 0.0;
-    for (int k = 1; k <= kL; ++k) {
-        A += ga[k];
-        Cq += gc[k];
-        if (k >= kS) pb_node_sweep(alpha, eps, pb_node_t(C.its, k), A, Bk[k], Cq, C.h1c, fh[k], fg[k]);
+    struct Iv {
+        double fa[K], fb[K], p[K], q[K];
+    };
+    Iv* iv = new Iv[TAB_N];
+    double* Bend = new double[TAB_N + 1];
+    double A = 0.0, D = 0.0, I2 = 0.0;
+    if (sweep) {
+        for (int i = 0; i < R.iE; ++i) {
+            if (i < R.iS) pb_iv_nodes<K, false>(C, alpha, i, iv[i].fa, iv[i].fb, iv[i].p, iv[i].q);
+            else pb_iv_nodes<K, true>(C, alpha, i, iv[i].fa, iv[i].fb, iv[i].p, iv[i].q);
+        }
+        Bend[R.iE] = 0.0;
+        for (int i = R.iE - 1; i >= R.iS; --i) Bend[i] = Bend[i + 1] + lob_total<K>(iv[i].fb);
     }
-    delete[] ga;
-    delete[] gb;
-    delete[] gc;
-    delete[] Bk;
+    for (int i = 0; i < TAB_N; ++i) {
+        double h[K] = {}, g[K] = {};
+        if (sweep && i < R.iS) A += lob_total<K>(iv[i].fa);
+        if (sweep && i >= R.iS && i < R.iF) {
+            if (i == R.iS) {
+                double v0, hv, h0, g0;
+                tab_span(i, v0, hv);
+                const double t0 = (v0 - 1.0) * C.its;
+                pb_series_eval(S.sh, S.sg, t0 * C.inv_e2, h0, g0);
+                I2 = t0 * t0 * g0;
+                D = -2.0 * h0 - t0 * g0;
+            }
+            const double ta = lob_total<K>(iv[i].fa);
+            pb_iv_flux<K>(C, i, A, Bend[i + 1], iv[i].fa, iv[i].fb, iv[i].p, iv[i].q);
+            A += ta;
+            pb_iv_values<K>(C, i, D, I2, iv[i].fa, iv[i].fb, h, g);
+            D += lob_total<K>(iv[i].fa);
+            I2 += lob_total<K>(iv[i].fb);
+        } else {
+            pb_iv_outside<K>(C, i, sweep, R.iS, S.sh, S.sg, h, g);
+        }
+        for (int k = 0; k < K; ++k) {
+            fh[i * K + k] = h[k];
+            fg[i * K + k] = g[k];
+        }
+    }
+    delete[] iv;
+    delete[] Bend;
 }
 
 }  // namespace swim

@@ -21,6 +21,64 @@ template <typename T> struct alignas(2 * sizeof(T)) V2 {
     T x, y;
 };
 
+// The constants of one system by one wave: in T (out) and, if out64 is not
+// null, in FP64 -- the values of sysconst_compute.  The scalars are lane 0's;
+// coefficient n of U and of V (a sum of 40 terms each) is taken by a lane of
+// its own, so that the set-up of a few systems does not wait for one thread's
+// 32 sums in turn (34 us before, for any number of systems up to a thousand).
+template <typename T>
+__device__ inline void sysconst_wave(double alpha, double eps, SysConst<T>* out, SysConst<double>* out64, int blob,
+                                     int lane)
+{
+    const bool pb = blob == 1 && alpha > 0.0;
+    const double g0 = pb ? pb_g0_closed(alpha * eps) : 0.0;
+    // the paper's blob at alpha > 0: its FP64 constants are all scalars, and
+    // its FP32 ones those of the reading's blob but for H1(0) and hoff
+    SysConst<double>* const p64 = sizeof(T) == 8 ? (SysConst<double>*)out : out64;
+    if (pb && p64 && lane == 0) sysconst_paper<double>(alpha, eps, g0, p64);
+    if (pb && sizeof(T) == 8) return;
+    if (lane == 0) {
+        SysConst<double> R;
+        sysconst_scalars<double>(alpha, eps, &R, pb ? 0 : blob);
+        if (!pb && out64) sysconst_cast_scalars<double>(R, out64);
+        if (pb) {
+            R.hoff = R.h1c + 0.5 * g0;
+            R.h1c = -0.5 * g0;
+        }
+        sysconst_cast_scalars<T>(R, out);
+    }
+    static_assert(NT_MAX == 16, "lanes 0..15: U, lanes 16..31: V");
+    if (lane < 32) {
+        double v = 0.0;
+        if (alpha != 0.0) {
+            const double a2 = alpha * alpha, w0 = a2 * (eps * eps), L0 = log(0.25 * w0);
+            const bool isU = lane < 16;
+            const int n = isU ? lane + 1 : lane - 14;  // U: 1..16, V: 2..17
+            double s0 = 0.0, s1 = 0.0, binom = 1.0, wp = 1.0;
+#pragma unroll 4
+            for (int m = 0; m < NSER_SETUP; ++m) {
+                const double p0 = isU ? SETUP_SERIES.I0[m] : SETUP_SERIES.A[m];
+                const double p1 = isU ? SETUP_SERIES.P0[m] : SETUP_SERIES.B[m];
+                if (m >= n) {
+                    s0 += binom * p0 * wp;
+                    s1 += binom * p1 * wp;
+                    binom = binom * (m + 1) * (1.0 / (double)(m - n + 1));
+                    wp *= w0;
+                }
+            }
+            double ap = a2;  // U: a2^n, V: a2^(n - 1)
+            for (int k = 1; k < (isU ? n : n - 1); ++k) ap *= a2;
+            v = (isU ? -0.5 * L0 * s0 + s1 : (n - 1) * (0.5 * L0 * s0 - s1)) * ap;
+        }
+        T* const o = lane < 16 ? out->U + lane : out->V + (lane - 16);
+        *o = (T)v;
+        if (!pb && out64) {
+            double* const o64 = lane < 16 ? out64->U + lane : out64->V + (lane - 16);
+            *o64 = v;
+        }
+    }
+}
+
 // position outside the run bound |x| <= 1e3 (or not finite)
 __device__ __forceinline__ bool bad_t(float x) { return !(fabsf(x) <= 1e3f); }
 __device__ __forceinline__ bool bad_t(double x) { return !(fabs(x) <= 1e3); }
@@ -59,6 +117,45 @@ __device__ __forceinline__ void tab_load_window(const TabSys* g, unsigned char* 
         const int ent = (i / EV - (int)TAB_BIAS) & 2047;
         dst[i] = ent < TAB_N ? src[ent * EV + (i % EV)] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+}
+
+// kernel values of one FP64 pair from its system's table in HBM (the
+// entries of one run, some 30 KB, stay in the caches; nine 16-byte loads per
+// pair): zeros and true for a pair beyond the table
+__device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double ts, double& Ht, double& H2)
+{
+    const double v = fma(t, ts, 1.0);
+    const uint32_t id = tab64_index(v);
+    const bool far = id >= (uint32_t)TAB_N;
+    typedef double f64x2_t __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) f64x2_t* GlobalD2;
+    const GlobalD2 p = (GlobalD2)(uintptr_t)((const char*)tab + (size_t)min(id, (uint32_t)(TAB_N - 1)) * sizeof(TabE64));
+    double c[18];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const f64x2_t w = p[k];
+        c[2 * k] = w.x;
+        c[2 * k + 1] = w.y;
+    }
+    const double x = tab64_x(v);
+    double h = c[8], g = c[17];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) {
+        h = fma(h, x, c[k]);
+        g = fma(g, x, c[9 + k]);
+    }
+    Ht = far ? 0.0 : h;
+    H2 = far ? 0.0 : g;
+    return far;
+}
+
+// direct FP64 evaluation of a pair beyond the table; not inlined, so that
+// its registers stay out of the pair loops
+__device__ __attribute__((noinline)) inline V2<double> kernel_far64(const SysConst<double>& C, double t)
+{
+    V2<double> v;
+    kernel_eval<double>(C, t, v.x, v.y);
+    return v;
 }
 
 // error-free (hi, lo) += d  (TwoSum, then renormalize)
@@ -113,17 +210,29 @@ __device__ __forceinline__ int opaque_uniform(int v)
 // slot of point i in the doubled source array
 __device__ __forceinline__ int src2_slot(int i) { return ((i >> 6) << 7) + (i & 63); }
 
-// kernel functions of one pair at offset (dx, dy).  FP64: direct evaluation.
-// FP32 (positions scaled by rho): the table (FAR = false; a pair beyond it
-// gives zeros and, with CHECK, sets far), or the direct evaluation of pairs
-// beyond the table only (FAR = true; zeros for the others).  H2 comes scaled
-// to the coordinates (H2 / sigma in FP32).
+// kernel functions of one pair at offset (dx, dy) (FP32: positions scaled by
+// rho): the table (FAR = false; a pair beyond it gives zeros and, with CHECK,
+// sets far), or the direct evaluation of pairs beyond the table only (FAR =
+// true; zeros for the others).  H2 comes scaled to the coordinates (H2 / sigma
+// in FP32).  et: FP32 the table in LDS, FP64 in HBM.
 template <typename T, bool FAR, bool CHECK = true, bool WRAP = false>
 __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const char* et, T dx, T dy, T& Ht, T& H2,
                                             bool& far)
 {
     if constexpr (sizeof(T) == 8) {
-        kernel_eval<T>(C, fma_t(dx, dx, dy * dy), Ht, H2);
+        const T t = fma_t(dx, dx, dy * dy);
+        if constexpr (!FAR) {
+            const bool f = tab64_lookup(et, t, C.ts, Ht, H2);
+            if constexpr (CHECK) far = far || f;
+        } else {
+            Ht = (T)0;
+            H2 = (T)0;
+            if (tab64_index(fma_t(t, C.ts, (T)1)) >= (uint32_t)TAB_N) {
+                const V2<T> v = kernel_far64(C, t);
+                Ht = v.x;
+                H2 = v.y;
+            }
+        }
     } else {
         const uint32_t bits = __builtin_bit_cast(uint32_t, fmaf(dx, dx, fmaf(dy, dy, 1.0f)));
         const uint32_t id = bits >> TAB_SHIFT;
@@ -224,20 +333,17 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const char* et
 // without the per-pair test (an index beyond it reads a zero entry).
 // WRAP: tab points at the table's LDS index window (tab_load_window)
 template <typename T, int TPL, int WPS, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const TabSys* tab, const Src4<T>* src2, int n,
+__device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int n,
                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
 #pragma unroll
     for (int c = 0; c < TPL; ++c) accx[c] = accy[c] = (T)0;
-    const char* et = nullptr;
-    if constexpr (WRAP) {
-        // tab is the table's LDS index window
-        et = reinterpret_cast<const char*>(tab);
-    } else if constexpr (sizeof(T) == 4) {
+    const char* et = reinterpret_cast<const char*>(tab);
+    if constexpr (!WRAP && sizeof(T) == 4) {
         // entry of index id at et + (id << 5) bytes: the bias goes into a
         // wave-uniform base (a register operand of the address arithmetic;
         // gfx9 address arithmetic takes no 32-bit literal)
-        et = reinterpret_cast<const char*>(tab->e) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
+        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     }
     const int B = (n + 63) >> 6;
     const int S = 32 * B * B;
@@ -252,7 +358,7 @@ __device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const TabSy
                 const int s_lo = lo - g + base, s_hi = hi - g + base;
                 const bool far =
                     sym_offsets<T, TPL, false, CHECK, WRAP>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
-                if constexpr (sizeof(T) == 4 && CHECK) {
+                if constexpr (CHECK) {
                     if (__any(far)) sym_offsets<T, TPL, true>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
                 }
             }
@@ -293,19 +399,17 @@ __device__ __forceinline__ bool sym_one_segment(int n, int wave, int& sa, int& s
 // pair_phase_sym for a wave whose share is the one segment found by
 // sym_one_segment (same sums, same order)
 template <typename T, int TPL, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ void pair_phase_seg(const SysConst<T>& C, const TabSys* tab, const Src4<T>* src2, int a,
+__device__ __forceinline__ void pair_phase_seg(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int a,
                                                int b, int s_lo, int s_hi, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
 #pragma unroll
     for (int c = 0; c < TPL; ++c) accx[c] = accy[c] = (T)0;
-    const char* et = nullptr;
-    if constexpr (WRAP) {
-        et = reinterpret_cast<const char*>(tab);
-    } else if constexpr (sizeof(T) == 4) {
-        et = reinterpret_cast<const char*>(tab->e) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
+    const char* et = reinterpret_cast<const char*>(tab);
+    if constexpr (!WRAP && sizeof(T) == 4) {
+        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     }
     const bool far = sym_offsets<T, TPL, false, CHECK, WRAP>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
-    if constexpr (sizeof(T) == 4 && CHECK) {
+    if constexpr (CHECK) {
         if (__any(far)) sym_offsets<T, TPL, true>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
     }
 }
@@ -345,7 +449,7 @@ __host__ __device__ constexpr bool tail_pays(int n)
 // sym_one_segment for 64 Bf points (seg[0] != 0: a single segment a = seg[1],
 // b = seg[2], offsets [seg[3], seg[4])), or null
 template <typename T, int TPL, int WPS>
-__device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const TabSys* tab, const Src4<T>* src2, int n,
+__device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int n,
                                                 int wave, int lane, T (&accx)[TPL], T (&accy)[TPL],
                                                 const int* seg = nullptr)
 {
@@ -354,9 +458,9 @@ __device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const TabS
         pair_phase_seg<T, TPL>(C, tab, src2, seg[1], seg[2], seg[3], seg[4], lane, accx, accy);
     else
         pair_phase_sym<T, TPL, WPS>(C, tab, src2, 64 * Bf, wave, lane, accx, accy);
-    const char* et = nullptr;
+    const char* et = reinterpret_cast<const char*>(tab);
     if constexpr (sizeof(T) == 4)
-        et = reinterpret_cast<const char*>(tab->e) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
+        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     const bool tl_live = lane < r;
     const Src4<T> tp = src2[src2_slot(64 * Bf + (tl_live ? lane : r - 1))];
     for (int j = wave; j < r; j += WPS) {
@@ -397,9 +501,7 @@ __device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const TabS
             }
         };
         pass(std::integral_constant<bool, false>());
-        if constexpr (sizeof(T) == 4) {
-            if (__any(far)) pass(std::integral_constant<bool, true>());
-        }
+        if (__any(far)) pass(std::integral_constant<bool, true>());
         bx = wave_total(bx);
         by = wave_total(by);
 #pragma unroll

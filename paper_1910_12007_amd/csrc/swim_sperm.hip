@@ -259,7 +259,7 @@ __host__ __device__ constexpr SpermLdsLayout sperm_lds_layout(int dtype, int tpl
 
 template <typename T, int TPL, int WPS>
 __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, const SysConst<T>& C,
-                             const TabSys* tab_g, TabSys* tab, Src4<T>* src, V2<T>* part, PosE<T>* pos, int* badw,
+                             const void* tab_g, TabSys* tab_s, Src4<T>* src, V2<T>* part, PosE<T>* pos, int* badw,
                              T* head, T* tail, int32_t* status)
 {
     constexpr bool COMP = sizeof(T) == 4;
@@ -281,7 +281,12 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
         __syncthreads();
         return;
     }
-    if constexpr (COMP) tab_load(tab_g + s, tab, tid, NT);
+    // FP32: the system's table copied into LDS; FP64 reads it in place
+    const void* tab = (const TabSys64*)tab_g + s;
+    if constexpr (COMP) {
+        tab_load((const TabSys*)tab_g + s, tab_s, tid, NT);
+        tab = tab_s;
+    }
     SpermK<T> K;
     K.kc2 = (T)(2.0 * sp[SWIM_SP_KC]);
     K.kt2 = (T)(2.0 * sp[SWIM_SP_KT]);
@@ -501,7 +506,7 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
 
 template <typename T, int TPL, int WPS>
 __global__ __launch_bounds__(64 * WPS) void k_sperm_forward(SpermShape g, SpermRun r, const SysConst<T>* sysc,
-                                                            const TabSys* tabs, int32_t* queue, T* head, T* tail,
+                                                            const void* tabs, int32_t* queue, T* head, T* tail,
                                                             int32_t* status)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -523,20 +528,23 @@ __global__ __launch_bounds__(64 * WPS) void k_sperm_forward(SpermShape g, SpermR
     }
 }
 
-// per-system constants; rows outside the model's domain are flagged
+// per-system constants, one wave per system; rows outside the model's domain
+// are flagged
 template <typename T>
-__global__ void k_sperm_setup(int64_t n_sys, int32_t nsw, double eps, const double* sysp, const double* swp,
-                              SysConst<T>* sysc, SysConst<double>* sysc64, int32_t* status, int blob)
+__global__ __launch_bounds__(64) void k_sperm_setup(int32_t nsw, double eps, const double* sysp, const double* swp,
+                                                    SysConst<T>* sysc, SysConst<double>* sysc64, int32_t* status,
+                                                    int blob)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n_sys) return;
+    const int64_t s = blockIdx.x;
+    const int lane = threadIdx.x;
     const double* p = sysp + (int64_t)SWIM_SP_NPARAM * s;
     const double alpha = p[SWIM_SP_ALPHA];
     bool ok = isfinite(alpha) && alpha >= 0.0 && alpha * eps <= 1.0;
-    for (int c = 0; c < SWIM_SP_NPARAM; ++c) ok = ok && isfinite(p[c]);
-    for (int c = 0; c < 3 * nsw; ++c) ok = ok && isfinite(swp[(int64_t)3 * nsw * s + c]);
-    status[s] = ok ? 0 : ST_BADPARAM;
-    sysconst_compute2<T>(ok ? alpha : 0.0, eps, sysc + s, sysc64 ? sysc64 + s : nullptr, blob);
+    for (int c = lane; c < SWIM_SP_NPARAM; c += 64) ok = ok && isfinite(p[c]);
+    for (int c = lane; c < 3 * nsw; c += 64) ok = ok && isfinite(swp[(int64_t)3 * nsw * s + c]);
+    ok = __all(ok);
+    if (lane == 0) status[s] = ok ? 0 : ST_BADPARAM;
+    sysconst_wave<T>(ok ? alpha : 0.0, eps, sysc + s, sysc64 ? sysc64 + s : nullptr, blob, lane);
 }
 
 // observables of a sperm run per system s and interval/sample k = 1..n_obs
@@ -609,7 +617,7 @@ hipError_t launch_sperm_t(int nblocks, const SpermShape& g, const SpermRun& r, c
 {
     const size_t lds = sperm_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS).total;
     hipLaunchKernelGGL((k_sperm_forward<T, TPL, WPS>), dim3(nblocks), dim3(64 * WPS), lds, st, g, r,
-                       (const SysConst<T>*)sysc, (const TabSys*)tabs, queue, (T*)head, (T*)tail, status);
+                       (const SysConst<T>*)sysc, tabs, queue, (T*)head, (T*)tail, status);
     return hipGetLastError();
 }
 
@@ -648,12 +656,12 @@ hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps,
                               hipStream_t st)
 {
     if (n_sys == 0) return hipSuccess;
-    const int nb = (int)((n_sys + 255) / 256);
+    const unsigned nb = (unsigned)n_sys;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_sperm_setup<float>, dim3(nb), dim3(256), 0, st, n_sys, nsw, eps, sysp, swp,
+        hipLaunchKernelGGL(k_sperm_setup<float>, dim3(nb), dim3(64), 0, st, nsw, eps, sysp, swp,
                            (SysConst<float>*)sysc, (SysConst<double>*)sysc64, status, blob);
     else
-        hipLaunchKernelGGL(k_sperm_setup<double>, dim3(nb), dim3(256), 0, st, n_sys, nsw, eps, sysp, swp,
+        hipLaunchKernelGGL(k_sperm_setup<double>, dim3(nb), dim3(64), 0, st, nsw, eps, sysp, swp,
                            (SysConst<double>*)sysc, (SysConst<double>*)nullptr, status, blob);
     return hipGetLastError();
 }
