@@ -62,7 +62,7 @@ struct DevBuf {
 enum BufId {
     B_OFF, B_SWOFF, B_NPT, B_NSW, B_ORDER, B_LIST, B_BLKS, B_BLKF, B_ALPHA, B_EPS, B_SYSC, B_QUEUE,
     B_PARAMS, B_DATA, B_OBS, B_SPEED, B_STATUS, B_DIST, B_TOL, B_ACC, B_BIG,
-    B_MLP_ACT, B_MLP_GRAD, B_MLP_BATCH, B_MLP_IDX, B_MLP_CNT,
+    B_MLP_ACT, B_MLP_IDX, B_MLP_CNT,
     B_PS_THETA, B_PS_X, B_PS_KEEP, B_PS_IDX, B_PS_NK, B_PS_SUM, B_DS_T, B_TAB, B_DONE, B_W16, B_SIGMA, B_LOGL,
     B_SP_SW, B_SP_HEAD, B_SP_TAIL, B_SP_G, B_SP_SIG, B_WTAB,
     B_BT_PSYS, B_BT_PT, B_BT_TSYS, B_BT_TT, B_BT_POFF, B_BT_PART,
@@ -79,7 +79,6 @@ int64_t mlp_offW(int l)
     return o;
 }
 int64_t mlp_offb(int l) { return mlp_offW(l) + (int64_t)MLP_W[l] * MLP_W[l + 1]; }
-constexpr int64_t MLP_NPARAM = 207393;
 
 }  // namespace
 
@@ -817,92 +816,64 @@ int forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, co
 }
 
 // ------------------------------------------------------------------------
-// surrogate MLP: forward and backward over M rows (workspace in the ctx)
-// activation workspace layout (floats): pre[4][M*256], H[4][M*256],
-// Y[M*33], dY[M*33], dA[2][M*256], rowsq[M]
+// surrogate MLP: workspace and constants of a training step over M rows
 // ------------------------------------------------------------------------
-struct MlpAct {
-    float* pre[4];
-    float* H[4];
-    float *Y, *dY, *dA[2], *sq;
-    MlpWs ws;  // split-K partial sums of the GEMMs
-};
-
-int mlp_act(swim_ctx* c, int64_t M, MlpAct* a)
+// The sums of C[M][N] over K run in slices of this many 32-wide pieces: as
+// many slices (at most 16) as it takes to spread the 64 x 64 tiles of C over
+// 256 compute units.  The kernels keep the slices as separate accumulators
+// whatever their own launch shape is, so the rule fixes the rounding.
+int mlp_slice(int64_t M, int64_t N, int64_t K)
 {
-    const int64_t H = 256, O = 33;
-    const int64_t ws = 1 << 20;  // partial sums: 16 slices of 256 x 256, or 4 of 1024 x 256
-    const int64_t total = 8 * M * H + 2 * M * O + 2 * M * H + M * O + ws;
-    TRY(ensure(c, B_MLP_ACT, (size_t)total * 4));
-    float* p = (float*)c->buf[B_MLP_ACT].p;
-    for (int l = 0; l < 4; ++l) a->pre[l] = p + l * M * H;
-    for (int l = 0; l < 4; ++l) a->H[l] = p + (4 + l) * M * H;
-    a->Y = p + 8 * M * H;
-    a->dY = a->Y + M * O;
-    a->dA[0] = a->dY + M * O;
-    a->dA[1] = a->dA[0] + M * H;
-    a->sq = a->dA[1] + M * H;
-    a->ws.part = a->sq + M * O;
-    a->ws.part_floats = ws;
-    return SWIM_OK;
+    const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64), chunks = (K + 31) / 32;
+    int64_t S = 1, kper = chunks;
+    if (chunks >= 2 && tiles < 256) {
+        S = std::min<int64_t>({chunks, (256 + tiles - 1) / tiles, 16});
+        while (S > 1 && S * M * N > (1 << 20)) --S;
+        kper = (chunks + S - 1) / S;
+    }
+    return (int)kper;
 }
 
-// forward pass; with T (training), the output layer's epilogue also forms
-// the gradient of the squared error, dY = 2 (Y - T) / (M 33), and the
-// squared errors (a.dY, a.sq)
-int mlp_forward(const float* X, const float* P, int64_t M, const MlpAct& a, float* Y, hipStream_t st,
-                const float* T = nullptr)
+// fills the parts of a step and its update that depend on M alone
+int mlp_plan(swim_ctx* c, int64_t M, MlpStep* a, MlpUpdate* u)
 {
-    const float* in = X;
-    int64_t ldin = MLP_W[0];
-    for (int l = 0; l < MLP_L; ++l) {
-        const int K = MLP_W[l], N = MLP_W[l + 1];
-        const float* W = P + mlp_offW(l);
-        GemmEpi E;
-        E.bias = P + mlp_offb(l);
-        if (l < MLP_L - 1) {
-            E.aux = a.H[l];
-            HIPCHK(launch_gemm_bf16(1, (int)M, N, K, in, ldin, 1, W, N, 1, a.pre[l], N, E, a.ws, st));
-            in = a.H[l];
-            ldin = N;
-        } else if (T) {
-            E.aux = a.dY;
-            E.T = T;
-            E.sq = a.sq;
-            E.sc = 2.0f / ((float)M * (float)N);
-            HIPCHK(launch_gemm_bf16(4, (int)M, N, K, in, ldin, 1, W, N, 1, Y, N, E, a.ws, st));
-        } else {
-            HIPCHK(launch_gemm_bf16(2, (int)M, N, K, in, ldin, 1, W, N, 1, Y, N, E, a.ws, st));
-        }
-    }
-    return SWIM_OK;
-}
-
-// gradients of the squared error into G (layout of the parameters), after
-// mlp_forward with the targets; loss (device, optional) = the sum of the
-// M x 33 squared errors
-int mlp_backward(const float* X, const float* P, int64_t M, const MlpAct& a, float* G, float* loss, hipStream_t st)
-{
-    const int O = MLP_W[MLP_L];
-    if (loss) HIPCHK(launch_sum(M * O, a.sq, loss, st));
-    const float* dA = a.dY;
-    int cur = 0;
-    for (int l = MLP_L - 1; l >= 0; --l) {
-        const int K = MLP_W[l], N = MLP_W[l + 1];
-        const float* Hin = l > 0 ? a.H[l - 1] : X;
-        // dW_l = Hin^T dA  (K x N, summed over the M rows)
-        HIPCHK(launch_gemm_bf16(0, K, N, (int)M, Hin, 1, K, dA, N, 1, G + mlp_offW(l), N, GemmEpi(), a.ws, st));
-        HIPCHK(launch_colsum((int)M, N, dA, N, G + mlp_offb(l), st));
-        if (l > 0) {
-            // dA_{l-1} = (dA W_l^T) * gelu'(pre_{l-1})
-            float* out = a.dA[cur];
-            GemmEpi E;
-            E.aux = a.pre[l - 1];
-            HIPCHK(launch_gemm_bf16(3, (int)M, K, N, dA, N, 1, P + mlp_offW(l), 1, N, out, K, E, a.ws, st));
-            dA = out;
-            cur ^= 1;
-        }
-    }
+    const int64_t Mpad = (M + 31) / 32 * 32;
+    const int H = MLP_W[1], O = MLP_W[MLP_L];
+    *a = MlpStep{};
+    *u = MlpUpdate{};
+    a->M = u->M = M;
+    a->Mpad = u->Mpad = Mpad;
+    a->sc = 2.0f / ((float)M * (float)O);
+    a->kf = a->kb = mlp_slice(M, H, H);
+    a->ko = mlp_slice(M, O, H);
+    a->kb4 = mlp_slice(M, H, O);
+    u->kw = mlp_slice(H, H, M);
+    u->kw4 = mlp_slice(H, O, M);
+    u->kw0 = mlp_slice(MLP_W[0], H, M);
+    // 16 rows per workgroup fill four times as many CUs at the usual batch of
+    // 1024; with two tiles the weights are read from L2 half as often
+    a->rt = M >= 8192 ? 2 : 1;
+    u->nwg = Mpad / (16 * a->rt);
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = (o + bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t oW = take((size_t)mlp_pack_count() * 2), oX = take((size_t)16 * Mpad * 2),
+                 oH = take((size_t)4 * H * Mpad * 2), oD = take((size_t)4 * H * Mpad * 2),
+                 oY = take((size_t)48 * Mpad * 2), oB = take((size_t)MLP_DBN * Mpad * 4),
+                 oL = take((size_t)u->nwg * 3 * 4);
+    TRY(ensure(c, B_MLP_ACT, o));
+    char* p = (char*)c->buf[B_MLP_ACT].p;
+    u->W = (uint16_t*)(p + oW);
+    a->W = u->W;
+    u->XT = a->XT = (uint16_t*)(p + oX);
+    u->HT = a->HT = (uint16_t*)(p + oH);
+    u->DT = a->DT = (uint16_t*)(p + oD);
+    u->YT = a->YT = (uint16_t*)(p + oY);
+    u->DF = a->DF = (float*)(p + oB);
+    u->lossp = a->lossp = (float*)(p + oL);
     return SWIM_OK;
 }
 
@@ -1777,10 +1748,18 @@ int surrogate_grad(swim_ctx* c, int64_t n, const float* X, const float* T, const
     TRY(check_ctx(c));
     if (n < 1 || n > (1 << 20) || !X || !T || !params || !grads) return fail(SWIM_EINVAL, "bad surrogate_grad arguments");
     hipStream_t st = pick(c, stream);
-    MlpAct a;
-    TRY(mlp_act(c, n, &a));
-    TRY(mlp_forward(X, params, n, a, a.Y, st, T));
-    TRY(mlp_backward(X, params, n, a, grads, loss, st));
+    MlpStep a;
+    MlpUpdate u;
+    TRY(mlp_plan(c, n, &a, &u));
+    a.X = X;
+    a.T = T;
+    a.nrows = n;
+    a.P = params;
+    u.g = grads;
+    u.loss = loss;
+    HIPCHK(launch_mlp_pack(params, u.W, st));
+    HIPCHK(launch_mlp_step(a, st));
+    HIPCHK(launch_mlp_update(false, u, st));
     return SWIM_OK;
 }
 
@@ -1792,25 +1771,32 @@ int surrogate_train(swim_ctx* c, int64_t n, const float* X, const float* T, cons
         !adam_m || !adam_v)
         return fail(SWIM_EINVAL, "bad surrogate_train arguments");
     hipStream_t st = pick(c, stream);
-    MlpAct a;
-    TRY(mlp_act(c, batch, &a));
-    TRY(ensure(c, B_MLP_GRAD, (size_t)MLP_NPARAM * 4));
-    TRY(ensure(c, B_MLP_BATCH, (size_t)batch * (MLP_W[0] + MLP_W[MLP_L]) * 4));
-    float* G = (float*)c->buf[B_MLP_GRAD].p;
-    float* Xb = (float*)c->buf[B_MLP_BATCH].p;
-    float* Tb = Xb + (size_t)batch * MLP_W[0];
-    const int64_t spe = n / batch;
+    MlpStep a;
+    MlpUpdate u;
+    TRY(mlp_plan(c, batch, &a, &u));
     const double b1 = 0.9, b2 = 0.999;
+    a.X = X;
+    a.T = T;
+    a.nrows = n;
+    a.P = u.p = params;
+    u.m = adam_m;
+    u.v = adam_v;
+    u.lr = lr;
+    u.b1 = (float)b1;
+    u.b2 = (float)b2;
+    u.eps = 1e-8f;
+    const int64_t spe = n / batch;
     int64_t t = 0;
+    HIPCHK(launch_mlp_pack(params, u.W, st));
     for (int e = 0; e < epochs; ++e) {
         for (int64_t s = 0; s < spe; ++s) {
             ++t;
-            HIPCHK(launch_gather_rows(batch, perm + (int64_t)e * n + s * batch, n, X, MLP_W[0], T, MLP_W[MLP_L], Xb, Tb,
-                                      st));
-            TRY(mlp_forward(Xb, params, batch, a, a.Y, st, Tb));
-            TRY(mlp_backward(Xb, params, batch, a, G, loss_out ? loss_out + e * spe + s : nullptr, st));
-            HIPCHK(launch_adam(MLP_NPARAM, params, G, adam_m, adam_v, lr, (float)b1, (float)b2,
-                               (float)(1.0 - std::pow(b1, (double)t)), (float)(1.0 - std::pow(b2, (double)t)), 1e-8f, st));
+            a.perm = perm + (int64_t)e * n + s * batch;
+            u.loss = loss_out ? loss_out + e * spe + s : nullptr;
+            u.c1 = (float)(1.0 - std::pow(b1, (double)t));
+            u.c2 = (float)(1.0 - std::pow(b2, (double)t));
+            HIPCHK(launch_mlp_step(a, st));
+            HIPCHK(launch_mlp_update(true, u, st));
         }
     }
     return SWIM_OK;

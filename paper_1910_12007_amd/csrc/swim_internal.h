@@ -121,32 +121,35 @@ hipError_t launch_gauss_loglik(int dtype, int64_t n, int32_t n_obs, const void* 
                                const double* sigma, const int32_t* status, double* logl, hipStream_t st);
 
 // surrogate MLP (swim_mlp.hip)
-// operands of the GEMM epilogues (unused ones may be null)
-struct GemmEpi {
-    const float* bias = nullptr;  // [N]
-    float* aux = nullptr;         // GELU: H out; DGELU: pre-activations in; MSE: dY out
-    const float* T = nullptr;     // MSE: targets [M][N]
-    float* sq = nullptr;          // MSE: squared errors out [M][N]
-    float sc = 0.0f;              // MSE: 2 / (M N)
+// one training step (swim_mlp.hip): rows through the network and back ...
+constexpr int MLP_DBN = 4 * 256 + 33;  // biases: hidden layers, then the outputs
+struct MlpStep {
+    const float *X, *T;         // [nrows][5], [nrows][33]
+    const int32_t* perm;        // rows of the batch (null: 0..M-1); an index outside [0, nrows) gives a NaN row
+    int64_t nrows, M, Mpad;     // rows of X and T, of the batch, the batch padded to 32
+    const float* P;             // parameters (the biases are read)
+    const uint16_t* W;          // packed bfloat16 weights (launch_mlp_pack)
+    uint16_t *XT, *HT, *DT, *YT;  // feature-major bfloat16 [16], [4][256], [4][256], [48] x Mpad
+    float* DF;                  // gradients in FP32, feature-major [MLP_DBN] x Mpad
+    float* lossp;               // squared errors [3] per workgroup
+    float sc;                   // 2 / (33 M)
+    int kf, ko, kb, kb4;        // 32-wide pieces per slice of the sums: hidden, output, back, back from the output
+    int rt;                     // 16-row tiles per workgroup (1 or 2)
 };
-// workspace of the split-K partial sums
-struct MlpWs {
-    float* part = nullptr;
-    int64_t part_floats = 0;
+// ... then weight gradients with Adam (or into g)
+struct MlpUpdate {
+    int64_t M, Mpad, nwg;       // nwg: workgroups of the step
+    const uint16_t *XT, *HT, *DT, *YT;
+    const float *DF, *lossp;
+    float *p, *m, *v, *g, *loss;  // loss may be null
+    uint16_t* W;
+    int kw, kw4, kw0;           // 32-row pieces per slice: hidden layers, output, input
+    float lr, b1, b2, c1, c2, eps;
 };
-// epi: 0 plain, 1 bias + GELU, 2 bias, 3 times GELU', 4 bias + MSE gradient
-hipError_t launch_gemm_bf16(int epi, int M, int N, int K, const float* A, int64_t sam, int64_t sak,
-                            const float* B, int64_t sbk, int64_t sbn, float* C, int64_t ldc,
-                            const GemmEpi& E, const MlpWs& ws, hipStream_t st);
-hipError_t launch_colsum(int M, int N, const float* A, int64_t lda, float* out, hipStream_t st);
-hipError_t launch_sum(int64_t n, const float* v, float* out, hipStream_t st);
-hipError_t launch_gather_rows(int M, const int32_t* perm, int64_t nrows, const float* X, int nx,
-                              const float* T, int nt, float* Xb, float* Tb, hipStream_t st);
-hipError_t launch_adam(int64_t n, float* p, const float* g, float* m, float* v, float lr, float b1,
-                       float b2, float c1, float c2, float eps, hipStream_t st);
-hipError_t launch_prescreen(int M, int N, int n_sum, const float* Y, const float* mu,
-                            const float* sd, const float* obs, float tol, float* dist,
-                            uint8_t* keep, hipStream_t st);
+int64_t mlp_pack_count();
+hipError_t launch_mlp_pack(const float* P, uint16_t* W, hipStream_t st);
+hipError_t launch_mlp_step(const MlpStep& a, hipStream_t st);
+hipError_t launch_mlp_update(bool adam, const MlpUpdate& u, hipStream_t st);
 hipError_t launch_compact(int64_t n, const uint8_t* keep, int32_t* counts, int64_t* idx,
                           int64_t* total, hipStream_t st);
 hipError_t launch_features(int64_t n, const double* theta, double b, double om, const float* mu,

@@ -1,16 +1,12 @@
-// swim_mlp.hip -- gfx950 kernels of the MLP surrogate: a BF16 MFMA GEMM
-// (v_mfma_f32_16x16x16bf16_1k, FP32 accumulation) with fused epilogues for
-// the forward layers (bias, GELU) and the backward pass (GELU'), column sums
-// for the bias gradients, the MSE loss gradient, Adam, and the prescreen
-// distance of ABC proposals.
+// swim_mlp.hip -- gfx950 kernels of the MLP surrogate: fused inference (all
+// layers per workgroup), a training step in two launches (the whole network
+// forward and back per block of rows; weight gradients with Adam), and the
+// data preparation, prescreen distance and compaction around them.
 //
-// GEMM operands are read as FP32 and rounded to bfloat16 (nearest, ties to
-// even) while they are staged into LDS, so the network computes with BF16
-// weights and activations and FP32 accumulation; FP32 master weights are
-// kept for Adam.
+// Every GEMM operand is rounded to bfloat16 (nearest, ties to even) and
+// products accumulate in FP32 on MFMA; FP32 master weights are kept for Adam.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <math.h>
 #include <stdint.h>
 
@@ -68,258 +64,11 @@ __device__ __forceinline__ float gelu_grad_f(float x)
     return fmaf(x, pdf, cdf);
 }
 
-// C(m, n) = sum_k A(m, k) B(k, n), A(m, k) = A[m*sam + k*sak],
-// B(k, n) = B[k*sbk + n*sbn], C(m, n) at C[m*ldc + n].  Epilogues:
-//   MLP_EPI_PLAIN  C = acc
-//   MLP_EPI_GELU   pre = acc + bias[n] -> C;  H = gelu(pre) -> aux
-//   MLP_EPI_BIAS   C = acc + bias[n]
-//   MLP_EPI_DGELU  C = acc * gelu'(aux(m, n))   (aux = pre-activations)
-//   MLP_EPI_MSE    Y = acc + bias[n] -> C; with d = Y - T(m, n):
-//                  dY = sc d -> aux (sc = 2 / (M N)), d^2 -> sq  (ldc = N)
-// Workgroup tile 64 x 64 (4 waves of 32 x 32 = 2 x 2 MFMA tiles), k chunks of 32.
-constexpr int GT = 64, GK = 32, GPAD = 8;
-
-// epilogue of one output element (the split-K fixup applies it too)
-template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(float v, int n, int64_t o, float* __restrict__ C, const GemmEpi& E)
+__device__ __forceinline__ float mlp_wave_sum(float v)
 {
-    if (EPI == 1) {
-        v += E.bias[n];
-        C[o] = v;
-        E.aux[o] = gelu_f(v);
-    } else if (EPI == 2) {
-        C[o] = v + E.bias[n];
-    } else if (EPI == 3) {
-        C[o] = v * gelu_grad_f(E.aux[o]);
-    } else if (EPI == 4) {
-        v += E.bias[n];
-        C[o] = v;
-        const float d = v - E.T[o];
-        E.aux[o] = E.sc * d;
-        E.sq[o] = d * d;
-    } else {
-        C[o] = v;
-    }
-}
-
-// Split K: with part != nullptr, workgroup z of the grid's third dimension
-// takes the k chunks [z kper, (z + 1) kper) and writes its raw sums to
-// part[z][M][N]; k_gemm_reduce adds the slices in order of z and applies the
-// epilogue (deterministic).  This fills the chip when the M x N tiles are
-// few (the weight gradients: 256 x 256 outputs summed over a batch of 1024).
-// (A last-arriving-workgroup reduction inside the GEMM was tried: its
-// device-scope fences, which write back the L2 of the XCD, made the GEMMs
-// 3-5x slower than the second launch.)
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_bf16(int M, int N, int K, const float* __restrict__ A, int64_t sam,
-                                                   int64_t sak, const float* __restrict__ B, int64_t sbk, int64_t sbn,
-                                                   float* __restrict__ C, int64_t ldc, GemmEpi E,
-                                                   float* __restrict__ part, int kper)
-{
-    __shared__ uint16_t As[GT][GK + GPAD];   // [m][k]
-    __shared__ uint16_t Bs[GT][GK + GPAD];   // [n][k]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4_t acc[2][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // consecutive threads take consecutive addresses of each operand: along k
-    // when its k stride is 1, along m (n) otherwise (the transposed operands
-    // of the backward pass)
-    const bool a_k_fast = sak == 1, b_n_fast = sbn == 1 || sbk != 1;
-    const int kbeg = part ? (int)blockIdx.z * kper * GK : 0;
-    const int kend = part ? min(K, kbeg + kper * GK) : K;
-    // the next chunk's operands are fetched into registers while the
-    // current chunk's MFMAs run
-    constexpr int PER = (GT * GK) / 256;
-    float ra[PER], rb[PER];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            const int r = a_k_fast ? e / GK : e % GT, kk = a_k_fast ? e % GK : e / GT;
-            const int m = m0 + r, k = k0 + kk;
-            ra[i] = (m < M && k < K) ? A[(int64_t)m * sam + (int64_t)k * sak] : 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            const int kk = b_n_fast ? e / GT : e % GK, c = b_n_fast ? e % GT : e / GK;
-            const int n = n0 + c, k = k0 + kk;
-            rb[i] = (n < N && k < K) ? B[(int64_t)k * sbk + (int64_t)n * sbn] : 0.0f;
-        }
-    };
-    if (kbeg < kend) fetch(kbeg);
-    for (int k0 = kbeg; k0 < kend; k0 += GK) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            const int r = a_k_fast ? e / GK : e % GT, kk = a_k_fast ? e % GK : e / GT;
-            As[r][kk] = f2bf(ra[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int e = tid + 256 * i;
-            const int kk = b_n_fast ? e / GT : e % GK, c = b_n_fast ? e % GT : e / GK;
-            Bs[c][kk] = f2bf(rb[i]);
-        }
-        __syncthreads();
-        if (k0 + GK < kend) fetch(k0 + GK);
-#pragma unroll
-        for (int ks = 0; ks < GK; ks += 16) {
-            // operand layout of the 16x16x16 MFMA: lane l holds row (l % 16)
-            // and k = 4 (l / 16) .. 4 (l / 16) + 3 of its 16-wide k slice
-            const int kq = ks + 4 * (lane >> 4);
-            bf16x4_t av[2], bv[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                // 8-byte aligned: rows of GK + GPAD = 40 elements, kq % 4 == 0
-                av[t] = __builtin_bit_cast(bf16x4_t, *reinterpret_cast<const uint2*>(&As[wm + 16 * t + (lane & 15)][kq]));
-                bv[t] = __builtin_bit_cast(bf16x4_t, *reinterpret_cast<const uint2*>(&Bs[wn + 16 * t + (lane & 15)][kq]));
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[a], bv[b], acc[a][b], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // result layout: lane l holds column (l % 16), rows 4 (l / 16) + r
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm + 16 * a + 4 * (lane >> 4) + r;
-                const int n = n0 + wn + 16 * b + (lane & 15);
-                if (m >= M || n >= N) continue;
-                if (part)
-                    part[((int64_t)blockIdx.z * M + m) * N + n] = acc[a][b][r];
-                else
-                    gemm_epilogue<EPI>(acc[a][b][r], n, (int64_t)m * ldc + n, C, E);
-            }
-}
-
-// C(m, n) = sum over z of part[z][m][n], z ascending, then the epilogue.  The
-// S <= GEMM_MAX_SPLIT loads are issued before the sum (independent, not a
-// chain of dependent load latencies).
-constexpr int GEMM_MAX_SPLIT = 16;
-template <int EPI>
-__global__ void k_gemm_reduce(int M, int N, int S, const float* __restrict__ part, float* __restrict__ C, int64_t ldc,
-                              GemmEpi E)
-{
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)M * N) return;
-    const int m = (int)(e / N), n = (int)(e % N);
-    float p[GEMM_MAX_SPLIT];
-#pragma unroll
-    for (int z = 0; z < GEMM_MAX_SPLIT; ++z) p[z] = z < S ? part[(int64_t)z * M * N + e] : 0.0f;
-    float v = 0.0f;
-#pragma unroll
-    for (int z = 0; z < GEMM_MAX_SPLIT; ++z)
-        if (z < S) v += p[z];
-    gemm_epilogue<EPI>(v, n, (int64_t)m * ldc + n, C, E);
-}
-
-// out[n] = sum_m A[m*lda + n]  (bias gradients): a workgroup of 1024
-// threads sums 8 columns, 128 row groups each summing every 128th row (8
-// rows for a batch of 1024, loads issued ahead of the adds), then the 128
-// partial sums of a column in a fixed tree (deterministic)
-__global__ __launch_bounds__(1024) void k_colsum(int M, int N, const float* __restrict__ A, int64_t lda,
-                                                 float* __restrict__ out)
-{
-    __shared__ float part[128][9];
-    const int c = threadIdx.x & 7, g = threadIdx.x >> 3;
-    const int n = blockIdx.x * 8 + c;
-    float s = 0.f;
-    if (n < N) {
-        int m = g;
-        for (; m + 128 * 7 < M; m += 128 * 8) {
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = A[(int64_t)(m + 128 * j) * lda + n];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += v[j];
-        }
-        for (; m < M; m += 128) s += A[(int64_t)m * lda + n];
-    }
-    part[g][c] = s;
-    __syncthreads();
-    for (int w = 64; w >= 1; w >>= 1) {
-        if (g < w) part[g][c] += part[g + w][c];
-        __syncthreads();
-    }
-    if (g == 0 && n < N) out[n] = part[0][c];
-}
-
-// out[0] = sum of v[0..n): one workgroup of 1024 threads, each summing a
-// strided share, then a fixed tree (the training loss)
-__global__ __launch_bounds__(1024) void k_sum(int64_t n, const float* __restrict__ v, float* __restrict__ out)
-{
-    __shared__ float part[1024];
-    float s = 0.f;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) s += v[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 512; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = part[0];
-}
-
-// rows of X and T picked by perm[0..M) into the batch buffers; an index
-// outside [0, nrows) yields a NaN row (the loss turns NaN) instead of a read
-// out of bounds
-__global__ void k_gather_rows(int M, const int32_t* perm, int64_t nrows, const float* X, int nx, const float* T, int nt,
-                              float* Xb, float* Tb)
-{
-    const int m = blockIdx.x;
-    if (m >= M) return;
-    const int64_t src = perm[m];
-    const bool ok = src >= 0 && src < nrows;
-    for (int c = threadIdx.x; c < nx + nt; c += blockDim.x) {
-        if (c < nx) Xb[(int64_t)m * nx + c] = ok ? X[src * nx + c] : NAN;
-        else Tb[(int64_t)m * nt + c - nx] = ok ? T[src * nt + c - nx] : NAN;
-    }
-}
-
-// Adam with bias-corrected moments: p -= lr mhat / (sqrt(vhat) + eps)
-__global__ void k_adam(int64_t n, float* p, const float* g, float* m, float* v, float lr, float b1, float b2, float c1,
-                       float c2, float eps)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = fmaf(b1, m[i], (1.0f - b1) * gi);
-    const float vi = fmaf(b2, v[i], (1.0f - b2) * gi * gi);
-    m[i] = mi;
-    v[i] = vi;
-    const float mh = mi / c1, vh = vi / c2;
-    p[i] -= lr * mh / (sqrtf(vh) + eps);
-}
-
-// Prescreen distance: de-standardize the predicted summaries, compare with the
-// observed summaries: d = sqrt(mean_j (mu_j + sd_j y_j - obs_j)^2) over the
-// first n_sum outputs; keep[m] = d <= tol.
-__global__ void k_prescreen(int M, int N, int n_sum, const float* Y, const float* mu, const float* sd,
-                            const float* obs, float tol, float* dist, uint8_t* keep)
-{
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= M) return;
-    float s = 0.f;
-    for (int j = 0; j < n_sum; ++j) {
-        const float d = fmaf(sd[j], Y[(int64_t)m * N + j], mu[j]) - obs[j];
-        s = fmaf(d, d, s);
-    }
-    const float d = sqrtf(s / (float)n_sum);
-    if (dist) dist[m] = d;
-    keep[m] = (d <= tol) ? 1 : 0;
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
 }
 
 // stream compaction of keep[0..n) into idx (ascending): per-block counts,
@@ -369,80 +118,6 @@ __global__ void k_scatter(int64_t n, const uint8_t* keep, const int32_t* offs, i
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_gemm_bf16(int epi, int M, int N, int K, const float* A, int64_t sam, int64_t sak, const float* B,
-                            int64_t sbk, int64_t sbn, float* C, int64_t ldc, const GemmEpi& E, const MlpWs& ws,
-                            hipStream_t st)
-{
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (epi == 4 && ldc != N) return hipErrorInvalidValue;
-    const int gx = (N + GT - 1) / GT, gy = (M + GT - 1) / GT, chunks = (K + GK - 1) / GK;
-    // split K into S slices when the output tiles alone leave CUs idle
-    int S = 1, kper = chunks;
-    if (ws.part && chunks >= 2 && gx * gy < 256) {
-        S = std::min({chunks, (256 + gx * gy - 1) / (gx * gy), GEMM_MAX_SPLIT});
-        while (S > 1 && (int64_t)S * M * N > ws.part_floats) --S;
-        kper = (chunks + S - 1) / S;
-        S = (chunks + kper - 1) / kper;
-    }
-    float* part = S > 1 ? ws.part : nullptr;
-    const dim3 grid(gx, gy, S);
-#define SWIM_GEMM_CASE(EP)                                                                                         \
-    case EP:                                                                                                       \
-        hipLaunchKernelGGL(k_gemm_bf16<EP>, grid, dim3(256), 0, st, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, E,  \
-                           part, kper);                                                                            \
-        if (part)                                                                                                  \
-            hipLaunchKernelGGL(k_gemm_reduce<EP>, dim3((unsigned)(((int64_t)M * N + 255) / 256)), dim3(256), 0,    \
-                               st, M, N, S, part, C, ldc, E);                                                      \
-        break;
-    switch (epi) {
-        SWIM_GEMM_CASE(0)
-        SWIM_GEMM_CASE(1)
-        SWIM_GEMM_CASE(2)
-        SWIM_GEMM_CASE(3)
-        SWIM_GEMM_CASE(4)
-    default: return hipErrorInvalidValue;
-    }
-#undef SWIM_GEMM_CASE
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(int M, int N, const float* A, int64_t lda, float* out, hipStream_t st)
-{
-    if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_colsum, dim3((N + 7) / 8), dim3(1024), 0, st, M, N, A, lda, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_sum(int64_t n, const float* v, float* out, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, st, n, v, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_rows(int M, const int32_t* perm, int64_t nrows, const float* X, int nx, const float* T, int nt,
-                              float* Xb, float* Tb, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_gather_rows, dim3(M), dim3(64), 0, st, M, perm, nrows, X, nx, T, nt, Xb, Tb);
-    return hipGetLastError();
-}
-
-hipError_t launch_adam(int64_t n, float* p, const float* g, float* m, float* v, float lr, float b1, float b2, float c1,
-                       float c2, float eps, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, p, g, m, v, lr, b1, b2, c1, c2,
-                       eps);
-    return hipGetLastError();
-}
-
-hipError_t launch_prescreen(int M, int N, int n_sum, const float* Y, const float* mu, const float* sd, const float* obs,
-                            float tol, float* dist, uint8_t* keep, hipStream_t st)
-{
-    if (M <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_prescreen, dim3((M + 255) / 256), dim3(256), 0, st, M, N, n_sum, Y, mu, sd, obs, tol, dist,
-                       keep);
-    return hipGetLastError();
-}
-
 hipError_t launch_compact(int64_t n, const uint8_t* keep, int32_t* counts, int64_t* idx, int64_t* total, hipStream_t st)
 {
     const int64_t nb = (n + 255) / 256;
@@ -911,6 +586,449 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Training step in two launches.
+//
+// k_mlp_step carries 16 RT rows through the whole network and back, one
+// workgroup of 16 waves: wave w owns features 16w..16w+15 of every hidden
+// layer, with v_mfma_f32_16x16x16bf16_1k (A = rows, B = weights).  The
+// activations pass between layers as bfloat16 through LDS, in the MFMA's
+// operand order (8 KB per 16 rows, double-buffered); pre-activations stay in
+// registers for gelu' on the way back; the weights come straight from L2 as
+// bfloat16 operand fragments (one 16-byte load per lane and 32 k), the next
+// layer's loaded ahead of the barrier.  It leaves bfloat16 copies of the
+// activations and of the gradients dA_l, feature-major, the gradients also in
+// FP32 (for the biases), and per-workgroup sums of the squared error.
+//
+// k_mlp_update forms the weight gradients dW_l = H_{l-1}^T dA_l: one workgroup
+// of 16 waves per 32 x 32 tile, wave z summing slice z of the rows, the slices
+// added in order through LDS; the same workgroup then takes the tile's Adam
+// step and refreshes the packed bfloat16 weights (or, for surrogate_grad,
+// writes the gradient).  Bias gradients and the loss take a few more
+// workgroups of the same launch.
+//
+// A batch of 1024 rows is 1.3 GFLOP, under 1 us of MFMA time: a step is bound
+// by launches and by the serial chain of nine layers, so there are two
+// launches (29 with one GEMM, reduction, column sum, gather and Adam kernel
+// each: 170 us a step) and nothing of a layer leaves the workgroup before the
+// next one needs it.  Rows per workgroup: 16 fill four times as many CUs at
+// the batch of 1024; from 8192 rows on, 32 halve the weights' L2 traffic.
+//
+// Sums over k run in slices of kper 32-wide chunks, each slice from zero, the
+// slices added in order (MlpSplit): the order the FP32 accumulation has had
+// with split-K launches, so a change of launch shape does not change a bit.
+// ---------------------------------------------------------------------------
+constexpr int MLP_HID = 256, MLP_OUTN = 33;  // hidden features, outputs
+// packed weights: forward B operands of layers 0..4, then backward ones of
+// layers 1..4; one fragment = 64 lanes x 8 values (layer 0: x 4)
+constexpr int64_t MLP_WB0 = 0, MLP_WB1 = 16 * 64 * 4, MLP_WB4 = MLP_WB1 + 3 * 65536,
+                  MLP_WT1 = MLP_WB4 + 3 * 8 * 512, MLP_WT4 = MLP_WT1 + 3 * 65536,
+                  MLP_WPK = MLP_WT4 + 16 * 2 * 512;
+
+// place of value (red, col) in a layer's fragments: red the summed index (nsp
+// 32-wide pieces of it), col the output feature
+__host__ __device__ constexpr int mlp_frag(int red, int col, int nsp)
+{
+    return (((col >> 4) * nsp + (red >> 5)) * 64 + (col & 15) + 16 * ((red >> 2) & 3)) * 8 + ((red >> 4) & 1) * 4 +
+           (red & 3);
+}
+
+__global__ void k_mlp_pack(const float* __restrict__ P, uint16_t* __restrict__ W)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= MLP_WPK) return;
+    float v = 0.0f;
+    if (e < MLP_WB1) {
+        const int j = e & 3, lane = (e >> 2) & 63, n = (int)(e >> 8) * 16 + (lane & 15), k = 4 * (lane >> 4) + j;
+        if (k < 5) v = P[mlp_offW_d(0) + (int64_t)k * MLP_HID + n];
+    } else {
+        // region start, layer, pieces of the summed index, forward or backward
+        const bool fwd = e < MLP_WT1;
+        const int64_t r0 = e < MLP_WB4 ? MLP_WB1 : fwd ? MLP_WB4 : e < MLP_WT4 ? MLP_WT1 : MLP_WT4;
+        const bool hid = r0 == MLP_WB1 || r0 == MLP_WT1;
+        const int l = hid ? 1 + (int)((e - r0) >> 16) : 4;
+        const int i = (int)(hid ? (e - r0) & 65535 : e - r0), nsp = (hid || fwd) ? 8 : 2;
+        const int x = i & 7, lane = (i >> 3) & 63, t = i >> 9;
+        const int red = 32 * (t % nsp) + 16 * (x >> 2) + 4 * (lane >> 4) + (x & 3), col = 16 * (t / nsp) + (lane & 15);
+        const int k = fwd ? red : col, n = fwd ? col : red, N = l == 4 ? MLP_OUTN : MLP_HID;
+        if (n < N) v = P[mlp_offW_d(l) + (int64_t)k * N + n];
+    }
+    W[e] = f2bf(v);
+}
+
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+// Features stored feature-major: row R of a batch sits at mlp_rowpos(R) of
+// its feature's Mpad values, in the order a lane's 16-byte load takes it as
+// the operand of two 16-row MFMAs
+__device__ __forceinline__ int64_t mlp_rowpos(int64_t R)
+{
+    return (R & ~(int64_t)31) + 8 * ((R >> 2) & 3) + 4 * ((R >> 4) & 1) + (R & 3);
+}
+
+// sum over nsp 32-wide pieces of this lane's operand pairs (a from LDS, b in
+// registers), in slices of kper pieces
+template <int NSP>
+__device__ __forceinline__ f32x4_t mlp_dot(const u32x4_t* a, const u32x4_t (&b)[8], int kper)
+{
+    f32x4_t sum = {0.f, 0.f, 0.f, 0.f}, acc = {0.f, 0.f, 0.f, 0.f};
+    int left = kper;
+#pragma unroll
+    for (int sp = 0; sp < NSP; ++sp) {
+        const u32x4_t av = a[sp * 64];
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4_t, u32x2_t{av[0], av[1]}),
+                                                        __builtin_bit_cast(bf16x4_t, u32x2_t{b[sp][0], b[sp][1]}), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4_t, u32x2_t{av[2], av[3]}),
+                                                        __builtin_bit_cast(bf16x4_t, u32x2_t{b[sp][2], b[sp][3]}), acc, 0, 0, 0);
+        if (--left == 0 || sp == NSP - 1) {
+            sum += acc;
+            acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            left = kper;
+        }
+    }
+    return sum;
+}
+
+template <int RT> __global__ __launch_bounds__(1024) void k_mlp_step(MlpStep a)
+{
+    __shared__ __align__(16) uint16_t frag[2][RT][8 * 512];  // operand fragments of the current and next layer
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row0 = (int64_t)blockIdx.x * 16 * RT;
+    const int n = 16 * w + c;  // this lane's feature
+    // where this lane's values go: rows 4q + r of feature n
+    const int fsp = w >> 1, fel = (w & 1) * 4 + (c & 3), fln = 16 * (c >> 2) + 4 * q;
+    bool live[RT][4];
+    int64_t pos[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        pos[t] = mlp_rowpos(row0 + 16 * t + 4 * q);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) live[t][r] = row0 + 16 * t + 4 * q + r < a.M;
+    }
+    auto load_w = [&](u32x4_t (&b)[8], int64_t off, int nsp, int tile) {
+        const u32x4_t* p = reinterpret_cast<const u32x4_t*>(a.W + off) + (int64_t)tile * nsp * 64 + lane;
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp)
+            if (sp < nsp) b[sp] = p[sp * 64];
+    };
+    // values of this lane (4 rows of feature n) to the fragments and, with
+    // rows beyond M zeroed, to the feature-major copy
+    auto put = [&](int buf, int t, const float (&v)[4], uint16_t* copy, int64_t feat) {
+        uint32_t h[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h[r] = f2bf(v[r]);
+            frag[buf][t][(fsp * 64 + fln + r) * 8 + fel] = (uint16_t)h[r];
+            if (!live[t][r]) h[r] = 0;
+        }
+        *reinterpret_cast<u32x2_t*>(copy + feat * a.Mpad + pos[t]) = u32x2_t{h[0] | h[1] << 16, h[2] | h[3] << 16};
+    };
+    // the gradients in FP32, for the bias gradients' sums over the rows
+    auto keep32 = [&](int t, const float (&v)[4], int64_t feat) {
+        *reinterpret_cast<f32x4_t*>(a.DF + feat * a.Mpad + row0 + 16 * t + 4 * q) = f32x4_t{v[0], v[1], v[2], v[3]};
+    };
+    float pre[4][RT][4];
+    u32x4_t wc[8], wn[8];
+    load_w(wc, MLP_WB1, 8, w);
+    // layer 0: the operand (row c, k = 4q..4q+3) straight from X
+    {
+        const bf16x4_t bv = __builtin_bit_cast(
+            bf16x4_t, *reinterpret_cast<const u32x2_t*>(a.W + MLP_WB0 + (int64_t)(w * 64 + lane) * 4));
+        const float b0 = a.P[mlp_offW_d(0) + 5 * MLP_HID + n];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int64_t R = row0 + 16 * t + c;
+            float x[4] = {0.f, 0.f, 0.f, 0.f};
+            if (q < 2 && R < a.M) {
+                const int64_t src = a.perm ? a.perm[R] : R;
+                const bool ok = src >= 0 && src < a.nrows;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * q + j < 5) x[j] = ok ? a.X[src * 5 + 4 * q + j] : NAN;
+            }
+            uint32_t h[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[j] = f2bf(x[j]);
+            if (w == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a.XT[(int64_t)(4 * q + j) * a.Mpad + mlp_rowpos(R)] = (uint16_t)h[j];
+            }
+            const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+            const f32x4_t s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                __builtin_bit_cast(bf16x4_t, u32x2_t{h[0] | h[1] << 16, h[2] | h[3] << 16}), bv, z, 0, 0, 0);
+            float g[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                pre[0][t][r] = s[r] + b0;
+                g[r] = gelu_f(pre[0][t][r]);
+            }
+            put(0, t, g, a.HT, n);
+        }
+    }
+    // hidden layers 1..3
+#pragma unroll
+    for (int l = 1; l < 4; ++l) {
+        const float bl = a.P[mlp_offW_d(l) + 65536 + n];
+        if (l < 3)
+            load_w(wn, MLP_WB1 + (int64_t)l * 65536, 8, w);
+        else if (w < 3)
+            load_w(wn, MLP_WB4, 8, w);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const f32x4_t s =
+                mlp_dot<8>(reinterpret_cast<const u32x4_t*>(frag[(l - 1) & 1][t]) + lane, wc, a.kf);
+            float g[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                pre[l][t][r] = s[r] + bl;
+                g[r] = gelu_f(pre[l][t][r]);
+            }
+            put(l & 1, t, g, a.HT + (int64_t)l * MLP_HID * a.Mpad, n);
+        }
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp) wc[sp] = wn[sp];
+    }
+    // output layer, its squared error and gradient dY = sc (Y - T): three waves;
+    // features 33..63 of dY are zero
+    load_w(wn, MLP_WT4, 2, w);
+    __syncthreads();
+    if (w < 4) {
+        float sq = 0.f;
+        const bool col = n < MLP_OUTN;
+        const float b4 = col ? a.P[mlp_offW_d(4) + MLP_HID * MLP_OUTN + n] : 0.f;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            float d[4] = {0.f, 0.f, 0.f, 0.f};
+            if (w < 3) {
+                const f32x4_t s = mlp_dot<8>(reinterpret_cast<const u32x4_t*>(frag[1][t]) + lane, wc, a.ko);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (col && live[t][r]) {
+                        const int64_t R = row0 + 16 * t + 4 * q + r;
+                        const int64_t src = a.perm ? a.perm[R] : R;
+                        const bool ok = src >= 0 && src < a.nrows;
+                        const float e = (s[r] + b4) - (ok ? a.T[src * MLP_OUTN + n] : NAN);
+                        d[r] = a.sc * e;
+                        sq += e * e;
+                    }
+                }
+            }
+            // the fragments' next buffer is free: layer 3 read buffer 0
+            if (w < 3) {
+                put(0, t, d, a.YT, n);
+                if (col) keep32(t, d, 4 * MLP_HID + n);
+            } else
+#pragma unroll
+                for (int r = 0; r < 4; ++r) frag[0][t][(fsp * 64 + fln + r) * 8 + fel] = 0;
+        }
+        if (w < 3) {
+            sq = mlp_wave_sum(sq);
+            if (lane == 0) a.lossp[(int64_t)blockIdx.x * 3 + w] = sq;
+        }
+    }
+    // back: dA_{l-1} = (dA_l W_l^T) gelu'(pre_{l-1})
+#pragma unroll
+    for (int l = 4; l >= 1; --l) {
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp) wc[sp] = wn[sp];
+        if (l > 1) load_w(wn, MLP_WT1 + (int64_t)(l - 2) * 65536, 8, w);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const u32x4_t* f = reinterpret_cast<const u32x4_t*>(frag[l & 1][t]) + lane;
+            const f32x4_t s = l == 4 ? mlp_dot<2>(f, wc, a.kb4) : mlp_dot<8>(f, wc, a.kb);
+            float g[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                g[r] = live[t][r] ? s[r] * gelu_grad_f(pre[l - 1][t][r]) : 0.f;
+            }
+            put((l & 1) ^ 1, t, g, a.DT + (int64_t)(l - 1) * MLP_HID * a.Mpad, n);
+            keep32(t, g, (l - 1) * MLP_HID + n);
+        }
+    }
+}
+
+// tiles of k_mlp_update: layers 1..3 (64 each), layer 4 (8 x 2), layer 0
+// (8), then 8 bias columns a workgroup, then the loss
+constexpr int MLP_UT = 3 * 64 + 16 + 8, MLP_UB = (MLP_DBN + 7) / 8;
+
+// Adam with bias-corrected moments: p -= lr mhat / (sqrt(vhat) + eps)
+__device__ __forceinline__ float mlp_adam(const MlpUpdate& u, int64_t i, float g)
+{
+    const float mi = fmaf(u.b1, u.m[i], (1.0f - u.b1) * g);
+    const float vi = fmaf(u.b2, u.v[i], (1.0f - u.b2) * g * g);
+    u.m[i] = mi;
+    u.v[i] = vi;
+    const float mh = mi / u.c1, vh = vi / u.c2;
+    const float p = u.p[i] - u.lr * mh / (sqrtf(vh) + u.eps);
+    u.p[i] = p;
+    return p;
+}
+
+template <bool ADAM> __global__ __launch_bounds__(1024) void k_mlp_update(MlpUpdate u)
+{
+    // the waves' tiles; rotating a row's columns by 8 per four rows spreads the
+    // MFMA result's rows over the banks
+    __shared__ float part[16][32][32];
+    auto at = [](int row, int col) { return (col + 8 * (row >> 2)) & 31; };
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+    const int z = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b = blockIdx.x;
+    if (b >= MLP_UT) {
+        b -= MLP_UT;
+        if (b < MLP_UB) {
+            // bias gradients, 8 columns a workgroup: 128 groups of rows each
+            // summing every 128th row, then a fixed tree over the groups
+            float(*red)[129] = reinterpret_cast<float(*)[129]>(&part[0][0][0]);
+            const int g = tid & 127, n = 8 * b + (tid >> 7);
+            float s = 0.f;
+            if (n < MLP_DBN)
+                for (int64_t m = g; m < u.M; m += 128) s += u.DF[(int64_t)n * u.Mpad + m];
+            red[tid >> 7][g] = s;
+            __syncthreads();
+            for (int w = 64; w >= 1; w >>= 1) {
+                if (g < w) red[tid >> 7][g] += red[tid >> 7][g + w];
+                __syncthreads();
+            }
+            if (g == 0 && n < MLP_DBN) {
+                const int l = n / MLP_HID;  // layers 0..3, then the 33 of layer 4
+                const int64_t i = mlp_offW_d(l) + (int64_t)mlp_k(l) * mlp_n(l) + (n - l * MLP_HID);
+                if (ADAM)
+                    mlp_adam(u, i, red[tid >> 7][0]);
+                else
+                    u.g[i] = red[tid >> 7][0];
+            }
+        } else if (u.loss) {
+            const int col = tid & 31, seg = tid >> 5;
+            float s = 0.f;
+            for (int64_t i = tid; i < 3 * u.nwg; i += 1024) s += u.lossp[i];
+            part[0][seg][col] = s;
+            __syncthreads();
+            if (seg == 0) {
+                s = 0.f;
+                for (int k = 0; k < 32; ++k) s += part[0][k][col];
+                part[1][0][col] = s;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s = 0.f;
+                for (int k = 0; k < 32; ++k) s += part[1][0][k];
+                *u.loss = s;
+            }
+        }
+        return;
+    }
+    int l, tk, tn;
+    if (b < 192) {
+        l = 1 + (b >> 6);
+        tk = (b >> 3) & 7;
+        tn = b & 7;
+    } else if (b < 208) {
+        l = 4;
+        tk = (b - 192) >> 1;
+        tn = b & 1;
+    } else {
+        l = 0;
+        tk = 0;
+        tn = b - 208;
+    }
+    const int K = l == 0 ? 5 : MLP_HID, N = l == 4 ? MLP_OUTN : MLP_HID;
+    const uint16_t* A = l == 0 ? u.XT : u.HT + (int64_t)(l - 1) * MLP_HID * u.Mpad;
+    const uint16_t* D = l == 4 ? u.YT : u.DT + (int64_t)l * MLP_HID * u.Mpad;
+    const int kper = l == 0 ? u.kw0 : l == 4 ? u.kw4 : u.kw;
+    const int chunks = (int)(u.Mpad >> 5), S = (chunks + kper - 1) / kper;  // slices: at most 16
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    const u32x4_t *pa[2], *pd[2];
+    bool la[2], ld[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int k = 32 * tk + 16 * t + c, n = 32 * tn + 16 * t + c;
+        la[t] = k < K;
+        ld[t] = n < N;
+        pa[t] = reinterpret_cast<const u32x4_t*>(A + (int64_t)(la[t] ? k : 0) * u.Mpad) + q;
+        pd[t] = reinterpret_cast<const u32x4_t*>(D + (int64_t)(ld[t] ? n : 0) * u.Mpad) + q;
+    }
+    f32x4_t acc[2][2] = {};
+    if (z < S) {
+        const int c1 = min(chunks, (z + 1) * kper);
+        for (int ch = z * kper; ch < c1; ++ch) {
+            u32x4_t av[2], dv[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                av[t] = la[t] ? pa[t][4 * ch] : zero;
+                dv[t] = ld[t] ? pd[t][4 * ch] : zero;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                            __builtin_bit_cast(bf16x4_t, u32x2_t{av[i][2 * h], av[i][2 * h + 1]}),
+                            __builtin_bit_cast(bf16x4_t, u32x2_t{dv[j][2 * h], dv[j][2 * h + 1]}), acc[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * i + 4 * q + r;
+                    part[z][row][at(row, 16 * j + c)] = acc[i][j][r];
+                }
+    }
+    __syncthreads();
+    const int kk = tid >> 5, nn = tid & 31, k = 32 * tk + kk, n = 32 * tn + nn;
+    if (k >= K || n >= N) return;
+    float g = 0.f;
+    for (int s = 0; s < S; ++s) g += part[s][kk][at(kk, nn)];
+    const int64_t i = mlp_offW_d(l) + (int64_t)k * N + n;
+    if (!ADAM) {
+        u.g[i] = g;
+        return;
+    }
+    const uint16_t h = f2bf(mlp_adam(u, i, g));
+    if (l == 0) {
+        u.W[MLP_WB0 + (int64_t)((n >> 4) * 64 + (n & 15) + 16 * (k >> 2)) * 4 + (k & 3)] = h;
+    } else if (l < 4) {
+        u.W[MLP_WB1 + (int64_t)(l - 1) * 65536 + mlp_frag(k, n, 8)] = h;
+        u.W[MLP_WT1 + (int64_t)(l - 1) * 65536 + mlp_frag(n, k, 8)] = h;
+    } else {
+        u.W[MLP_WB4 + mlp_frag(k, n, 8)] = h;
+        u.W[MLP_WT4 + mlp_frag(n, k, 2)] = h;
+    }
+}
+
+int64_t mlp_pack_count() { return MLP_WPK; }
+
+hipError_t launch_mlp_pack(const float* P, uint16_t* W, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_mlp_pack, dim3((unsigned)((MLP_WPK + 255) / 256)), dim3(256), 0, st, P, W);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_step(const MlpStep& a, hipStream_t st)
+{
+    if (a.rt == 1)
+        hipLaunchKernelGGL(k_mlp_step<1>, dim3((unsigned)(a.Mpad / 16)), dim3(1024), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_mlp_step<2>, dim3((unsigned)(a.Mpad / 32)), dim3(1024), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_update(bool adam, const MlpUpdate& u, hipStream_t st)
+{
+    const dim3 grid(MLP_UT + MLP_UB + 1);
+    if (adam)
+        hipLaunchKernelGGL(k_mlp_update<true>, grid, dim3(1024), 0, st, u);
+    else
+        hipLaunchKernelGGL(k_mlp_update<false>, grid, dim3(1024), 0, st, u);
+    return hipGetLastError();
 }
 
 size_t mlp_fused_lds_bytes() { return (size_t)(2 * 256 * MLP_WP) * sizeof(uint16_t); }
