@@ -52,7 +52,7 @@ VALU_OPS_PER_PAIR = 17.8
 PAIR_LOOP_VALU_OPS = 15.75  # the sperm kernel's symmetric pair loop alone (ISA, per ordered pair)
 FP32_FLOP_PER_PAIR = 21
 NONPACKED_FP32_PEAK_TFLOPS = 78.6
-# the FP32 large-system step, k_big_pairs (every pair once for both points,
+# the FP32 large-system step, k_tile_pairs (every pair once for both points,
 # FP64 accumulation) and k_big_update: 26.2 VALU lane-operations per ordered
 # pair evaluation from SQ_INSTS_VALU
 # (profiles/k_big_pairs_dense_64x8x512_counters.md; the one-sided
@@ -224,7 +224,7 @@ def dense_leg(ctx, stream, samples=64, steps=1000, dt_div=64):
     d = done.cpu().numpy().astype(np.int64)
     pairs = float(np.sum(d * 4096 * 4096))
     out = {"workload": f"{samples} samples x 8 swimmers x N=512 (2x4 grid, spacing 1.5), {steps} Euler steps of "
-                       f"dt=2e-5/{dt_div} (stability), FP32, symmetric large-system step (k_big_pairs + k_big_update)",
+                       f"dt=2e-5/{dt_div} (stability), FP32, symmetric large-system step (k_tile_pairs + k_big_update)",
            "ms": ms, "pair_evals_per_s": pairs / (ms * 1e-3), "swimmer_steps_per_s": float(np.sum(d)) * 8 / (ms * 1e-3),
            "runs_stopped": int(np.sum(status.cpu().numpy() != 0)),
            "fp32_tflops": FP32_FLOP_PER_PAIR * pairs / (ms * 1e-3) / 1e12,

@@ -98,7 +98,7 @@ int swim_version(void);
  *   SWIM_OPT_BIG_TPL the large-system step (systems above 512 points):
  *                    0 (automatic: FP32 takes the symmetric step, every
  *                    pair evaluated once for both points, in tile pairs of
- *                    256 points with a partial-sum buffer reduced in a
+ *                    128 points with a partial-sum buffer reduced in a
  *                    fixed order; FP64 the one-sided kernel at one target
  *                    per lane), or 1, 2, 4: the one-sided kernel at that
  *                    many targets per lane;

@@ -60,12 +60,12 @@ struct DevBuf {
 };
 
 enum BufId {
-    B_OFF, B_SWOFF, B_NPT, B_NSW, B_ORDER, B_LIST, B_BLKS, B_BLKF, B_ALPHA, B_EPS, B_SYSC, B_QUEUE,
+    B_UP, B_SYSC, B_QUEUE,
     B_PARAMS, B_DATA, B_OBS, B_SPEED, B_STATUS, B_DIST, B_TOL, B_ACC, B_BIG,
     B_MLP_ACT, B_MLP_IDX, B_MLP_CNT,
     B_PS_THETA, B_PS_X, B_PS_KEEP, B_PS_IDX, B_PS_NK, B_PS_SUM, B_DS_T, B_TAB, B_DONE, B_W16, B_SIGMA, B_LOGL,
     B_SP_SW, B_SP_HEAD, B_SP_TAIL, B_SP_G, B_SP_SIG, B_WTAB,
-    B_BT_PSYS, B_BT_PT, B_BT_TSYS, B_BT_TT, B_BT_POFF, B_BT_PART,
+    B_BT_PART, B_BT_SRC,
     B_NBUF
 };
 
@@ -84,19 +84,18 @@ int64_t mlp_offb(int l) { return mlp_offW(l) + (int64_t)MLP_W[l] * MLP_W[l + 1];
 
 // Workspace of swim_pair_velocity_noalloc: a fixed device array in place of
 // the context's allocations.  Sections (256-byte aligned): system offsets,
-// alpha, eps, the block list (system, first target) of the pair kernel, the
+// alpha, eps, the first workgroup of each system, the
 // per-system constants (in the working type and in FP64) and the kernel
 // tables.  Every section is written by the call before its kernels read it,
 // so nothing needs clearing between calls.
 constexpr int64_t NOALLOC_MAX_SYS = 64;      // systems per call
-constexpr int64_t NOALLOC_MAX_BLOCKS = 4160; // pair-kernel blocks (256 targets each) per call
+constexpr int64_t NOALLOC_MAX_BLOCKS = 4160; // blocks of 256 targets per call
 constexpr size_t na_align(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t NA_OFF = 0;
 constexpr size_t NA_ALPHA = na_align(NA_OFF + (NOALLOC_MAX_SYS + 1) * 8);
 constexpr size_t NA_EPS = na_align(NA_ALPHA + NOALLOC_MAX_SYS * 8);
-constexpr size_t NA_BLKS = na_align(NA_EPS + NOALLOC_MAX_SYS * 8);
-constexpr size_t NA_BLKF = na_align(NA_BLKS + NOALLOC_MAX_BLOCKS * 8);
-constexpr size_t NA_SYSC = na_align(NA_BLKF + NOALLOC_MAX_BLOCKS * 8);  // end of the staged host data
+constexpr size_t NA_BLK = na_align(NA_EPS + NOALLOC_MAX_SYS * 8);
+constexpr size_t NA_SYSC = na_align(NA_BLK + (NOALLOC_MAX_SYS + 1) * 8);  // end of the staged host data
 constexpr size_t NA_SYSC64 = na_align(NA_SYSC + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
 constexpr size_t NA_TAB = na_align(NA_SYSC64 + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
 constexpr size_t NA_BYTES = na_align(NA_TAB + NOALLOC_MAX_SYS * sizeof(TabSys64));  // ~6.6 MB (FP32 tables share it)
@@ -137,7 +136,7 @@ struct swim_ctx {
     int64_t graph_launches = 0, graph_captures = 0;
     DevBuf buf[B_NBUF];
     void* pinned = nullptr;
-    size_t pinned_cap = 0, pin_off = 0;
+    size_t pinned_cap = 0, pin_off = 0, put_end = 0;
     hipEvent_t up_ev = nullptr;
     hipEvent_t sw_ev = nullptr;        // orders work across a change of stream
     // auxiliary streams (default priority) and events that run the size
@@ -178,12 +177,17 @@ int ensure(swim_ctx* c, BufId id, size_t bytes)
 }
 
 // Host->device staging through one pinned buffer.  begin_uploads waits for
-// the previous call's copies, then stage() appends and enqueues copies.
+// the previous call's copies; put() then appends to the call's upload buffer
+// (one copy, by end_uploads), stage() copies into a buffer of its own that
+// outlives the call's own uploads (an ABC or TMCMC step's rows and data,
+// which the forward runs inside it read).
 int begin_uploads(swim_ctx* c, size_t total)
 {
     HIPCHK(hipEventSynchronize(c->up_ev));
     c->pin_off = 0;
+    c->put_end = 0;
     total += 64 * 32;
+    TRY(ensure(c, B_UP, total));
     if (total > c->pinned_cap) {
         if (c->pinned) HIPCHK(hipHostFree(c->pinned));
         c->pinned = nullptr;
@@ -209,8 +213,26 @@ int stage(swim_ctx* c, const void* src, size_t bytes, BufId dst, hipStream_t st)
     return SWIM_OK;
 }
 
+// Host array -> the call's upload buffer, *dev its device address there: all
+// arrays of a call go over in the one copy of end_uploads (a copy of its own
+// each cost 4.5 us on the stream, five to eight per call).  They stay until
+// the context's next begin_uploads.
+template <typename V> int put(swim_ctx* c, const V* src, size_t count, const V** dev)
+{
+    c->pin_off = (c->pin_off + 63) & ~(size_t)63;
+    const size_t bytes = count * sizeof(V);
+    if (c->pin_off + bytes > c->pinned_cap || c->pin_off + bytes > c->buf[B_UP].cap)
+        return fail(SWIM_EINVAL, "internal: staging overflow");
+    if (bytes) memcpy((char*)c->pinned + c->pin_off, src, bytes);
+    *dev = (const V*)((char*)c->buf[B_UP].p + c->pin_off);
+    c->pin_off += bytes;
+    c->put_end = c->pin_off;
+    return SWIM_OK;
+}
+
 int end_uploads(swim_ctx* c, hipStream_t st)
 {
+    if (c->put_end) HIPCHK(hipMemcpyAsync(c->buf[B_UP].p, c->pinned, c->put_end, hipMemcpyHostToDevice, st));
     HIPCHK(hipEventRecord(c->up_ev, st));
     return SWIM_OK;
 }
@@ -412,6 +434,44 @@ int64_t tab64_chunk(swim_ctx* c, int64_t n_sys)
     return m;
 }
 
+// The tile-pair path's layout of the systems added to it (host), and its upload
+struct TilePlan {
+    std::vector<int64_t> list, off0{0}, tile0{0}, slot0, pt0;
+    std::vector<int32_t> cnt;
+    int64_t slots = 0;
+
+    void add(int64_t s, int64_t first, int32_t n)
+    {
+        list.push_back(s);
+        pt0.push_back(first);
+        cnt.push_back(n);
+    }
+    void finish()
+    {
+        for (int32_t n : cnt) {
+            const int64_t nt = (n + BIG_TILE_POINTS - 1) / BIG_TILE_POINTS;
+            off0.push_back(off0.back() + nt * (nt - 1) / 2);
+            tile0.push_back(tile0.back() + nt);
+            slot0.push_back(slots);
+            slots += nt * nt;
+        }
+    }
+    size_t bytes() const { return (size_t)slots * BIG_TILE_POINTS * 2 * sizeof(double); }
+    size_t upload_bytes() const { return (list.size() * 6 + 2) * 8; }
+    int upload(swim_ctx* c, BigTiles* t) const
+    {
+        t->n_big = (int64_t)list.size();
+        t->n_tiles = tile0.back();
+        t->n_pairs = off0.back() + t->n_tiles;
+        TRY(put(c, list.data(), list.size(), &t->list));
+        TRY(put(c, off0.data(), off0.size(), &t->off0));
+        TRY(put(c, tile0.data(), tile0.size(), &t->tile0));
+        TRY(put(c, slot0.data(), slot0.size(), &t->slot0));
+        TRY(put(c, pt0.data(), pt0.size(), &t->pt0));
+        return put(c, cnt.data(), cnt.size(), &t->cnt);
+    }
+};
+
 // ------------------------------------------------------------------------
 // forward run (shared by swim_forward and abc_step)
 // ------------------------------------------------------------------------
@@ -476,33 +536,10 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     const bool big_sym = dtype == SWIM_F32 && c->opt_big_tpl == 0;
     const int tpl_big = c->opt_big_tpl ? c->opt_big_tpl : 1;
     std::vector<int64_t> blk_s, blk_f;
-    std::vector<int64_t> bp_sys, bt_sys, bt_poff;
-    std::vector<int32_t> bp_tile, bt_tile;
-    int64_t bt_slots = 0;
+    TilePlan plan;
     if (big_sym) {
-        // tile pairs: the off-diagonal ones (twice the work) first, so that
-        // the launch's tail holds the lighter diagonal ones
-        bt_poff.assign(n_sys, 0);
-        std::vector<int64_t> dg_sys;
-        std::vector<int32_t> dg_tile;
-        for (int64_t s : big_list) {
-            const int nt = (pts[s] + BIG_TILE_POINTS - 1) / BIG_TILE_POINTS;
-            if (nt > 0xFFFF) return fail(SWIM_EINVAL, "system of %d points exceeds the large-system tiling", pts[s]);
-            bt_poff[s] = bt_slots;
-            bt_slots += (int64_t)nt * nt;
-            for (int ta = 0; ta < nt; ++ta) {
-                bt_sys.push_back(s);
-                bt_tile.push_back(ta);
-                dg_sys.push_back(s);
-                dg_tile.push_back(ta | (ta << 16));
-                for (int tb = ta + 1; tb < nt; ++tb) {
-                    bp_sys.push_back(s);
-                    bp_tile.push_back(ta | (tb << 16));
-                }
-            }
-        }
-        bp_sys.insert(bp_sys.end(), dg_sys.begin(), dg_sys.end());
-        bp_tile.insert(bp_tile.end(), dg_tile.begin(), dg_tile.end());
+        for (int64_t s : big_list) plan.add(s, big_off[s], pts[s]);
+        plan.finish();
     } else {
         for (int64_t s : big_list)
             for (int64_t f = 0; f < pts[s]; f += 256 * tpl_big) {
@@ -512,36 +549,27 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     }
     const size_t es = dtype == SWIM_F32 ? 4 : 8;
     size_t total = (sw_off.size() + big_off.size() + big_list.size() + 2 * blk_s.size()) * 8 +
-                   (nsw.size() + order.size()) * 4 + n_sys * 4 + 64 +
-                   (bp_sys.size() + bt_sys.size() + bt_poff.size()) * 8 + (bp_tile.size() + bt_tile.size()) * 4 +
-                   6 * 256;
+                   (nsw.size() + order.size()) * 4 + n_sys * 4 + plan.upload_bytes();
     TRY(begin_uploads(c, total));
-    TRY(stage(c, sw_off.data(), sw_off.size() * 8, B_SWOFF, st));
-    TRY(stage(c, big_off.data(), big_off.size() * 8, B_OFF, st));
-    TRY(stage(c, N, n_sys * 4, B_NPT, st));
-    TRY(stage(c, nsw.data(), nsw.size() * 4, B_NSW, st));
-    TRY(stage(c, order.data(), order.size() * 4, B_ORDER, st));
-    TRY(stage(c, big_list.data(), big_list.size() * 8, B_LIST, st));
-    TRY(stage(c, blk_s.data(), blk_s.size() * 8, B_BLKS, st));
-    TRY(stage(c, blk_f.data(), blk_f.size() * 8, B_BLKF, st));
-    if (big_sym) {
-        TRY(stage(c, bp_sys.data(), bp_sys.size() * 8, B_BT_PSYS, st));
-        TRY(stage(c, bp_tile.data(), bp_tile.size() * 4, B_BT_PT, st));
-        TRY(stage(c, bt_sys.data(), bt_sys.size() * 8, B_BT_TSYS, st));
-        TRY(stage(c, bt_tile.data(), bt_tile.size() * 4, B_BT_TT, st));
-        TRY(stage(c, bt_poff.data(), bt_poff.size() * 8, B_BT_POFF, st));
-    }
+    Batch b;
+    const int32_t* order_dev;
+    const int64_t *list_dev, *blks_dev, *blkf_dev;
+    BigTiles bt{};
+    TRY(put(c, sw_off.data(), sw_off.size(), &b.sw_off));
+    TRY(put(c, big_off.data(), big_off.size(), &b.pt_off));
+    TRY(put(c, N, n_sys, &b.npt));
+    TRY(put(c, nsw.data(), nsw.size(), &b.nswim));
+    TRY(put(c, order.data(), order.size(), &order_dev));
+    TRY(put(c, big_list.data(), big_list.size(), &list_dev));
+    TRY(put(c, blk_s.data(), blk_s.size(), &blks_dev));
+    TRY(put(c, blk_f.data(), blk_f.size(), &blkf_dev));
+    if (big_sym) TRY(plan.upload(c, &bt));
     TRY(end_uploads(c, st));
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     TRY(ensure(c, B_QUEUE, 8 * 4));
     TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
-    Batch b;
     b.n_sys = n_sys;
-    b.pt_off = (const int64_t*)c->buf[B_OFF].p;
-    b.sw_off = (const int64_t*)c->buf[B_SWOFF].p;
-    b.npt = (const int32_t*)c->buf[B_NPT].p;
-    b.nswim = (const int32_t*)c->buf[B_NSW].p;
     b.params = params_dev;
     b.sysc = sysc;
     b.sysc64 = sysc64;
@@ -621,7 +649,10 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         }
         S.head0 = base + 8 * one;
         if (big_sym) {
-            TRY(ensure(c, B_BT_PART, (size_t)bt_slots * BIG_TILE_POINTS * 2 * sizeof(double)));
+            TRY(ensure(c, B_BT_PART, plan.bytes()));
+            TRY(ensure(c, B_BT_SRC, (size_t)big_pts * 4 * sizeof(float)));
+            bt.part = c->buf[B_BT_PART].p;
+            bt.src = c->buf[B_BT_SRC].p;
             HIPCHK(prepare_big_pairs());
         } else {
             if (big_step_lds_bytes(dtype, max_big) > 160 * 1024)
@@ -629,21 +660,10 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
             HIPCHK(prepare_big_step(dtype, tpl_big, max_big));
         }
     }
-    BigTiles bt_pairs{}, bt_tiles{};
-    if (big_sym) {
-        bt_pairs.sys = (const int64_t*)c->buf[B_BT_PSYS].p;
-        bt_pairs.tile = (const int32_t*)c->buf[B_BT_PT].p;
-        bt_pairs.poff = (const int64_t*)c->buf[B_BT_POFF].p;
-        bt_pairs.part = c->buf[B_BT_PART].p;
-        bt_tiles = bt_pairs;
-        bt_tiles.sys = (const int64_t*)c->buf[B_BT_TSYS].p;
-        bt_tiles.tile = (const int32_t*)c->buf[B_BT_TT].p;
-    }
     // the launch sequence of the run (uploads above are not part of it)
     auto launch_all = [&]() -> hipError_t {
-        hipError_t e = launch_sysconst_batch(dtype, n_sys, (const int64_t*)c->buf[B_SWOFF].p,
-                                             (const int32_t*)c->buf[B_NPT].p, params_dev, run.eps_over_ds, sysc,
-                                             sysc64, status, c->opt_blob, st);
+        hipError_t e = launch_sysconst_batch(dtype, n_sys, b.sw_off, b.npt, params_dev, run.eps_over_ds, sysc, sysc64,
+                                             status, c->opt_blob, st);
         if (e == hipSuccess) e = build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st);
         if (e == hipSuccess) e = launch_fill_i32((int32_t*)c->buf[B_QUEUE].p, 0, 8, st);
         if (e == hipSuccess && c->opt_time) e = hipEventRecord(c->time_ev[0], st);
@@ -663,27 +683,24 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
             Batch bb = b;
             bb.n_sys = bk[k].count;
             e = launch_forward(dtype, bk[k].tpl, bk[k].wps, bk[k].nblocks, bb, run,
-                               (const int32_t*)c->buf[B_ORDER].p + bk[k].start, (int32_t*)c->buf[B_QUEUE].p + k, obs,
+                               order_dev + bk[k].start, (int32_t*)c->buf[B_QUEUE].p + k, obs,
                                speed, status, steps_done, lane_stream(bk[k].lane % lanes));
         }
         if (!big_list.empty() && e == hipSuccess) {
             const hipStream_t st_big = lane_stream(big_lane % lanes);
-            e = launch_big_init(dtype, (const int64_t*)c->buf[B_LIST].p, (int64_t)big_list.size(), b, S, status, obs,
+            e = launch_big_init(dtype, list_dev, (int64_t)big_list.size(), b, S, status, obs,
                                 run.n_obs, st_big);
+            if (big_sym && e == hipSuccess) e = launch_big_sources(bt, b, S, st_big);
             for (int step = 0; step < run.steps && e == hipSuccess; ++step) {
                 if (big_sym) {
-                    e = launch_big_pairs((int64_t)bp_sys.size(), bt_pairs, b, S, step, run, status, st_big);
-                    if (e == hipSuccess)
-                        e = launch_big_update((int64_t)bt_sys.size(), bt_tiles, b, S, step, run, obs, status,
-                                              steps_done, st_big);
+                    e = launch_big_sym_step(bt, b, S, step, run, obs, status, steps_done, st_big);
                 } else {
-                    e = launch_big_step(dtype, tpl_big, (int64_t)blk_s.size(), (const int64_t*)c->buf[B_BLKS].p,
-                                        (const int64_t*)c->buf[B_BLKF].p, max_big, b, S, step, run, obs, status,
+                    e = launch_big_step(dtype, tpl_big, (int64_t)blk_s.size(), blks_dev, blkf_dev, max_big, b, S, step, run, obs, status,
                                         steps_done, st_big);
                 }
             }
             if (e == hipSuccess)
-                e = launch_big_finish(dtype, (const int64_t*)c->buf[B_LIST].p, (int64_t)big_list.size(), b, S,
+                e = launch_big_finish(dtype, list_dev, (int64_t)big_list.size(), b, S,
                                       run.steps & 1, run, speed, status, steps_done, st_big);
         }
         for (int l = 1; l < lanes && e == hipSuccess; ++l) {
@@ -723,20 +740,13 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         h.add(q.lane);
     }
     h.add(big_lane);
-    const void* ptrs[] = {params_dev, obs, speed, status, steps_done, sysc, sysc64, b.tab, c->buf[B_SWOFF].p,
-                          c->buf[B_OFF].p, c->buf[B_NPT].p, c->buf[B_NSW].p, c->buf[B_ORDER].p, c->buf[B_LIST].p,
+    // (the arrays of the upload buffer lie where its start and the sizes put them)
+    const void* ptrs[] = {params_dev, obs, speed, status, steps_done, sysc, sysc64, b.tab, c->buf[B_UP].p,
                           c->buf[B_QUEUE].p, c->buf[B_BIG].p, st};
     h.add_bytes(ptrs, sizeof(ptrs));
-    // the large-system step's own lists: only those its launches read (the
-    // other path's buffers are shared with other calls, which may move them)
-    if (!big_list.empty()) {
-        const void* bptrs[] = {c->buf[B_BLKS].p, c->buf[B_BLKF].p};
-        const void* sptrs[] = {c->buf[B_BT_PSYS].p, c->buf[B_BT_PT].p, c->buf[B_BT_TSYS].p,
-                               c->buf[B_BT_TT].p,   c->buf[B_BT_POFF].p, c->buf[B_BT_PART].p};
-        if (big_sym)
-            h.add_bytes(sptrs, sizeof(sptrs));
-        else
-            h.add_bytes(bptrs, sizeof(bptrs));
+    if (!big_list.empty() && big_sym) {
+        const void* sptrs[] = {bt.part, bt.src};
+        h.add_bytes(sptrs, sizeof(sptrs));
     }
     const uint64_t key = h.v;
     ++c->graph_clock;
@@ -1020,32 +1030,57 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
                                const double* eps, const void* x, const void* y, const void* fx, const void* fy,
                                void* ux, void* uy, hipStream_t st)
 {
-    int64_t maxn = 0;
-    for (int64_t s = 0; s < n_sys; ++s) maxn = std::max(maxn, sys_off[s + 1] - sys_off[s]);
-    const int tpl = maxn >= 2048 ? 2 : 1;
-    std::vector<int64_t> bs, bf;
-    for (int64_t s = 0; s < n_sys; ++s)
-        for (int64_t f = 0; f < sys_off[s + 1] - sys_off[s]; f += 256 * tpl) {
-            bs.push_back(s);
-            bf.push_back(f);
+    // FP32 systems take the tile-pair path (every pair once, two launches)
+    // from 1024 points on, and from 512 on in calls of 2^24 pairs and more;
+    // below, the one-sided kernel's single launch is as short or shorter.
+    // Whole calls, one-sided against tile pairs: 1 x 256 points 49 and 56 us,
+    // 1 x 512 55 and 58, 64 x 512 69 and 70, 512 x 512 240 and 192, 1 x 1024
+    // 65 and 58, 1 x 4096 128 and 72, 16 x 4096 330 and 222.  Systems whose
+    // partial sums would pass 1 GiB in all stay one-sided.
+    double pairs = 0.0;
+    for (int64_t s = 0; s < n_sys; ++s) pairs += (double)(sys_off[s + 1] - sys_off[s]) * (double)(sys_off[s + 1] - sys_off[s]);
+    TilePlan plan;
+    if (dtype == SWIM_F32) {
+        double part = 0.0;
+        for (int64_t s = 0; s < n_sys; ++s) {
+            const int64_t n = sys_off[s + 1] - sys_off[s];
+            const double nt = std::ceil((double)n / BIG_TILE_POINTS), bytes = nt * nt * BIG_TILE_POINTS * 16.0;
+            if (n < (pairs >= 16777216.0 ? 512 : 1024) || part + bytes > 1073741824.0) continue;
+            part += bytes;
+            plan.add(s, sys_off[s], (int32_t)n);
         }
-    TRY(begin_uploads(c, (n_sys + 1) * 8 + 2 * n_sys * 8 + 2 * bs.size() * 8));
-    TRY(stage(c, sys_off, (n_sys + 1) * 8, B_OFF, st));
-    TRY(stage(c, alpha, n_sys * 8, B_ALPHA, st));
-    TRY(stage(c, eps, n_sys * 8, B_EPS, st));
-    TRY(stage(c, bs.data(), bs.size() * 8, B_BLKS, st));
-    TRY(stage(c, bf.data(), bf.size() * 8, B_BLKF, st));
+    }
+    plan.finish();
+    if (plan.slots && ensure(c, B_BT_PART, plan.bytes()) == SWIM_ENOMEM) {
+        (void)hipGetLastError();
+        plan = TilePlan();
+    }
+    std::vector<int64_t> blk0(n_sys + 1, 0);
+    size_t q = 0;  // next system of the plan
+    for (int64_t s = 0; s < n_sys; ++s) {
+        const bool tiled = q < plan.list.size() && plan.list[q] == s;
+        q += tiled ? 1 : 0;
+        blk0[s + 1] = blk0[s] + (tiled ? 0 : (sys_off[s + 1] - sys_off[s] + 63) / 64);
+    }
+    TRY(begin_uploads(c, 4 * (n_sys + 1) * 8 + plan.upload_bytes()));
+    const int64_t *off_dev, *blk_dev;
+    const double *alpha_dev, *eps_dev;
+    BigTiles bt{};
+    TRY(put(c, sys_off, n_sys + 1, &off_dev));
+    TRY(put(c, blk0.data(), n_sys + 1, &blk_dev));
+    TRY(put(c, alpha, n_sys, &alpha_dev));
+    TRY(put(c, eps, n_sys, &eps_dev));
+    TRY(plan.upload(c, &bt));
     TRY(end_uploads(c, st));
+    bt.part = c->buf[B_BT_PART].p;
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
-    HIPCHK(launch_sysconst(dtype, n_sys, (const double*)c->buf[B_ALPHA].p, (const double*)c->buf[B_EPS].p, sysc,
-                           sysc64, c->opt_blob, st));
+    HIPCHK(launch_sysconst(dtype, n_sys, alpha_dev, eps_dev, sysc, sysc64, c->opt_blob, st));
     TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     void* tab = c->buf[B_TAB].p;
     HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
-    HIPCHK(launch_pair_velocity(dtype, tpl, (int64_t)bs.size(), (const int64_t*)c->buf[B_BLKS].p,
-                                (const int64_t*)c->buf[B_BLKF].p, (const int64_t*)c->buf[B_OFF].p, sysc, tab, x, y,
-                                fx, fy, ux, uy, st));
+    HIPCHK(launch_pair_velocity(dtype, n_sys, blk0[n_sys], blk_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
+    HIPCHK(launch_tile_velocity(bt, sysc, tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
 }
 
@@ -1119,15 +1154,10 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     memcpy(host + NA_OFF, sys_off, (size_t)(n_sys + 1) * 8);
     memcpy(host + NA_ALPHA, alpha, (size_t)n_sys * 8);
     memcpy(host + NA_EPS, eps, (size_t)n_sys * 8);
-    int64_t* bs = (int64_t*)(host + NA_BLKS);
-    int64_t* bf = (int64_t*)(host + NA_BLKF);
-    int64_t k = 0;
-    for (int64_t s = 0; s < n_sys; ++s)
-        for (int64_t f = 0; f < sys_off[s + 1] - sys_off[s]; f += 256 * tpl) {
-            bs[k] = s;
-            bf[k] = f;
-            ++k;
-        }
+    int64_t* blk0 = (int64_t*)(host + NA_BLK);
+    blk0[0] = 0;
+    for (int64_t s = 0; s < n_sys; ++s) blk0[s + 1] = blk0[s] + (sys_off[s + 1] - sys_off[s] + 63) / 64;
+    const int64_t n_wg = blk0[n_sys];
     hipStream_t st = pick(c, stream);
     HIPCHK(hipMemcpyWithStream(ws, host, NA_SYSC, hipMemcpyHostToDevice, st));
     void* sysc = ws + NA_SYSC;
@@ -1136,8 +1166,8 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
                            c->opt_blob, st));
     void* tab = ws + NA_TAB;
     HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
-    HIPCHK(launch_pair_velocity(dtype, tpl, nb, (const int64_t*)(ws + NA_BLKS), (const int64_t*)(ws + NA_BLKF),
-                                (const int64_t*)(ws + NA_OFF), sysc, tab, x, y, fx, fy, ux, uy, st));
+    HIPCHK(launch_pair_velocity(dtype, n_sys, n_wg, (const int64_t*)(ws + NA_BLK), (const int64_t*)(ws + NA_OFF), sysc,
+                                tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
 }
 
@@ -1187,13 +1217,13 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
     // the pair kernel from the system's table, as in the forward runs (built
     // on the device from the FP64 kernel functions)
     TRY(begin_uploads(c, 16));
-    TRY(stage(c, &alpha, 8, B_ALPHA, st));
-    TRY(stage(c, &eps, 8, B_EPS, st));
+    const double *alpha_dev, *eps_dev;
+    TRY(put(c, &alpha, 1, &alpha_dev));
+    TRY(put(c, &eps, 1, &eps_dev));
     TRY(end_uploads(c, st));
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, 1, &sysc, &sysc64));
-    HIPCHK(launch_sysconst(dtype, 1, (const double*)c->buf[B_ALPHA].p, (const double*)c->buf[B_EPS].p, sysc, sysc64,
-                           c->opt_blob, st));
+    HIPCHK(launch_sysconst(dtype, 1, alpha_dev, eps_dev, sysc, sysc64, c->opt_blob, st));
     TRY(ensure(c, B_TAB, table_bytes(dtype)));
     const void* tab = c->buf[B_TAB].p;
     HIPCHK(build_tables(c, dtype, 1, sysc, sysc64, c->buf[B_TAB].p, st));
@@ -1226,12 +1256,14 @@ int swim_elastic_forces(swim_ctx* c, int32_t dtype, int64_t n_fil, const int32_t
     if (!x || !y || !fx || !fy) return fail(SWIM_EINVAL, "null data pointer");
     hipStream_t st = pick(c, stream);
     TRY(begin_uploads(c, (n_fil + 1) * 8 + n_fil * 4 + n_fil * SWIM_NPARAM * 8));
-    TRY(stage(c, off.data(), off.size() * 8, B_OFF, st));
-    TRY(stage(c, N, n_fil * 4, B_NPT, st));
-    TRY(stage(c, params, n_fil * SWIM_NPARAM * 8, B_PARAMS, st));
+    const int64_t* off_dev;
+    const int32_t* npt_dev;
+    const double* par_dev;
+    TRY(put(c, off.data(), off.size(), &off_dev));
+    TRY(put(c, N, n_fil, &npt_dev));
+    TRY(put(c, params, n_fil * SWIM_NPARAM, &par_dev));
     TRY(end_uploads(c, st));
-    HIPCHK(launch_forces(dtype, n_fil, (const int64_t*)c->buf[B_OFF].p, (const int32_t*)c->buf[B_NPT].p,
-                         (const double*)c->buf[B_PARAMS].p, t, x, y, fx, fy, st));
+    HIPCHK(launch_forces(dtype, n_fil, off_dev, npt_dev, par_dev, t, x, y, fx, fy, st));
     return SWIM_OK;
 }
 

@@ -50,9 +50,9 @@ hipError_t launch_sysconst_batch(int dtype, int64_t n_sys, const int64_t* sw_off
                                  int32_t* status, int blob, hipStream_t st);
 hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const double* eps,
                            void* sysc, void* sysc64, int blob, hipStream_t st);
-hipError_t launch_pair_velocity(int dtype, int tpl, int64_t n_blocks, const int64_t* blk_sys,
-                                const int64_t* blk_first, const int64_t* pt_off, const void* sysc,
-                                const void* tab, const void* x, const void* y, const void* fx,
+// blk0: first 64-target workgroup of each system (prefix, n_sys + 1), nb their number
+hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* pt_off,
+                                const void* sysc, const void* tab, const void* x, const void* y, const void* fx,
                                 const void* fy, void* ux, void* uy, hipStream_t st);
 // bytes of one system's kernel table (TabSys, TabSys64)
 size_t table_bytes(int dtype);
@@ -82,21 +82,28 @@ struct BigState {
     void* yl[2];
     void* head0;   // [n_filaments][2] T, initial head positions
 };
-// the symmetric FP32 large-system step: tile pairs (pairs kernel) or tiles
-// (update kernel) of BIG_T = 256 points, and the partial-sum slots
+// the symmetric FP32 tile-pair path: the systems that take it, cut into
+// tiles of BIG_TILE_POINTS points, every pair of tiles one workgroup
+constexpr int BIG_TILE_POINTS = 128;
 struct BigTiles {
-    const int64_t* sys;   // [n_items] system
-    const int32_t* tile;  // [n_items] ta | tb << 16 (tile pairs, ta <= tb), or the tile
-    const int64_t* poff;  // [n_sys] first partial slot of a large system (nt * nt slots)
-    void* part;           // slots of 256 double pairs: slot poff + t * nt + q = tile t's sums over tile q
+    int64_t n_big, n_pairs, n_tiles;  // systems, tile pairs and tiles of all of them
+    const int64_t* list;   // [n_big] system
+    const int64_t* off0;   // [n_big + 1] first off-diagonal tile pair
+    const int64_t* tile0;  // [n_big + 1] first tile
+    const int64_t* slot0;  // [n_big] first partial slot (nt * nt slots)
+    const int64_t* pt0;    // [n_big] first point
+    const int32_t* cnt;    // [n_big] points
+    void* part;            // slots of one double pair per point: slot t * nt + q = tile t's sums over tile q
+    void* src;             // forward runs: sources of all points (position, force)
 };
-constexpr int BIG_TILE_POINTS = 256;
-size_t big_pair_lds_bytes();
+// velocities for given forces
+hipError_t launch_tile_velocity(const BigTiles& bt, const void* sysc, const void* tab, const void* x, const void* y,
+                                const void* fx, const void* fy, void* ux, void* uy, hipStream_t st);
+// forward steps: the first step's sources, then tile pairs and the update
 hipError_t prepare_big_pairs();
-hipError_t launch_big_pairs(int64_t n_pairs, const BigTiles& bt, const Batch& b, const BigState& s, int step,
-                            const Run& r, const int32_t* status, hipStream_t st);
-hipError_t launch_big_update(int64_t n_tiles, const BigTiles& bt, const Batch& b, const BigState& s, int step,
-                             const Run& r, void* obs, int32_t* status, int32_t* steps_done, hipStream_t st);
+hipError_t launch_big_sources(const BigTiles& bt, const Batch& b, const BigState& s, hipStream_t st);
+hipError_t launch_big_sym_step(const BigTiles& bt, const Batch& b, const BigState& s, int step, const Run& r, void* obs,
+                               int32_t* status, int32_t* steps_done, hipStream_t st);
 hipError_t launch_big_init(int dtype, const int64_t* list, int64_t n_list, const Batch& b,
                            const BigState& s, int32_t* status, void* obs, int32_t n_obs,
                            hipStream_t st);

@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "swim_internal.h"
 #include "swim_math.h"
 #include "swim_pairsum.h"
@@ -431,44 +433,54 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n)
     if (i < n) p[i] = v;
 }
 
-// ---------------------------------------------------------------------------
-// standalone dense velocity sum (one evaluation of eq. BrV)
-// block b handles targets [blk_first[b], +256*TPL) of system blk_sys[b];
-// sources stream through LDS in tiles of 256 points.
-// ---------------------------------------------------------------------------
-template <typename T, int TPL>
-__global__ __launch_bounds__(256) void k_pair_velocity(const int64_t* blk_sys, const int64_t* blk_first,
-                                                        const int64_t* pt_off, const SysConst<T>* sysc,
-                                                        const void* tabs, const T* x, const T* y, const T* fx,
-                                                        const T* fy, T* ux, T* uy)
+// the item of a prefix array (first[0..n], ascending) that index i falls in
+__device__ __forceinline__ int64_t prefix_item(const int64_t* first, int64_t n, int64_t i)
 {
-    __shared__ Src4<T> tile[256];
-    __shared__ double red[2][4];
-    __shared__ TabSys tab_s[1];
-    TabSys* tab = tab_s;
-    const int tid = threadIdx.x;
-    const int64_t s = blk_sys[blockIdx.x];
-    const int64_t first = blk_first[blockIdx.x];
+    int64_t lo = 0, hi = n;  // first[lo] <= i < first[hi]
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) / 2;
+        if (first[mid] <= i) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// ---------------------------------------------------------------------------
+// standalone dense velocity sum (one evaluation of eq. BrV), one-sided: a
+// workgroup takes 64 targets of one system, one per lane, and its eight waves
+// split the sources (streamed through LDS in tiles of 512) between them;
+// the waves' sums are added in order.  blk0[s]: first workgroup of system s.
+// Bound by the chain of pair evaluations per lane: with one wave per 64
+// targets over all sources, 256 or 512 targets a workgroup, two FP64 systems
+// of 200 points took 78 us.
+// ---------------------------------------------------------------------------
+constexpr int VEL_WAVES = 8, VEL_TILE = 512;
+template <typename T>
+__global__ __launch_bounds__(64 * VEL_WAVES) void k_pair_velocity(int64_t n_sys, const int64_t* blk0,
+                                                                  const int64_t* pt_off, const SysConst<T>* sysc,
+                                                                  const void* tabs, const T* x, const T* y,
+                                                                  const T* fx, const T* fy, T* ux, T* uy)
+{
+    __shared__ Src4<T> tile[VEL_TILE];
+    __shared__ V2<double> part[VEL_WAVES][64];
+    __shared__ double red[2][VEL_WAVES];
+    // the FP32 table (FP64 reads its own from HBM)
+    __shared__ std::conditional_t<sizeof(T) == 4, TabSys, int> tab_s[1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s = prefix_item(blk0, n_sys, blockIdx.x);
     const int64_t p0 = pt_off[s];
     const int64_t n = pt_off[s + 1] - p0;
+    const int64_t i = ((int64_t)blockIdx.x - blk0[s]) * 64 + lane;
     const SysConst<T>& C = sysc[s];
-    if constexpr (sizeof(T) == 4) tab_load((const TabSys*)tabs + s, tab, tid, 256);
+    if constexpr (sizeof(T) == 4) tab_load((const TabSys*)tabs + s, tab_s, tid, 64 * VEL_WAVES);
     // FP32 accumulates in FP64 (pair_accumulate_x); FP64 in FP64
-    T xi[TPL], yi[TPL], ax[TPL], ay[TPL];
-    double axd[TPL], ayd[TPL];
-#pragma unroll
-    for (int k = 0; k < TPL; ++k) {
-        const int64_t i = first + tid + 256 * k;
-        xi[k] = i < n ? x[p0 + i] : (T)0;
-        yi[k] = i < n ? y[p0 + i] : (T)0;
-        ax[k] = (T)0;
-        ay[k] = (T)0;
-        axd[k] = ayd[k] = 0.0;
-    }
+    const T xi[1] = {i < n ? x[p0 + i] : (T)0}, yi[1] = {i < n ? y[p0 + i] : (T)0};
+    double ax[1] = {0.0}, ay[1] = {0.0};
     // sum of the forces in FP64: it multiplies H1(0) in every target's
     // velocity, and the forces of a filament cancel to a small total
     double sfx = 0.0, sfy = 0.0;
-    for (int64_t j0 = 0; j0 < n; j0 += 256) {
+    for (int64_t j0 = 0; j0 < n; j0 += VEL_TILE) {
         const int64_t j = j0 + tid;
         Src4<T> v;
         if (j < n) {
@@ -484,34 +496,32 @@ __global__ __launch_bounds__(256) void k_pair_velocity(const int64_t* blk_sys, c
         __syncthreads();
         tile[tid] = v;
         __syncthreads();
-        const int m = (int)((n - j0) < 256 ? (n - j0) : 256);
+        const int m = (int)min<int64_t>(VEL_TILE, n - j0), per = (m + VEL_WAVES - 1) / VEL_WAVES;
+        const int lo = min(m, w * per), hi = min(m, lo + per);
         if constexpr (sizeof(T) == 4)
-            pair_accumulate_x<TPL>(C, tab, tile, m, xi, yi, axd, ayd);
+            pair_accumulate_x<1>(C, tab_s, tile + lo, hi - lo, xi, yi, ax, ay);
         else
-            pair_accumulate<T, TPL>(C, (const TabSys64*)tabs + s, tile, m, xi, yi, ax, ay);
+            pair_accumulate<T, 1>(C, (const TabSys64*)tabs + s, tile + lo, hi - lo, xi, yi, ax, ay);
     }
     sfx = wave_sum(sfx);
     sfy = wave_sum(sfy);
-    if ((tid & 63) == 0) {
-        red[0][tid >> 6] = sfx;
-        red[1][tid >> 6] = sfy;
+    if (lane == 0) {
+        red[0][w] = sfx;
+        red[1][w] = sfy;
     }
+    part[w][lane] = V2<double>{ax[0], ay[0]};
     __syncthreads();
-    const double SFxd = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    const double SFyd = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    if (w != 0 || i >= n) return;
+    double SFx = 0.0, SFy = 0.0, u = 0.0, v = 0.0;
 #pragma unroll
-    for (int k = 0; k < TPL; ++k) {
-        const int64_t i = first + tid + 256 * k;
-        if (i < n) {
-            if constexpr (sizeof(T) == 4) {
-                ux[p0 + i] = (T)fma((double)C.h1c, SFxd, axd[k]);
-                uy[p0 + i] = (T)fma((double)C.h1c, SFyd, ayd[k]);
-            } else {
-                ux[p0 + i] = fma_t(C.h1c, (T)SFxd, ax[k]);
-                uy[p0 + i] = fma_t(C.h1c, (T)SFyd, ay[k]);
-            }
-        }
+    for (int k = 0; k < VEL_WAVES; ++k) {
+        SFx += red[0][k];
+        SFy += red[1][k];
+        u += part[k][lane].x;
+        v += part[k][lane].y;
     }
+    ux[p0 + i] = (T)fma((double)C.h1c, SFx, u);
+    uy[p0 + i] = (T)fma((double)C.h1c, SFy, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -1189,13 +1199,13 @@ __global__ __launch_bounds__(256) void k_big_step(const int64_t* blk_sys, const 
 
 // ---------------------------------------------------------------------------
 // large systems in FP32, symmetric: every pair of points is evaluated once
-// per step and serves both ends.  Points form tiles of BIG_T = 256 (four
-// blocks of 64); one workgroup of four waves takes one pair of tiles
-// (ta <= tb) of one system.  Wave w holds block w of tile ta as targets, one
-// point per lane, and runs over the blocks of tile tb (from block w on when
-// ta == tb) with the lane schedule of the small systems: at offset s lane l
-// pairs its target with point (l + s) mod 64 of the block, whose sums rotate
-// down one lane per offset.  Both ends accumulate in FP64 as in
+// and serves both ends, in forward steps and in velocity sums of given
+// forces.  Points form tiles of 128 (two blocks of 64); one workgroup of
+// four waves takes one pair of tiles (ta <= tb) of one system.  A wave holds
+// a block of tile ta as targets, one point per lane, and runs over a block of
+// tile tb (its own or a later one when ta == tb) with the lane schedule of
+// the small systems: at offset s lane l pairs its target with point (l + s) mod 64 of
+// the block, whose sums rotate down one lane per offset.  Both ends accumulate in FP64 as in
 // pair_accumulate_x (the constant part of Ht in two floats, exact products).
 // The workgroup leaves tile ta's sums over tile tb and tile tb's over tile
 // ta in two slots of a partial-sum buffer (one slot when ta == tb); then
@@ -1268,75 +1278,107 @@ __device__ __forceinline__ bool big_sym_block(const SysConst<float>& C, const Ta
     return far;
 }
 
-constexpr int BIG_T = BIG_TILE_POINTS;  // points per tile of the symmetric large-system step
+constexpr int BT = BIG_TILE_POINTS;  // points per tile: two blocks
+static_assert(BT == 128, "four waves, one per block pair of two tiles");
 
-// LDS of k_big_pairs: [table][tile ta, BIG_T][tile tb, each block twice][the
-// four waves' sums of tile tb's points]
-constexpr size_t BIG_PAIR_SRC = sizeof(TabSys);
-constexpr size_t BIG_PAIR_SRC2 = BIG_PAIR_SRC + BIG_T * sizeof(Src4<float>);
-constexpr size_t BIG_PAIR_PB = BIG_PAIR_SRC2 + 2 * BIG_T * sizeof(Src4<float>);
-constexpr size_t BIG_PAIR_LDS = BIG_PAIR_PB + 4 * BIG_T * sizeof(V2<double>);
+// LDS of k_tile_pairs: [table][tile ta][tile tb, each block twice][sums of
+// tile tb's points by block of ta][sums of tile ta's points by block of tb]
+struct TileLds {
+    static constexpr size_t src = sizeof(TabSys), src2 = src + BT * sizeof(Src4<float>),
+                            pb = src2 + 2 * BT * sizeof(Src4<float>), pa = pb + 2 * BT * sizeof(V2<double>),
+                            total = pa + 2 * BT * sizeof(V2<double>);
+};
 static_assert(sizeof(TabSys) % 16 == 0, "16-byte aligned LDS sections");
 
-__global__ __launch_bounds__(256) void k_big_pairs(BigTiles bt, Batch b, BigState S, int step, Run r,
+// One workgroup of four waves per tile pair (ta <= tb) of one system, one wave
+// per block pair: the off-diagonal pairs of all systems first, then the
+// diagonal ones (three quarters of the work, so that they fill the launch's
+// tail).  Sources: bt.src (position, force), or x, y, fx, fy (SOA).  40 KB of
+// LDS: four workgroups share a CU, one's table copy and sums overlapping the
+// others' pair loops.  Bound by VALU issue (47.5 operations per pair and
+// both ends, FP64 accumulation among them).  Tiles of 256 points (a wave per
+// block of ta running over four blocks of tb, three workgroups a CU) took 832
+// us against 702 for a velocity sum of 64 x 4096 points, and 49 against 30 us
+// for the step of two such systems, whose 272 pairs leave most of the chip idle.
+template <bool SOA>
+__global__ __launch_bounds__(256) void k_tile_pairs(BigTiles bt, const SysConst<float>* sysc, const TabSys* tabs,
+                                                    const float* x, const float* y, const float* fx, const float* fy,
                                                     const int32_t* status)
 {
+    using L = TileLds;
     extern __shared__ __align__(16) unsigned char smem[];
     TabSys* tab = reinterpret_cast<TabSys*>(smem);
-    Src4<float>* sa = reinterpret_cast<Src4<float>*>(smem + BIG_PAIR_SRC);
-    Src4<float>* sb2 = reinterpret_cast<Src4<float>*>(smem + BIG_PAIR_SRC2);
-    V2<double>* pb = reinterpret_cast<V2<double>*>(smem + BIG_PAIR_PB);
+    Src4<float>* sa = reinterpret_cast<Src4<float>*>(smem + L::src);
+    Src4<float>* sb2 = reinterpret_cast<Src4<float>*>(smem + L::src2);
+    V2<double>* pb = reinterpret_cast<V2<double>*>(smem + L::pb);
+    V2<double>* pa = reinterpret_cast<V2<double>*>(smem + L::pa);
     __shared__ int s_status;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t s = bt.sys[blockIdx.x];
-    const int tt = bt.tile[blockIdx.x];
-    const int ta = tt & 0xffff, tb = tt >> 16;
-    // one read of the status per workgroup, broadcast (uniform exit)
-    if (tid == 0) s_status = status[s];
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s_status) != 0) return;
-    tab_load((const TabSys*)b.tab + s, tab, tid, 256);
-    const int64_t p0 = b.pt_off[s];
-    const int N = b.npt[s];
-    const int n = N * b.nswim[s];
-    const int nt = (n + BIG_T - 1) / BIG_T;
-    const int64_t f0 = b.sw_off[s];
-    const int cur = step & 1;
-    const float* xh = (const float*)S.xh[cur] + p0;
-    const float* yh = (const float*)S.yh[cur] + p0;
-    const float* xl = (const float*)S.xl[cur] + p0;
-    const float* yl = (const float*)S.yl[cur] + p0;
-    const float t = (float)((double)step * r.dt);
-    const SysConst<float> C = ((const SysConst<float>*)b.sysc)[s];
+    // which system and tiles
+    const int64_t n_off = bt.off0[bt.n_big];
+    int64_t g;
+    int ta, tb;
+    if ((int64_t)blockIdx.x < n_off) {
+        g = prefix_item(bt.off0, bt.n_big, blockIdx.x);
+        const int64_t k = (int64_t)blockIdx.x - bt.off0[g];  // pair k: tb (tb - 1) / 2 + ta, ta < tb
+        int64_t t = (int64_t)(0.5 * (1.0 + sqrt(1.0 + 8.0 * (double)k)));
+        while (t * (t - 1) / 2 > k) --t;
+        while (t * (t + 1) / 2 <= k) ++t;
+        tb = (int)t;
+        ta = (int)(k - t * (t - 1) / 2);
+    } else {
+        g = prefix_item(bt.tile0, bt.n_big, (int64_t)blockIdx.x - n_off);
+        ta = tb = (int)((int64_t)blockIdx.x - n_off - bt.tile0[g]);
+    }
+    const int64_t s = bt.list[g];
+    if (status) {
+        // one read of the status per workgroup, broadcast (uniform exit)
+        if (tid == 0) s_status = status[s];
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(s_status) != 0) return;
+    }
+    tab_load(tabs + s, tab, tid, 256);
+    const int64_t p0 = bt.pt0[g];
+    const int n = bt.cnt[g], nt = (n + BT - 1) / BT;
+    const SysConst<float>& C = sysc[s];
     const bool diag = ta == tb;
     // sources of both tiles; points beyond n: at point n - 1, no force (they
     // add nothing and their own sums are not used)
-    for (int jj = tid; jj < BIG_T; jj += 256) {
-        const int ib = tb * BIG_T + jj;
-        Src4<float> v = big_source<float>(b, xh, yh, xl, yl, f0, N, min(ib, n - 1), t);
-        if (ib >= n) v.fx = v.fy = 0.0f;
-        const int k = ((jj >> 6) << 7) + (jj & 63);
+    auto source = [&](int i) {
+        const int64_t k = p0 + min(i, n - 1);
+        Src4<float> v;
+        if constexpr (SOA) {
+            v.x = x[k];
+            v.y = y[k];
+            v.fx = fx[k];
+            v.fy = fy[k];
+        } else {
+            v = reinterpret_cast<const Src4<float>*>(bt.src)[k];
+        }
+        if (i >= n) v.fx = v.fy = 0.0f;
+        return v;
+    };
+    // the first two waves load tile tb, the others tile ta
+    const int jj = tid & (BT - 1);
+    if (tid < BT) {
+        const Src4<float> v = source(tb * BT + jj);
+        const int k = src2_slot(jj);
         sb2[k] = v;
         sb2[k + 64] = v;
-        if (!diag) {
-            const int ia = ta * BIG_T + jj;
-            Src4<float> u = big_source<float>(b, xh, yh, xl, yl, f0, N, min(ia, n - 1), t);
-            if (ia >= n) u.fx = u.fy = 0.0f;
-            sa[jj] = u;
-        }
+    } else if (!diag) {
+        sa[jj] = source(ta * BT + jj);
     }
-    for (int k = tid; k < 4 * BIG_T; k += 256) pb[k] = V2<double>{0.0, 0.0};
     __syncthreads();
-    const Src4<float> ti = diag ? sb2[(w << 7) + lane] : sa[(w << 6) + lane];
+    const int a = w >> 1, bb = w & 1;  // this wave's block pair
+    const Src4<float> ti = diag ? sb2[(a << 7) + lane] : sa[(a << 6) + lane];
     const double tfx = ti.fx, tfy = ti.fy;
-    double ax = 0.0, ay = 0.0;
-    for (int bb = diag ? w : 0; bb < 4; ++bb) {
+    double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
+    if (!diag || bb >= a) {
         // the diagonal block: offsets 1..32, offset 32 for lanes 0..31
-        const bool dblk = diag && bb == w;
+        const bool dblk = diag && bb == a;
         const int s_lo = dblk ? 1 : 0, s_full = dblk ? 32 : 64, s_hi = dblk ? 33 : 64;
         const Src4<float>* sp = sb2 + (bb << 7);
-        double bx, by;
         const bool far = big_sym_block<false>(C, tab, ti, tfx, tfy, sp, s_lo, s_full, s_hi, lane, ax, ay, bx, by);
         if (__any(far)) {
             double fx2, fy2;
@@ -1344,64 +1386,151 @@ __global__ __launch_bounds__(256) void k_big_pairs(BigTiles bt, Batch b, BigStat
             bx += fx2;
             by += fy2;
         }
-        pb[w * BIG_T + (bb << 6) + lane] = V2<double>{bx, by};
     }
-    V2<double>* const pbuf = reinterpret_cast<V2<double>*>(bt.part);
-    V2<double>* part = pbuf + (bt.poff[s] + (int64_t)ta * nt + tb) * BIG_T;
-    if (diag) {
-        // this wave's targets are points of the same tile: their sums join
-        // the moving-point sums of their own block
-        V2<double>& e = pb[w * BIG_T + (w << 6) + lane];
-        e.x += ax;
-        e.y += ay;
-    } else {
-        part[(w << 6) + lane] = V2<double>{ax, ay};
-    }
+    pb[a * BT + (bb << 6) + lane] = V2<double>{bx, by};
+    pa[bb * BT + (a << 6) + lane] = V2<double>{ax, ay};
     __syncthreads();
-    // tile tb's sums over tile ta (the whole tile's when ta == tb): the four
-    // waves' slots in order
-    V2<double> u = pb[tid];
-#pragma unroll
-    for (int q = 1; q < 4; ++q) {
-        u.x += pb[q * BIG_T + tid].x;
-        u.y += pb[q * BIG_T + tid].y;
+    // slot (t, q): tile t's sums over tile q; a diagonal pair's two kinds of
+    // sums share one slot
+    V2<double>* const pbuf = reinterpret_cast<V2<double>*>(bt.part) + bt.slot0[g] * BT;
+    if (tid < BT) {
+        V2<double> u = pb[tid], v = pa[tid];
+        u.x += pb[BT + tid].x;
+        u.y += pb[BT + tid].y;
+        v.x += pa[BT + tid].x;
+        v.y += pa[BT + tid].y;
+        if (diag) {
+            u.x += v.x;
+            u.y += v.y;
+        } else {
+            pbuf[((int64_t)ta * nt + tb) * BT + tid] = v;
+        }
+        pbuf[((int64_t)tb * nt + ta) * BT + tid] = u;
     }
-    pbuf[(bt.poff[s] + (int64_t)tb * nt + ta) * BIG_T + tid] = u;
 }
 
-// the Euler step of the symmetric large-system path: one workgroup per tile,
-// a point's velocity the sum of its tile's slots in tile order
-__global__ __launch_bounds__(256) void k_big_update(BigTiles bt, Batch b, BigState S, int step, Run r, float* obs,
-                                                     int32_t* status, int32_t* steps_done)
+// the velocities of the tile-pair path for given forces: a point's slots in
+// tile order, and H1(0) times the sum of the forces (FP64: they cancel)
+__global__ __launch_bounds__(256) void k_tile_velocity(BigTiles bt, const SysConst<float>* sysc, const float* fx,
+                                                       const float* fy, float* ux, float* uy)
 {
-    __shared__ int s_status;
+    __shared__ double red[2][4];
     const int tid = threadIdx.x;
-    const int64_t s = bt.sys[blockIdx.x];
-    const int tile = bt.tile[blockIdx.x];
-    if (tid == 0) s_status = status[s];
+    const int64_t g = prefix_item(bt.tile0, bt.n_big, blockIdx.x);
+    const int tile = (int)((int64_t)blockIdx.x - bt.tile0[g]);
+    const int64_t p0 = bt.pt0[g];
+    const int n = bt.cnt[g], nt = (n + BT - 1) / BT;
+    double sfx = 0.0, sfy = 0.0;
+    for (int j = tid; j < n; j += 256) {
+        sfx += fx[p0 + j];
+        sfy += fy[p0 + j];
+    }
+    sfx = wave_sum(sfx);
+    sfy = wave_sum(sfy);
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = sfx;
+        red[1][tid >> 6] = sfy;
+    }
+    __syncthreads();
+    const int64_t i = (int64_t)tile * BT + tid;
+    if (tid >= BT || i >= n) return;
+    const V2<double>* src = reinterpret_cast<const V2<double>*>(bt.part) + (bt.slot0[g] + (int64_t)tile * nt) * BT + tid;
+    double u = 0.0, v = 0.0;
+    for (int q = 0; q < nt; ++q) {
+        const V2<double> e = src[(int64_t)q * BT];
+        u += e.x;
+        v += e.y;
+    }
+    const double h1c = sysc[bt.list[g]].h1c;
+    ux[p0 + i] = (float)fma(h1c, red[0][0] + red[0][1] + red[0][2] + red[0][3], u);
+    uy[p0 + i] = (float)fma(h1c, red[1][0] + red[1][1] + red[1][2] + red[1][3], v);
+}
+
+// sources (position, force at t = 0) of the large systems' first step
+__global__ __launch_bounds__(256) void k_big_sources(BigTiles bt, Batch b, BigState S)
+{
+    const int64_t g = blockIdx.y, s = bt.list[g], p0 = bt.pt0[g];
+    const int n = bt.cnt[g];
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256)
+        reinterpret_cast<Src4<float>*>(bt.src)[p0 + i] =
+            big_source<float>(b, (const float*)S.xh[0] + p0, (const float*)S.yh[0] + p0, (const float*)S.xl[0] + p0,
+                              (const float*)S.yl[0] + p0, b.sw_off[s], b.npt[s], i, 0.0f);
+}
+
+// The Euler step of the tile-pair path, one workgroup per tile: a point's
+// velocity is the sum of its tile's slots in tile order (SG groups of threads
+// each a share of the slots, added in order), then the new positions of the
+// tile and of two points on either side, and from them the elastic forces of
+// the tile's points at the new time: the sources of the next step, formed
+// once per point instead of by every tile pair that reads them.
+constexpr int BIG_HALO = 2, UPD_PT = (BT + 2 * BIG_HALO + 63) / 64 * 64, UPD_SG = 4;
+__global__ __launch_bounds__(UPD_PT* UPD_SG) void k_big_update(BigTiles bt, Batch b, BigState S, int step, Run r,
+                                                               float* obs, int32_t* status, int32_t* steps_done)
+{
+    constexpr int PT = UPD_PT, SG = UPD_SG;
+    __shared__ V2<double> sum[SG][PT];
+    __shared__ float4 pos[PT];  // hi x, hi y, lo x, lo y
+    __shared__ int s_status;
+    const int tid = threadIdx.x % PT, sg = threadIdx.x / PT;
+    const int64_t g = prefix_item(bt.tile0, bt.n_big, blockIdx.x);
+    const int tile = (int)((int64_t)blockIdx.x - bt.tile0[g]);
+    const int64_t s = bt.list[g];
+    if (threadIdx.x == 0) s_status = status[s];
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(s_status) != 0) return;
-    const int64_t p0 = b.pt_off[s];
-    const int N = b.npt[s];
-    const int n = N * b.nswim[s];
-    const int nt = (n + BIG_T - 1) / BIG_T;
+    const int64_t p0 = bt.pt0[g];
+    const int N = b.npt[s], n = bt.cnt[g], nt = (n + BT - 1) / BT;
     const int64_t f0 = b.sw_off[s];
     const int cur = step & 1, nxt = cur ^ 1;
-    const int64_t i = (int64_t)tile * BIG_T + tid;
-    if (i >= n) return;
-    const V2<double>* src = reinterpret_cast<const V2<double>*>(bt.part) + (bt.poff[s] + (int64_t)tile * nt) * BIG_T + tid;
+    const int i = tile * BT + tid - BIG_HALO;  // this thread's point (halo points belong to the next tiles)
+    const bool held = tid < BT + 2 * BIG_HALO && i >= 0 && i < n;
+    const bool own = held && tid >= BIG_HALO && tid < BT + BIG_HALO;
     double ux = 0.0, uy = 0.0;
-    for (int q = 0; q < nt; ++q) {
-        const V2<double> v = src[(int64_t)q * BIG_T];
-        ux += v.x;
-        uy += v.y;
+    if (held) {
+        const int t = i / BT, per = (nt + SG - 1) / SG, q1 = min(nt, (sg + 1) * per);
+        const V2<double>* src =
+            reinterpret_cast<const V2<double>*>(bt.part) + (bt.slot0[g] + (int64_t)t * nt) * BT + (i - t * BT);
+#pragma unroll 4
+        for (int q = sg * per; q < q1; ++q) {
+            const V2<double> v = src[(int64_t)q * BT];
+            ux += v.x;
+            uy += v.y;
+        }
     }
-    const float* xh = (const float*)S.xh[cur] + p0;
-    const float* yh = (const float*)S.yh[cur] + p0;
-    const float* xl = (const float*)S.xl[cur] + p0;
-    const float* yl = (const float*)S.yl[cur] + p0;
-    big_update_point<float>(S, step, r, s, p0, f0, N, i, nxt, xh[i], yh[i], xl[i], yl[i], (float)ux, (float)uy, obs,
-                            status, steps_done);
+    sum[sg][tid] = V2<double>{ux, uy};
+    __syncthreads();
+    if (sg == 0 && held) {
+#pragma unroll
+        for (int k = 1; k < SG; ++k) {
+            ux += sum[k][tid].x;
+            uy += sum[k][tid].y;
+        }
+        float hx = ((const float*)S.xh[cur])[p0 + i], hy = ((const float*)S.yh[cur])[p0 + i];
+        float lx = ((const float*)S.xl[cur])[p0 + i], ly = ((const float*)S.yl[cur])[p0 + i];
+        const float dt = (float)r.dt;
+        if (own)
+            big_update_point<float>(S, step, r, s, p0, f0, N, i, nxt, hx, hy, lx, ly, (float)ux, (float)uy, obs,
+                                    status, steps_done);
+        acc2(hx, lx, dt * (float)ux);
+        acc2(hy, ly, dt * (float)uy);
+        pos[tid] = make_float4(hx, hy, lx, ly);
+    }
+    __syncthreads();
+    const int j = tile * BT + (int)threadIdx.x;
+    if ((int)threadIdx.x < BT && j < n) {
+        const int m = j / N, p = j - m * N, base = m * N - (tile * BT - BIG_HALO);
+        const FilP<float> q = load_filp<float>(b.params, f0 + m, N);
+        auto seg = [&](int k, float& dx, float& dy) {
+            const float4 e = pos[base + k], f = pos[base + k + 1];
+            dx = (f.x - e.x) + (f.z - e.z);
+            dy = (f.y - e.y) + (f.w - e.w);
+        };
+        Src4<float> v;
+        point_force<float>(seg, p, q, (float)((double)(step + 1) * r.dt), v.fx, v.fy);
+        v.x = pos[threadIdx.x + BIG_HALO].x;
+        v.y = pos[threadIdx.x + BIG_HALO].y;
+        reinterpret_cast<Src4<float>*>(bt.src)[p0 + j] = v;
+    }
 }
 
 template <typename T>
@@ -1603,29 +1732,48 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, int TPL>
-static void pair_launch(int64_t nb, const int64_t* bs, const int64_t* bf, const int64_t* off, const void* sysc,
-                        const void* tab, const void* x, const void* y, const void* fx, const void* fy, void* ux,
-                        void* uy, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_pair_velocity<T, TPL>), dim3((unsigned)nb), dim3(256), 0, st, bs, bf, off,
-                       (const SysConst<T>*)sysc, tab, (const T*)x, (const T*)y, (const T*)fx,
-                       (const T*)fy, (T*)ux, (T*)uy);
-}
-
-hipError_t launch_pair_velocity(int dtype, int tpl, int64_t nb, const int64_t* bs, const int64_t* bf,
-                                const int64_t* off, const void* sysc, const void* tab, const void* x, const void* y,
-                                const void* fx, const void* fy, void* ux, void* uy, hipStream_t st)
+hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* off,
+                                const void* sysc, const void* tab, const void* x, const void* y, const void* fx,
+                                const void* fy, void* ux, void* uy, hipStream_t st)
 {
     if (nb <= 0) return hipSuccess;
-#define PAIR_CASE(T, P) \
-    case P: pair_launch<T, P>(nb, bs, bf, off, sysc, tab, x, y, fx, fy, ux, uy, st); break;
-    if (dtype == 0) {
-        switch (tpl) { PAIR_CASE(float, 1) PAIR_CASE(float, 2) PAIR_CASE(float, 4) default: return hipErrorInvalidValue; }
-    } else {
-        switch (tpl) { PAIR_CASE(double, 1) PAIR_CASE(double, 2) PAIR_CASE(double, 4) default: return hipErrorInvalidValue; }
+    const dim3 grid((unsigned)nb), block(64 * VEL_WAVES);
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_pair_velocity<float>, grid, block, 0, st, n_sys, blk0, off, (const SysConst<float>*)sysc,
+                           tab, (const float*)x, (const float*)y, (const float*)fx, (const float*)fy, (float*)ux,
+                           (float*)uy);
+    else
+        hipLaunchKernelGGL(k_pair_velocity<double>, grid, block, 0, st, n_sys, blk0, off,
+                           (const SysConst<double>*)sysc, tab, (const double*)x, (const double*)y, (const double*)fx,
+                           (const double*)fy, (double*)ux, (double*)uy);
+    return hipGetLastError();
+}
+
+template <bool SOA>
+static hipError_t tile_prepare()
+{
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_tile_pairs<SOA>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)TileLds::total);
+        if (e != hipSuccess) return e;
+        attr = true;
     }
-#undef PAIR_CASE
+    return hipSuccess;
+}
+
+hipError_t launch_tile_velocity(const BigTiles& bt, const void* sysc, const void* tab, const void* x, const void* y,
+                                const void* fx, const void* fy, void* ux, void* uy, hipStream_t st)
+{
+    if (bt.n_big <= 0) return hipSuccess;
+    hipError_t e = tile_prepare<true>();
+    if (e != hipSuccess) return e;
+    const SysConst<float>* C = (const SysConst<float>*)sysc;
+    hipLaunchKernelGGL(k_tile_pairs<true>, dim3((unsigned)bt.n_pairs), dim3(256), TileLds::total, st, bt, C,
+                       (const TabSys*)tab, (const float*)x, (const float*)y, (const float*)fx, (const float*)fy,
+                       (const int32_t*)nullptr);
+    hipLaunchKernelGGL(k_tile_velocity, dim3((unsigned)bt.n_tiles), dim3(256), 0, st, bt, C, (const float*)fx,
+                       (const float*)fy, (float*)ux, (float*)uy);
     return hipGetLastError();
 }
 
@@ -1818,35 +1966,25 @@ hipError_t launch_big_step(int dtype, int tpl, int64_t nb, const int64_t* bs, co
 #undef BIG_CASE
 }
 
-size_t big_pair_lds_bytes() { return BIG_PAIR_LDS; }
+// raise k_tile_pairs' dynamic-LDS limit (outside any stream capture)
+hipError_t prepare_big_pairs() { return tile_prepare<false>(); }
 
-// raise k_big_pairs' dynamic-LDS limit (outside any stream capture)
-hipError_t prepare_big_pairs()
+hipError_t launch_big_sources(const BigTiles& bt, const Batch& b, const BigState& s, hipStream_t st)
 {
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_big_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)BIG_PAIR_LDS);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
-    return hipSuccess;
-}
-
-hipError_t launch_big_pairs(int64_t n_pairs, const BigTiles& bt, const Batch& b, const BigState& s, int step,
-                            const Run& r, const int32_t* status, hipStream_t st)
-{
-    if (n_pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_big_pairs, dim3((unsigned)n_pairs), dim3(256), BIG_PAIR_LDS, st, bt, b, s, step, r, status);
+    if (bt.n_big <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_big_sources, dim3(16, (unsigned)bt.n_big), dim3(256), 0, st, bt, b, s);
     return hipGetLastError();
 }
 
-hipError_t launch_big_update(int64_t n_tiles, const BigTiles& bt, const Batch& b, const BigState& s, int step,
-                             const Run& r, void* obs, int32_t* status, int32_t* steps_done, hipStream_t st)
+hipError_t launch_big_sym_step(const BigTiles& bt, const Batch& b, const BigState& s, int step, const Run& r, void* obs,
+                               int32_t* status, int32_t* steps_done, hipStream_t st)
 {
-    if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_big_update, dim3((unsigned)n_tiles), dim3(256), 0, st, bt, b, s, step, r, (float*)obs,
-                       status, steps_done);
+    if (bt.n_big <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tile_pairs<false>, dim3((unsigned)bt.n_pairs), dim3(256), TileLds::total, st, bt,
+                       (const SysConst<float>*)b.sysc, (const TabSys*)b.tab, (const float*)nullptr,
+                       (const float*)nullptr, (const float*)nullptr, (const float*)nullptr, (const int32_t*)status);
+    hipLaunchKernelGGL(k_big_update, dim3((unsigned)bt.n_tiles), dim3(UPD_PT * UPD_SG), 0, st, bt, b, s, step, r,
+                       (float*)obs, status, steps_done);
     return hipGetLastError();
 }
 
