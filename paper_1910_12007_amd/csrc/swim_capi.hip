@@ -1216,8 +1216,10 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
     hipStream_t st = pick(c, stream);
     // the pair kernel from the system's table, as in the forward runs (built
     // on the device from the FP64 kernel functions)
-    TRY(begin_uploads(c, 16));
+    TRY(begin_uploads(c, 16 + sizeof(fc)));
     const double *alpha_dev, *eps_dev;
+    const FieldConst* fc_dev;
+    TRY(put(c, &fc, 1, &fc_dev));
     TRY(put(c, &alpha, 1, &alpha_dev));
     TRY(put(c, &eps, 1, &eps_dev));
     TRY(end_uploads(c, st));
@@ -1230,10 +1232,10 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
     void* wtab = nullptr;
     if (dtype == SWIM_F32) {
         // and the pressure weight's table on the same intervals
-        TRY(ensure(c, B_WTAB, (size_t)TAB_N * 16));
+        TRY(ensure(c, B_WTAB, (size_t)(TAB_N + 1) * 16));
         wtab = c->buf[B_WTAB].p;
     }
-    HIPCHK(launch_flow_field(dtype, n, x, y, fx, fy, fc, nt, tx, ty, u, v, p, tab, wtab, st));
+    HIPCHK(launch_flow_field(dtype, n, x, y, fx, fy, fc_dev, nt, tx, ty, u, v, p, tab, wtab, st));
     return SWIM_OK;
 }
 

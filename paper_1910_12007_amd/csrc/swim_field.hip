@@ -25,7 +25,7 @@ namespace swim {
 
 namespace {
 
-constexpr int FIELD_TILE = 1024;
+constexpr int FIELD_TILE = 256;  // sources per LDS tile, threads per workgroup
 
 // pressure weight m(r) / (2 pi r^2) at t = r^2, in FP64
 __device__ double field_weight(const FieldConst& fc, double t)
@@ -50,11 +50,16 @@ __device__ double field_weight(const FieldConst& fc, double t)
 
 // FP32 table of the pressure weight on the kernel table's intervals of
 // v = 1 + sigma t: the cubic through its FP64 values at the nodes 0, 1/4,
-// 3/4, 1 of each interval (one thread per interval)
-__global__ __launch_bounds__(256) void k_weight_table(FieldConst fc, float4* wt)
+// 3/4, 1 of each interval (one thread per interval), then a zero entry
+__global__ __launch_bounds__(256) void k_weight_table(const FieldConst* fcp, float4* wt)
 {
+    const FieldConst& fc = *fcp;
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= TAB_N) return;
+    if (i > TAB_N) return;
+    if (i == TAB_N) {
+        wt[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        return;
+    }
     const int e = i >> TAB_M, j = i & ((1 << TAB_M) - 1);
     const double a = ldexp(1.0, e);
     const double v0 = a * (1.0 + (double)j / (double)(1 << TAB_M)), hv = a / (double)(1 << TAB_M);
@@ -66,109 +71,207 @@ __global__ __launch_bounds__(256) void k_weight_table(FieldConst fc, float4* wt)
     wt[i] = make_float4(c[0], c[1], c[2], c[3]);
 }
 
-// tab: the system's kernel table (TabSys, TabSys64), used for every pair
-// inside it; beyond it the direct evaluation
-template <typename T>
-__global__ __launch_bounds__(256) void k_flow_field(int64_t n, const T* x, const T* y, const T* fx, const T* fy,
-                                                    FieldConst fc, int64_t nt, const T* tx, const T* ty, T* u, T* v,
-                                                    T* p, const void* tab_g, const float4* wtab)
+// FP32 values of a pair beyond the tables (or not finite), evaluated directly;
+// not inlined, so that its registers stay out of the pair loop
+struct FieldFar {
+    float Ht, H2;
+    double w;
+};
+__device__ __attribute__((noinline)) FieldFar field_far(const FieldConst& fc, float t2, double t)
 {
-    __shared__ Src4<T> tile[FIELD_TILE];
-    const SysConst<T> C = *reinterpret_cast<const SysConst<T>*>(sizeof(T) == 4 ? (const void*)&fc.c32
-                                                                                   : (const void*)&fc.c64);
-    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    FieldFar f;
+    kernel_eval<float>(fc.c32, t2, f.Ht, f.H2);
+    f.w = field_weight(fc, t);
+    return f;
+}
+// one interval of the two FP32 tables together: Ht, H2 / sigma and the
+// pressure weight, three 16-byte reads at one address
+struct alignas(16) FieldE {
+    float4 h, g, w;
+};
+// a source in both precisions (position times rho in FP32)
+struct alignas(16) FieldSrc {
+    double x, y, fx, fy;
+    float4 f;
+};
+
+// FP32 fields, TPL targets per thread.  The kernel table and the pressure
+// weight's are merged in LDS (34 KB); sources pass through LDS in both
+// precisions, so that a pair costs the FP64 difference (for the pressure),
+// the FP32 table lookup on scaled positions, three cubics and three FP64
+// accumulations: ~40 operations, bound by VALU issue.  Neighbouring targets
+// read the same few entries.  A picture of 1024 x 1024 targets and 256
+// sources took 727 us with the tables gathered from L1, positions converted
+// and the forces summed again by every thread.  Two targets per thread share
+// a source's reads where the picture fills the chip anyway.
+template <int TPL>
+__global__ __launch_bounds__(FIELD_TILE) void k_flow_field32(int64_t n, const float* x, const float* y,
+                                                             const float* fx, const float* fy, const FieldConst* fcp,
+                                                             int64_t nt, const float* tx, const float* ty, float* u,
+                                                             float* v, float* p, const TabSys* tab, const float4* wtab)
+{
+    __shared__ FieldE tb[TAB_N + 1];
+    __shared__ FieldSrc tile[FIELD_TILE];
+    __shared__ double red[2][FIELD_TILE / 64];
+    const FieldConst& fc = *fcp;
+    const int tid = threadIdx.x;
+    for (int i = tid; i <= TAB_N; i += FIELD_TILE) {
+        const float4* e = reinterpret_cast<const float4*>(&tab->e[i]);
+        tb[i] = FieldE{e[0], e[1], wtab[i]};
+    }
+    const float rho = fc.c32.tr;
+    int64_t a[TPL];
+    double X[TPL], Y[TPL], su[TPL], sv[TPL], sp[TPL];
+#pragma unroll
+    for (int q = 0; q < TPL; ++q) {
+        a[q] = ((int64_t)blockIdx.x * TPL + q) * FIELD_TILE + tid;
+        X[q] = a[q] < nt ? (double)tx[a[q]] : 0.0;
+        Y[q] = a[q] < nt ? (double)ty[a[q]] : 0.0;
+        su[q] = sv[q] = sp[q] = 0.0;
+    }
+    double sfx = 0.0, sfy = 0.0;
+    for (int64_t j0 = 0; j0 < n; j0 += FIELD_TILE) {
+        const int m = (int)min<int64_t>(FIELD_TILE, n - j0);
+        __syncthreads();
+        if (tid < m) {
+            const int64_t j = j0 + tid;
+            const float4 f = make_float4(fx[j], fy[j], 0.f, 0.f);
+            tile[tid] = FieldSrc{(double)x[j], (double)y[j], (double)f.x, (double)f.y, f};
+            sfx += (double)f.x;
+            sfy += (double)f.y;
+        }
+        __syncthreads();
+        bool far = false;
+        for (int k = 0; k < m; ++k) {
+            const FieldSrc s = tile[k];
+#pragma unroll
+            for (int q = 0; q < TPL; ++q) {
+                const double dxd = X[q] - s.x, dyd = Y[q] - s.y;
+                const float dx = (float)dxd * rho, dy = (float)dyd * rho;
+                const uint32_t bits = __builtin_bit_cast(uint32_t, fmaf(dx, dx, fmaf(dy, dy, 1.0f)));
+                const uint32_t id = bits >> TAB_SHIFT;
+                far = far || id >= TAB_END;
+                const FieldE& e = tb[min(id, TAB_END) - TAB_BIAS];
+                const float uu = tab_u(bits);
+                const float4 h = e.h, g = e.g, w = e.w;
+                const float Ht = fmaf(fmaf(fmaf(h.w, uu, h.z), uu, h.y), uu, h.x);
+                const float H2 = fmaf(fmaf(fmaf(g.w, uu, g.z), uu, g.y), uu, g.x);
+                const float wt = fmaf(fmaf(fmaf(w.w, uu, w.z), uu, w.y), uu, w.x);
+                const float h2fd = H2 * fmaf(s.f.x, dx, s.f.y * dy);
+                su[q] += (double)fmaf(Ht, s.f.x, h2fd * dx);
+                sv[q] += (double)fmaf(Ht, s.f.y, h2fd * dy);
+                sp[q] = fma(fma(s.fx, dxd, s.fy * dyd), (double)wt, sp[q]);
+            }
+        }
+        if (__any(far)) {
+            // pairs beyond the tables (or not finite), evaluated directly
+            for (int k = 0; k < m; ++k) {
+                const FieldSrc s = tile[k];
+#pragma unroll
+                for (int q = 0; q < TPL; ++q) {
+                    const double dxd = X[q] - s.x, dyd = Y[q] - s.y;
+                    const float dx = (float)dxd, dy = (float)dyd, sx = dx * rho, sy = dy * rho;
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, fmaf(sx, sx, fmaf(sy, sy, 1.0f)));
+                    if ((bits >> TAB_SHIFT) < TAB_END) continue;
+                    const FieldFar f = field_far(fc, fmaf(dx, dx, dy * dy), fma(dxd, dxd, dyd * dyd));
+                    const float h2fd = f.H2 * fmaf(s.f.x, dx, s.f.y * dy);
+                    su[q] += (double)fmaf(f.Ht, s.f.x, h2fd * dx);
+                    sv[q] += (double)fmaf(f.Ht, s.f.y, h2fd * dy);
+                    sp[q] = fma(fma(s.fx, dxd, s.fy * dyd), f.w, sp[q]);
+                }
+            }
+        }
+    }
+    // the forces' sum, for the constant part H1(0)
+    sfx = wave_total(sfx);
+    sfy = wave_total(sfy);
+    __syncthreads();
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = sfx;
+        red[1][tid >> 6] = sfy;
+    }
+    __syncthreads();
+    sfx = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    sfy = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    static_assert(FIELD_TILE == 256, "four waves");
+#pragma unroll
+    for (int q = 0; q < TPL; ++q) {
+        if (a[q] < nt) {
+            u[a[q]] = (float)fma(fc.h1c, sfx, su[q]);
+            v[a[q]] = (float)fma(fc.h1c, sfy, sv[q]);
+            p[a[q]] = (float)sp[q];
+        }
+    }
+}
+
+// FP64 fields: the kernel from the system's FP64 table (direct beyond it),
+// the pressure weight directly
+__global__ __launch_bounds__(FIELD_TILE) void k_flow_field64(int64_t n, const double* x, const double* y,
+                                                             const double* fx, const double* fy,
+                                                             const FieldConst* fcp,
+                                                             int64_t nt, const double* tx, const double* ty, double* u,
+                                                             double* v, double* p, const TabSys64* tab)
+{
+    __shared__ Src4<double> tile[FIELD_TILE];
+    const FieldConst& fc = *fcp;
+    const int tid = threadIdx.x;
+    const int64_t a = (int64_t)blockIdx.x * FIELD_TILE + tid;
     const bool live = a < nt;
-    const double X = live ? (double)tx[a] : 0.0, Y = live ? (double)ty[a] : 0.0;
+    const double X = live ? tx[a] : 0.0, Y = live ? ty[a] : 0.0;
     double su = 0.0, sv = 0.0, sp = 0.0, sfx = 0.0, sfy = 0.0;
     for (int64_t j0 = 0; j0 < n; j0 += FIELD_TILE) {
         const int m = (int)min<int64_t>(FIELD_TILE, n - j0);
         __syncthreads();
-        for (int k = threadIdx.x; k < m; k += 256) {
-            Src4<T> s;
-            s.x = x[j0 + k];
-            s.y = y[j0 + k];
-            s.fx = fx[j0 + k];
-            s.fy = fy[j0 + k];
-            tile[k] = s;
-        }
+        if (tid < m) tile[tid] = Src4<double>{x[j0 + tid], y[j0 + tid], fx[j0 + tid], fy[j0 + tid]};
         __syncthreads();
         for (int k = 0; k < m; ++k) {
-            const Src4<T> s = tile[k];
-            sfx += (double)s.fx;
-            sfy += (double)s.fy;
-            const double dxd = X - (double)s.x, dyd = Y - (double)s.y;
-            const T dx = (T)dxd, dy = (T)dyd;
-            T Ht = (T)0, H2 = (T)0;
-            const T t2 = fma_t(dx, dx, dy * dy);
-            bool direct = true;
-            if constexpr (sizeof(T) == 4) {
-                const uint32_t bits = tab_bits(t2, C.ts);
-                const uint32_t id = bits >> TAB_SHIFT;
-                if (id < TAB_END) {
-                    tab_eval(((const TabSys*)tab_g)->e[id - TAB_BIAS], tab_u(bits), Ht, H2);
-                    H2 *= C.ts;  // the table holds H2 / sigma
-                    direct = false;
-                }
-            } else {
-                direct = tab64_lookup(tab_g, t2, C.ts, Ht, H2);
+            const Src4<double> s = tile[k];
+            sfx += s.fx;
+            sfy += s.fy;
+            const double dx = X - s.x, dy = Y - s.y, t = fma(dx, dx, dy * dy), fd = fma(s.fx, dx, s.fy * dy);
+            double Ht, H2;
+            if (tab64_lookup(tab, t, fc.c64.ts, Ht, H2)) {
+                const V2<double> d = kernel_far64(fc.c64, t);
+                Ht = d.x;
+                H2 = d.y;
             }
-            if (direct) {
-                if constexpr (sizeof(T) == 8) {
-                    const V2<T> v = kernel_far64(C, t2);
-                    Ht = v.x;
-                    H2 = v.y;
-                } else {
-                    kernel_eval<T>(C, t2, Ht, H2);
-                }
-            }
-            const T fd = fma_t(s.fx, dx, s.fy * dy);
-            su += (double)fma_t(Ht, s.fx, H2 * fd * dx);
-            sv += (double)fma_t(Ht, s.fy, H2 * fd * dy);
-            // pressure weight m(r) / (2 pi r^2): FP32 from the weight table
-            // inside it, else in FP64
-            const double t = fma(dxd, dxd, dyd * dyd);
-            double w = 0.0;
-            bool wdirect = true;
-            if constexpr (sizeof(T) == 4) {
-                if (wtab) {
-                    const uint32_t bits = tab_bits(t2, C.ts);
-                    const uint32_t id = bits >> TAB_SHIFT;
-                    if (id < TAB_END) {
-                        const float4 c = wtab[id - TAB_BIAS];
-                        const float uu = tab_u(bits);
-                        w = (double)fmaf(fmaf(fmaf(c.w, uu, c.z), uu, c.y), uu, c.x);
-                        wdirect = false;
-                    }
-                }
-            }
-            if (wdirect) w = field_weight(fc, t);
-            sp = fma((double)s.fx * dxd + (double)s.fy * dyd, w, sp);
+            su += fma(Ht, s.fx, H2 * fd * dx);
+            sv += fma(Ht, s.fy, H2 * fd * dy);
+            sp = fma(s.fx * dx + s.fy * dy, field_weight(fc, t), sp);
         }
     }
     if (live) {
-        u[a] = (T)fma(fc.h1c, sfx, su);
-        v[a] = (T)fma(fc.h1c, sfy, sv);
-        p[a] = (T)sp;
+        u[a] = fma(fc.h1c, sfx, su);
+        v[a] = fma(fc.h1c, sfy, sv);
+        p[a] = sp;
     }
 }
 
 }  // namespace
 
 hipError_t launch_flow_field(int dtype, int64_t n, const void* x, const void* y, const void* fx, const void* fy,
-                             const FieldConst& fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,
+                             const FieldConst* fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,
                              void* p, const void* tab, void* wtab, hipStream_t st)
 {
     if (nt == 0) return hipSuccess;
-    if (wtab) hipLaunchKernelGGL(k_weight_table, dim3((TAB_N + 255) / 256), dim3(256), 0, st, fc, (float4*)wtab);
-    const unsigned nb = (unsigned)((nt + 255) / 256);
-    if (dtype == 0)
-        hipLaunchKernelGGL(k_flow_field<float>, dim3(nb), dim3(256), 0, st, n, (const float*)x, (const float*)y,
-                           (const float*)fx, (const float*)fy, fc, nt, (const float*)tx, (const float*)ty, (float*)u,
-                           (float*)v, (float*)p, tab, (const float4*)wtab);
-    else
-        hipLaunchKernelGGL(k_flow_field<double>, dim3(nb), dim3(256), 0, st, n, (const double*)x, (const double*)y,
-                           (const double*)fx, (const double*)fy, fc, nt, (const double*)tx, (const double*)ty,
-                           (double*)u, (double*)v, (double*)p, tab, (const float4*)nullptr);
+    if (dtype == 0) {
+        hipLaunchKernelGGL(k_weight_table, dim3(TAB_N / 256 + 1), dim3(256), 0, st, fc, (float4*)wtab);
+        const float *X = (const float*)x, *Y = (const float*)y, *FX = (const float*)fx, *FY = (const float*)fy;
+        // two targets per thread from 2^18 targets on (four workgroups per CU)
+        if (nt >= (1 << 18))
+            hipLaunchKernelGGL(k_flow_field32<2>, dim3((unsigned)((nt + 2 * FIELD_TILE - 1) / (2 * FIELD_TILE))),
+                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc, nt, (const float*)tx, (const float*)ty,
+                               (float*)u, (float*)v, (float*)p, (const TabSys*)tab, (const float4*)wtab);
+        else
+            hipLaunchKernelGGL(k_flow_field32<1>, dim3((unsigned)((nt + FIELD_TILE - 1) / FIELD_TILE)),
+                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc, nt, (const float*)tx, (const float*)ty,
+                               (float*)u, (float*)v, (float*)p, (const TabSys*)tab, (const float4*)wtab);
+    } else {
+        hipLaunchKernelGGL(k_flow_field64, dim3((unsigned)((nt + FIELD_TILE - 1) / FIELD_TILE)), dim3(FIELD_TILE), 0, st,
+                           n, (const double*)x, (const double*)y, (const double*)fx, (const double*)fy, fc, nt,
+                           (const double*)tx, (const double*)ty, (double*)u, (double*)v, (double*)p,
+                           (const TabSys64*)tab);
+    }
     return hipGetLastError();
 }
 

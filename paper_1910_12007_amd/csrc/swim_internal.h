@@ -237,7 +237,7 @@ struct FieldConst {
     double ser[FIELD_NSER];
 };
 hipError_t launch_flow_field(int dtype, int64_t n, const void* x, const void* y, const void* fx, const void* fy,
-                             const FieldConst& fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,
+                             const FieldConst* fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,  // fc: device
                              void* p, const void* tab, void* wtab, hipStream_t st);
 
 }  // namespace swim
