@@ -90,9 +90,14 @@ int swim_version(void);
 /* Launch options of a context (the autotuner sets the first two):
  *   SWIM_OPT_WPS     wavefronts that share one system in the persistent
  *                    kernel, splitting its pair work: 0 (automatic: the
- *                    autotuned value, else 8 for FP32 systems of 65..128
- *                    points and 16 otherwise), 1, 2, 4, 8, 16 (reduced
- *                    when the partial sums would not fit LDS).  Systems above 256 points need at least 2: a
+ *                    autotuned value, else by points and by how many systems
+ *                    share the GPU: FP64 8; FP32 up to 128 points 8, or 4 up
+ *                    to 64 points in calls of more than two systems per
+ *                    compute unit; above 128 points 16, or 8 up to 384 points
+ *                    in calls of more than one system per compute unit, if
+ *                    the call's systems lie in one size class), 1, 2, 4, 8,
+ *                    16 (reduced when the partial sums would not fit LDS).
+ *                    Systems above 256 points need at least 2: a
  *                    forward call with 1 and such a system fails with
  *                    SWIM_EINVAL (the automatic choice never takes 1 there);
  *   SWIM_OPT_BIG_TPL the large-system step (systems above 512 points):

@@ -586,13 +586,26 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         q.tpl = bucket_span[k].first;
         q.start = bucket_span[k].second;
         q.count = (k + 1 < bucket_span.size() ? bucket_span[k + 1].second : (int64_t)order.size()) - q.start;
-        // untuned default: 16 waves, except FP32 systems of 65..128 points,
-        // which take 8 (16 offsets of the pair schedule per wave instead of 8
-        // halves the per-wave share of each step's fixed work; two systems
-        // per CU either way), and FP64 runs, which take 8 (222 VGPRs; 16
-        // waves have 128 and spill 239 of them: 7.3 against 3.8 us per step
-        // at N = 64)
-        const int wps_default = (dtype == SWIM_F64 || q.tpl == 2) ? 8 : 16;
+        // untuned default.  FP32, by the call's persistent systems and the
+        // compute units: a system alone on its CU wants the waves that finish
+        // its step soonest, systems that share CUs the ones that spend least
+        // on each step's fixed work.  us per step for 16 / 8 / 4 waves, N
+        // points: 16 systems, N = 64 1.9/1.6/1.8, 128 3.0/2.8/4.0, 192
+        // 4.9/5.6/8.3, 256 6.9/8.7/13.7, 384 15.4/17.7/29, 512 25.5/30.5/52;
+        // 1024 systems, 64 4.9/4.0/3.3, 128 8.7/7.9/7.5, 192 18.8/15.9/15.2,
+        // 256 27.3/26.3/29.3, 384 61.6/55.5/62.7, 512 103/123/114.  (128
+        // points keep 8 waves in large batches too: the runs that outlive a
+        // batch's blow-ups are twice as fast as with 4.)  Beside other buckets
+        // the longest runs' own speed counts (1024 systems of 64..512 points:
+        // 30.0 ms with the few-systems choice throughout, 32.1 with the
+        // many-systems one).  FP64 takes 8 (222 VGPRs; 16 waves have 128 and
+        // spill 239 of them: 7.3 against 3.8 us per step at N = 64).
+        const bool many = (int64_t)order.size() > c->num_cu && bucket_span.size() == 1;
+        int wps_default = 8;
+        if (dtype == SWIM_F32) {
+            if (q.tpl == 1) wps_default = many && (int64_t)order.size() > 2 * c->num_cu ? 4 : 8;
+            else if (q.tpl >= 3) wps_default = many && q.tpl != 8 ? 8 : 16;
+        }
         q.wps = c->opt_wps ? c->opt_wps : (c->tuned_wps[dtype][q.tpl] ? c->tuned_wps[dtype][q.tpl] : wps_default);
         // at most FWD_MAX_WINDOWS point windows per lane: fewer waves are not
         // built (their one-wave instantiations exceed 256 VGPRs and spill to
