@@ -1399,19 +1399,32 @@ int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_spe
     const int n = sh.n_swim * (sh.n_flag + sh.n_head);
     const int tpl = choose_tpl(n);
     // waves per system.  FP32, one-swimmer systems, us per step for 2/4/8
-    // waves: 256 systems 11.0/7.0/5.5, 512 11.6/7.8/10.6, 1024 12.0/15.0/20.9,
-    // 2000 23.4/29.5/41.4.  The most waves that keep the launch within eight
-    // waves per CU.  FP64 is fastest with eight at every size measured.
+    // waves: 256 systems 5.9/4.2/3.4, 512 6.2/4.7/4.2, 1024 6.8/5.6/8.3,
+    // 2000 8.2/10.7/16.4; two swimmers, 256 systems 14.2/7.8/5.5, 512
+    // 15.9/8.9/10.8, 1000 15.7/17.2/21.8.  The most waves that keep the launch
+    // within what a CU holds, 16 waves up to 128 points, 8 above.  FP64 is
+    // fastest with eight at every size measured.
     int wps = 8;
-    if (dtype == SWIM_F32)
-        wps = n_sys * 8 <= 8 * (int64_t)c->num_cu ? 8 : n_sys * 4 <= 8 * (int64_t)c->num_cu ? 4 : 2;
+    if (dtype == SWIM_F32) {
+        const int64_t waves = (tpl <= 2 ? 16 : 8) * (int64_t)c->num_cu;
+        wps = n_sys * 8 <= waves ? 8 : n_sys * 4 <= waves ? 4 : 2;
+    }
     if (c->opt_wps == 2 || c->opt_wps == 4 || c->opt_wps == 8) wps = c->opt_wps;
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     TRY(ensure(c, B_QUEUE, 8 * 4));
     HIPCHK(prepare_sperm(dtype, tpl, wps));
-    const int per_cu = sperm_blocks_per_cu(dtype, tpl, wps);
+    // the whole table in LDS if every system gets a workgroup at once that way,
+    // else its first 24 octaves (distances to 2^12 eps; the rest is read from
+    // HBM), for more systems in flight: 12 KB instead of 22, eight one-swimmer
+    // systems per CU instead of five
+    r.oct = SPERM_OCT_ALL;
+    int per_cu = sperm_blocks_per_cu(dtype, tpl, wps, g, r.oct);
+    if (dtype == SWIM_F32 && n_sys > (int64_t)per_cu * c->num_cu) {
+        r.oct = SPERM_OCT_HEAD;
+        per_cu = sperm_blocks_per_cu(dtype, tpl, wps, g, r.oct);
+    }
     const int nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(n_sys, (int64_t)per_cu * c->num_cu));
     HIPCHK(launch_sperm_setup(dtype, n_sys, sh.n_swim, sh.eps, sys_params, swim_params, sysc, sysc64, status,
                               c->opt_blob, st));

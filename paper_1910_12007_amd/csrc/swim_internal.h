@@ -199,15 +199,17 @@ struct SpermRun {
     int64_t n_sys;
     const double* sysp;  // [n_sys][SWIM_SP_NPARAM]
     const double* swp;   // [n_sys * nsw][3]: x0, y0, phase
-    int32_t steps, obs_every, n_obs, pad;
+    int32_t steps, obs_every, n_obs;
+    int32_t oct;         // FP32: octaves of the table that a system keeps in LDS
     double dt;
 };
 hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps, const double* sysp,
                               const double* swp, void* sysc, void* sysc64, int32_t* status, int blob,
                               hipStream_t st);
-size_t sperm_lds_bytes(int dtype, int tpl, int wps);
 hipError_t prepare_sperm(int dtype, int tpl, int wps);
-int sperm_blocks_per_cu(int dtype, int tpl, int wps);
+// FP32 octaves in LDS: the whole table, or the first
+constexpr int SPERM_OCT_ALL = 44, SPERM_OCT_HEAD = 24;
+int sperm_blocks_per_cu(int dtype, int tpl, int wps, const SpermShape& g, int oct);
 // persistent run, one workgroup of wps wavefronts per system (tpl in
 // {1,2,3,4,6,8}, wps in {2,4,8})
 hipError_t launch_sperm_forward(int dtype, int tpl, int wps, int nblocks, const SpermShape& g, const SpermRun& r,

@@ -149,13 +149,44 @@ __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double t
     return far;
 }
 
-// direct FP64 evaluation of a pair beyond the table; not inlined, so that
-// its registers stay out of the pair loops
+// direct evaluation of a pair beyond the table; not inlined, so that its
+// registers (and the scalars that its hoisted coefficients take) stay out of
+// the pair loops
 __device__ __attribute__((noinline)) inline V2<double> kernel_far64(const SysConst<double>& C, double t)
 {
     V2<double> v;
     kernel_eval<double>(C, t, v.x, v.y);
     return v;
+}
+__device__ __attribute__((noinline)) inline V2<float> kernel_far32(const SysConst<float>& C, float t)
+{
+    V2<float> v;
+    kernel_eval<float>(C, t, v.x, v.y);
+    return v;
+}
+
+// The first octaves of a system's FP32 table in LDS: entry id (the bits of v
+// >> TAB_SHIFT) below end at et + 32 id, the zero entry at end; pairs from
+// end on read the whole table in HBM
+struct TabHead {
+    const char* et;
+    uint32_t end;
+    const TabE* all;
+};
+constexpr uint32_t tab_end(const char*) { return TAB_END; }
+__device__ __forceinline__ uint32_t tab_end(const TabHead& h) { return h.end; }
+__device__ __forceinline__ const char* tab_at(const char* et) { return et; }
+__device__ __forceinline__ const char* tab_at(const TabHead& h) { return h.et; }
+
+// copy the first octaves of one system's FP32 table (end - TAB_BIAS entries
+// and a zero entry) from HBM into LDS
+__device__ __forceinline__ void tab_load_head(const TabSys* g, TabE* tab, int entries, int tid, int nthreads)
+{
+    const float4* src = reinterpret_cast<const float4*>(g->e);
+    float4* dst = reinterpret_cast<float4*>(tab);
+    constexpr int EV = (int)(sizeof(TabE) / sizeof(float4));
+    for (int i = tid; i < (entries + 1) * EV; i += nthreads)
+        dst[i] = i < entries * EV ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // error-free (hi, lo) += d  (TwoSum, then renormalize)
@@ -207,6 +238,22 @@ __device__ __forceinline__ int opaque_uniform(int v)
     return r;
 }
 
+// The base that pair_kernel reads a table by.  FP32: the entry of index id lies
+// at et + (id << 5) bytes, so the bias goes into a wave-uniform base (a
+// register operand of the address arithmetic; gfx9 address arithmetic takes no
+// 32-bit literal).
+template <typename T, bool WRAP> __device__ __forceinline__ const char* tab_base(const void* tab)
+{
+    const char* et = reinterpret_cast<const char*>(tab);
+    if constexpr (!WRAP && sizeof(T) == 4) et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
+    return et;
+}
+template <typename T, bool WRAP> __device__ __forceinline__ TabHead tab_base(TabHead tab)
+{
+    tab.et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
+    return tab;
+}
+
 // slot of point i in the doubled source array
 __device__ __forceinline__ int src2_slot(int i) { return ((i >> 6) << 7) + (i & 63); }
 
@@ -214,15 +261,16 @@ __device__ __forceinline__ int src2_slot(int i) { return ((i >> 6) << 7) + (i & 
 // rho): the table (FAR = false; a pair beyond it gives zeros and, with CHECK,
 // sets far), or the direct evaluation of pairs beyond the table only (FAR =
 // true; zeros for the others).  H2 comes scaled to the coordinates (H2 / sigma
-// in FP32).  et: FP32 the table in LDS, FP64 in HBM.
-template <typename T, bool FAR, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const char* et, T dx, T dy, T& Ht, T& H2,
+// in FP32).  et: FP32 the table in LDS (or its first octaves, a TabHead: FAR
+// then reads the rest of the table in HBM), FP64 in HBM.
+template <typename T, bool FAR, bool CHECK = true, bool WRAP = false, typename Tab>
+__device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et, T dx, T dy, T& Ht, T& H2,
                                             bool& far)
 {
     if constexpr (sizeof(T) == 8) {
         const T t = fma_t(dx, dx, dy * dy);
         if constexpr (!FAR) {
-            const bool f = tab64_lookup(et, t, C.ts, Ht, H2);
+            const bool f = tab64_lookup(tab_at(et), t, C.ts, Ht, H2);
             if constexpr (CHECK) far = far || f;
         } else {
             Ht = (T)0;
@@ -237,7 +285,7 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const char* et
         const uint32_t bits = __builtin_bit_cast(uint32_t, fmaf(dx, dx, fmaf(dy, dy, 1.0f)));
         const uint32_t id = bits >> TAB_SHIFT;
         if constexpr (!FAR) {
-            if constexpr (CHECK) far = far || id >= TAB_END;
+            if constexpr (CHECK) far = far || id >= tab_end(et);
             if constexpr (WRAP) {
                 // the index window at LDS address 0 (tab_load_window): the
                 // entry's address is its offset in the window (an LDS
@@ -248,14 +296,17 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const char* et
                 tab_eval(e, tab_u(bits), Ht, H2);
 #endif
             } else {
-                tab_eval(*reinterpret_cast<const TabE*>(et + (min(id, TAB_END) << 5)), tab_u(bits), Ht, H2);
+                tab_eval(*reinterpret_cast<const TabE*>(tab_at(et) + (min(id, tab_end(et)) << 5)), tab_u(bits), Ht, H2);
             }
         } else {
             Ht = 0.0f;
             H2 = 0.0f;
             if (id >= TAB_END) {
-                kernel_eval<float>(C, fmaf(dx, dx, dy * dy) * C.its, Ht, H2);
-                H2 *= C.its;
+                const V2<float> v = kernel_far32(C, fmaf(dx, dx, dy * dy) * C.its);
+                Ht = v.x;
+                H2 = v.y * C.its;
+            } else if constexpr (std::is_same<Tab, TabHead>::value) {
+                if (id >= et.end) tab_eval(et.all[id - TAB_BIAS], tab_u(bits), Ht, H2);
             }
         }
     }
@@ -263,8 +314,8 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const char* et
 
 // offsets [s_lo, s_hi) of block pair (a, b); adds the target sums to block
 // a's and the moving points' sums to block b's accumulators of this lane
-template <typename T, int TPL, bool FAR, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const char* et, const Src4<T>* src2, int a, int b,
+template <typename T, int TPL, bool FAR, bool CHECK = true, bool WRAP = false, typename Tab>
+__device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et, const Src4<T>* src2, int a, int b,
                                             int s_lo, int s_hi, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
     const Src4<T> ti = src2[(a << 7) + lane];
@@ -289,6 +340,10 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const char* et
         by = lane_rot(fma_t(mxy, ti.fx, fma_t(myy, ti.fy, by)));
     };
     int s = __builtin_amdgcn_readfirstlane(s_lo);
+    if constexpr (FAR) {
+#pragma unroll 1
+        for (; s < s_full; ++s) offset(sp[s]);
+    }
     for (; s + 1 < s_full; s += 2) {
         offset(sp[s]);
         offset(sp[s + 1]);
@@ -332,19 +387,13 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const char* et
 // guarantees that no FP32 pair lies beyond the table, which then is read
 // without the per-pair test (an index beyond it reads a zero entry).
 // WRAP: tab points at the table's LDS index window (tab_load_window)
-template <typename T, int TPL, int WPS, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int n,
+template <typename T, int TPL, int WPS, bool CHECK = true, bool WRAP = false, typename Tab>
+__device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int n,
                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
 #pragma unroll
     for (int c = 0; c < TPL; ++c) accx[c] = accy[c] = (T)0;
-    const char* et = reinterpret_cast<const char*>(tab);
-    if constexpr (!WRAP && sizeof(T) == 4) {
-        // entry of index id at et + (id << 5) bytes: the bias goes into a
-        // wave-uniform base (a register operand of the address arithmetic;
-        // gfx9 address arithmetic takes no 32-bit literal)
-        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
-    }
+    const auto et = tab_base<T, WRAP>(tab);
     const int B = (n + 63) >> 6;
     const int S = 32 * B * B;
     const int per = (S + WPS - 1) / WPS;
@@ -398,16 +447,13 @@ __device__ __forceinline__ bool sym_one_segment(int n, int wave, int& sa, int& s
 
 // pair_phase_sym for a wave whose share is the one segment found by
 // sym_one_segment (same sums, same order)
-template <typename T, int TPL, bool CHECK = true, bool WRAP = false>
-__device__ __forceinline__ void pair_phase_seg(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int a,
+template <typename T, int TPL, bool CHECK = true, bool WRAP = false, typename Tab>
+__device__ __forceinline__ void pair_phase_seg(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int a,
                                                int b, int s_lo, int s_hi, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
 #pragma unroll
     for (int c = 0; c < TPL; ++c) accx[c] = accy[c] = (T)0;
-    const char* et = reinterpret_cast<const char*>(tab);
-    if constexpr (!WRAP && sizeof(T) == 4) {
-        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
-    }
+    const auto et = tab_base<T, WRAP>(tab);
     const bool far = sym_offsets<T, TPL, false, CHECK, WRAP>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
     if constexpr (CHECK) {
         if (__any(far)) sym_offsets<T, TPL, true>(C, et, src2, a, b, s_lo, s_hi, lane, accx, accy);
@@ -421,6 +467,104 @@ template <typename T> __device__ __forceinline__ T wave_total(T v)
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// v of the lane that lies R lanes further on (cyclically) in its row of 16
+template <int R> __device__ __forceinline__ float row_rot(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + R, 0xF, 0xF, false));
+}
+template <int R> __device__ __forceinline__ double row_rot(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + R, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// lanes 0..31: v.x + v.x of the lane 32 above; lanes 32..63: v.y + v.y of the
+// lane 32 below (a swap of register halves, then one addition)
+__device__ __forceinline__ float half_sums(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                    false, false);
+    const uint32_t a = r[0], b = r[1];
+    return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+// even rows of 16 lanes: x + x of the next row; odd rows: y + y of the row before
+__device__ __forceinline__ float row_sums(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y),
+                                                    false, false);
+    const uint32_t a = r[0], b = r[1];
+    return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+__device__ __forceinline__ double half_sums(double x, double y)
+{
+    const uint64_t a = __builtin_bit_cast(uint64_t, x), b = __builtin_bit_cast(uint64_t, y);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double row_sums(double x, double y)
+{
+    const uint64_t a = __builtin_bit_cast(uint64_t, x), b = __builtin_bit_cast(uint64_t, y);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// value of one lane in every lane
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// One wave's share of the symmetric schedule of B blocks as where it starts
+// (block pair (a, b), offset s) and how many offsets it takes: the shares of
+// pair_phase_sym.  Step-invariant: a run finds it once.
+struct PairShare {
+    int a, b, s, count;
+};
+template <int WPS> __device__ __forceinline__ PairShare pair_share(int B, int wave)
+{
+    const int S = 32 * B * B, per = (S + WPS - 1) / WPS;
+    const int g0 = min(S, wave * per);
+    PairShare p{0, 0, 1, min(S, g0 + per) - g0};
+    int g = g0;
+    for (int len = 32; p.count > 0 && g >= len; len = p.a == p.b ? 32 : 64) {
+        g -= len;
+        if (++p.b == B) p.b = ++p.a;
+    }
+    p.s = g + (p.a == p.b ? 1 : 0);
+    return p;
+}
+
+// the pair sums of one share (the sums of pair_phase_sym in its order, as one
+// piece of code for any share)
+template <typename T, int TPL, typename Tab>
+__device__ __forceinline__ void pair_walk(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int B,
+                                          PairShare p, int lane, T (&accx)[TPL], T (&accy)[TPL])
+{
+#pragma unroll
+    for (int c = 0; c < TPL; ++c) accx[c] = accy[c] = (T)0;
+    const auto et = tab_base<T, false>(tab);
+    while (p.count > 0) {
+        const int hi = min(p.s + p.count, p.a == p.b ? 33 : 64);
+        const bool far = sym_offsets<T, TPL, false>(C, et, src2, p.a, p.b, p.s, hi, lane, accx, accy);
+        if (__any(far)) sym_offsets<T, TPL, true>(C, et, src2, p.a, p.b, p.s, hi, lane, accx, accy);
+        p.count -= hi - p.s;
+        if (++p.b == B) p.b = ++p.a;
+        p.s = p.a == p.b ? 1 : 0;
+    }
 }
 
 // Whether the tail schedule below does less work than the padded symmetric
@@ -443,32 +587,24 @@ __host__ __device__ constexpr bool tail_pays(int n)
 //    summed over the wavefront once and kept by lane j;
 //  * tail point j as a source within the tail: lanes l < r take the pair
 //    (tail l, tail j) for target tail l only.
-// Every ordered pair is taken once.  The full blocks' offsets are split
-// over the waves as in pair_phase_sym; tail point j goes to wave j mod WPS.
-// seg: this wave's share of the full blocks' schedule as found by
-// sym_one_segment for 64 Bf points (seg[0] != 0: a single segment a = seg[1],
-// b = seg[2], offsets [seg[3], seg[4])), or null
-template <typename T, int TPL, int WPS>
-__device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const void* tab, const Src4<T>* src2, int n,
-                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL],
-                                                const int* seg = nullptr)
+// Every ordered pair is taken once; tail point j goes to wave j mod WPS, and the
+// full blocks' part is pair_walk's.  The kernel values within the tail are
+// evaluated for four, two or one sources at once in groups of lanes (r <= 16,
+// 32, 63) and handed to the lanes that sum them; the sums over the wavefront
+// take two tail points at once in register halves and rows (10 operations for
+// four sums, without LDS), instead of one source, and one sum of six LDS
+// permutes, at a time.
+template <typename T, int TPL, int WPS, typename Tab>
+__device__ __forceinline__ void pair_tail(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int n, int wave,
+                                          int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
     const int Bf = n >> 6, r = n & 63;
-    if (seg && seg[0])
-        pair_phase_seg<T, TPL>(C, tab, src2, seg[1], seg[2], seg[3], seg[4], lane, accx, accy);
-    else
-        pair_phase_sym<T, TPL, WPS>(C, tab, src2, 64 * Bf, wave, lane, accx, accy);
-    const char* et = reinterpret_cast<const char*>(tab);
-    if constexpr (sizeof(T) == 4)
-        et = reinterpret_cast<const char*>(tab) + opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
-    const bool tl_live = lane < r;
-    const Src4<T> tp = src2[src2_slot(64 * Bf + (tl_live ? lane : r - 1))];
-    for (int j = wave; j < r; j += WPS) {
-        const Src4<T> q = src2[src2_slot(64 * Bf + j)];
-        T bx = (T)0, by = (T)0;
+    const auto et = tab_base<T, false>(tab);
+    const Src4<T>* tail = src2 + src2_slot(64 * Bf);
+    // tail point q's pairs with the full blocks; its own sums in bx, by
+    auto against_blocks = [&](const Src4<T>& q, T& bx, T& by) {
         bool far = false;
-        // one pass over tail point j's pairs; FAR selects the direct
-        // evaluation of pairs beyond the FP32 table (zeros for the others)
+        bx = by = (T)0;
         auto pass = [&](auto far_tag) {
             constexpr bool FAR = decltype(far_tag)::value;
 #pragma unroll
@@ -486,30 +622,76 @@ __device__ __forceinline__ void pair_phase_tail(const SysConst<T>& C, const void
                     by = fma_t(mxy, ti.fx, fma_t(myy, ti.fy, by));
                 }
             }
-            const T dx = tp.x - q.x, dy = tp.y - q.y;
-            T Ht, H2;
-            pair_kernel<T, FAR>(C, et, dx, dy, Ht, H2, far);
-            Ht = tl_live ? Ht : (T)0;
-            H2 = tl_live ? H2 : (T)0;
-            const T fdj = H2 * fma_t(q.fx, dx, q.fy * dy);
-#pragma unroll
-            for (int c = 0; c < TPL; ++c) {
-                if (c == Bf) {
-                    accx[c] = fma_t(Ht, q.fx, fma_t(fdj, dx, accx[c]));
-                    accy[c] = fma_t(Ht, q.fy, fma_t(fdj, dy, accy[c]));
-                }
-            }
         };
         pass(std::integral_constant<bool, false>());
         if (__any(far)) pass(std::integral_constant<bool, true>());
-        bx = wave_total(bx);
-        by = wave_total(by);
+    };
+    const bool live = lane < r;
+    const Src4<T> tp = tail[live ? lane : r - 1];
+    const int lg = r <= 16 ? 4 : r <= 32 ? 5 : 6, L = 1 << lg;  // lanes of a group
+    const Src4<T> gp = tail[min(lane & (L - 1), r - 1)];
+    // kernel values of (tail point lane mod L, tail point j + WPS group)
+    auto kernel_values = [&](int j, T& Ht, T& H2) {
+        const Src4<T> q = tail[min(j + WPS * (lane >> lg), r - 1)];
+        const T dx = gp.x - q.x, dy = gp.y - q.y;
+        bool far = false;
+        pair_kernel<T, false>(C, et, dx, dy, Ht, H2, far);
+        if (__any(far)) {
+            T Hf, Gf;
+            pair_kernel<T, true>(C, et, dx, dy, Hf, Gf, far);
+            Ht += Hf;  // one of the two is zero
+            H2 += Gf;
+        }
+    };
+    T tx = (T)0, ty = (T)0;  // sums of tail point `lane`
+    T h = (T)0, g = (T)0, h2 = (T)0, g2 = (T)0;
+    int at = 0;  // group of tail point j
+    for (int j = wave; j < r; j += 2 * WPS) {
+        const int j2 = j + WPS;
+        if (at == 0) kernel_values(j, h, g);
+        T hj = h, gj = g, hk, gk;
+        if (lg == 6) {
+            kernel_values(min(j2, r - 1), h2, g2);
+            hk = h2;
+            gk = g2;
+        } else {
+            const int from = (at << lg) + (lane & (L - 1));
+            hj = __shfl(h, from, 64);
+            gj = __shfl(g, from, 64);
+            hk = __shfl(h, from + L, 64);
+            gk = __shfl(g, from + L, 64);
+            at = lg == 4 ? at ^ 2 : 0;
+        }
+        const Src4<T> q = tail[j], q2 = tail[min(j2, r - 1)];
+        T bx = (T)0, by = (T)0, cx = (T)0, cy = (T)0;
+        if (Bf > 0) {
+            against_blocks(q, bx, by);
+            if (j2 < r) against_blocks(q2, cx, cy);
+        }
+        // rows 0..3: x of j, x of j2, y of j, y of j2
+        T z = row_sums(half_sums(bx, by), half_sums(cx, cy));
+        z += row_rot<8>(z);
+        z += row_rot<4>(z);
+        z += row_rot<2>(z);
+        z += row_rot<1>(z);
+        auto within = [&](const Src4<T>& s, T Ht, T H2, int js, T sx, T sy) {
+            const T dx = tp.x - s.x, dy = tp.y - s.y;
+            Ht = live ? Ht : (T)0;
+            H2 = live ? H2 : (T)0;
+            const T fdj = H2 * fma_t(s.fx, dx, s.fy * dy);
+            tx = fma_t(Ht, s.fx, fma_t(fdj, dx, tx));
+            ty = fma_t(Ht, s.fy, fma_t(fdj, dy, ty));
+            tx += lane == js ? sx : (T)0;
+            ty += lane == js ? sy : (T)0;
+        };
+        within(q, hj, gj, j, lane_value(z, 0), lane_value(z, 32));
+        if (j2 < r) within(q2, hk, gk, j2, lane_value(z, 16), lane_value(z, 48));
+    }
 #pragma unroll
-        for (int c = 0; c < TPL; ++c) {
-            if (c == Bf && lane == j) {
-                accx[c] += bx;
-                accy[c] += by;
-            }
+    for (int c = 0; c < TPL; ++c) {
+        if (c == Bf) {
+            accx[c] += tx;
+            accy[c] += ty;
         }
     }
 }

@@ -7,9 +7,11 @@
 // One workgroup runs one system for all its steps (a persistent kernel fed
 // by a work queue).  The pair sum uses the symmetric lane schedule of
 // swim_pairsum.h, with the partly filled last block of 64 points taken
-// point by point (74 points per swimmer leave 10 in it).  The elastic forces are computed per point from the
-// positions in LDS: every point evaluates the springs and curvature nodes it
-// belongs to, so forces need no atomics and no per-term buffers.
+// point by point (74 points per swimmer leave 10 in it).  The elastic forces
+// take two passes over the points: every point evaluates the curvature node it
+// is the centre of and the spring to its next point (a head point its
+// diameter, the first flagellum points the neck springs) into LDS, and after a
+// barrier sums the terms it belongs to, in a fixed order without atomics.
 //
 // Discrete energy (trapezoid rule, centred differences; every spring has the
 // form K (l/L0 - 1)^2 L0):
@@ -93,10 +95,10 @@ template <typename T> __device__ __forceinline__ T spring_coef(V2<T> d, T L0, T 
 }
 
 // curvature node (A, B, C) with segments d1 = X_B - X_A, d2 = X_C - X_B and
-// parameter step h: energy W (kappa - k0)^2 h; returns -dE/dX of the point
-// in role r (0: A, 1: B, 2: C) of this node.
+// parameter step h: energy E = W (kappa - k0)^2 h; f[r] = dkappa/dX of the
+// point in role r (0: A, 1: B, 2: C) of this node; returns dE/dkappa.
 template <typename T>
-__device__ __forceinline__ V2<T> node_force(V2<T> d1, V2<T> d2, T inv2h, T invh2, T h, T W2, T k0, int r)
+__device__ __forceinline__ T node_terms(V2<T> d1, V2<T> d2, T inv2h, T invh2, T h, T W2, T k0, V2<T> (&f)[3])
 {
     const T a = (d2.x + d1.x) * inv2h;
     const T b = (d2.y + d1.y) * inv2h;
@@ -119,112 +121,120 @@ __device__ __forceinline__ V2<T> node_force(V2<T> d1, V2<T> d2, T inv2h, T invh2
     const T dkb = -p * rS32 - b * n3;
     const T dkp = -b * rS32;
     const T dkq = a * rS32;
-    V2<T> g;  // dkappa/dX of the point in role r
-    if (r == 0) {
-        g.x = fma_t(-dka, inv2h, dkp * invh2);
-        g.y = fma_t(-dkb, inv2h, dkq * invh2);
-    } else if (r == 1) {
-        g.x = (T)-2 * dkp * invh2;
-        g.y = (T)-2 * dkq * invh2;
-    } else {
-        g.x = fma_t(dka, inv2h, dkp * invh2);
-        g.y = fma_t(dkb, inv2h, dkq * invh2);
-    }
-    g.x = -co * g.x;
-    g.y = -co * g.y;
-    return g;
+    // dkappa/dX of the point in role r
+    f[0].x = fma_t(-dka, inv2h, dkp * invh2);
+    f[0].y = fma_t(-dkb, inv2h, dkq * invh2);
+    f[1].x = (T)-2 * dkp * invh2;
+    f[1].y = (T)-2 * dkq * invh2;
+    f[2].x = fma_t(dka, inv2h, dkp * invh2);
+    f[2].y = fma_t(dkb, inv2h, dkq * invh2);
+    return co;
 }
 
-// per-system stiffnesses (twice the energy coefficients) and lengths in T
-template <typename T> struct SpermK {
-    T kt2, kc2, kht2, khc2, knt2, kna2;
-    T ds, inv2ds, invds2, ds2;
-    T ch, inv2ch, invch2, ch2;
-    T dh, dh2, kh0;  // diameter 2 H_r, its square, preferred head curvature 1/H_r
-    T L0[5], L02[5];
+// what one point evaluates and which terms it gathers (indices of the
+// system's points; step-invariant).  Its chain is the flagellum or, closed to
+// a ring, the head.
+template <typename T> struct SpermPt {
+    int pv, nx;      // neighbours in its chain (itself at the flagellum's ends)
+    int ps;          // point whose next-spring is its previous one (the last flagellum point's, zero, for the first)
+    int sa, sb;      // ends of its second spring: a diameter, or a neck spring
+    int edge;        // the neck springs' slot it writes, or -1
+    int role;        // 1..5: neck point nf-1, nf-2, c-1, c, c+1
+    bool node, next, head;  // it is the centre of a curvature node, has a next-spring, lies in the head
+    T inv2h, invh2, h, W2;  // node
+    T L0, L02, K2;          // next-spring
+    T M0, M02, J2;          // second spring
+    T zA, zB;               // flagellum: preferred curvature zA cos(omega t) + zB sin(omega t)
 };
 
-// elastic force on point p (index within its swimmer; its swimmer's points
-// start at P in LDS).  zh[0..2]: preferred curvature of flagellum nodes
-// p-1, p, p+1 now.
-template <typename T>
-__device__ __forceinline__ V2<T> sperm_force(const SpermShape& g, const SpermK<T>& K, const PosE<T>* P, int p,
-                                             const T (&zh)[3])
+// neck spring q (slot order: nf-1 to c-1, c, c+1; nf-2 to c-1, c+1)
+__device__ __forceinline__ int neck_from(const SpermShape& g, int q) { return q < 3 ? g.nf - 1 : g.nf - 2; }
+__device__ __forceinline__ int neck_to(const SpermShape& g, int q)
 {
-    const int nf = g.nf, nh = g.nh, c = nf + nh / 2;
-    const PosE<T> X = P[p];
-    V2<T> F;
-    F.x = (T)0;
-    F.y = (T)0;
-    auto spring = [&](int q, T L0, T L02, T K2) {
-        const V2<T> d = pos_diff(P[q], X);
-        const T cf = spring_coef(d, L0, L02, K2);
-        F.x = fma_t(cf, d.x, F.x);
-        F.y = fma_t(cf, d.y, F.y);
-    };
-    auto node = [&](int a, int b, int cc, T inv2h, T invh2, T h, T W2, T k0, int r) {
-        const PosE<T> A = P[a], B = P[b], C = P[cc];
-        const V2<T> f = node_force(pos_diff(B, A), pos_diff(C, B), inv2h, invh2, h, W2, k0, r);
-        F.x += f.x;
-        F.y += f.y;
-    };
-    if (p < nf) {
-        if (p >= 1) spring(p - 1, K.ds, K.ds2, K.kt2);
-        if (p <= nf - 2) spring(p + 1, K.ds, K.ds2, K.kt2);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int j = p + 1 - r;  // node j, in which p has role r
-            if (j >= 1 && j <= nf - 2) node(j - 1, j, j + 1, K.inv2ds, K.invds2, K.ds, K.kc2, zh[2 - r], r);
-        }
-        if (p == nf - 1) {
-            spring(c - 1, K.L0[0], K.L02[0], K.knt2);
-            spring(c, K.L0[1], K.L02[1], K.knt2);
-            spring(c + 1, K.L0[2], K.L02[2], K.knt2);
-        } else if (p == nf - 2) {
-            spring(c - 1, K.L0[3], K.L02[3], K.knt2);
-            spring(c + 1, K.L0[4], K.L02[4], K.knt2);
-        }
-    } else {
-        const int m = p - nf;
-        auto hp = [&](int k) { return nf + (k + nh) % nh; };
-        spring(hp(m - 1), K.ch, K.ch2, K.kht2);
-        spring(hp(m + 1), K.ch, K.ch2, K.kht2);
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int j = m + 1 - r;
-            node(hp(j - 1), hp(j), hp(j + 1), K.inv2ch, K.invch2, K.ch, K.khc2, K.kh0, r);
-        }
-        spring(hp(m + nh / 2), K.dh, K.dh2, K.kht2);
-        if (p == c - 1) {
-            spring(nf - 1, K.L0[0], K.L02[0], K.knt2);
-            spring(nf - 2, K.L0[3], K.L02[3], K.knt2);
-        } else if (p == c) {
-            spring(nf - 1, K.L0[1], K.L02[1], K.knt2);
-        } else if (p == c + 1) {
-            spring(nf - 1, K.L0[2], K.L02[2], K.knt2);
-            spring(nf - 2, K.L0[4], K.L02[4], K.knt2);
-        }
-    }
-    // neck angle: E = K (z1.z2)^2, dE/dz1 = 2K (z1.z2) z2, dE/dz2 = 2K (z1.z2) z1
-    if (p == nf - 1 || p == c - 1 || p == c || p == c + 1) {
-        const V2<T> z1 = pos_diff(P[c], P[nf - 1]), z2 = pos_diff(P[c + 1], P[c - 1]);
-        const T w = K.kna2 * fma_t(z1.x, z2.x, z1.y * z2.y);
-        if (p == nf - 1) {
-            F.x = fma_t(w, z2.x, F.x);
-            F.y = fma_t(w, z2.y, F.y);
-        } else if (p == c) {
-            F.x = fma_t(-w, z2.x, F.x);
-            F.y = fma_t(-w, z2.y, F.y);
-        } else if (p == c + 1) {
-            F.x = fma_t(-w, z1.x, F.x);
-            F.y = fma_t(-w, z1.y, F.y);
-        } else {
-            F.x = fma_t(w, z1.x, F.x);
-            F.y = fma_t(w, z1.y, F.y);
-        }
-    }
-    return F;
+    const int c = g.nf + g.nh / 2;
+    return q < 3 ? c - 1 + q : q == 3 ? c - 1 : c + 1;
 }
+
+// (cos x, sin x); not inlined: the argument reduction's registers and literals
+// would stay allocated through the step loop (202 VGPRs, two waves per SIMD)
+__device__ __attribute__((noinline)) V2<double> cos_sin(double x)
+{
+    V2<double> v;
+    sincos(x, &v.y, &v.x);
+    return v;
+}
+
+template <typename T>
+__device__ SpermPt<T> sperm_point(const SpermShape& g, const double* sp, double phase, int base, int p)
+{
+    SpermPt<T> P;
+    const int nf = g.nf, nh = g.nh, c = nf + nh / 2;
+    P.head = p >= nf;
+    P.edge = -1;
+    P.zA = P.zB = (T)0;
+    P.M0 = P.M02 = (T)1;
+    P.J2 = (T)0;
+    int pv, nx, ps, sa = p, sb = p;
+    if (P.head) {
+        const int m = p - nf;
+        pv = nf + (m + nh - 1) % nh;
+        nx = nf + (m + 1) % nh;
+        ps = pv;
+        sb = nf + (m + nh / 2) % nh;
+        P.node = P.next = true;
+        P.inv2h = (T)(0.5 / g.ch);
+        P.invh2 = (T)(1.0 / (g.ch * g.ch));
+        P.h = P.L0 = (T)g.ch;
+        P.L02 = (T)(g.ch * g.ch);
+        P.W2 = (T)(2.0 * sp[SWIM_SP_KHC]);
+        P.K2 = P.J2 = (T)(2.0 * sp[SWIM_SP_KHT]);
+        P.M0 = (T)(2.0 * g.hr);
+        P.M02 = (T)(4.0 * g.hr * g.hr);
+    } else {
+        pv = max(p - 1, 0);
+        nx = min(p + 1, nf - 1);
+        ps = p >= 1 ? p - 1 : nf - 1;
+        P.node = p >= 1 && p <= nf - 2;
+        P.next = p <= nf - 2;
+        P.inv2h = (T)(0.5 / g.ds);
+        P.invh2 = (T)(1.0 / (g.ds * g.ds));
+        P.h = P.L0 = (T)g.ds;
+        P.L02 = (T)(g.ds * g.ds);
+        P.W2 = (T)(2.0 * sp[SWIM_SP_KC]);
+        P.K2 = (T)(2.0 * sp[SWIM_SP_KT]);
+        if (p < 5) {
+            P.edge = p;
+            sa = neck_from(g, p);
+            sb = neck_to(g, p);
+            P.M0 = (T)g.L0[p];
+            P.M02 = (T)(g.L0[p] * g.L0[p]);
+            P.J2 = (T)(2.0 * sp[SWIM_SP_KNT]);
+        }
+        if (P.node) {
+            const double a = sp[SWIM_SP_A], eta = sp[SWIM_SP_ETA];
+            const double sj = (double)p * g.ds, psi = eta * sj + phase;
+            const double u = -2.0 * a * eta, v = a * (1.0 - sj) * eta * eta;
+            const V2<double> cs = cos_sin(psi);
+            P.zA = (T)(u * cs.x - v * cs.y);
+            P.zB = (T)(u * cs.y + v * cs.x);
+        }
+    }
+    P.role = p == nf - 1 ? 1 : p == nf - 2 ? 2 : p == c - 1 ? 3 : p == c ? 4 : p == c + 1 ? 5 : 0;
+    P.pv = base + pv;
+    P.nx = base + nx;
+    P.ps = base + ps;
+    P.sa = base + sa;
+    P.sb = base + sb;
+    return P;
+}
+
+// the terms in LDS: per point the node's curvature gradients at its neighbours
+// and the next-spring's force, per swimmer the neck springs
+template <typename T> struct SpermTerms {
+    Src4<T>* ends;  // [n] (f[0], f[2]) of the node
+    Src4<T>* next;  // [n] (the next-spring's force, the node's dE/dkappa, unused)
+    Src4<T>* neck;  // [5 nsw] (coefficient, d, unused)
+};
 
 // initial position of point p of a swimmer whose first flagellum point is (x0, y0)
 __device__ __forceinline__ void sperm_initial(const SpermShape& g, double x0, double y0, int p, double& x, double& y)
@@ -235,8 +245,9 @@ __device__ __forceinline__ void sperm_initial(const SpermShape& g, double x0, do
     } else {
         const int m = p - g.nf;
         const double xc = (x0 + (double)(g.nf - 1) * g.ds) + g.hr + g.dn;
-        x = xc + g.hr * cos((double)m * g.dth);
-        y = y0 + g.hr * sin((double)m * g.dth);
+        const V2<double> cs = cos_sin((double)m * g.dth);
+        x = xc + g.hr * cs.x;
+        y = y0 + g.hr * cs.y;
     }
 }
 
@@ -244,29 +255,53 @@ struct SpermLdsLayout {
     size_t tab, src, part, pos, bad, total;
 };
 __host__ __device__ constexpr size_t al16(size_t x) { return (x + 15) & ~(size_t)15; }
-__host__ __device__ constexpr SpermLdsLayout sperm_lds_layout(int dtype, int tpl, int wps)
+// n points of nsw swimmers, the table's first oct octaves (FP32).  The terms of
+// the forces and the partial sums share one region: each is read before the
+// barrier that the other is written behind.
+__host__ __device__ constexpr SpermLdsLayout sperm_lds_layout(int dtype, int wps, int n, int nsw, int oct)
 {
-    const size_t e = dtype == 0 ? 4 : 8, nmax = 64 * (size_t)tpl;
+    const size_t e = dtype == 0 ? 4 : 8, nb = ((size_t)n + 63) / 64;
+    const size_t part = (size_t)wps * n * 2 * e, terms = ((size_t)n * 8 + 20 * (size_t)nsw) * e;
     SpermLdsLayout L{};
     L.tab = 0;
-    L.src = dtype == 0 ? al16(sizeof(TabSys)) : 0;
-    L.part = al16(L.src + 2 * nmax * 4 * e);
-    L.pos = al16(L.part + (size_t)wps * nmax * 2 * e);
-    L.bad = al16(L.pos + nmax * 16);
+    L.src = dtype == 0 ? ((size_t)(oct << TAB_M) + 1) * sizeof(TabE) : 0;
+    L.part = al16(L.src + 128 * nb * 4 * e);
+    L.pos = al16(L.part + (part > terms ? part : terms));
+    L.bad = al16(L.pos + (size_t)n * 16);
     L.total = al16(L.bad + 4 * (size_t)wps);
     return L;
 }
 
+template <typename T> __device__ __forceinline__ Src4<T> neck_term(V2<T> d, T cf)
+{
+    Src4<T> v;
+    v.x = cf;
+    v.y = d.x;
+    v.fx = d.y;
+    v.fy = (T)0;
+    return v;
+}
+
+// neck spring of rest length L0 from point p to point q (not inlined: only a
+// flagellum of four points needs it apart)
+template <typename T>
+__device__ __attribute__((noinline)) void neck_spring(const PosE<T>* p, const PosE<T>* q, T L0, T L02, T K2,
+                                                      Src4<T>* to)
+{
+    const V2<T> d = pos_diff(*q, *p);
+    *to = neck_term(d, spring_coef(d, L0, L02, K2));
+}
+
 template <typename T, int TPL, int WPS>
 __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, const SysConst<T>& C,
-                             const void* tab_g, TabSys* tab_s, Src4<T>* src, V2<T>* part, PosE<T>* pos, int* badw,
+                             const void* tab_g, TabE* tab_s, Src4<T>* src, V2<T>* part, PosE<T>* pos, int* badw,
                              T* head, T* tail, int32_t* status)
 {
     constexpr bool COMP = sizeof(T) == 4;
     constexpr int NMAX = 64 * TPL, NT = 64 * WPS, PPT = (NMAX + NT - 1) / NT;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int np = g.nf + g.nh, nsw = g.nsw, n = np * nsw;
+    const int nf = g.nf, hc = g.nh / 2, np = nf + g.nh, nsw = g.nsw, n = np * nsw;
     const int nobs1 = r.n_obs + 1;
     const double* sp = r.sysp + (int64_t)SWIM_SP_NPARAM * s;
     const double* sw = r.swp + (int64_t)3 * nsw * s;
@@ -281,43 +316,23 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
         __syncthreads();
         return;
     }
-    // FP32: the system's table copied into LDS; FP64 reads it in place
-    const void* tab = (const TabSys64*)tab_g + s;
+    // FP32: the table's first octaves copied into LDS; FP64 reads it in place
+    std::conditional_t<COMP, TabHead, const void*> tab;
     if constexpr (COMP) {
-        tab_load((const TabSys*)tab_g + s, tab_s, tid, NT);
-        tab = tab_s;
+        const TabSys* all = (const TabSys*)tab_g + s;
+        tab_load_head(all, tab_s, r.oct << TAB_M, tid, NT);
+        tab = TabHead{reinterpret_cast<const char*>(tab_s), TAB_BIAS + ((uint32_t)r.oct << TAB_M), all->e};
+    } else {
+        tab = (const TabSys64*)tab_g + s;
     }
-    SpermK<T> K;
-    K.kc2 = (T)(2.0 * sp[SWIM_SP_KC]);
-    K.kt2 = (T)(2.0 * sp[SWIM_SP_KT]);
-    K.kht2 = (T)(2.0 * sp[SWIM_SP_KHT]);
-    K.khc2 = (T)(2.0 * sp[SWIM_SP_KHC]);
-    K.knt2 = (T)(2.0 * sp[SWIM_SP_KNT]);
-    K.kna2 = (T)(2.0 * sp[SWIM_SP_KNA]);
-    K.ds = (T)g.ds;
-    K.inv2ds = (T)(0.5 / g.ds);
-    K.invds2 = (T)(1.0 / (g.ds * g.ds));
-    K.ds2 = (T)(g.ds * g.ds);
-    K.ch = (T)g.ch;
-    K.inv2ch = (T)(0.5 / g.ch);
-    K.invch2 = (T)(1.0 / (g.ch * g.ch));
-    K.ch2 = (T)(g.ch * g.ch);
-    K.dh = (T)(2.0 * g.hr);
-    K.dh2 = (T)(4.0 * g.hr * g.hr);
-    K.kh0 = (T)(1.0 / g.hr);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        K.L0[i] = (T)g.L0[i];
-        K.L02[i] = (T)(g.L0[i] * g.L0[i]);
-    }
-    const double a = sp[SWIM_SP_A], eta = sp[SWIM_SP_ETA], om = sp[SWIM_SP_OMEGA];
+    const T kna2 = (T)(2.0 * sp[SWIM_SP_KNA]), kh0 = (T)(1.0 / g.hr);
+    const double om = sp[SWIM_SP_OMEGA];
     const T dt = (T)r.dt;
     const T rho = COMP ? C.tr : (T)1;
 
-    // owned points i = tid + NT k: positions in registers, and for flagellum
-    // points the preferred-curvature coefficients of nodes p-1, p, p+1:
-    // zhat_j(t) = A_j cos(omega t) + B_j sin(omega t)
-    T xh[PPT], yh[PPT], xl[PPT], yl[PPT], zA[PPT][3], zB[PPT][3];
+    // owned points i = tid + NT k: positions in registers
+    T xh[PPT], yh[PPT], xl[PPT], yl[PPT];
+    SpermPt<T> pt[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         const int i = tid + NT * k;
@@ -330,16 +345,8 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
         xl[k] = COMP ? (T)(X - (double)xh[k]) : (T)0;
         yl[k] = COMP ? (T)(Y - (double)yh[k]) : (T)0;
         if (held) pos[i] = pos_make<T>(xh[k], yh[k], xl[k], yl[k]);
-        const double ph = held ? sw[3 * m + 2] : 0.0;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int j = p - 1 + q;
-            const double sj = (double)j * g.ds, psi = eta * sj + ph;
-            const double u = -2.0 * a * eta, v = a * (1.0 - sj) * eta * eta;
-            const bool nd = held && p < g.nf && j >= 1 && j <= g.nf - 2;
-            zA[k][q] = nd ? (T)(u * cos(psi) - v * sin(psi)) : (T)0;
-            zB[k][q] = nd ? (T)(u * sin(psi) + v * cos(psi)) : (T)0;
-        }
+        pt[k] = sperm_point<T>(g, sp, held ? sw[3 * m + 2] : 0.0, m * np, p);
+        if (pt[k].edge >= 0) pt[k].edge += 5 * m;
     }
     // padding points n .. 64 B - 1 of the last block: no force, at the start
     // position of point n - 1 (they add nothing to the sums)
@@ -358,21 +365,108 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
     // cos, sin of omega t: FP32 runs rotate by omega dt in FP64, FP64 runs
     // evaluate them directly
     double rc = 1.0, rs = 0.0;
-    const double cd = cos(om * r.dt), sd = sin(om * r.dt);
+    const V2<double> rot = cos_sin(om * r.dt);
     __syncthreads();
 
-    // forces at the current positions (pos in LDS) into src; observation
-    // sample o of the head centres and tail ends
+    SpermTerms<T> tm;
+    tm.ends = reinterpret_cast<Src4<T>*>(part);
+    tm.next = tm.ends + n;
+    tm.neck = tm.next + n;
+    // forces at the current positions (pos in LDS) into src.  A point's terms
+    // in order: its previous and next spring, the nodes next, own and previous,
+    // a diameter, the neck.  (One pass in which every point evaluates each
+    // spring and node it belongs to takes three nodes instead of one, in two
+    // divergent halves for flagellum and head, and five neck branches.)
     auto forces = [&]() {
+        V2<T> d2[PPT], f1[PPT], dm[PPT];
+        T c2[PPT], cm[PPT], co[PPT];
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             const int i = tid + NT * k;
             if (i < n) {
-                const int m = i / np, p = i - m * np;
-                T zh[3];
+                const SpermPt<T>& P = pt[k];
+                const PosE<T> X = pos_make<T>(xh[k], yh[k], xl[k], yl[k]);
+                const V2<T> d1 = pos_diff(X, pos[P.pv]);
+                d2[k] = pos_diff(pos[P.nx], X);
+                const T zh = P.head ? kh0 : fma_t(P.zA, (T)rc, P.zB * (T)rs);
+                V2<T> f[3];
+                co[k] = node_terms<T>(d1, d2[k], P.inv2h, P.invh2, P.h, P.W2, zh, f);
+                co[k] = P.node ? co[k] : (T)0;
 #pragma unroll
-                for (int q = 0; q < 3; ++q) zh[q] = fma_t(zA[k][q], (T)rc, zB[k][q] * (T)rs);
-                const V2<T> F = sperm_force<T>(g, K, pos + m * np, p, zh);
+                for (int q = 0; q < 3; ++q) {
+                    f[q].x = P.node ? f[q].x : (T)0;
+                    f[q].y = P.node ? f[q].y : (T)0;
+                }
+                f1[k] = f[1];
+                c2[k] = spring_coef(d2[k], P.L0, P.L02, P.K2);
+                c2[k] = P.next ? c2[k] : (T)0;
+                Src4<T> e;
+                e.x = f[0].x;
+                e.y = f[0].y;
+                e.fx = f[2].x;
+                e.fy = f[2].y;
+                tm.ends[i] = e;
+                Src4<T> sv;
+                sv.x = c2[k] * d2[k].x;
+                sv.y = c2[k] * d2[k].y;
+                sv.fx = co[k];
+                sv.fy = (T)0;
+                tm.next[i] = sv;
+                dm[k] = pos_diff(pos[P.sb], pos[P.sa]);
+                cm[k] = spring_coef(dm[k], P.M0, P.M02, P.J2);
+                if (P.edge >= 0) tm.neck[P.edge] = neck_term(dm[k], cm[k]);
+                cm[k] = P.head ? cm[k] : (T)0;
+                // (four flagellum points: the last takes neck spring 4, too)
+                if (nf < 5 && P.role == 1)
+                    neck_spring(pos + (i - 1), pos + (i + 2 + hc), (T)g.L0[4], (T)(g.L0[4] * g.L0[4]),
+                                (T)(2.0 * sp[SWIM_SP_KNT]), tm.neck + 5 * ((i - 3) / np) + 4);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+            const int i = tid + NT * k;
+            if (i < n) {
+                const SpermPt<T>& P = pt[k];
+                const Src4<T> sp0 = tm.next[P.ps];
+                const Src4<T> en = tm.ends[P.nx], ep = tm.ends[P.pv];
+                const T con = tm.next[P.nx].fx, cop = tm.next[P.pv].fx;
+                V2<T> F;
+                F.x = fma_t(c2[k], d2[k].x, -sp0.x);
+                F.y = fma_t(c2[k], d2[k].y, -sp0.y);
+                F.x = fma_t(-cop, ep.fx, fma_t(-co[k], f1[k].x, fma_t(-con, en.x, F.x)));
+                F.y = fma_t(-cop, ep.fy, fma_t(-co[k], f1[k].y, fma_t(-con, en.y, F.y)));
+                F.x = fma_t(cm[k], dm[k].x, F.x);
+                F.y = fma_t(cm[k], dm[k].y, F.y);
+                if (P.role != 0) {
+                    // the neck springs this point ends, then the neck angle:
+                    // E = K (z1.z2)^2, dE/dz1 = 2K (z1.z2) z2, dE/dz2 = 2K (z1.z2) z1
+                    const int base = P.role == 1 ? i - (nf - 1) : P.role == 2 ? i - (nf - 2) : i - (nf + hc) - (P.role - 4);
+                    const Src4<T>* N = tm.neck + 5 * (base / np);
+                    const T sg = P.role <= 2 ? (T)1 : (T)-1;
+                    auto add = [&](int q) {
+                        const Src4<T> e = N[q];
+                        F.x = fma_t(e.x, sg * e.y, F.x);
+                        F.y = fma_t(e.x, sg * e.fx, F.y);
+                    };
+                    if (P.role == 1 || P.role == 3) add(0);
+                    if (P.role == 2 || P.role == 3) add(3);
+                    if (P.role == 1 || P.role == 4) add(1);
+                    if (P.role == 1 || P.role == 5) add(2);
+                    if (P.role == 2 || P.role == 5) add(4);
+                    if (P.role != 2) {
+                        const int c = base + nf + hc;
+                        V2<T> z1;
+                        z1.x = N[1].y;
+                        z1.y = N[1].fx;
+                        const V2<T> z2 = pos_diff(pos[c + 1], pos[c - 1]);
+                        const T w = kna2 * fma_t(z1.x, z2.x, z1.y * z2.y);
+                        const V2<T> z = (P.role == 1 || P.role == 4) ? z2 : z1;
+                        const T sw = (P.role == 1 || P.role == 3) ? w : -w;
+                        F.x = fma_t(sw, z.x, F.x);
+                        F.y = fma_t(sw, z.y, F.y);
+                    }
+                }
                 Src4<T> v;
                 v.x = xh[k] * rho;
                 v.y = yh[k] * rho;
@@ -409,40 +503,34 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
             t[1] = (T)ty;
         }
     };
-    observe(0);
-    forces();
-    __syncthreads();
     int st = 0;
-    int obs_left = r.obs_every, obs_k = 1;
+    int obs_left = r.obs_every, obs_k = 0;
+    bool due = true;  // an observation of the present positions
     // this wave's share of the symmetric schedule (of the full blocks when
-    // the tail schedule takes the rest), found once when it is one segment
+    // the tail schedule takes the rest)
     const bool tail_sched = tail_pays(n);
-    int seg[5] = {0, 0, 0, 0, 0};
-    {
-        int a = 0, b = 0, lo = 0, hi = 0;
-        const bool one = sym_one_segment<WPS>(tail_sched ? 64 * (n >> 6) : n, wave, a, b, lo, hi);
-        seg[0] = __builtin_amdgcn_readfirstlane(one ? 1 : 0);
-        seg[1] = __builtin_amdgcn_readfirstlane(a);
-        seg[2] = __builtin_amdgcn_readfirstlane(b);
-        seg[3] = __builtin_amdgcn_readfirstlane(lo);
-        seg[4] = __builtin_amdgcn_readfirstlane(hi);
-    }
-    for (int step = 0; step < r.steps; ++step) {
+    const int B = tail_sched ? n >> 6 : (n + 63) >> 6;
+    PairShare share = pair_share<WPS>(B, wave);
+    share.a = __builtin_amdgcn_readfirstlane(share.a);
+    share.b = __builtin_amdgcn_readfirstlane(share.b);
+    share.s = __builtin_amdgcn_readfirstlane(share.s);
+    share.count = __builtin_amdgcn_readfirstlane(share.count);
+    for (int step = 0;; ++step) {
+        if (due) observe(obs_k++);
+        if (step == r.steps) break;
+        forces();
+        __syncthreads();
         {
             T ax[TPL], ay[TPL];
-            if (tail_sched)
-                pair_phase_tail<T, TPL, WPS>(C, tab, src, n, wave, lane, ax, ay, seg);
-            else if (seg[0])
-                pair_phase_seg<T, TPL>(C, tab, src, seg[1], seg[2], seg[3], seg[4], lane, ax, ay);
-            else
-                pair_phase_sym<T, TPL, WPS>(C, tab, src, n, wave, lane, ax, ay);
+            pair_walk<T, TPL>(C, tab, src, B, share, lane, ax, ay);
+            if (tail_sched) pair_tail<T, TPL, WPS>(C, tab, src, n, wave, lane, ax, ay);
 #pragma unroll
             for (int c = 0; c < TPL; ++c) {
-                if (64 * c < n) {
+                if (64 * c + lane < n) {
                     V2<T> v;
                     v.x = ax[c];
                     v.y = ay[c];
-                    part[wave * NMAX + 64 * c + lane] = v;
+                    part[wave * n + 64 * c + lane] = v;
                 }
             }
         }
@@ -455,7 +543,7 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
             if (i < n) {
                 V2<T> pv[WPS];
 #pragma unroll
-                for (int w = 0; w < WPS; ++w) pv[w] = part[w * NMAX + i];
+                for (int w = 0; w < WPS; ++w) pv[w] = part[w * n + i];
                 T ux = (T)0, uy = (T)0;
 #pragma unroll
                 for (int w = 0; w < WPS; ++w) {
@@ -475,12 +563,12 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
         }
         if constexpr (COMP) {
             const double c0 = rc;
-            rc = fma(c0, cd, -rs * sd);
-            rs = fma(rs, cd, c0 * sd);
+            rc = fma(c0, rot.x, -rs * rot.y);
+            rs = fma(rs, rot.x, c0 * rot.y);
         } else {
-            const double wt = om * ((double)(step + 1) * r.dt);
-            rc = cos(wt);
-            rs = sin(wt);
+            const V2<double> cs = cos_sin(om * ((double)(step + 1) * r.dt));
+            rc = cs.x;
+            rs = cs.y;
         }
         {
             const bool b1 = __ballot(bad == 1) != 0, b2 = __ballot(bad == 2) != 0;
@@ -493,26 +581,33 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
             st = (bflags & 1) ? 1 : 2;
             break;
         }
-        if (r.obs_every > 0 && --obs_left == 0) {
-            obs_left = r.obs_every;
-            observe(obs_k++);
-        }
-        forces();
-        __syncthreads();
+        due = r.obs_every > 0 && --obs_left == 0;
+        if (due) obs_left = r.obs_every;
     }
     if (tid == 0) status[s] = st;
     __syncthreads();
 }
 
+// Bound by VALU issue in large batches (about 2300 wave-operations a step of 74
+// points, 1350 of them the pairs'), by the chain of one step in small ones.
+// Large batches therefore want the waves that hide a step's four barriers and
+// table reads: 128 VGPRs (the far-field evaluation and the trigonometry called,
+// not inlined) and 20 KB of LDS (24 octaves of the table) let eight systems of
+// two waves share a CU, where 202 VGPRs allowed four.  With the forces in two
+// passes and the tail sums in registers, 2000 one-swimmer systems take 8.2 us
+// per step against 14.7, 1024 5.6 against 7.8, one system 3.3 against 4.6; 1000
+// of two swimmers 15.7 against 19.1 (above 128 points 128 VGPRs spill, and 168
+// measure 18.8).
 template <typename T, int TPL, int WPS>
-__global__ __launch_bounds__(64 * WPS) void k_sperm_forward(SpermShape g, SpermRun r, const SysConst<T>* sysc,
-                                                            const void* tabs, int32_t* queue, T* head, T* tail,
-                                                            int32_t* status)
+__global__ __launch_bounds__(64 * WPS, sizeof(T) == 4 && TPL <= 2 ? 4 : 1) void k_sperm_forward(
+    SpermShape g, SpermRun r, const SysConst<T>* sysc, const void* tabs, int32_t* queue, T* head, T* tail,
+    int32_t* status)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_item;
-    const SpermLdsLayout lay = sperm_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS);
-    TabSys* tab = reinterpret_cast<TabSys*>(smem + lay.tab);
+    const SpermLdsLayout lay =
+        sperm_lds_layout(sizeof(T) == 4 ? 0 : 1, WPS, g.nsw * (g.nf + g.nh), g.nsw, r.oct);
+    TabE* tab = reinterpret_cast<TabE*>(smem + lay.tab);
     Src4<T>* src = reinterpret_cast<Src4<T>*>(smem + lay.src);
     V2<T>* part = reinterpret_cast<V2<T>*>(smem + lay.part);
     PosE<T>* pos = reinterpret_cast<PosE<T>*>(smem + lay.pos);
@@ -611,11 +706,16 @@ __global__ void k_gauss_loglik2(int64_t n, int32_t n_obs, const double* g, const
     logl[i] = -m * log(2.0 * M_PI) - m * (log(sa) + log(sb)) - 0.5 * (Ja / (sa * sa) + Jb / (sb * sb));
 }
 
+size_t sperm_lds_bytes(int dtype, int wps, const SpermShape& g, int oct)
+{
+    return sperm_lds_layout(dtype, wps, g.nsw * (g.nf + g.nh), g.nsw, oct).total;
+}
+
 template <typename T, int TPL, int WPS>
 hipError_t launch_sperm_t(int nblocks, const SpermShape& g, const SpermRun& r, const void* sysc, const void* tabs,
                           int32_t* queue, void* head, void* tail, int32_t* status, hipStream_t st)
 {
-    const size_t lds = sperm_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS).total;
+    const size_t lds = sperm_lds_bytes(sizeof(T) == 4 ? 0 : 1, WPS, g, r.oct);
     hipLaunchKernelGGL((k_sperm_forward<T, TPL, WPS>), dim3(nblocks), dim3(64 * WPS), lds, st, g, r,
                        (const SysConst<T>*)sysc, tabs, queue, (T*)head, (T*)tail, status);
     return hipGetLastError();
@@ -649,8 +749,6 @@ template <typename F> hipError_t sperm_dispatch(int dtype, int tpl, int wps, F f
 
 }  // namespace
 
-size_t sperm_lds_bytes(int dtype, int tpl, int wps) { return sperm_lds_layout(dtype, tpl, wps).total; }
-
 hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps, const double* sysp,
                               const double* swp, void* sysc, void* sysc64, int32_t* status, int blob,
                               hipStream_t st)
@@ -671,18 +769,20 @@ hipError_t prepare_sperm(int dtype, int tpl, int wps)
     return sperm_dispatch(dtype, tpl, wps, [&](auto* tt, auto tp, auto wp) {
         using T = std::remove_pointer_t<decltype(tt)>;
         const void* k = sperm_kernel_ptr<T, decltype(tp)::value, decltype(wp)::value>();
-        return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)sperm_lds_bytes(dtype, tpl, wps));
+        // (the most that any call of this instantiation takes: a call must not
+        // lower the limit that another thread's launch needs)
+        const size_t most = sperm_lds_layout(dtype, wps, 64 * tpl, 8 * tpl, TAB_OCT).total;
+        return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
     });
 }
 
-int sperm_blocks_per_cu(int dtype, int tpl, int wps)
+int sperm_blocks_per_cu(int dtype, int tpl, int wps, const SpermShape& g, int oct)
 {
     int nb = 0;
     const hipError_t e = sperm_dispatch(dtype, tpl, wps, [&](auto* tt, auto tp, auto wp) {
         using T = std::remove_pointer_t<decltype(tt)>;
         const void* k = sperm_kernel_ptr<T, decltype(tp)::value, decltype(wp)::value>();
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64 * wps, sperm_lds_bytes(dtype, tpl, wps));
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64 * wps, sperm_lds_bytes(dtype, wps, g, oct));
     });
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
