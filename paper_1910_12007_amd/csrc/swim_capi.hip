@@ -60,7 +60,7 @@ struct DevBuf {
 };
 
 enum BufId {
-    B_UP, B_SYSC, B_QUEUE,
+    B_UP, B_SYSC, B_QUEUE, B_ORDER,
     B_PARAMS, B_DATA, B_OBS, B_SPEED, B_STATUS, B_DIST, B_TOL, B_ACC, B_BIG,
     B_MLP_ACT, B_MLP_IDX, B_MLP_CNT,
     B_PS_THETA, B_PS_X, B_PS_KEEP, B_PS_IDX, B_PS_NK, B_PS_SUM, B_DS_T, B_TAB, B_DONE, B_W16, B_SIGMA, B_LOGL,
@@ -513,20 +513,14 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
             max_big = std::max(max_big, pts[s]);
         }
     }
-    // longest-first order inside every bucket; in a merged bucket, the
-    // systems merged in from smaller buckets first (each group longest-
-    // first): in a launch of their own they would have started at once,
-    // and behind the larger group they would start only once all of its
-    // systems are taken (in a generation whose large draws mostly blow up,
-    // the few long runs are then the last to start)
+    // largest-first order inside every bucket (where a merged bucket's systems
+    // wait for a workgroup, k_order_runs puts the likely long runs first)
     std::vector<int32_t> order;
     std::vector<std::pair<int, int64_t>> bucket_span;  // (tpl, start)
     for (int t : TPL_CHOICES) {
         auto& v = bucket[t - 1];
         if (v.empty()) continue;
-        std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) {
-            return tpl_of[a] != tpl_of[b] ? tpl_of[a] < tpl_of[b] : pts[a] > pts[b];
-        });
+        std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) { return pts[a] > pts[b]; });
         bucket_span.push_back({t, (int64_t)order.size()});
         order.insert(order.end(), v.begin(), v.end());
     }
@@ -579,6 +573,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     struct Bucket {
         int tpl, wps, nblocks, lane = 0;
         int64_t start, count;
+        bool reorder = false;  // its queue order comes from k_order_runs
     };
     std::vector<Bucket> bk;
     for (size_t k = 0; k < bucket_span.size(); ++k) {
@@ -623,6 +618,24 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         HIPCHK(prepare_forward(dtype, q.tpl, q.wps));
         bk.push_back(q);
     }
+    // a merged bucket with more systems than workgroups gets its queue order on
+    // the device; in the others the systems' sizes differ little
+    OrderSegs seg{};
+    int n_seg = 0;
+    for (Bucket& q : bk) {
+        bool merged = false;
+        for (int64_t k = q.start; k < q.start + q.count; ++k) merged = merged || tpl_of[order[k]] != q.tpl;
+        q.reorder = merged && q.count > q.nblocks && q.count <= ORDER_MAX && n_seg < ORDER_SEGS;
+        if (!q.reorder) continue;
+        seg.start[n_seg] = q.start;
+        seg.count[n_seg++] = (int32_t)q.count;
+    }
+    int32_t* queue_dev = nullptr;
+    if (n_seg) {
+        TRY(ensure(c, B_ORDER, order.size() * 4));
+        queue_dev = (int32_t*)c->buf[B_ORDER].p;
+    }
+    auto bucket_order = [&](const Bucket& q) { return (q.reorder ? queue_dev : order_dev) + q.start; };
     // lanes of the concurrent launch (longest processing time first): each
     // part, in decreasing pair work, goes to the lane with the least work
     int big_lane = 0;
@@ -679,6 +692,8 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
                                              status, c->opt_blob, st);
         if (e == hipSuccess) e = build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st);
         if (e == hipSuccess) e = launch_fill_i32((int32_t*)c->buf[B_QUEUE].p, 0, 8, st);
+        if (e == hipSuccess)
+            e = launch_order_runs(n_seg, seg, order_dev, b.sw_off, b.npt, params_dev, run.dt, queue_dev, st);
         if (e == hipSuccess && c->opt_time) e = hipEventRecord(c->time_ev[0], st);
         // Buckets (and the large systems) are independent: with more than
         // one, they run side by side, the call's stream and up to N_AUX
@@ -696,7 +711,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
             Batch bb = b;
             bb.n_sys = bk[k].count;
             e = launch_forward(dtype, bk[k].tpl, bk[k].wps, bk[k].nblocks, bb, run,
-                               order_dev + bk[k].start, (int32_t*)c->buf[B_QUEUE].p + k, obs,
+                               bucket_order(bk[k]), (int32_t*)c->buf[B_QUEUE].p + k, obs,
                                speed, status, steps_done, lane_stream(bk[k].lane % lanes));
         }
         if (!big_list.empty() && e == hipSuccess) {
@@ -755,7 +770,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     h.add(big_lane);
     // (the arrays of the upload buffer lie where its start and the sizes put them)
     const void* ptrs[] = {params_dev, obs, speed, status, steps_done, sysc, sysc64, b.tab, c->buf[B_UP].p,
-                          c->buf[B_QUEUE].p, c->buf[B_BIG].p, st};
+                          queue_dev, c->buf[B_QUEUE].p, c->buf[B_BIG].p, st};
     h.add_bytes(ptrs, sizeof(ptrs));
     if (!big_list.empty() && big_sym) {
         const void* sptrs[] = {bt.part, bt.src};

@@ -66,6 +66,15 @@ hipError_t launch_forces(int dtype, int64_t n_fil, const int64_t* fil_off, const
 hipError_t launch_forward(int dtype, int tpl, int wps, int n_blocks, const Batch& b,
                           const Run& r, const int32_t* order, int32_t* queue, void* obs,
                           void* speed, int32_t* status, int32_t* steps_done, hipStream_t st);
+// queue order of some buckets (segments of the order array, at most
+// ORDER_MAX systems each): long runs first
+constexpr int ORDER_SEGS = 6, ORDER_MAX = 262144;
+struct OrderSegs {
+    int64_t start[ORDER_SEGS];
+    int32_t count[ORDER_SEGS];
+};
+hipError_t launch_order_runs(int n_seg, const OrderSegs& seg, const int32_t* in, const int64_t* sw_off,
+                             const int32_t* npt, const double* params, double dt, int32_t* out, hipStream_t st);
 // smallest waves per system of the persistent kernel for tpl targets per lane
 int forward_min_wps(int tpl);
 size_t forward_lds_bytes(int dtype, int tpl, int wps);
