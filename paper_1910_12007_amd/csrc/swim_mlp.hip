@@ -55,7 +55,10 @@ __device__ __forceinline__ float gelu_f(float x)
     p = fmaf(p, t, 0.254829592f);
     // exp(-a^2/2) / 2, the halving folded into the exponent
     const float e = __builtin_amdgcn_exp2f(fmaf(a * a, -0.5f * 1.4426950408889634f, -1.0f));
-    return fmaf(-(a * t), p * e, fmaxf(x, 0.0f));
+    // max(x, 0) on the bits: fmaxf takes another operation to quiet its operand
+    // (a NaN comes through the product either way)
+    const float r = __builtin_bit_cast(float, max(__builtin_bit_cast(int, x), 0));
+    return fmaf(-(a * t), p * e, r);
 }
 
 __device__ __forceinline__ float gelu_grad_f(float x)
@@ -383,18 +386,25 @@ hipError_t launch_flag_bounded(int64_t n, const float* T, int nt, int n_disp, fl
 // layer's k slice p, i.e. the k order within each 32-wide slice is
 //   slot 8q + j  <->  k = 4q + j (j < 4),  16 + 4q + (j - 4) (j >= 4),
 // and the packed weights (k_pack_w16) use the same order.  So activations
-// never touch LDS; the weights, a bfloat16 copy packed per layer as W^T
-// [n][k] (k in that slot order, padded to a multiple of 32, n of the last
-// layer to 48), pass through LDS in chunks of MLP_KC = 32 k,
-// double-buffered: the next chunk (of this layer or the next) is read into
-// registers while the current one feeds the MFMAs.  40 KB of LDS, 158
-// VGPRs (three waves per SIMD); FP32 accumulation over the slices in order.  MODE 0 writes the outputs;
-// MODE 1 computes the prescreen distance of every row.
+// never touch LDS; the weights, a bfloat16 copy packed as operand fragments (k
+// padded to a multiple of 32, n of the last layer to 48), pass through LDS in
+// chunks of MLP_KC = 32 k, double-buffered: the next chunk (of this layer or
+// the next) goes from L2 to LDS by loads that take no registers while the
+// current one feeds the MFMAs, and a fragment is read in lane order, without
+// bank conflicts or address arithmetic.  FP32 accumulation over the slices in
+// order.  MODE 0 writes the outputs; MODE 1 computes the prescreen distance of
+// every row.
+// Bound by the vector ALUs: 14 operations per activation, two of them at a
+// quarter of the rate, are 0.55 ms for 1M rows; the MFMAs' 0.18 and the weights'
+// way out of LDS, 0.35, hide behind them only in other waves, so the count of
+// waves decides: 126 VGPRs and 32 KB, four per SIMD.  One prescreen of 1M rows
+// takes 714 us; with the chunks through registers and padded rows (166 VGPRs,
+// three waves) 981; with 64-bit addresses per lane for the loads 756 at three
+// waves, 855 at four, with spills.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-constexpr int TT = 1;  // 16-row tiles per wave (two: 256 registers and spills, no faster)
-constexpr int MLP_RT = 64 * TT, MLP_KC = 32, MLP_WP = MLP_KC + 8;
+constexpr int MLP_RT = 64, MLP_KC = 32;
 constexpr int MLP_NL = 5;
 constexpr int mlp_kp(int l) { return l == 0 ? 32 : 256; }   // padded K
 constexpr int mlp_np(int l) { return l == MLP_NL - 1 ? 48 : 256; }  // padded N
@@ -419,191 +429,176 @@ __host__ __device__ constexpr int mlp_slot_k(int s)
     return (s & 7) < 4 ? 4 * (s >> 3) + (s & 7) : 16 + 4 * (s >> 3) + (s & 7) - 4;
 }
 
-// bfloat16 copy of the weights, transposed, k in slot order, padded (zeros)
+// bfloat16 copy of the weights, transposed, k in slot order, padded (zeros),
+// as operand fragments: chunk by chunk, tile by tile, the eight values of each
+// lane in a row
 __global__ void k_pack_w16(const float* P, uint16_t* W16)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= MLP_W16_TOTAL) return;
     int l = 0;
     while (l + 1 < MLP_NL && e >= mlp_w16_off(l + 1)) ++l;
-    const int64_t i = e - mlp_w16_off(l);
-    const int n = (int)(i / mlp_kp(l)), kk = (int)(i % mlp_kp(l));
-    const int k = (kk & ~31) + mlp_slot_k(kk & 31);
+    const int i = (int)(e - mlp_w16_off(l)), nt = mlp_np(l) / 16;
+    const int j = i & 7, lane = (i >> 3) & 63, tile = (i >> 9) % nt, chunk = (i >> 9) / nt;
+    const int n = 16 * tile + (lane & 15), k = MLP_KC * chunk + mlp_slot_k(8 * (lane >> 4) + j);
     const float v = (n < mlp_n(l) && k < mlp_k(l)) ? P[mlp_offW_d(l) + (int64_t)k * mlp_n(l) + n] : 0.0f;
     W16[e] = f2bf(v);
 }
 
-// weight chunk c of layer l (rows n < Np(l), slots [32c, 32c + 32)) as
-// per-thread 16-byte pieces: global -> registers, registers -> LDS.  A row
-// is 4 pieces; 256 rows are 1024 pieces, 4 per thread (the last layer's 48
-// rows: the first 192 pieces).
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-struct WChunk {
-    u32x4_t v[4];
-};
-__device__ __forceinline__ const uint16_t* mlp_wl(const uint16_t* W16, int l)
+// one chunk of NP fragments (1 KB each) at byte `at` of the packed weights,
+// from L2 into LDS without registers; complete behind this wave's wait and the
+// workgroup's barrier (chunk_ready)
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __amdgpu_buffer_rsrc_t WBuf;
+__device__ __forceinline__ WBuf wbuf(const uint16_t* W16)
 {
-    return W16 + (l == 0 ? 0 : mlp_w16_off(1) + (int64_t)(l - 1) * 65536);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W16), 0, (int)(MLP_W16_TOTAL * 2), 0x00020000);
 }
-__device__ __forceinline__ int mlp_chunks(int l) { return l == 0 ? 1 : 256 / MLP_KC; }
-// this thread's pieces of layer l's chunks: element offsets in the packed
-// layer (chunk 0; chunk c adds 32 c) and in the LDS buffer (-1: none)
-struct WAddr {
-    int src[4], dst[4];
-};
-__device__ __forceinline__ void wchunk_addr(int l, int tid, WAddr& a)
+#else
+typedef const uint16_t* WBuf;
+__device__ inline WBuf wbuf(const uint16_t* W16) { return W16; }
+#endif
+template <int NP> __device__ __forceinline__ void chunk_fetch(WBuf W, int at, uint16_t* to, int wave, int lane)
 {
-    const int Kp = l == 0 ? 32 : 256, np4 = 4 * (l == MLP_NL - 1 ? 48 : 256);
+#if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q, ec = min(e, np4 - 1);  // clamped: always a valid piece
-        a.src[q] = (ec >> 2) * Kp + 8 * (ec & 3);
-        a.dst[q] = e < np4 ? (e >> 2) * MLP_WP + 8 * (e & 3) : -1;
+    for (int i = 0; i < (NP + 3) / 4; ++i) {
+        const int piece = wave + 4 * i;
+        if (NP % 4 == 0 || piece < NP)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(W, (__attribute__((address_space(3))) void*)(to + 512 * piece), 16,
+                                                     16 * lane, at + 1024 * piece, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);  // not behind the products that hide it
+#endif
 }
-__device__ __forceinline__ void wchunk_load(const uint16_t* Wl, const WAddr& a, int c, WChunk& w)
+__device__ __forceinline__ void chunk_ready()
 {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w.v[q] = *reinterpret_cast<const u32x4_t*>(Wl + a.src[q] + MLP_KC * c);
-}
-__device__ __forceinline__ void wchunk_store(const WAddr& a, const WChunk& w, uint16_t* Ws)
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (a.dst[q] >= 0) *reinterpret_cast<u32x4_t*>(Ws + a.dst[q]) = w.v[q];
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+    __syncthreads();
 }
 __device__ __forceinline__ uint32_t pack_bf2(float a, float b)
 {
     return __builtin_bit_cast(uint32_t, bf16x2_t{(__bf16)a, (__bf16)b});
 }
+// acc[c] += chunk's tile c times the row tile's slice h
+template <int NT>
+__device__ __forceinline__ void chunk_mfma(const uint16_t* Ws, u32x4_t h, int lane, f32x4_t (&acc)[16])
+{
+    const bf16x8_t hv = __builtin_bit_cast(bf16x8_t, h);
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        const bf16x8_t wv = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(Ws + 512 * c + 8 * lane));
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, hv, acc[c], 0, 0, 0);
+    }
+}
+// GELU, bfloat16: tiles 2p, 2p + 1 -> slice p of the next layer's operand
+__device__ __forceinline__ void mlp_activate(const f32x4_t (&acc)[16], u32x4_t (&h)[8])
+{
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        const f32x4_t a0 = acc[2 * p], a1 = acc[2 * p + 1];
+        h[p] = u32x4_t{pack_bf2(gelu_f(a0[0]), gelu_f(a0[1])), pack_bf2(gelu_f(a0[2]), gelu_f(a0[3])),
+                       pack_bf2(gelu_f(a1[0]), gelu_f(a1[1])), pack_bf2(gelu_f(a1[2]), gelu_f(a1[3]))};
+    }
+}
 
 template <int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_fused(int64_t M, const float* __restrict__ X,
-                                                   const uint16_t* __restrict__ W16, const float* __restrict__ P,
-                                                   float* __restrict__ Y, const float* __restrict__ out_mu,
-                                                   const float* __restrict__ out_sd, const float* __restrict__ obs,
-                                                   int n_sum, float tol, float* __restrict__ dist,
-                                                   uint8_t* __restrict__ keep)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_mlp_fused(
+    int64_t M, const float* __restrict__ X, const uint16_t* __restrict__ W16, const float* __restrict__ P,
+    float* __restrict__ Y, const float* __restrict__ out_mu, const float* __restrict__ out_sd,
+    const float* __restrict__ obs, int n_sum, float tol, float* __restrict__ dist, uint8_t* __restrict__ keep)
 {
-    extern __shared__ __align__(16) uint16_t mlp_smem[];
-    uint16_t* Wb = mlp_smem;  // [2][256][MLP_WP], double-buffered
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __align__(16) uint16_t Wa[16 * 512], Wb[16 * 512];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = lane >> 4;
-    // this lane's rows of the batch (one per row tile) and output slots
-    int64_t row[TT];
+    // this lane's row of the batch
+    const int64_t row = (int64_t)blockIdx.x * MLP_RT + 16 * wave + (lane & 15);
+    const WBuf W = wbuf(W16);
+    int next = 0;  // byte of the chunk fetched next
+    chunk_fetch<16>(W, next, Wa, wave, lane);
+    next += 16 * 1024;
+    f32x4_t acc[16];
+    u32x4_t h[8];
+    // hidden layers start from the bias (C^T[n][m] = b[n])
+    auto from_bias = [&](int l) {
+        const float* bias = P + mlp_offW_d(l) + (int64_t)mlp_k(l) * mlp_n(l);
 #pragma unroll
-    for (int t = 0; t < TT; ++t) row[t] = (int64_t)blockIdx.x * MLP_RT + 16 * TT * wave + 16 * t + (lane & 15);
-    // B operands of the current layer: 8 slices x 2 row tiles (layer 0: the
-    // five inputs in slice 0, slot order, zeros elsewhere)
-    u32x4_t hb[TT][8];
-#pragma unroll
-    for (int t = 0; t < TT; ++t) {
+        for (int c = 0; c < 16; ++c) acc[c] = *reinterpret_cast<const f32x4_t*>(bias + 16 * c + 4 * q);
+    };
+    {
+        // layer 0: the five inputs in slot order, zeros elsewhere
         float xin[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = mlp_slot_k(8 * q + j);
-            xin[j] = (k < 5 && row[t] < M) ? X[row[t] * 5 + k] : 0.0f;
+            xin[j] = (k < 5 && row < M) ? X[row * 5 + k] : 0.0f;
         }
-        hb[t][0] = u32x4_t{pack_bf2(xin[0], xin[1]), pack_bf2(xin[2], xin[3]), pack_bf2(xin[4], xin[5]),
-                           pack_bf2(xin[6], xin[7])};
-#pragma unroll
-        for (int p = 1; p < 8; ++p) hb[t][p] = u32x4_t{0u, 0u, 0u, 0u};
+        from_bias(0);
+        chunk_ready();
+        chunk_fetch<16>(W, next, Wb, wave, lane);
+        next += 16 * 1024;
+        chunk_mfma<16>(Wa, u32x4_t{pack_bf2(xin[0], xin[1]), pack_bf2(xin[2], xin[3]), pack_bf2(xin[4], xin[5]),
+                                   pack_bf2(xin[6], xin[7])},
+                       lane, acc);
+        mlp_activate(acc, h);
     }
-    WChunk nxt;
-    WAddr wa_cur, wa_next;
-    wchunk_addr(0, tid, wa_cur);
-    wchunk_load(mlp_wl(W16, 0), wa_cur, 0, nxt);
-    wchunk_store(wa_cur, nxt, Wb);
-    int g = 0;
+    // chunk c of layers 1.. lies in Wb (c even) or Wa (c odd)
 #pragma unroll 1
-    for (int l = 0; l < MLP_NL; ++l) {
-        const int NT = l == MLP_NL - 1 ? 3 : 16;  // 16-row tiles of n
-        const int nchunk = mlp_chunks(l);
-        const uint16_t* Wl = mlp_wl(W16, l);
-        const uint16_t* Wn = mlp_wl(W16, l + 1 < MLP_NL ? l + 1 : l);
-        if (l + 1 < MLP_NL) wchunk_addr(l + 1, tid, wa_next);
-        const float* bias = P + mlp_offW_d(l) + (int64_t)mlp_k(l) * mlp_n(l);
-        // hidden layers start from the bias (C^T[n][m] = b[n]), the last
-        // layer adds it to its 33 outputs
-        f32x4_t acc[TT][16];
+    for (int l = 1; l < MLP_NL - 1; ++l) {
+        from_bias(l);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const f32x4_t b0 = l < MLP_NL - 1 ? *reinterpret_cast<const f32x4_t*>(bias + 16 * c + 4 * q)
-                                              : f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t = 0; t < TT; ++t) acc[t][c] = b0;
+        for (int c = 0; c < 8; ++c) {
+            chunk_ready();  // chunk c there; nobody reads the other buffer any more
+            if (c < 7 || l + 1 < MLP_NL - 1)
+                chunk_fetch<16>(W, next, c & 1 ? Wb : Wa, wave, lane);
+            else
+                chunk_fetch<3>(W, next, Wb, wave, lane);
+            next += 16 * 1024;
+            chunk_mfma<16>(c & 1 ? Wa : Wb, h[c], lane, acc);
         }
+        mlp_activate(acc, h);
+    }
+    next = (int)(mlp_w16_off(MLP_NL - 1) * 2) + 3 * 1024;
 #pragma unroll
-        for (int ch = 0; ch < 8; ++ch) {
-            if (ch < nchunk) {
-                // chunk g stored by every thread; the previous reader of
-                // Wbuf[(g + 1) & 1] done
-                __syncthreads();
-                const bool same = ch + 1 < nchunk, more = same || l + 1 < MLP_NL;
-                if (more) wchunk_load(same ? Wl : Wn, same ? wa_cur : wa_next, same ? ch + 1 : 0, nxt);
-                const uint16_t* Ws = Wb + (g & 1) * 256 * MLP_WP;
+    for (int c = 0; c < 3; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int c = 0; c < 16; ++c) {
-                    if (c < NT) {
-                        const bf16x8_t wv = __builtin_bit_cast(
-                            bf16x8_t, *reinterpret_cast<const u32x4_t*>(Ws + (16 * c + (lane & 15)) * MLP_WP + 8 * q));
+    for (int c = 0; c < 8; ++c) {
+        chunk_ready();
+        if (c < 7) chunk_fetch<3>(W, next + 3 * 1024 * c, c & 1 ? Wb : Wa, wave, lane);
+        chunk_mfma<3>(c & 1 ? Wa : Wb, h[c], lane, acc);
+    }
+    const float* bias = P + mlp_offW_d(MLP_NL - 1) + (int64_t)mlp_k(MLP_NL - 1) * mlp_n(MLP_NL - 1);
+    if constexpr (MODE == 0) {
 #pragma unroll
-                        for (int t = 0; t < TT; ++t)
-                            acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                wv, __builtin_bit_cast(bf16x8_t, hb[t][ch]), acc[t][c], 0, 0, 0);
-                    }
-                }
-                if (more) wchunk_store(same ? wa_cur : wa_next, nxt, Wb + ((g + 1) & 1) * 256 * MLP_WP);
-                ++g;
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int n = 16 * c + 4 * q + r;
+                if (n < 33 && row < M) Y[row * 33 + n] = acc[c][r] + bias[n];
             }
-        }
-        if (l + 1 < MLP_NL) wa_cur = wa_next;
-        if (l < MLP_NL - 1) {
-            // GELU, bfloat16: tiles 2p, 2p + 1 -> slice p of the next
-            // layer's operand
+    } else {
+        // prescreen: d = sqrt(mean_{n < n_sum} (mu_n + sd_n y_n - obs_n)^2)
+        float sq = 0.f;
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-                for (int t = 0; t < TT; ++t) {
-                    const f32x4_t a0 = acc[t][2 * p], a1 = acc[t][2 * p + 1];
-                    hb[t][p] = u32x4_t{pack_bf2(gelu_f(a0[0]), gelu_f(a0[1])), pack_bf2(gelu_f(a0[2]), gelu_f(a0[3])),
-                                       pack_bf2(gelu_f(a1[0]), gelu_f(a1[1])), pack_bf2(gelu_f(a1[2]), gelu_f(a1[3]))};
+            for (int r = 0; r < 4; ++r) {
+                const int n = 16 * c + 4 * q + r;
+                if (n < n_sum) {
+                    const float dv = fmaf(out_sd[n], acc[c][r] + bias[n], out_mu[n]) - obs[n];
+                    sq = fmaf(dv, dv, sq);
                 }
             }
-        } else if (MODE == 0) {
-#pragma unroll
-            for (int t = 0; t < TT; ++t)
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int n = 16 * c + 4 * q + r;
-                        if (n < 33 && row[t] < M) Y[row[t] * 33 + n] = acc[t][c][r] + bias[n];
-                    }
-        } else {
-            // prescreen: d = sqrt(mean_{n < n_sum} (mu_n + sd_n y_n - obs_n)^2)
-#pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                float sq = 0.f;
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int n = 16 * c + 4 * q + r;
-                        if (n < n_sum) {
-                            const float dv = fmaf(out_sd[n], acc[t][c][r] + bias[n], out_mu[n]) - obs[n];
-                            sq = fmaf(dv, dv, sq);
-                        }
-                    }
-                // the four lanes of row m (lane % 16 equal), fixed order
-                sq += __shfl_xor(sq, 16, 64);
-                sq += __shfl_xor(sq, 32, 64);
-                if (q == 0 && row[t] < M) {
-                    const float d = sqrtf(sq / (float)n_sum);
-                    if (dist) dist[row[t]] = d;
-                    keep[row[t]] = (d <= tol) ? 1 : 0;
-                }
-            }
+        // the four lanes of row m (lane % 16 equal), fixed order
+        sq += __shfl_xor(sq, 16, 64);
+        sq += __shfl_xor(sq, 32, 64);
+        if (q == 0 && row < M) {
+            const float d = sqrtf(sq / (float)n_sum);
+            if (dist) dist[row] = d;
+            keep[row] = (d <= tol) ? 1 : 0;
         }
     }
 }
@@ -1051,7 +1046,6 @@ hipError_t launch_mlp_update(bool adam, const MlpUpdate& u, hipStream_t st)
     return hipGetLastError();
 }
 
-size_t mlp_fused_lds_bytes() { return (size_t)(2 * 256 * MLP_WP) * sizeof(uint16_t); }
 int64_t mlp_w16_count() { return MLP_W16_TOTAL; }
 
 hipError_t launch_pack_w16(const float* P, uint16_t* W16, hipStream_t st)
@@ -1065,14 +1059,13 @@ hipError_t launch_mlp_fused(int mode, int64_t M, const float* X, const uint16_t*
                             float* dist, uint8_t* keep, hipStream_t st)
 {
     if (M <= 0) return hipSuccess;
-    const size_t lds = mlp_fused_lds_bytes();
     const dim3 grid((unsigned)((M + MLP_RT - 1) / MLP_RT));
     if (mode == 0)
-        hipLaunchKernelGGL(k_mlp_fused<0>, grid, dim3(256), lds, st, M, X, W16, P, Y, out_mu, out_sd, obs, n_sum, tol,
-                           dist, keep);
+        hipLaunchKernelGGL(k_mlp_fused<0>, grid, dim3(256), 0, st, M, X, W16, P, Y, out_mu, out_sd, obs, n_sum, tol, dist,
+                           keep);
     else
-        hipLaunchKernelGGL(k_mlp_fused<1>, grid, dim3(256), lds, st, M, X, W16, P, Y, out_mu, out_sd, obs, n_sum, tol,
-                           dist, keep);
+        hipLaunchKernelGGL(k_mlp_fused<1>, grid, dim3(256), 0, st, M, X, W16, P, Y, out_mu, out_sd, obs, n_sum, tol, dist,
+                           keep);
     return hipGetLastError();
 }
 
