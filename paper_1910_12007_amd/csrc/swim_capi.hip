@@ -710,6 +710,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         for (size_t k = 0; k < bk.size() && e == hipSuccess; ++k) {
             Batch bb = b;
             bb.n_sys = bk[k].count;
+            bb.alone = bk[k].nblocks <= c->num_cu;
             e = launch_forward(dtype, bk[k].tpl, bk[k].wps, bk[k].nblocks, bb, run,
                                bucket_order(bk[k]), (int32_t*)c->buf[B_QUEUE].p + k, obs,
                                speed, status, steps_done, lane_stream(bk[k].lane % lanes));

@@ -549,12 +549,14 @@ __global__ void k_forces(int64_t n_fil, const int64_t* fil_off, const int32_t* n
 }
 
 
-// FP32 launch shapes whose table is held as the 64 KiB LDS index window
-// (one operation less per pair): those that already run at most two
-// systems per CU, where two windows and the rest of the layout fit the LDS
+// FP32 launch shapes whose table is held as a 64 KiB LDS window, in finer
+// pieces while all points lie within their reach (four operations less per
+// pair than the whole table with its clamped index): those that run at most
+// two systems per CU (eight waves up to 128 points) or one (16 waves above)
+// anyway, where the windows and the rest of the layout fit the LDS
 __host__ __device__ constexpr bool fwd_window(int dtype, int tpl, int wps)
 {
-    return dtype == 0 && tpl <= 2 && wps == 8;
+    return dtype == 0 && ((tpl <= 2 && wps == 8) || (tpl >= 3 && wps == 16));
 }
 
 // Queue order of a merged bucket's systems when they outnumber its workgroups:
@@ -772,7 +774,7 @@ __device__ __forceinline__ void lane_force(int fl, T xh, T yh, T xl, T yl, T ss2
     Fy = fma_t(-con, gAyn, Fy);
 }
 
-template <typename T, int TPL, int WPS>
+template <typename T, int TPL, int WPS, bool AHEAD>
 __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>& L, T* obs, T* speed,
                            int32_t* status, int32_t* steps_done, bool refuse)
 {
@@ -804,7 +806,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     const double dsd = 1.0 / (double)(N - 1);
     constexpr bool WIN = fwd_window(COMP ? 0 : 1, TPL, WPS);
     if constexpr (WIN)
-        tab_load_window((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
+        tab_load_quads((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
     else if constexpr (COMP)
         tab_load((const TabSys*)b.tab + s, L.tab, tid, NT);
     const int nwin = (n + FWD_WIN - 1) / FWD_WIN;
@@ -815,6 +817,12 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     // the pair phase of FP32 runs works on positions scaled by the table's
     // rho (an exact power of two); registers keep the unscaled state
     const T rho = COMP ? C.tr : (T)1;
+    // positions beyond which a step needs a look: the run bound, or, while the
+    // finer pieces of the table serve, their reach
+    T bound = (T)1e3;
+    bool wide = !WIN;  // the table window holds all octaves
+    if constexpr (WIN) bound = fminf(1e3f, TAB_QUAD_REACH / rho);
+    auto outside = [&](T x, T y) { return !(fabs(x) <= bound) || !(fabs(y) <= bound); };
 
     // window state: point i = 60 g + lane - 2 of window g = wave + WPS q
     T xh[OWNW], yh[OWNW], xl[OWNW], yl[OWNW], ss2[OWNW], sb2[OWNW], ka[OWNW], kb[OWNW];
@@ -890,8 +898,26 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         L.src[slot] = v;
         L.src[slot + 64] = v;
     }
-    if (pwave) point_forces();
+    if (pwave) {
+        point_forces();
+        bool out = false;
+#pragma unroll
+        for (int q = 0; q < OWNW; ++q) out = out || ((fl[q] & FL_OWN) && outside(xh[q], yh[q]));
+        const bool any = __any(out);
+        if (lane == 0) L.bad[wave] = any ? 1 : 0;
+    }
     __syncthreads();
+    // from now on with all octaves of the table, in the coarser pieces
+    auto widen = [&]() {
+        wide = true;
+        bound = (T)1e3;
+        __syncthreads();  // (nobody reads the finer pieces any more)
+        tab_load_window((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
+        __syncthreads();
+    };
+    if constexpr (WIN) {
+        if (__any(lane < pw ? L.bad[lane] : 0)) widen();
+    }
     int st = 0, done = r.steps;
     const int nblk64 = (n + 63) >> 6;
     // this wave's share of the pair schedule when it is one segment
@@ -917,10 +943,21 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
             // (FP64 reads its table from HBM and tests every pair)
             T ax[TPL], ay[TPL];
             const void* tab = COMP ? (const void*)L.tab : (const void*)((const TabSys64*)b.tab + s);
-            if (one_seg)
-                pair_phase_seg<T, TPL, !COMP, WIN>(C, tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
-            else
-                pair_phase_sym<T, TPL, WPS, !COMP, WIN>(C, tab, L.src, n, wave, lane, ax, ay);
+            auto pairs = [&](auto mode) {
+                constexpr int W = decltype(mode)::value;
+                if (one_seg)
+                    pair_phase_seg<T, TPL, !COMP, W>(C, tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
+                else
+                    pair_phase_sym<T, TPL, WPS, !COMP, W>(C, tab, L.src, n, wave, lane, ax, ay);
+            };
+            if constexpr (WIN) {
+                if (wide)
+                    pairs(std::integral_constant<int, 1>());
+                else
+                    pairs(std::integral_constant<int, AHEAD ? 3 : 2>());
+            } else {
+                pairs(std::integral_constant<int, 0>());
+            }
 #pragma unroll
             for (int c = 0; c < TPL; ++c) {
                 if (c < nblk64) {
@@ -956,8 +993,8 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                         xh[q] = fma_t(dt, ux, xh[q]);
                         yh[q] = fma_t(dt, uy, yh[q]);
                     }
-                    if ((fl[q] & FL_OWN) && (bad_t(xh[q]) || bad_t(yh[q])))
-                        bad = (isfinite(xh[q]) && isfinite(yh[q])) ? 2 : 1;
+                    if ((fl[q] & FL_OWN) && outside(xh[q], yh[q]))
+                        bad |= !(isfinite(xh[q]) && isfinite(yh[q])) ? 1 : bad_t(xh[q]) || bad_t(yh[q]) ? 2 : 8;
                 }
                 if constexpr (COMP) {
                     const double c = rc[q], sn = rs[q];
@@ -970,18 +1007,23 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                 }
             }
             point_forces();
-            const bool b1 = __ballot(bad == 1) != 0, b2 = __ballot(bad == 2) != 0;
-            const bool b4 = __ballot(rejected) != 0;
-            if (lane == 0) L.bad[wave] = (b1 ? 1 : 0) | (b2 ? 2 : 0) | (b4 ? 4 : 0);
+            bad |= rejected ? 4 : 0;
+            int flags = 0;
+            if (__any(bad))
+                flags = (__any(bad & 1) ? 1 : 0) | (__any(bad & 2) ? 2 : 0) | (__any(bad & 4) ? 4 : 0) |
+                        (__any(bad & 8) ? 8 : 0);
+            if (lane == 0) L.bad[wave] = flags;
         }
         __syncthreads();
         // the point waves' flags, one per lane, combined by ballot (uniform)
         const int bw = lane < pw ? L.bad[lane] : 0;
-        const int badw = (__ballot(bw & 1) ? 1 : 0) | (__ballot(bw & 2) ? 2 : 0) | (__ballot(bw & 4) ? 4 : 0);
-        if (badw) {
-            st = (badw & 1) ? 1 : (badw & 2) ? 2 : SWIM_ST_REJECTED_;
-            done = step + 1;
-            break;
+        if (__any(bw)) {
+            if (__any(bw & 7)) {
+                st = __any(bw & 1) ? 1 : __any(bw & 2) ? 2 : SWIM_ST_REJECTED_;
+                done = step + 1;
+                break;
+            }
+            if constexpr (WIN) widen();
         }
         if (r.obs_every > 0 && --obs_left == 0) {
             obs_left = r.obs_every;
@@ -1035,8 +1077,10 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
 // VGPRs (8 waves per SIMD): two systems then share a CU, so that one's
 // barriers and LDS latency overlap the other's pair phase (without the
 // bound the build takes 92 VGPRs and one system per CU; the spills the bound
-// costs lie outside the pair loop)
-template <typename T, int TPL, int WPS>
+// costs lie outside the pair loop).  AHEAD: the pair loop on the table window
+// reads ahead (above 128 points, and up to 128 where no workgroup shares a CU;
+// a build of its own, since both loops in one cost shared CUs 1.7 %)
+template <typename T, int TPL, int WPS, bool AHEAD = (TPL >= 3)>
 __global__ __launch_bounds__(64 * WPS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && TPL <= 2 && WPS == 16
                                                                                  ? 8
                                                                                  : 1))) void
@@ -1076,7 +1120,7 @@ k_forward(Batch b, Run r, const int32_t* order, int32_t* queue, T* obs, T* speed
         __syncthreads();
         if (item >= b.n_sys) break;
         const int s = __builtin_amdgcn_readfirstlane(order[item]);
-        run_system<T, TPL, WPS>(b, r, s, L, obs, speed, status, steps_done, refuse);
+        run_system<T, TPL, WPS, AHEAD>(b, r, s, L, obs, speed, status, steps_done, refuse);
     }
 }
 
@@ -1865,6 +1909,9 @@ static hipError_t fwd_prepare()
     if (lds > attr_lds) {
         hipError_t e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS) && e == hipSuccess)
+            e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS, fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS)>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_lds = lds;
     }
@@ -1878,6 +1925,13 @@ static hipError_t fwd_launch(int nblocks, const Batch& b, const Run& r, const in
     const size_t lds = forward_lds_bytes(sizeof(T) == 4 ? 0 : 1, TPL, WPS);
     hipError_t e = fwd_prepare<T, TPL, WPS>();
     if (e != hipSuccess) return e;
+    if constexpr (fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS)) {
+        if (b.alone) {
+            hipLaunchKernelGGL((k_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), lds, st, b, r, order, q,
+                               (T*)obs, (T*)speed, status, done);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((k_forward<T, TPL, WPS>), dim3(nblocks), dim3(64 * WPS), lds, st, b, r, order, q, (T*)obs,
                        (T*)speed, status, done);
     return hipGetLastError();

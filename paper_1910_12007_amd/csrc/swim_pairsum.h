@@ -119,6 +119,62 @@ __device__ __forceinline__ void tab_load_window(const TabSys* g, unsigned char* 
     }
 }
 
+// The first 32 octaves in finer pieces, in the same 64 KiB: 64 intervals per
+// octave, each with its centre c, a quadratic of Ht and a cubic of H2 in
+// v - c.  The difference is exact and takes one operation where the scaled u
+// takes two, and Ht one product less: 27.5 operations per pair against 29.5.
+// Formed from the table in HBM in FP64 when a system starts (Ht with its low
+// part): the cubics moved to the new centres, Ht's cubic term economized
+// (Chebyshev: y^3 ~ 3/4 s^2 y for |y| <= s, at most 4e-8 of ln v's scale).  An
+// interval's halves lie at byte (bits >> 13) & 0x7FF0 of each; v from 2^32 on would
+// alias, so its user keeps all points within TAB_QUAD_REACH scaled units.  The
+// two halves of an entry lie apart: a read of 16-byte pieces spreads over all
+// banks, with 32-byte entries over half of them (bank conflicts 1.05e6 against
+// 0.49e6 cycles, and no gain: 48 runs 1292 us).  4096 runs of 128 points, 400
+// steps: 10.27 ms against 10.45 on the cubics' window; 1024 runs of 64..512
+// points: 24.7 ms against 26.9 on the whole table.
+struct alignas(16) TabQ {
+    float c, h[3];  // at its offset
+};
+struct alignas(16) TabQ2 {
+    float g[4];     // TAB_QUAD_G bytes on
+};
+constexpr uint32_t TAB_QUAD_G = 32768;
+static_assert(sizeof(TabQ) == 16 && sizeof(TabQ2) == 16 && TAB_M == 4 && TAB_OCT >= 32,
+              "four pieces per interval of the table");
+constexpr float TAB_QUAD_REACH = 23000.0f;  // 1 + 2 (2 * 23000)^2 < 2^32
+__device__ __forceinline__ uint32_t tab_quad_off(uint32_t bits) { return (bits >> 13) & 0x7FF0u; }
+
+__device__ inline void tab_load_quads(const TabSys* g, unsigned char* win, int tid, int nthreads)
+{
+    TabQ* dst = reinterpret_cast<TabQ*>(win);
+    TabQ2* dst2 = reinterpret_cast<TabQ2*>(win + TAB_QUAD_G);
+    for (int k = tid; k < (int)(TAB_QUAD_G / sizeof(TabQ)); k += nthreads) {
+        const int e = ((k >> 6) + 1) & 31, j = k & 63, i = (e << TAB_M) + (j >> 2);
+        const TabE t = g->e[i];
+        const double K = ldexp(1.0, TAB_SHIFT + TAB_M - e);            // du / dv
+        const double u = (double)((2 * (j & 3) + 1) << (TAB_SHIFT - 3));  // u of the centre
+        const double s2 = ldexp(1.0, 2 * (e - 7));                     // half width, squared
+        auto moved = [&](const float (&p)[4], double p0lo, double (&o)[4]) {
+            const double a = p[0] + p0lo, b = p[1], c = p[2], d = p[3];
+            o[0] = fma(fma(fma(d, u, c), u, b), u, a);
+            o[1] = fma(fma(3.0 * d, u, 2.0 * c), u, b) * K;
+            o[2] = fma(3.0 * d, u, c) * K * K;
+            o[3] = d * K * K * K;
+        };
+        double h[4], q[4];
+        moved(t.h, (double)g->h0lo[i], h);
+        moved(t.g, 0.0, q);
+        TabQ o;
+        o.c = ldexpf(1.0f + (float)(2 * j + 1) * (1.0f / 128.0f), e);
+        o.h[0] = (float)h[0];
+        o.h[1] = (float)fma(0.75 * s2, h[3], h[1]);
+        o.h[2] = (float)h[2];
+        dst[k] = o;
+        dst2[k] = TabQ2{{(float)q[0], (float)q[1], (float)q[2], (float)q[3]}};
+    }
+}
+
 // kernel values of one FP64 pair from its system's table in HBM (the
 // entries of one run, some 30 KB, stay in the caches; nine 16-byte loads per
 // pair): zeros and true for a pair beyond the table
@@ -242,13 +298,13 @@ __device__ __forceinline__ int opaque_uniform(int v)
 // at et + (id << 5) bytes, so the bias goes into a wave-uniform base (a
 // register operand of the address arithmetic; gfx9 address arithmetic takes no
 // 32-bit literal).
-template <typename T, bool WRAP> __device__ __forceinline__ const char* tab_base(const void* tab)
+template <typename T, int WRAP> __device__ __forceinline__ const char* tab_base(const void* tab)
 {
     const char* et = reinterpret_cast<const char*>(tab);
     if constexpr (!WRAP && sizeof(T) == 4) et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     return et;
 }
-template <typename T, bool WRAP> __device__ __forceinline__ TabHead tab_base(TabHead tab)
+template <typename T, int WRAP> __device__ __forceinline__ TabHead tab_base(TabHead tab)
 {
     tab.et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     return tab;
@@ -257,13 +313,46 @@ template <typename T, bool WRAP> __device__ __forceinline__ TabHead tab_base(Tab
 // slot of point i in the doubled source array
 __device__ __forceinline__ int src2_slot(int i) { return ((i >> 6) << 7) + (i & 63); }
 
+// the scheduler moves nothing over this point
+__device__ __forceinline__ void reads_stay()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// One pair's entry of the finer pieces (at LDS address 0) on its way: the loads
+// are issued where it is looked up, the kernel functions formed where they are
+// needed
+struct QuadLook {
+    float v;
+    TabQ h;
+    TabQ2 g;
+    __device__ __forceinline__ void fetch(float dx, float dy)
+    {
+        v = fmaf(dx, dx, fmaf(dy, dy, 1.0f));
+#if defined(__HIP_DEVICE_COMPILE__)
+        // (LDS addresses, which only the device pass compiles)
+        const uint32_t at = tab_quad_off(__builtin_bit_cast(uint32_t, v));
+        h = *(const __attribute__((address_space(3))) TabQ*)(uintptr_t)at;
+        g = *(const __attribute__((address_space(3))) TabQ2*)(uintptr_t)(at + TAB_QUAD_G);
+#endif
+    }
+    __device__ __forceinline__ void values(float& Ht, float& H2) const
+    {
+        const float u = v - h.c;
+        Ht = fmaf(fmaf(h.h[2], u, h.h[1]), u, h.h[0]);
+        H2 = fmaf(fmaf(fmaf(g.g[3], u, g.g[2]), u, g.g[1]), u, g.g[0]);
+    }
+};
+
 // kernel functions of one pair at offset (dx, dy) (FP32: positions scaled by
 // rho): the table (FAR = false; a pair beyond it gives zeros and, with CHECK,
 // sets far), or the direct evaluation of pairs beyond the table only (FAR =
 // true; zeros for the others).  H2 comes scaled to the coordinates (H2 / sigma
 // in FP32).  et: FP32 the table in LDS (or its first octaves, a TabHead: FAR
 // then reads the rest of the table in HBM), FP64 in HBM.
-template <typename T, bool FAR, bool CHECK = true, bool WRAP = false, typename Tab>
+template <typename T, bool FAR, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et, T dx, T dy, T& Ht, T& H2,
                                             bool& far)
 {
@@ -286,7 +375,11 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et,
         const uint32_t id = bits >> TAB_SHIFT;
         if constexpr (!FAR) {
             if constexpr (CHECK) far = far || id >= tab_end(et);
-            if constexpr (WRAP) {
+            if constexpr (WRAP >= 2) {
+                QuadLook e;
+                e.fetch(dx, dy);
+                e.values(Ht, H2);
+            } else if constexpr (WRAP == 1) {
                 // the index window at LDS address 0 (tab_load_window): the
                 // entry's address is its offset in the window (an LDS
                 // address, which only the device pass compiles)
@@ -314,7 +407,7 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et,
 
 // offsets [s_lo, s_hi) of block pair (a, b); adds the target sums to block
 // a's and the moving points' sums to block b's accumulators of this lane
-template <typename T, int TPL, bool FAR, bool CHECK = true, bool WRAP = false, typename Tab>
+template <typename T, int TPL, bool FAR, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et, const Src4<T>* src2, int a, int b,
                                             int s_lo, int s_hi, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
@@ -328,10 +421,7 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
     // the pair's 2x2 tensor Ht I + H2 d d^T (5 operations) applied to both
     // ends' forces (8 FMAs): 13 operations against 14 for the two dot
     // products F.d, their scaling by H2 and the four terms of each end
-    auto offset = [&](const Src4<T>& q) {
-        const T dx = ti.x - q.x, dy = ti.y - q.y;
-        T Ht, H2;
-        pair_kernel<T, FAR, CHECK, WRAP>(C, et, dx, dy, Ht, H2, far);
+    auto apply = [&](const Src4<T>& q, T dx, T dy, T Ht, T H2) {
         const T hx = H2 * dx, hy = H2 * dy;
         const T mxx = fma_t(hx, dx, Ht), myy = fma_t(hy, dy, Ht), mxy = hx * dy;
         ax = fma_t(mxx, q.fx, fma_t(mxy, q.fy, ax));
@@ -339,16 +429,64 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
         bx = lane_rot(fma_t(mxx, ti.fx, fma_t(mxy, ti.fy, bx)));
         by = lane_rot(fma_t(mxy, ti.fx, fma_t(myy, ti.fy, by)));
     };
+    auto offset = [&](const Src4<T>& q) {
+        const T dx = ti.x - q.x, dy = ti.y - q.y;
+        T Ht, H2;
+        pair_kernel<T, FAR, CHECK, WRAP>(C, et, dx, dy, Ht, H2, far);
+        apply(q, dx, dy, Ht, H2);
+    };
     int s = __builtin_amdgcn_readfirstlane(s_lo);
-    if constexpr (FAR) {
+    if constexpr (WRAP == 3) {
+        // one offset ahead with the table entry and two with the point, so that
+        // neither LDS read is waited for where it is issued (the last ones lie
+        // past the range, within the workgroup's LDS, and are dropped).  Pays
+        // where a SIMD has two waves, for its eight register moves do not where
+        // it has four: 48 runs of 128 points 1230 us against 1272, 4096 of them
+        // 10.5 ms against 10.25
+        struct Stage {
+            Src4<T> q;
+            T dx, dy;
+            QuadLook e;
+        };
+        auto look = [&](Stage& g) {
+            g.dx = ti.x - g.q.x;
+            g.dy = ti.y - g.q.y;
+            g.e.fetch(g.dx, g.dy);
+        };
+        // the stage's offset; its place goes to the next point
+        auto take = [&](Stage& g, const Src4<T>& next) {
+            T Ht, H2;
+            g.e.values(Ht, H2);
+            apply(g.q, g.dx, g.dy, Ht, H2);
+            g.q = next;
+        };
+        if (s < s_full) {
+            Stage g0, g1;
+            g0.q = sp[s];
+            g1.q = sp[s + 1];
+            look(g0);
+            for (; s + 1 < s_full; s += 2) {
+                look(g1);
+                const Src4<T> n0 = sp[s + 2];
+                reads_stay();
+                take(g0, n0);
+                look(g0);
+                const Src4<T> n1 = sp[s + 3];
+                reads_stay();
+                take(g1, n1);
+            }
+            if (s < s_full) take(g0, g0.q);
+        }
+    } else if constexpr (FAR) {
 #pragma unroll 1
         for (; s < s_full; ++s) offset(sp[s]);
+    } else {
+        for (; s + 1 < s_full; s += 2) {
+            offset(sp[s]);
+            offset(sp[s + 1]);
+        }
+        if (s < s_full) offset(sp[s]);
     }
-    for (; s + 1 < s_full; s += 2) {
-        offset(sp[s]);
-        offset(sp[s + 1]);
-    }
-    if (s < s_full) offset(sp[s]);
     if (s_full < s_hi) {
         // offset 32 within a block: lanes 32..63 repeat lanes 0..31's couples
         const Src4<T> q = sp[32];
@@ -386,8 +524,9 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
 // the partial velocity of point 64c + lane.  CHECK = false: the caller
 // guarantees that no FP32 pair lies beyond the table, which then is read
 // without the per-pair test (an index beyond it reads a zero entry).
-// WRAP: tab points at the table's LDS index window (tab_load_window)
-template <typename T, int TPL, int WPS, bool CHECK = true, bool WRAP = false, typename Tab>
+// WRAP: tab points at the table's LDS index window (1: tab_load_window,
+// 2: tab_load_quads; 3: the same, read ahead)
+template <typename T, int TPL, int WPS, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int n,
                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
@@ -447,7 +586,7 @@ __device__ __forceinline__ bool sym_one_segment(int n, int wave, int& sa, int& s
 
 // pair_phase_sym for a wave whose share is the one segment found by
 // sym_one_segment (same sums, same order)
-template <typename T, int TPL, bool CHECK = true, bool WRAP = false, typename Tab>
+template <typename T, int TPL, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ void pair_phase_seg(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int a,
                                                int b, int s_lo, int s_hi, int lane, T (&accx)[TPL], T (&accy)[TPL])
 {
