@@ -284,7 +284,8 @@ __global__ __launch_bounds__(64) void k_sysconst_batch(const int64_t* sw_off, co
 constexpr int TAB_CHUNK = 21;
 constexpr int TAB_WAVES = (TAB_N + 1 + TAB_CHUNK - 1) / TAB_CHUNK;  // waves per system
 
-__global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const SysConst<double>* sysc64, TabSys* tab)
+__global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const SysConst<double>* sysc64, TabSys* tab,
+                                                    float* g0lo)
 {
     const int64_t w = blockIdx.x;
     const int lane = threadIdx.x;
@@ -309,7 +310,10 @@ __global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const
         tab_interval(sysc64[s], i, tab[s].e[i], &tab[s].h0lo[i]);  // the zero entry
         return;
     }
-    tab_assemble(sysc64[s], h, g, tab[s].e[i], &tab[s].h0lo[i]);
+    TabE e;
+    tab_assemble(sysc64[s], h, g, e, &tab[s].h0lo[i]);
+    tab[s].e[i] = e;
+    if (g0lo) g0lo[TAB_N * s + i] = (float)(sysc64[s].its * g[0] - (double)e.g[0]);
 }
 
 // Kernel tables by the interval sweep (pb_iv_*), one workgroup of TAB_N
@@ -361,7 +365,7 @@ template <bool REVB> __device__ void pb_block_scan2(double& a, double& b, double
 
 template <int K>
 __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const SysConst<double>* __restrict__ sysc64,
-                                                             void* __restrict__ tab)
+                                                             void* __restrict__ tab, float* __restrict__ g0lo)
 {
     __shared__ double s_red[2 * PB_BLOCK / 64];
     __shared__ double s_sh[PB_NSER - 1], s_sg[PB_NSER - 1];
@@ -413,7 +417,10 @@ __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const S
     if constexpr (K == 7) {
         TabSys& T = reinterpret_cast<TabSys*>(tab)[s];
         const double h4[4] = {fh[0], fh[2], fh[4], fh[6]}, g4[4] = {fg[0], fg[2], fg[4], fg[6]};
-        tab_assemble(C, h4, g4, T.e[i], &T.h0lo[i]);
+        TabE e;
+        tab_assemble(C, h4, g4, e, &T.h0lo[i]);
+        T.e[i] = e;
+        if (g0lo) g0lo[TAB_N * s + i] = (float)(C.its * g4[0] - (double)e.g[0]);
         if (i == 0) tab_interval(C, TAB_N, T.e[TAB_N], &T.h0lo[TAB_N]);  // the zero entry
     } else {
         TabE64& e = reinterpret_cast<TabSys64*>(tab)[s].e[i];
@@ -806,7 +813,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     const double dsd = 1.0 / (double)(N - 1);
     constexpr bool WIN = fwd_window(COMP ? 0 : 1, TPL, WPS);
     if constexpr (WIN)
-        tab_load_quads((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
+        tab_load_quads((const TabSys*)b.tab + s, b.tab_g0lo + TAB_N * s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
     else if constexpr (COMP)
         tab_load((const TabSys*)b.tab + s, L.tab, tid, NT);
     const int nwin = (n + FWD_WIN - 1) / FWD_WIN;
@@ -1807,18 +1814,19 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
 
 size_t table_bytes(int dtype) { return dtype == 0 ? sizeof(TabSys) : sizeof(TabSys64); }
 
-hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st)
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, float* g0lo, int blob,
+                              hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     if (dtype == 1)
         hipLaunchKernelGGL(k_table_build_pb<9>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab);
+                           (const SysConst<double>*)sysc64, tab, (float*)nullptr);
     else if (blob == 1)
         hipLaunchKernelGGL(k_table_build_pb<7>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab);
+                           (const SysConst<double>*)sysc64, tab, g0lo);
     else
         hipLaunchKernelGGL(k_table_build, dim3((unsigned)(n * TAB_WAVES)), dim3(64), 0, st, s0, n,
-                           (const SysConst<double>*)sysc64, (TabSys*)tab);
+                           (const SysConst<double>*)sysc64, (TabSys*)tab, g0lo);
     return hipGetLastError();
 }
 

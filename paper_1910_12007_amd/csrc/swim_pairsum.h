@@ -123,10 +123,13 @@ __device__ __forceinline__ void tab_load_window(const TabSys* g, unsigned char* 
 // octave, each with its centre c, a quadratic of Ht and a cubic of H2 in
 // v - c.  The difference is exact and takes one operation where the scaled u
 // takes two, and Ht one product less: 27.5 operations per pair against 29.5.
-// Formed from the table in HBM in FP64 when a system starts (Ht with its low
-// part): the cubics moved to the new centres, Ht's cubic term economized
-// (Chebyshev: y^3 ~ 3/4 s^2 y for |y| <= s, at most 4e-8 of ln v's scale).  An
-// interval's halves lie at byte (bits >> 13) & 0x7FF0 of each; v from 2^32 on would
+// Formed from the table in HBM in FP64 when a system starts (with the low parts
+// of the constant terms, so that these are rounded once): the cubics moved to
+// the new centres, Ht's cubic term economized (Chebyshev: y^3 ~ 3/4 s^2 y for
+// |y| <= s, at most 4e-8 of ln v's scale).  Mean relative errors against FP64 at
+// alpha 0.05..10, N 64..512: Ht 2.9e-8 (cubics 2.9e-8), H2 4.4e-8..8.6e-8
+// (4.5e-8..8.7e-8).  An interval's halves lie at byte (bits >> 13) & 0x7FF0 of
+// each; v from 2^32 on would
 // alias, so its user keeps all points within TAB_QUAD_REACH scaled units.  The
 // two halves of an entry lie apart: a read of 16-byte pieces spreads over all
 // banks, with 32-byte entries over half of them (bank conflicts 1.05e6 against
@@ -145,7 +148,7 @@ static_assert(sizeof(TabQ) == 16 && sizeof(TabQ2) == 16 && TAB_M == 4 && TAB_OCT
 constexpr float TAB_QUAD_REACH = 23000.0f;  // 1 + 2 (2 * 23000)^2 < 2^32
 __device__ __forceinline__ uint32_t tab_quad_off(uint32_t bits) { return (bits >> 13) & 0x7FF0u; }
 
-__device__ inline void tab_load_quads(const TabSys* g, unsigned char* win, int tid, int nthreads)
+__device__ inline void tab_load_quads(const TabSys* g, const float* g0lo, unsigned char* win, int tid, int nthreads)
 {
     TabQ* dst = reinterpret_cast<TabQ*>(win);
     TabQ2* dst2 = reinterpret_cast<TabQ2*>(win + TAB_QUAD_G);
@@ -164,7 +167,7 @@ __device__ inline void tab_load_quads(const TabSys* g, unsigned char* win, int t
         };
         double h[4], q[4];
         moved(t.h, (double)g->h0lo[i], h);
-        moved(t.g, 0.0, q);
+        moved(t.g, (double)g0lo[i], q);
         TabQ o;
         o.c = ldexpf(1.0f + (float)(2 * j + 1) * (1.0f / 128.0f), e);
         o.h[0] = (float)h[0];
