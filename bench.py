@@ -37,36 +37,36 @@ sys.path.insert(0, ROOT)
 # FLOP against the FP32 vector peak of 157.3 TFLOP/s.  Algorithmic work per
 # ordered pair evaluation of eq. (BrV) in its FP32 form: per distinct pair
 # (one evaluation serves both ends, symmetric schedule) the difference
-# vector (2), v = |d|^2 + 1 (2 FMA), the two cubics of the table (6 FMA),
+# vector (2), v = |d|^2 + 1 (2 FMA), the two functions by cubics (6 FMA; the
+# kernel's finer table pieces take a quadratic for one of them),
 # and for each end F.d times H2 (MUL, FMA, MUL) and the two accumulations
 # (4 FMA): 42 FLOP (FMA = 2) per distinct pair, 21 per ordered pair.  The
 # kernel is bound by VALU instruction issue, not FLOP: integer and float
 # operations share the issue slots.  rocprofv3's SQ_INSTS_VALU over the
-# launch gives 17.8 VALU lane-operations per ordered pair evaluation, all
-# work of the step included (the symmetric pair loop alone is 14.75 in the
+# launch gives 16.6 VALU lane-operations per ordered pair evaluation, all
+# work of the step included (the symmetric pair loop alone is 13.75 in the
 # ISA); the issue peak without packed FP32 is 256 CUs x 4 SIMDs x 16 lanes
 # per clock x 2.4 GHz = 39.3e12 lane-operations/s, i.e. 78.6 TFLOP/s of FMA
 # (the build keeps packed FP32 off).
-# (profiles/k_forward_batch_4096x128_counters.md)
-VALU_OPS_PER_PAIR = 17.8
+# (profiles/kernel_counters_and_times.md)
+VALU_OPS_PER_PAIR = 16.6
 PAIR_LOOP_VALU_OPS = 15.75  # the sperm kernel's symmetric pair loop alone (ISA, per ordered pair)
 FP32_FLOP_PER_PAIR = 21
 NONPACKED_FP32_PEAK_TFLOPS = 78.6
 # the FP32 large-system step, k_tile_pairs (every pair once for both points,
-# FP64 accumulation) and k_big_update: 26.2 VALU lane-operations per ordered
-# pair evaluation from SQ_INSTS_VALU
-# (profiles/k_big_pairs_dense_64x8x512_counters.md; the one-sided
-# k_big_step<float, 1> it replaced took 39.9)
-VALU_OPS_PER_PAIR_BIG = 26.2
+# FP64 accumulation) and k_big_update: 25.0 VALU lane-operations per ordered
+# pair evaluation from SQ_INSTS_VALU (profiles/kernel_counters_and_times.md;
+# the one-sided k_big_step<float, 1> it replaced took 39.9)
+VALU_OPS_PER_PAIR_BIG = 25.0
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 FP32_PEAK_TFLOPS = 157.3
 # HBM bytes of one launch of that kernel on this workload, from rocprofv3
-# FETCH_SIZE and WRITE_SIZE (KiB per dispatch: 46324.6 and 2227.1) scaled by
+# FETCH_SIZE and WRITE_SIZE (KiB per dispatch: 48827.0 and 2231.8) scaled by
 # the same counters over a 256 MiB device copy (x2.0 and x1.0), for the
-# kernel as it stands (profiles/k_forward_batch_4096x128_counters.md): almost
-# all of it the 4096 kernel tables (22.5 KiB each) read once into LDS; set
+# kernel as it stands (profiles/kernel_counters_and_times.md): almost all of it
+# the first 32 octaves of the 4096 kernel tables read once into LDS; set
 # it to None whenever the kernel changes until the counters are taken again
-TRAFFIC_BYTES = (46324.6 * 2.00 + 2227.1 * 1.00) * 1024
+TRAFFIC_BYTES = (48827.0 * 2.00 + 2231.8 * 1.00) * 1024
 
 
 def load_data():
