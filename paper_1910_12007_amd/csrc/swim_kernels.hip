@@ -624,7 +624,7 @@ __global__ __launch_bounds__(1024) void k_order_runs(OrderSegs seg, const int32_
 // index window) starts at LDS address 0 and a pair's entry address needs
 // no base
 struct FwdLdsLayout {
-    size_t tab, src, part, bad, total;
+    size_t tab, src, part, bad, trig, total;
 };
 __host__ __device__ constexpr size_t fwd_align16(size_t x) { return (x + 15) & ~(size_t)15; }
 __host__ __device__ constexpr FwdLdsLayout fwd_lds_layout(int dtype, int tpl, int wps)
@@ -635,7 +635,8 @@ __host__ __device__ constexpr FwdLdsLayout fwd_lds_layout(int dtype, int tpl, in
     L.src = dtype == 0 ? fwd_align16(fwd_window(dtype, tpl, wps) ? TAB_WIN_BYTES : sizeof(TabSys)) : 0;
     L.part = fwd_align16(L.src + 2 * nmax * 4 * e);
     L.bad = fwd_align16(L.part + (size_t)wps * nmax * 2 * e);
-    L.total = fwd_align16(L.bad + 4 * ((size_t)wps + 1));  // wave flags, then the queue item
+    L.trig = fwd_align16(L.bad + 4 * ((size_t)wps + 1));  // (after the wave flags and the queue item)
+    L.total = L.trig + (dtype == 0 ? 0 : 2 * (nmax / 3) * 16);
     return L;
 }
 
@@ -688,6 +689,7 @@ template <typename T> struct FwdLds {
     Src4<T>* src;  // [2 NMAX] positions (hi part) and forces, each block of 64 twice
     V2<T>* part;   // [WPS][NMAX] partial velocities
     int* bad;      // [WPS] wave flags: 1 non-finite position, 2 beyond the bound
+    V2<double>* trig;  // FP64: (cos, sin) of omega t per filament, this step's and the next one's
 };
 
 constexpr int FWD_WIN = 60;  // points published per point-phase window
@@ -834,13 +836,14 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     // window state: point i = 60 g + lane - 2 of window g = wave + WPS q
     T xh[OWNW], yh[OWNW], xl[OWNW], yl[OWNW], ss2[OWNW], sb2[OWNW], ka[OWNW], kb[OWNW];
     double rc[OWNW], rs[OWNW], cd[OWNW], sd[OWNW];  // cos, sin of omega t; rotation by omega dt
-    int fl[OWNW];
+    int fl[OWNW], fil[OWNW];
 #pragma unroll
     for (int q = 0; q < OWNW; ++q) {
         const int g = wave + WPS * q;
         const int i = FWD_WIN * g + lane - 2;
         const bool held = g < nwin && i >= 0 && i < n;
         const int m = held ? i / N : 0, p = held ? i - m * N : 0;
+        fil[q] = m;
         const double* P = b.params + 9 * (f0 + m);
         const double X = held ? P[7] + (double)p * dsd : 0.0, Y = held ? P[8] : 0.0;
         xh[q] = (T)X;
@@ -872,6 +875,19 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     const bool early = r.stop_data != nullptr && nsw == 1;
     double ssq = 0.0;
     bool rejected = false;
+    // FP64: a wave without point work evaluates cos and sin of omega t for the
+    // next step while the point waves work on this one (in these they are 0.4 us
+    // of a chain of 3.8); two buffers, by the step's parity
+    const bool helped = !COMP && pw < WPS;
+    auto help = [&](int next) {
+        for (int m = lane; m < nsw; m += 64) {
+            const double wt = b.params[9 * (f0 + m) + 4] * ((double)next * r.dt);
+            V2<double> v;
+            v.x = cos(wt);
+            v.y = sin(wt);
+            L.trig[(next & 1) * nsw + m] = v;
+        }
+    };
     // forces of the held points at the current time; owners publish them
     auto point_forces = [&]() {
 #pragma unroll
@@ -912,6 +928,8 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         for (int q = 0; q < OWNW; ++q) out = out || ((fl[q] & FL_OWN) && outside(xh[q], yh[q]));
         const bool any = __any(out);
         if (lane == 0) L.bad[wave] = any ? 1 : 0;
+    } else if (helped && wave == WPS - 1) {
+        help(1);
     }
     __syncthreads();
     // from now on with all octaves of the table, in the coarser pieces
@@ -1007,6 +1025,10 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                     const double c = rc[q], sn = rs[q];
                     rc[q] = fma(c, cd[q], -sn * sd[q]);
                     rs[q] = fma(sn, cd[q], c * sd[q]);
+                } else if (helped) {
+                    const V2<double> v = L.trig[((step + 1) & 1) * nsw + fil[q]];
+                    rc[q] = v.x;
+                    rs[q] = v.y;
                 } else {
                     const double wt = cd[q] * ((double)(step + 1) * r.dt);
                     rc[q] = cos(wt);
@@ -1020,6 +1042,8 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                 flags = (__any(bad & 1) ? 1 : 0) | (__any(bad & 2) ? 2 : 0) | (__any(bad & 4) ? 4 : 0) |
                         (__any(bad & 8) ? 8 : 0);
             if (lane == 0) L.bad[wave] = flags;
+        } else if (helped && wave == WPS - 1) {
+            help(step + 2);
         }
         __syncthreads();
         // the point waves' flags, one per lane, combined by ballot (uniform)
@@ -1100,6 +1124,7 @@ k_forward(Batch b, Run r, const int32_t* order, int32_t* queue, T* obs, T* speed
     L.src = reinterpret_cast<Src4<T>*>(smem + lay.src);
     L.part = reinterpret_cast<V2<T>*>(smem + lay.part);
     L.bad = reinterpret_cast<int*>(smem + lay.bad);
+    L.trig = reinterpret_cast<V2<double>*>(smem + lay.trig);
     int& s_item = L.bad[WPS];
     // the pair loop of the index-window layout addresses the table from LDS
     // address 0, where the dynamic LDS starts while the kernel declares no
