@@ -627,12 +627,21 @@ struct FwdLdsLayout {
     size_t tab, src, part, bad, trig, total;
 };
 __host__ __device__ constexpr size_t fwd_align16(size_t x) { return (x + 15) & ~(size_t)15; }
-__host__ __device__ constexpr FwdLdsLayout fwd_lds_layout(int dtype, int tpl, int wps)
+// FP64 launch shapes that have a second build with the table in LDS (99 KB of
+// it, so one workgroup per CU), for launches whose workgroups share no CU: from
+// the caches, a pair's nine 16-byte reads are bound by the L1's 64 bytes a clock.
+// 2 runs of 64 points 3.4 -> 2.5 us a step, 4 of 200 points 36 -> 18; the copy
+// is under 2 us, so runs of a few steps keep the caches.
+__host__ __device__ constexpr bool fwd_lds64(int dtype, int tpl, int wps) { return dtype == 1 && tpl <= 4 && wps == 8; }
+constexpr int FWD_LDS64_STEPS = 8;
+__host__ __device__ constexpr FwdLdsLayout fwd_lds_layout(int dtype, int tpl, int wps, bool lds64 = false)
 {
     const size_t e = dtype == 0 ? sizeof(float) : sizeof(double), nmax = 64 * (size_t)tpl;
     FwdLdsLayout L{};
     L.tab = 0;
-    L.src = dtype == 0 ? fwd_align16(fwd_window(dtype, tpl, wps) ? TAB_WIN_BYTES : sizeof(TabSys)) : 0;
+    L.src = dtype == 0 ? fwd_align16(fwd_window(dtype, tpl, wps) ? TAB_WIN_BYTES : sizeof(TabSys))
+            : lds64    ? sizeof(TabSys64)
+                       : 0;
     L.part = fwd_align16(L.src + 2 * nmax * 4 * e);
     L.bad = fwd_align16(L.part + (size_t)wps * nmax * 2 * e);
     L.trig = fwd_align16(L.bad + 4 * ((size_t)wps + 1));  // (after the wave flags and the queue item)
@@ -818,6 +827,12 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         tab_load_quads((const TabSys*)b.tab + s, b.tab_g0lo + TAB_N * s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
     else if constexpr (COMP)
         tab_load((const TabSys*)b.tab + s, L.tab, tid, NT);
+    constexpr bool LDS64 = !COMP && AHEAD;
+    if constexpr (LDS64) {
+        const float4* from = reinterpret_cast<const float4*>((const TabSys64*)b.tab + s);
+#pragma unroll 4
+        for (int i = tid; i < (int)(sizeof(TabSys64) / 16); i += NT) reinterpret_cast<float4*>(L.tab)[i] = from[i];
+    }
     const int nwin = (n + FWD_WIN - 1) / FWD_WIN;
     const int pw = min(WPS, nwin);     // waves with point work
     const bool pwave = wave < pw;      // uniform within a wave
@@ -981,7 +996,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                 else
                     pairs(std::integral_constant<int, AHEAD ? 3 : 2>());
             } else {
-                pairs(std::integral_constant<int, 0>());
+                pairs(std::integral_constant<int, LDS64 ? 4 : 0>());
             }
 #pragma unroll
             for (int c = 0; c < TPL; ++c) {
@@ -1111,7 +1126,8 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
 // costs lie outside the pair loop).  AHEAD: the pair loop on the table window
 // reads ahead (above 128 points, and up to 128 where no workgroup shares a CU;
 // a build of its own, since both loops in one cost shared CUs 1.7 %)
-template <typename T, int TPL, int WPS, bool AHEAD = (TPL >= 3)>
+// FP64: AHEAD builds hold the table in LDS (fwd_lds64).
+template <typename T, int TPL, int WPS, bool AHEAD = (sizeof(T) == 4 && TPL >= 3)>
 __global__ __launch_bounds__(64 * WPS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && TPL <= 2 && WPS == 16
                                                                                  ? 8
                                                                                  : 1))) void
@@ -1119,7 +1135,7 @@ k_forward(Batch b, Run r, const int32_t* order, int32_t* queue, T* obs, T* speed
 {
     extern __shared__ __align__(16) unsigned char smem[];
     FwdLds<T> L;
-    const FwdLdsLayout lay = fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS);
+    const FwdLdsLayout lay = fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS, sizeof(T) == 8 && AHEAD);
     L.tab = reinterpret_cast<TabSys*>(smem + lay.tab);
     L.src = reinterpret_cast<Src4<T>*>(smem + lay.src);
     L.part = reinterpret_cast<V2<T>*>(smem + lay.part);
@@ -1132,7 +1148,7 @@ k_forward(Batch b, Run r, const int32_t* order, int32_t* queue, T* obs, T* speed
     // (status SWIM_ST_BADPARAM, NaN outputs) rather than run on wrong data
     bool refuse = false;
 #if defined(__HIP_DEVICE_COMPILE__)
-    refuse = fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS) &&
+    refuse = (fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS) || (sizeof(T) == 8 && AHEAD)) &&
              (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)smem != 0u;
 #endif
     // Instruction-issue priority of this launch's waves against the other
@@ -1932,6 +1948,12 @@ hipError_t launch_order_runs(int n_seg, const OrderSegs& seg, const int32_t* in,
 
 size_t forward_lds_bytes(int dtype, int tpl, int wps) { return fwd_lds_layout(dtype, tpl, wps).total; }
 
+// shapes with a second build for launches whose workgroups share no CU
+template <typename T> constexpr bool fwd_alone_build(int tpl, int wps)
+{
+    return fwd_window(sizeof(T) == 4 ? 0 : 1, tpl, wps) || fwd_lds64(sizeof(T) == 4 ? 0 : 1, tpl, wps);
+}
+
 // raise the kernel's dynamic-LDS limit to what its launches need (outside
 // any stream capture: a launch inside a capture finds it already set)
 template <typename T, int TPL, int WPS>
@@ -1942,9 +1964,12 @@ static hipError_t fwd_prepare()
     if (lds > attr_lds) {
         hipError_t e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS) && e == hipSuccess)
-            e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS, fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS)>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if constexpr (fwd_alone_build<T>(TPL, WPS)) {
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS, true>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS, sizeof(T) == 8).total);
+        }
         if (e != hipSuccess) return e;
         attr_lds = lds;
     }
@@ -1958,9 +1983,10 @@ static hipError_t fwd_launch(int nblocks, const Batch& b, const Run& r, const in
     const size_t lds = forward_lds_bytes(sizeof(T) == 4 ? 0 : 1, TPL, WPS);
     hipError_t e = fwd_prepare<T, TPL, WPS>();
     if (e != hipSuccess) return e;
-    if constexpr (fwd_window(sizeof(T) == 4 ? 0 : 1, TPL, WPS)) {
-        if (b.alone) {
-            hipLaunchKernelGGL((k_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), lds, st, b, r, order, q,
+    if constexpr (fwd_alone_build<T>(TPL, WPS)) {
+        if (b.alone && (sizeof(T) == 4 || r.steps >= FWD_LDS64_STEPS)) {
+            const size_t own = fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS, sizeof(T) == 8).total;
+            hipLaunchKernelGGL((k_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), own, st, b, r, order, q,
                                (T*)obs, (T*)speed, status, done);
             return hipGetLastError();
         }

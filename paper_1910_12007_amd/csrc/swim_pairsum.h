@@ -181,6 +181,8 @@ __device__ inline void tab_load_quads(const TabSys* g, const float* g0lo, unsign
 // kernel values of one FP64 pair from its system's table in HBM (the
 // entries of one run, some 30 KB, stay in the caches; nine 16-byte loads per
 // pair): zeros and true for a pair beyond the table
+// (LDS: the table lies at LDS address 0 instead)
+template <bool LDS = false>
 __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double ts, double& Ht, double& H2)
 {
     const double v = fma(t, ts, 1.0);
@@ -190,9 +192,15 @@ __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double t
     typedef const __attribute__((address_space(1))) f64x2_t* GlobalD2;
     const GlobalD2 p = (GlobalD2)(uintptr_t)((const char*)tab + (size_t)min(id, (uint32_t)(TAB_N - 1)) * sizeof(TabE64));
     double c[18];
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const __attribute__((address_space(3))) f64x2_t* LdsD2;
+    const LdsD2 pl = (LdsD2)(uintptr_t)(min(id, (uint32_t)(TAB_N - 1)) * (uint32_t)sizeof(TabE64));
+#else
+    const GlobalD2 pl = p;
+#endif
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const f64x2_t w = p[k];
+        const f64x2_t w = LDS ? pl[k] : p[k];
         c[2 * k] = w.x;
         c[2 * k + 1] = w.y;
     }
@@ -362,7 +370,7 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et,
     if constexpr (sizeof(T) == 8) {
         const T t = fma_t(dx, dx, dy * dy);
         if constexpr (!FAR) {
-            const bool f = tab64_lookup(tab_at(et), t, C.ts, Ht, H2);
+            const bool f = tab64_lookup<WRAP == 4>(tab_at(et), t, C.ts, Ht, H2);
             if constexpr (CHECK) far = far || f;
         } else {
             Ht = (T)0;
@@ -528,7 +536,8 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
 // guarantees that no FP32 pair lies beyond the table, which then is read
 // without the per-pair test (an index beyond it reads a zero entry).
 // WRAP: tab points at the table's LDS index window (1: tab_load_window,
-// 2: tab_load_quads; 3: the same, read ahead)
+// 2: tab_load_quads; 3: the same, read ahead; 4: FP64, the table at LDS address
+// 0)
 template <typename T, int TPL, int WPS, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int n,
                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL])
