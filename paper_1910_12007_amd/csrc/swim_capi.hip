@@ -1438,8 +1438,10 @@ int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_spe
     // else its first 24 octaves (distances to 2^12 eps; the rest is read from
     // HBM), for more systems in flight: 12 KB instead of 22, eight one-swimmer
     // systems per CU instead of five
-    r.oct = SPERM_OCT_ALL;
-    int per_cu = sperm_blocks_per_cu(dtype, tpl, wps, g, r.oct);
+    // (FP64: all 99 KB, where no workgroup shares a CU and the run is long enough
+    // for the copy)
+    r.oct = dtype == SWIM_F32 || (sperm_lds64(dtype, tpl, wps) && n_sys <= c->num_cu && steps >= 8) ? SPERM_OCT_ALL : 0;
+    int per_cu = dtype == SWIM_F32 || !r.oct ? sperm_blocks_per_cu(dtype, tpl, wps, g, r.oct) : 1;
     if (dtype == SWIM_F32 && n_sys > (int64_t)per_cu * c->num_cu) {
         r.oct = SPERM_OCT_HEAD;
         per_cu = sperm_blocks_per_cu(dtype, tpl, wps, g, r.oct);

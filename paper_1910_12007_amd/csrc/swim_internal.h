@@ -212,7 +212,7 @@ struct SpermRun {
     const double* sysp;  // [n_sys][SWIM_SP_NPARAM]
     const double* swp;   // [n_sys * nsw][3]: x0, y0, phase
     int32_t steps, obs_every, n_obs;
-    int32_t oct;         // FP32: octaves of the table that a system keeps in LDS
+    int32_t oct;         // octaves of the table that a system keeps in LDS (FP64: all or none)
     double dt;
 };
 hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps, const double* sysp,
@@ -221,6 +221,8 @@ hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps,
 hipError_t prepare_sperm(int dtype, int tpl, int wps);
 // FP32 octaves in LDS: the whole table, or the first
 constexpr int SPERM_OCT_ALL = 44, SPERM_OCT_HEAD = 24;
+// FP64 shapes with a second build that holds the whole table in LDS (SpermRun::oct != 0)
+constexpr bool sperm_lds64(int dtype, int tpl, int wps) { return dtype == 1 && tpl <= 4 && wps == 8; }
 int sperm_blocks_per_cu(int dtype, int tpl, int wps, const SpermShape& g, int oct);
 // persistent run, one workgroup of wps wavefronts per system (tpl in
 // {1,2,3,4,6,8}, wps in {2,4,8})

@@ -181,9 +181,10 @@ __device__ inline void tab_load_quads(const TabSys* g, const float* g0lo, unsign
 // kernel values of one FP64 pair from its system's table in HBM (the
 // entries of one run, some 30 KB, stay in the caches; nine 16-byte loads per
 // pair): zeros and true for a pair beyond the table
-// (LDS: the table lies at LDS address 0 instead)
+// (LDS: the table lies at that LDS address instead)
 template <bool LDS = false>
-__device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double ts, double& Ht, double& H2)
+__device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double ts, double& Ht, double& H2,
+                                             uint32_t at = 0)
 {
     const double v = fma(t, ts, 1.0);
     const uint32_t id = tab64_index(v);
@@ -194,7 +195,7 @@ __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double t
     double c[18];
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef const __attribute__((address_space(3))) f64x2_t* LdsD2;
-    const LdsD2 pl = (LdsD2)(uintptr_t)(min(id, (uint32_t)(TAB_N - 1)) * (uint32_t)sizeof(TabE64));
+    const LdsD2 pl = (LdsD2)(uintptr_t)(at + min(id, (uint32_t)(TAB_N - 1)) * (uint32_t)sizeof(TabE64));
 #else
     const GlobalD2 pl = p;
 #endif
@@ -240,10 +241,22 @@ struct TabHead {
     uint32_t end;
     const TabE* all;
 };
+// a system's FP64 table in LDS, at that LDS address
+struct TabLds64 {
+    uint32_t at;
+};
 constexpr uint32_t tab_end(const char*) { return TAB_END; }
 __device__ __forceinline__ uint32_t tab_end(const TabHead& h) { return h.end; }
 __device__ __forceinline__ const char* tab_at(const char* et) { return et; }
 __device__ __forceinline__ const char* tab_at(const TabHead& h) { return h.et; }
+__device__ __forceinline__ bool tab64_at(const char* et, double t, double ts, double& Ht, double& H2)
+{
+    return tab64_lookup(et, t, ts, Ht, H2);
+}
+__device__ __forceinline__ bool tab64_at(const TabLds64& h, double t, double ts, double& Ht, double& H2)
+{
+    return tab64_lookup<true>(nullptr, t, ts, Ht, H2, h.at);
+}
 
 // copy the first octaves of one system's FP32 table (end - TAB_BIAS entries
 // and a zero entry) from HBM into LDS
@@ -315,6 +328,7 @@ template <typename T, int WRAP> __device__ __forceinline__ const char* tab_base(
     if constexpr (!WRAP && sizeof(T) == 4) et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
     return et;
 }
+template <typename T, int WRAP> __device__ __forceinline__ TabLds64 tab_base(TabLds64 tab) { return tab; }
 template <typename T, int WRAP> __device__ __forceinline__ TabHead tab_base(TabHead tab)
 {
     tab.et += opaque_uniform(-(int)(TAB_BIAS * sizeof(TabE)));
@@ -370,7 +384,11 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et,
     if constexpr (sizeof(T) == 8) {
         const T t = fma_t(dx, dx, dy * dy);
         if constexpr (!FAR) {
-            const bool f = tab64_lookup<WRAP == 4>(tab_at(et), t, C.ts, Ht, H2);
+            bool f;
+            if constexpr (WRAP == 4)
+                f = tab64_lookup<true>(nullptr, t, C.ts, Ht, H2);
+            else
+                f = tab64_at(et, t, C.ts, Ht, H2);
             if constexpr (CHECK) far = far || f;
         } else {
             Ht = (T)0;

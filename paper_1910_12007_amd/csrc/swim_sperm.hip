@@ -255,7 +255,8 @@ struct SpermLdsLayout {
     size_t tab, src, part, pos, bad, total;
 };
 __host__ __device__ constexpr size_t al16(size_t x) { return (x + 15) & ~(size_t)15; }
-// n points of nsw swimmers, the table's first oct octaves (FP32).  The terms of
+// n points of nsw swimmers, the table's first oct octaves (FP64: all or none).
+// The terms of
 // the forces and the partial sums share one region: each is read before the
 // barrier that the other is written behind.
 __host__ __device__ constexpr SpermLdsLayout sperm_lds_layout(int dtype, int wps, int n, int nsw, int oct)
@@ -264,7 +265,7 @@ __host__ __device__ constexpr SpermLdsLayout sperm_lds_layout(int dtype, int wps
     const size_t part = (size_t)wps * n * 2 * e, terms = ((size_t)n * 8 + 20 * (size_t)nsw) * e;
     SpermLdsLayout L{};
     L.tab = 0;
-    L.src = dtype == 0 ? ((size_t)(oct << TAB_M) + 1) * sizeof(TabE) : 0;
+    L.src = dtype == 0 ? ((size_t)(oct << TAB_M) + 1) * sizeof(TabE) : oct ? sizeof(TabSys64) : 0;
     L.part = al16(L.src + 128 * nb * 4 * e);
     L.pos = al16(L.part + (part > terms ? part : terms));
     L.bad = al16(L.pos + (size_t)n * 16);
@@ -292,7 +293,7 @@ __device__ __attribute__((noinline)) void neck_spring(const PosE<T>* p, const Po
     *to = neck_term(d, spring_coef(d, L0, L02, K2));
 }
 
-template <typename T, int TPL, int WPS>
+template <typename T, int TPL, int WPS, bool L64>
 __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, const SysConst<T>& C,
                              const void* tab_g, TabE* tab_s, Src4<T>* src, V2<T>* part, PosE<T>* pos, int* badw,
                              T* head, T* tail, int32_t* status)
@@ -316,12 +317,20 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
         __syncthreads();
         return;
     }
-    // FP32: the table's first octaves copied into LDS; FP64 reads it in place
-    std::conditional_t<COMP, TabHead, const void*> tab;
+    // FP32: the table's first octaves copied into LDS; FP64 reads it in place, or
+    // (L64) copies all of it
+    std::conditional_t<COMP, TabHead, std::conditional_t<L64, TabLds64, const void*>> tab;
     if constexpr (COMP) {
         const TabSys* all = (const TabSys*)tab_g + s;
         tab_load_head(all, tab_s, r.oct << TAB_M, tid, NT);
         tab = TabHead{reinterpret_cast<const char*>(tab_s), TAB_BIAS + ((uint32_t)r.oct << TAB_M), all->e};
+    } else if constexpr (L64) {
+        const float4* from = reinterpret_cast<const float4*>((const TabSys64*)tab_g + s);
+#pragma unroll 4
+        for (int i = tid; i < (int)(sizeof(TabSys64) / 16); i += NT) reinterpret_cast<float4*>(tab_s)[i] = from[i];
+#if defined(__HIP_DEVICE_COMPILE__)
+        tab = TabLds64{(uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)tab_s};
+#endif
     } else {
         tab = (const TabSys64*)tab_g + s;
     }
@@ -598,7 +607,10 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
 // per step against 14.7, 1024 5.6 against 7.8, one system 3.3 against 4.6; 1000
 // of two swimmers 15.7 against 19.1 (above 128 points 128 VGPRs spill, and 168
 // measure 18.8).
-template <typename T, int TPL, int WPS>
+// L64: FP64 with the table in LDS, for launches whose workgroups share no CU
+// (from the caches a pair's nine 16-byte reads are bound by the L1): one system
+// 10.5 -> 7.2 us per step, four of two swimmers 27 -> 12.6.
+template <typename T, int TPL, int WPS, bool L64 = false>
 __global__ __launch_bounds__(64 * WPS, sizeof(T) == 4 && TPL <= 2 ? 4 : 1) void k_sperm_forward(
     SpermShape g, SpermRun r, const SysConst<T>* sysc, const void* tabs, int32_t* queue, T* head, T* tail,
     int32_t* status)
@@ -619,7 +631,7 @@ __global__ __launch_bounds__(64 * WPS, sizeof(T) == 4 && TPL <= 2 ? 4 : 1) void 
         const int item = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
         if (item >= r.n_sys) break;
-        sperm_system<T, TPL, WPS>(g, r, item, sysc[item], tabs, tab, src, part, pos, badw, head, tail, status);
+        sperm_system<T, TPL, WPS, L64>(g, r, item, sysc[item], tabs, tab, src, part, pos, badw, head, tail, status);
     }
 }
 
@@ -716,6 +728,13 @@ hipError_t launch_sperm_t(int nblocks, const SpermShape& g, const SpermRun& r, c
                           int32_t* queue, void* head, void* tail, int32_t* status, hipStream_t st)
 {
     const size_t lds = sperm_lds_bytes(sizeof(T) == 4 ? 0 : 1, WPS, g, r.oct);
+    if constexpr (sperm_lds64(sizeof(T) == 4 ? 0 : 1, TPL, WPS)) {
+        if (r.oct) {
+            hipLaunchKernelGGL((k_sperm_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), lds, st, g, r,
+                               (const SysConst<T>*)sysc, tabs, queue, (T*)head, (T*)tail, status);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((k_sperm_forward<T, TPL, WPS>), dim3(nblocks), dim3(64 * WPS), lds, st, g, r,
                        (const SysConst<T>*)sysc, tabs, queue, (T*)head, (T*)tail, status);
     return hipGetLastError();
@@ -771,7 +790,14 @@ hipError_t prepare_sperm(int dtype, int tpl, int wps)
         const void* k = sperm_kernel_ptr<T, decltype(tp)::value, decltype(wp)::value>();
         // (the most that any call of this instantiation takes: a call must not
         // lower the limit that another thread's launch needs)
-        const size_t most = sperm_lds_layout(dtype, wps, 64 * tpl, 8 * tpl, TAB_OCT).total;
+        const size_t most = sperm_lds_layout(dtype, wps, 64 * tpl, 8 * tpl, dtype == 0 ? TAB_OCT : 0).total;
+        if constexpr (sperm_lds64(sizeof(T) == 4 ? 0 : 1, decltype(tp)::value, decltype(wp)::value)) {
+            const void* k64 =
+                reinterpret_cast<const void*>(&k_sperm_forward<T, decltype(tp)::value, decltype(wp)::value, true>);
+            const hipError_t e = hipFuncSetAttribute(k64, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)sperm_lds_layout(1, wps, 64 * tpl, 8 * tpl, 1).total);
+            if (e != hipSuccess) return e;
+        }
         return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
     });
 }
