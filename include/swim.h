@@ -285,9 +285,11 @@ int swim_elastic_forces(swim_ctx *ctx, int32_t dtype, int64_t n_fil, const int32
  * over workgroups (SWIM_OPT_BIG_TPL).  The buckets and the large systems
  * run side by side on the context's stream and up to three more; with more
  * than four such parts, adjacent buckets closest in size merge (the smaller
- * systems run in the larger bucket's launch) until four remain.  Waves of
- * larger buckets issue at a higher priority where launches share a CU.  FP32 systems whose pairs could lie beyond
- * the FP32 kernel table within the position bound (2829 (N-1) / eps_over_ds
+ * systems run in the larger bucket's launch) until four remain; in a merged
+ * launch that queues, the runs that forward Euler's bound expects to complete
+ * come first.  Waves of larger buckets issue at a higher priority where
+ * launches share a CU.  FP32 systems whose pairs could lie beyond the FP32
+ * kernel table within the position bound (2829 (N-1) / eps_over_ds
  * >= 2^22, i.e. eps_over_ds well below 1.5) take the large-system step at
  * any size, since the persistent kernel does not test for such pairs.
  * Asynchronous. */
