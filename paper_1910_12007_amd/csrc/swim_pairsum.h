@@ -128,8 +128,9 @@ __device__ __forceinline__ void tab_load_window(const TabSys* g, unsigned char* 
 // the new centres, Ht's cubic term economized (Chebyshev: y^3 ~ 3/4 s^2 y for
 // |y| <= s, at most 4e-8 of ln v's scale).  Mean relative errors against FP64 at
 // alpha 0.05..10, N 64..512: Ht 2.9e-8 (cubics 2.9e-8), H2 4.4e-8..8.6e-8
-// (4.5e-8..8.7e-8).  An interval's halves lie at byte (bits >> 13) & 0x7FF0 of
-// each; v from 2^32 on would
+// (4.5e-8..8.7e-8); largest, Ht where it is small, 1.7e-7 (1.3e-7), H2 1.1e-6
+// (1.1e-6); the runs' own errors against FP64 are unchanged.  An interval's
+// halves lie at byte (bits >> 13) & 0x7FF0 of each; v from 2^32 on would
 // alias, so its user keeps all points within TAB_QUAD_REACH scaled units.  The
 // two halves of an entry lie apart: a read of 16-byte pieces spreads over all
 // banks, with 32-byte entries over half of them (bank conflicts 1.05e6 against
