@@ -708,7 +708,8 @@ int abc_prescreened(swim_ctx *ctx, const abc_model *model, int32_t N, const floa
  * follows the FP32 device path: cubic pieces of a per-system table in
  * v = 1 + sigma t (sigma the power of four with sigma eps^2 in [1, 4);
  * 16 pieces per octave, v < 2^44), built from the FP64 evaluation; direct
- * FP32 evaluation beyond.  blob: SWIM_BLOB_READING or SWIM_BLOB_PAPER (as
+ * FP32 evaluation beyond.  SWIM_F64 follows the FP64 one: degree-8 pieces on
+ * the same intervals, direct FP64 evaluation beyond.  blob: SWIM_BLOB_READING or SWIM_BLOB_PAPER (as
  * SWIM_OPT_BLOB); SWIM_EINVAL otherwise. */
 int swim_kernel_eval_host(int32_t dtype, double alpha, double eps, int32_t blob, int64_t n, const double *t,
                           double *h1t, double *h2, double *h1c);

@@ -1772,11 +1772,28 @@ int swim_kernel_eval_host(int32_t dtype, double alpha, double eps, int32_t blob,
         }
         *h1c = C.h1c;
     } else {
+        // the device's FP64 path: the system's table, direct evaluation beyond
         SysConst<double> C;
         sysconst_compute<double>(alpha, eps, &C, blob);
+        std::vector<double> fh(9 * TAB_N), fg(9 * TAB_N);
+        pb_table_host<9>(C, fh.data(), fg.data());
+        std::vector<TabE64> tab(TAB_N);
+        for (int i = 0; i < TAB_N; ++i) {
+            double h9[9], g9[9];
+            for (int k = 0; k < 9; ++k) {
+                h9[k] = fh[9 * i + k];
+                g9[k] = fg[9 * i + k];
+            }
+            tab64_entry(i, h9, g9, tab[i]);
+        }
         for (int64_t i = 0; i < n; ++i) {
             double a, b;
-            kernel_eval<double>(C, t[i], a, b);
+            const double y = t[i] * C.ts, v = 1.0 + y;
+            const uint32_t id = tab64_index(v);
+            if (id < (uint32_t)TAB_N)
+                tab64_eval(tab[id].h, tab[id].g, id, tab64_x(y, v, id), a, b);
+            else
+                kernel_eval<double>(C, t[i], a, b);
             h1t[i] = a;
             h2[i] = b;
         }

@@ -423,14 +423,7 @@ __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const S
         if (g0lo) g0lo[TAB_N * s + i] = (float)(C.its * g4[0] - (double)e.g[0]);
         if (i == 0) tab_interval(C, TAB_N, T.e[TAB_N], &T.h0lo[TAB_N]);  // the zero entry
     } else {
-        TabE64& e = reinterpret_cast<TabSys64*>(tab)[s].e[i];
-        double c[9];
-        tab64_poly(fh, c);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) e.h[k] = c[k];
-        tab64_poly(fg, c);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) e.g[k] = c[k];
+        tab64_entry(i, fh, fg, reinterpret_cast<TabSys64*>(tab)[s].e[i]);
     }
 }
 

@@ -1302,6 +1302,10 @@ SWIM_HD void pb_node_far(double alpha, double eps, double t, double h1c, double&
     fh = Mt - g - h1c;
 }
 
+// sigma t at which the FP64 tables take the first interval's node 0 (t = 0 in
+// the FP32 ones): Ht ~ t there, and the table holds its ratio to t
+constexpr double TAB64_Y0 = 0x1p-100;
+
 // Ht, H2 at the nodes of an interval outside the sweep: the near-contact
 // series below it, the far field beyond; systems without a sweep (alpha = 0,
 // or the reading's blob): the closed forms
@@ -1314,7 +1318,8 @@ SWIM_HD void pb_iv_outside(const SysConst<double>& C, int i, bool sweep, int iS,
     const double alpha = sqrt(C.a2);
 #pragma unroll 1
     for (int k = 0; k < K; k += K == 7 ? 2 : 1) {  // K = 7: the cubic's nodes 0, 1/4, 3/4, 1 alone
-        const double t = fmax((v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, 1e-300);
+        double t = fmax((v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, 1e-300);
+        if (K == 9 && i == 0 && k == 0) t = TAB64_Y0 * C.its;
         double h, g;
         if (!sweep)
             kernel_eval_closed<double>(C, t, h, g);
@@ -1332,10 +1337,16 @@ SWIM_HD void pb_iv_outside(const SysConst<double>& C, int i, bool sweep, int iS,
 }
 
 // FP64 kernel tables: on the same intervals, Ht and H2 as polynomials of
-// degree 8 in x in [-1, 1) through the K = 9 nodes (error ~1e-17 of the
-// function's scale: the singularities lie 33 half-widths away), about one
-// rounding beyond the node values.  Interval and x come exactly from the bits
-// of the double v.
+// degree 8 through the K = 9 nodes (their error is ~1e-17 of the function's
+// scale: the singularities lie 33 half-widths away).  The interval comes from
+// the bits of the double v = 1 + y, y = sigma t (exact, sigma a power of two);
+// the coordinate x in [-1, 1) from y itself, x = (y - (c - 1)) 2^(5 - e) about
+// the interval's centre c (c - 1 and the scaling exact, one rounding): v has
+// lost the low bits of a small t.  The first interval is expanded about t = 0
+// instead, x = 32 y in [0, 2), and holds Ht / x, so that Ht keeps its relative
+// accuracy down to contact.  Against 60 digits, r = 1e-4..0.3 eps, the reading's
+// blob: Ht to 5.4e-16, H2 to 6.6e-16 (direct evaluation 7.1e-16, 6.6e-16; with x
+// from the bits of v and the first interval about its centre 5e-13 at 0.01 eps).
 struct alignas(16) TabE64 {
     double h[9], g[9];
 };
@@ -1368,27 +1379,56 @@ SWIM_HD void tab64_poly(const double (&f)[9], double (&c)[9])
     c[0] += f[4];
 }
 
-// interval of v = 1 + sigma t (>= TAB_N: beyond the table, NaN included) and
-// the coordinate x in [-1, 1) on it
+// the entry of interval i from its node values
+SWIM_HD void tab64_entry(int i, double (&fh)[9], double (&fg)[9], TabE64& out)
+{
+    double c[9];
+    if (i == 0) {
+        // Ht / x; node 0 lies at y = TAB64_Y0 (pb_iv_outside)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) fh[k] /= k == 0 ? 32.0 * TAB64_Y0 : 2.0 * LOB9_XI[k];
+    }
+    auto put = [&](const double (&f)[9], double (&o)[9]) {
+        tab64_poly(f, c);
+        if (i == 0) {  // about the interval's start: x -> x + 1 (Horner's shift)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int k = 7; k >= j; --k) c[k] -= c[k + 1];
+            c[0] = f[0];
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) o[k] = c[k];
+    };
+    put(fh, out.h);
+    put(fg, out.g);
+}
+
+// interval of v = 1 + y (>= TAB_N: beyond the table, NaN included)
 SWIM_HD uint32_t tab64_index(double v)
 {
     return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32 >> (20 - TAB_M)) - (1023u << TAB_M);
 }
-SWIM_HD double tab64_x(double v)
+// the coordinate of y on interval id, that of v = 1 + y
+SWIM_HD double tab64_x(double y, double v, uint32_t id)
 {
-    const uint64_t m = (__builtin_bit_cast(uint64_t, v) << TAB_M) & 0x000FFFFFFFFFFFFFull;
-    return fma(2.0, __builtin_bit_cast(double, m | 0x3FF0000000000000ull), -3.0);
+    const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32);
+    const uint32_t mid = id == 0 ? 0u : 1u << (19 - TAB_M);
+    const double c = __builtin_bit_cast(double, (uint64_t)((hi & ~((1u << (20 - TAB_M)) - 1u)) | mid) << 32);
+    const double s = __builtin_bit_cast(double, (uint64_t)(((2047u + TAB_M) << 20) - (hi & 0x7FF00000u)) << 32);
+    return (y - (c - 1.0)) * s;
 }
-SWIM_HD void tab64_eval(const TabE64& e, double x, double& Ht, double& H2)
+// Ht and H2 by the polynomials h and g at x on interval id
+SWIM_HD void tab64_eval(const double* h, const double* g, uint32_t id, double x, double& Ht, double& H2)
 {
-    double h = e.h[8], g = e.g[8];
+    double a = h[8], b = g[8];
 #pragma unroll
     for (int k = 7; k >= 0; --k) {
-        h = fma(h, x, e.h[k]);
-        g = fma(g, x, e.g[k]);
+        a = fma(a, x, h[k]);
+        b = fma(b, x, g[k]);
     }
-    Ht = h;
-    H2 = g;
+    Ht = id == 0 ? a * x : a;
+    H2 = b;
 }
 
 // Host form of the sweep (the device kernel splits the same intervals over a

@@ -187,7 +187,7 @@ template <bool LDS = false>
 __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double ts, double& Ht, double& H2,
                                              uint32_t at = 0)
 {
-    const double v = fma(t, ts, 1.0);
+    const double y = t * ts, v = 1.0 + y;
     const uint32_t id = tab64_index(v);
     const bool far = id >= (uint32_t)TAB_N;
     typedef double f64x2_t __attribute__((ext_vector_type(2)));
@@ -206,13 +206,8 @@ __device__ __forceinline__ bool tab64_lookup(const void* tab, double t, double t
         c[2 * k] = w.x;
         c[2 * k + 1] = w.y;
     }
-    const double x = tab64_x(v);
-    double h = c[8], g = c[17];
-#pragma unroll
-    for (int k = 7; k >= 0; --k) {
-        h = fma(h, x, c[k]);
-        g = fma(g, x, c[9 + k]);
-    }
+    double h, g;
+    tab64_eval(c, c + 9, id, tab64_x(y, v, id), h, g);
     Ht = far ? 0.0 : h;
     H2 = far ? 0.0 : g;
     return far;
