@@ -407,7 +407,7 @@ __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const S
             tab_span(R.iS, v0, hv);
             const double t0 = (v0 - 1.0) * C.its;
             pb_series_eval(s_sh, s_sg, t0 * C.inv_e2, h0, g0);
-            pb_iv_values<K>(C, i, D + (-2.0 * h0 - t0 * g0), I2 + t0 * t0 * g0, fa, fb, fh, fg);
+            pb_iv_values<K>(C, i, D + (-2.0 * h0 - t0 * g0), I2 + t0 * (t0 * g0), fa, fb, fh, fg);
         } else {
             pb_iv_outside<K>(C, i, true, iS, s_sh, s_sg, fh, fg);
         }

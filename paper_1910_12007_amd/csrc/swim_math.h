@@ -1153,11 +1153,13 @@ SWIM_HD void pb_iv_nodes(const SysConst<double>& C, double alpha, int i, double 
 {
     double v0, hv;
     tab_span(i, v0, hv);
-    const double w = 0.25 * hv * C.its * (1.5 / PI) * C.eps * C.e2;
+    const double w = 0.25 * hv * C.its * (1.5 / PI);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const double t = fmax((v0 - 1.0 + hv * lob_xi<K>(k)) * C.its, 1e-300);
-        const double rR = rsqrt_nr(t + C.e2), rR2 = rR * rR, f = w * (rR2 * rR2 * rR);
+        // (products of (eps/R)^3 and dt/R^2: powers of a length would overflow
+        // from eps = 1e-61 on)
+        const double rR = rsqrt_nr(t + C.e2), y = C.eps * rR, f = (w * rR) * rR * (y * y * y);
         const double z = alpha * (t * rsqrt_nr(t));
         double I0, zI1, K0, zK1;
         pb_bessel<WITHK, K == 7 ? 14 : 27>(z, I0, zI1, K0, zK1);
@@ -1292,7 +1294,7 @@ SWIM_HD void pb_node_far(double alpha, double eps, double t, double h1c, double&
     const double e2 = eps * eps, R2 = t + e2, rR = rsqrt_nr(R2), rR2 = rR * rR, ra2 = rcp_nr(alpha * alpha);
     const double w = ra2 * rR2, y = e2 * rR2;
     const PbFar F = w < 1e-5 ? pb_far_sums<5>(w, y) : pb_far_sums<PB_NA>(w, y);
-    const double pre = (1.5 / PI) * e2 * eps * ra2 * (rR2 * rR2 * rR);
+    const double yR = eps * rR, pre = (1.5 / PI) * w * (yR * yR * yR);
     const double g = -pre * F.sg;
     const double rg = -pre * (t * rR2) * F.sr;
     const double m = 1.0 - y * (eps * rR);
@@ -1468,7 +1470,7 @@ template <int K> inline void pb_table_host(const SysConst<double>& C, double* fh
                 tab_span(i, v0, hv);
                 const double t0 = (v0 - 1.0) * C.its;
                 pb_series_eval(S.sh, S.sg, t0 * C.inv_e2, h0, g0);
-                I2 = t0 * t0 * g0;
+                I2 = t0 * (t0 * g0);
                 D = -2.0 * h0 - t0 * g0;
             }
             const double ta = lob_total<K>(iv[i].fa);

@@ -69,3 +69,15 @@ def test_zero_distance():
             assert h[0] == 0.0 and np.all(np.isfinite(h)) and np.all(np.isfinite(g))
             # Ht is proportional to t, H2 constant
             assert abs(h[2] / h[1] / 1e270 - 1) < 1e-12 and g[0] == g[1] and abs(g[2] / g[0] - 1) < 1e-12
+
+
+@pytest.mark.parametrize("alpha", [2.0, 80.0])
+@pytest.mark.parametrize("e", [-250, -200, 200, 250])
+def test_scale_invariance(alpha, e):
+    """The paper blob's values depend on alpha eps and r / eps alone (H2 times a
+    length squared): in units 2^e times as long, every operation scales exactly."""
+    eps, s = 0.0125, 2.0 ** e
+    t = (np.geomspace(1e-3, 1e9, 60) * eps) ** 2
+    h0, g0, _ = swim.swim_kernel_eval_host(swim.SWIM_F64, alpha, eps, t, blob=swim.SWIM_BLOB_PAPER)
+    h, g, _ = swim.swim_kernel_eval_host(swim.SWIM_F64, alpha / s, eps * s, t * s * s, blob=swim.SWIM_BLOB_PAPER)
+    assert np.array_equal(h, h0) and np.array_equal(g * s * s, g0)
