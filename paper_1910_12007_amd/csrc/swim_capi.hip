@@ -415,10 +415,9 @@ int sysconst_buffers(swim_ctx* c, int32_t dtype, int64_t n_sys, void** sysc, voi
 }
 
 // the systems' kernel tables from their FP64 constants (an FP64 run's own)
-hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, void* sysc64, void* tab, hipStream_t st,
-                        float* g0lo = nullptr)
+hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, void* sysc64, void* tab, hipStream_t st)
 {
-    return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, g0lo, c->opt_blob, st);
+    return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, c->opt_blob, st);
 }
 
 // FP64 calls keep one kernel table of 99 KB per system in HBM: larger
@@ -563,9 +562,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     TRY(ensure(c, B_QUEUE, 8 * 4));
-    TRY(ensure(c, B_TAB, (size_t)n_sys * (table_bytes(dtype) + (dtype == SWIM_F32 ? TAB_N * sizeof(float) : 0))));
-    float* g0lo = dtype == SWIM_F32 ? (float*)((char*)c->buf[B_TAB].p + (size_t)n_sys * table_bytes(dtype)) : nullptr;
-    b.tab_g0lo = g0lo;
+    TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     b.n_sys = n_sys;
     b.params = params_dev;
     b.sysc = sysc;
@@ -693,7 +690,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     auto launch_all = [&]() -> hipError_t {
         hipError_t e = launch_sysconst_batch(dtype, n_sys, b.sw_off, b.npt, params_dev, run.eps_over_ds, sysc, sysc64,
                                              status, c->opt_blob, st);
-        if (e == hipSuccess) e = build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st, g0lo);
+        if (e == hipSuccess) e = build_tables(c, dtype, n_sys, sysc, sysc64, c->buf[B_TAB].p, st);
         if (e == hipSuccess) e = launch_fill_i32((int32_t*)c->buf[B_QUEUE].p, 0, 8, st);
         if (e == hipSuccess)
             e = launch_order_runs(n_seg, seg, order_dev, b.sw_off, b.npt, params_dev, run.dt, queue_dev, st);

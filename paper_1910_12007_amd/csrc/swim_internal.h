@@ -24,7 +24,6 @@ struct Batch {
     const void* sysc;        // SysConst<T>[n_sys]
     const void* sysc64;      // SysConst<double>[n_sys] (FP32 runs: builds the kernel tables)
     const void* tab;         // kernel tables: TabSys[n_sys] (FP32), TabSys64[n_sys] (FP64)
-    const float* tab_g0lo;   // FP32: TAB_N per system, H2 at its intervals' starts minus the tables' FP32 values
     int32_t alone;           // persistent runs: no more workgroups than compute units
 };
 
@@ -59,9 +58,7 @@ hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int6
 // bytes of one system's kernel table (TabSys, TabSys64)
 size_t table_bytes(int dtype);
 // kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s]
-// (g0lo, if not null: what Batch::tab_g0lo holds)
-hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, float* g0lo, int blob,
-                              hipStream_t st);
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st);
 hipError_t launch_forces(int dtype, int64_t n_fil, const int64_t* fil_off, const int32_t* npt,
                          const double* params, double t, const void* x, const void* y, void* fx,
                          void* fy, hipStream_t st);

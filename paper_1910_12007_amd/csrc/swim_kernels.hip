@@ -284,8 +284,7 @@ __global__ __launch_bounds__(64) void k_sysconst_batch(const int64_t* sw_off, co
 constexpr int TAB_CHUNK = 21;
 constexpr int TAB_WAVES = (TAB_N + 1 + TAB_CHUNK - 1) / TAB_CHUNK;  // waves per system
 
-__global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const SysConst<double>* sysc64, TabSys* tab,
-                                                    float* g0lo)
+__global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const SysConst<double>* sysc64, TabSys* tab)
 {
     const int64_t w = blockIdx.x;
     const int lane = threadIdx.x;
@@ -313,7 +312,6 @@ __global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const
     TabE e;
     tab_assemble(sysc64[s], h, g, e, &tab[s].h0lo[i]);
     tab[s].e[i] = e;
-    if (g0lo) g0lo[TAB_N * s + i] = (float)(sysc64[s].its * g[0] - (double)e.g[0]);
 }
 
 // Kernel tables by the interval sweep (pb_iv_*), one workgroup of TAB_N
@@ -365,7 +363,7 @@ template <bool REVB> __device__ void pb_block_scan2(double& a, double& b, double
 
 template <int K>
 __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const SysConst<double>* __restrict__ sysc64,
-                                                             void* __restrict__ tab, float* __restrict__ g0lo)
+                                                             void* __restrict__ tab)
 {
     __shared__ double s_red[2 * PB_BLOCK / 64];
     __shared__ double s_sh[PB_NSER - 1], s_sg[PB_NSER - 1];
@@ -420,7 +418,6 @@ __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const S
         TabE e;
         tab_assemble(C, h4, g4, e, &T.h0lo[i]);
         T.e[i] = e;
-        if (g0lo) g0lo[TAB_N * s + i] = (float)(C.its * g4[0] - (double)e.g[0]);
         if (i == 0) tab_interval(C, TAB_N, T.e[TAB_N], &T.h0lo[TAB_N]);  // the zero entry
     } else {
         tab64_entry(i, fh, fg, reinterpret_cast<TabSys64*>(tab)[s].e[i]);
@@ -549,11 +546,10 @@ __global__ void k_forces(int64_t n_fil, const int64_t* fil_off, const int32_t* n
 }
 
 
-// FP32 launch shapes whose table is held as a 64 KiB LDS window, in finer
-// pieces while all points lie within their reach (four operations less per
-// pair than the whole table with its clamped index): those that run at most
-// two systems per CU (eight waves up to 128 points) or one (16 waves above)
-// anyway, where the windows and the rest of the layout fit the LDS
+// FP32 launch shapes whose table is held as the 64 KiB LDS index window (an
+// address without a bias and a clamp, two operations less per pair): those that
+// run at most two systems per CU (eight waves up to 128 points) or one (16 waves
+// above) anyway, where the windows and the rest of the layout fit the LDS
 __host__ __device__ constexpr bool fwd_window(int dtype, int tpl, int wps)
 {
     return dtype == 0 && ((tpl <= 2 && wps == 8) || (tpl >= 3 && wps == 16));
@@ -817,7 +813,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     const double dsd = 1.0 / (double)(N - 1);
     constexpr bool WIN = fwd_window(COMP ? 0 : 1, TPL, WPS);
     if constexpr (WIN)
-        tab_load_quads((const TabSys*)b.tab + s, b.tab_g0lo + TAB_N * s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
+        tab_load_window((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
     else if constexpr (COMP)
         tab_load((const TabSys*)b.tab + s, L.tab, tid, NT);
     constexpr bool LDS64 = !COMP && AHEAD;
@@ -834,12 +830,6 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
     // the pair phase of FP32 runs works on positions scaled by the table's
     // rho (an exact power of two); registers keep the unscaled state
     const T rho = COMP ? C.tr : (T)1;
-    // positions beyond which a step needs a look: the run bound, or, while the
-    // finer pieces of the table serve, their reach
-    T bound = (T)1e3;
-    bool wide = !WIN;  // the table window holds all octaves
-    if constexpr (WIN) bound = fminf(1e3f, TAB_QUAD_REACH / rho);
-    auto outside = [&](T x, T y) { return !(fabs(x) <= bound) || !(fabs(y) <= bound); };
 
     // window state: point i = 60 g + lane - 2 of window g = wave + WPS q
     T xh[OWNW], yh[OWNW], xl[OWNW], yl[OWNW], ss2[OWNW], sb2[OWNW], ka[OWNW], kb[OWNW];
@@ -929,28 +919,11 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         L.src[slot] = v;
         L.src[slot + 64] = v;
     }
-    if (pwave) {
+    if (pwave)
         point_forces();
-        bool out = false;
-#pragma unroll
-        for (int q = 0; q < OWNW; ++q) out = out || ((fl[q] & FL_OWN) && outside(xh[q], yh[q]));
-        const bool any = __any(out);
-        if (lane == 0) L.bad[wave] = any ? 1 : 0;
-    } else if (helped && wave == WPS - 1) {
+    else if (helped && wave == WPS - 1)
         help(1);
-    }
     __syncthreads();
-    // from now on with all octaves of the table, in the coarser pieces
-    auto widen = [&]() {
-        wide = true;
-        bound = (T)1e3;
-        __syncthreads();  // (nobody reads the finer pieces any more)
-        tab_load_window((const TabSys*)b.tab + s, reinterpret_cast<unsigned char*>(L.tab), tid, NT);
-        __syncthreads();
-    };
-    if constexpr (WIN) {
-        if (__any(lane < pw ? L.bad[lane] : 0)) widen();
-    }
     int st = 0, done = r.steps;
     const int nblk64 = (n + 63) >> 6;
     // this wave's share of the pair schedule when it is one segment
@@ -976,21 +949,11 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
             // (FP64 reads its table from HBM and tests every pair)
             T ax[TPL], ay[TPL];
             const void* tab = COMP ? (const void*)L.tab : (const void*)((const TabSys64*)b.tab + s);
-            auto pairs = [&](auto mode) {
-                constexpr int W = decltype(mode)::value;
-                if (one_seg)
-                    pair_phase_seg<T, TPL, !COMP, W>(C, tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
-                else
-                    pair_phase_sym<T, TPL, WPS, !COMP, W>(C, tab, L.src, n, wave, lane, ax, ay);
-            };
-            if constexpr (WIN) {
-                if (wide)
-                    pairs(std::integral_constant<int, 1>());
-                else
-                    pairs(std::integral_constant<int, AHEAD ? 3 : 2>());
-            } else {
-                pairs(std::integral_constant<int, LDS64 ? 4 : 0>());
-            }
+            constexpr int W = WIN ? (AHEAD ? 2 : 1) : LDS64 ? 4 : 0;
+            if (one_seg)
+                pair_phase_seg<T, TPL, !COMP, W>(C, tab, L.src, seg_a, seg_b, seg_lo, seg_hi, lane, ax, ay);
+            else
+                pair_phase_sym<T, TPL, WPS, !COMP, W>(C, tab, L.src, n, wave, lane, ax, ay);
 #pragma unroll
             for (int c = 0; c < TPL; ++c) {
                 if (c < nblk64) {
@@ -1026,8 +989,8 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
                         xh[q] = fma_t(dt, ux, xh[q]);
                         yh[q] = fma_t(dt, uy, yh[q]);
                     }
-                    if ((fl[q] & FL_OWN) && outside(xh[q], yh[q]))
-                        bad |= !(isfinite(xh[q]) && isfinite(yh[q])) ? 1 : bad_t(xh[q]) || bad_t(yh[q]) ? 2 : 8;
+                    if ((fl[q] & FL_OWN) && (bad_t(xh[q]) || bad_t(yh[q])))
+                        bad |= isfinite(xh[q]) && isfinite(yh[q]) ? 2 : 1;
                 }
                 if constexpr (COMP) {
                     const double c = rc[q], sn = rs[q];
@@ -1047,8 +1010,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
             bad |= rejected ? 4 : 0;
             int flags = 0;
             if (__any(bad))
-                flags = (__any(bad & 1) ? 1 : 0) | (__any(bad & 2) ? 2 : 0) | (__any(bad & 4) ? 4 : 0) |
-                        (__any(bad & 8) ? 8 : 0);
+                flags = (__any(bad & 1) ? 1 : 0) | (__any(bad & 2) ? 2 : 0) | (__any(bad & 4) ? 4 : 0);
             if (lane == 0) L.bad[wave] = flags;
         } else if (helped && wave == WPS - 1) {
             help(step + 2);
@@ -1057,12 +1019,9 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
         // the point waves' flags, one per lane, combined by ballot (uniform)
         const int bw = lane < pw ? L.bad[lane] : 0;
         if (__any(bw)) {
-            if (__any(bw & 7)) {
-                st = __any(bw & 1) ? 1 : __any(bw & 2) ? 2 : SWIM_ST_REJECTED_;
-                done = step + 1;
-                break;
-            }
-            if constexpr (WIN) widen();
+            st = __any(bw & 1) ? 1 : __any(bw & 2) ? 2 : SWIM_ST_REJECTED_;
+            done = step + 1;
+            break;
         }
         if (r.obs_every > 0 && --obs_left == 0) {
             obs_left = r.obs_every;
@@ -1116,11 +1075,12 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
 // VGPRs (8 waves per SIMD): two systems then share a CU, so that one's
 // barriers and LDS latency overlap the other's pair phase (without the
 // bound the build takes 92 VGPRs and one system per CU; the spills the bound
-// costs lie outside the pair loop).  AHEAD: the pair loop on the table window
-// reads ahead (above 128 points, and up to 128 where no workgroup shares a CU;
-// a build of its own, since both loops in one cost shared CUs 1.7 %)
-// FP64: AHEAD builds hold the table in LDS (fwd_lds64).
-template <typename T, int TPL, int WPS, bool AHEAD = (sizeof(T) == 4 && TPL >= 3)>
+// costs lie outside the pair loop).  AHEAD: FP32, the pair loop on the table
+// window reads ahead, up to 128 points where no workgroup shares a CU (a build of
+// its own: 48 runs of 128 points 1251 us against 1287, but 4096 of them 11.07 ms
+// against 10.45; above 128 points, 16 waves, it gives nothing: 600 runs of 512
+// points, 200 steps, 15.4 against 15.1 ms); FP64, the table in LDS (fwd_lds64).
+template <typename T, int TPL, int WPS, bool AHEAD = false>
 __global__ __launch_bounds__(64 * WPS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && TPL <= 2 && WPS == 16
                                                                                  ? 8
                                                                                  : 1))) void
@@ -1848,19 +1808,18 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
 
 size_t table_bytes(int dtype) { return dtype == 0 ? sizeof(TabSys) : sizeof(TabSys64); }
 
-hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, float* g0lo, int blob,
-                              hipStream_t st)
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     if (dtype == 1)
         hipLaunchKernelGGL(k_table_build_pb<9>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab, (float*)nullptr);
+                           (const SysConst<double>*)sysc64, tab);
     else if (blob == 1)
         hipLaunchKernelGGL(k_table_build_pb<7>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab, g0lo);
+                           (const SysConst<double>*)sysc64, tab);
     else
         hipLaunchKernelGGL(k_table_build, dim3((unsigned)(n * TAB_WAVES)), dim3(64), 0, st, s0, n,
-                           (const SysConst<double>*)sysc64, (TabSys*)tab, g0lo);
+                           (const SysConst<double>*)sysc64, (TabSys*)tab);
     return hipGetLastError();
 }
 
@@ -1941,10 +1900,10 @@ hipError_t launch_order_runs(int n_seg, const OrderSegs& seg, const int32_t* in,
 
 size_t forward_lds_bytes(int dtype, int tpl, int wps) { return fwd_lds_layout(dtype, tpl, wps).total; }
 
-// shapes with a second build for launches whose workgroups share no CU
-template <typename T> constexpr bool fwd_alone_build(int tpl, int wps)
+// shapes with a second build: FP32 reading ahead, FP64 with the table in LDS
+template <typename T> constexpr bool fwd_second_build(int tpl, int wps)
 {
-    return fwd_window(sizeof(T) == 4 ? 0 : 1, tpl, wps) || fwd_lds64(sizeof(T) == 4 ? 0 : 1, tpl, wps);
+    return sizeof(T) == 4 ? tpl <= 2 && fwd_window(0, tpl, wps) : fwd_lds64(1, tpl, wps);
 }
 
 // raise the kernel's dynamic-LDS limit to what its launches need (outside
@@ -1957,7 +1916,7 @@ static hipError_t fwd_prepare()
     if (lds > attr_lds) {
         hipError_t e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if constexpr (fwd_alone_build<T>(TPL, WPS)) {
+        if constexpr (fwd_second_build<T>(TPL, WPS)) {
             if (e == hipSuccess)
                 e = hipFuncSetAttribute((const void*)k_forward<T, TPL, WPS, true>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1976,7 +1935,7 @@ static hipError_t fwd_launch(int nblocks, const Batch& b, const Run& r, const in
     const size_t lds = forward_lds_bytes(sizeof(T) == 4 ? 0 : 1, TPL, WPS);
     hipError_t e = fwd_prepare<T, TPL, WPS>();
     if (e != hipSuccess) return e;
-    if constexpr (fwd_alone_build<T>(TPL, WPS)) {
+    if constexpr (fwd_second_build<T>(TPL, WPS)) {
         if (b.alone && (sizeof(T) == 4 || r.steps >= FWD_LDS64_STEPS)) {
             const size_t own = fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS, sizeof(T) == 8).total;
             hipLaunchKernelGGL((k_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), own, st, b, r, order, q,

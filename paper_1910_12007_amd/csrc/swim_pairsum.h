@@ -93,89 +93,32 @@ __device__ __forceinline__ void tab_load(const TabSys* g, TabSys* tab, int tid, 
 }
 
 // The FP32 table as a 64 KiB index window: the entry of index id (the bits
-// of v >> TAB_SHIFT, TAB_BIAS for v = 1) sits at byte (id << 5) mod 2^16,
-// so the address of a pair's entry is (bits >> (TAB_SHIFT - 5)) & 0xFFE0:
-// two operations, no bias and no clamp.  Entries 16.. of the table fill
-// bytes [0, 32 (TAB_N - 16)), entries 0..15 (v in [1, 2)) the top 512
-// bytes, and every other slot is zero: the indices of finite v beyond the
-// table (TAB_END .. 4079) land on zeros, as the zero entry TAB_N does for a
-// clamped index.  Non-finite v (4080..4095) alias entries 0..15; their
-// positions are non-finite already and end the run.
-constexpr uint32_t TAB_WIN_BYTES = 65536;
+// of v >> TAB_SHIFT, TAB_BIAS for v = 1) sits at byte (id << 4) mod 2^15, Ht's
+// coefficients there and H2's TAB_WIN_G bytes on, so the address of a pair's
+// entry is (bits >> (TAB_SHIFT - 4)) & 0x7FF0: two operations, no bias and no
+// clamp.  Entries 16.. of the table fill slots 0 .. TAB_N - 17, entries 0..15
+// (v in [1, 2)) the last 16 slots, and every other slot is zero: the indices of
+// finite v beyond the table (TAB_END .. 4079) land on zeros, as the zero entry
+// TAB_N does for a clamped index.  Non-finite v (4080..4095) alias entries
+// 0..15; their positions are non-finite already and end the run.  The two halves
+// of an entry lie apart: a read of 16-byte pieces spreads over all banks, with
+// 32-byte entries over half of them.
+constexpr uint32_t TAB_WIN_BYTES = 65536, TAB_WIN_G = TAB_WIN_BYTES / 2;
 static_assert(TAB_M == 4 && sizeof(TabE) == 32 && TAB_BIAS == 2032 && TAB_END <= 4080,
               "the index window holds 2048 entries of v's octaves 0..127");
-__device__ __forceinline__ uint32_t tab_win_off(uint32_t bits) { return (bits >> (TAB_SHIFT - 5)) & 0xFFE0u; }
+__device__ __forceinline__ uint32_t tab_win_off(uint32_t bits) { return (bits >> (TAB_SHIFT - 4)) & 0x7FF0u; }
 
 // copy one system's FP32 kernel table from HBM into its LDS index window
 __device__ __forceinline__ void tab_load_window(const TabSys* g, unsigned char* win, int tid, int nthreads)
 {
     const float4* src = reinterpret_cast<const float4*>(g->e);
     float4* dst = reinterpret_cast<float4*>(win);
-    constexpr int NV = (int)(TAB_WIN_BYTES / sizeof(float4)), EV = (int)(sizeof(TabE) / sizeof(float4));
-    for (int i = tid; i < NV; i += nthreads) {
-        // slot id mod 2048 holds entry id - TAB_BIAS
-        const int ent = (i / EV - (int)TAB_BIAS) & 2047;
-        dst[i] = ent < TAB_N ? src[ent * EV + (i % EV)] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-}
-
-// The first 32 octaves in finer pieces, in the same 64 KiB: 64 intervals per
-// octave, each with its centre c, a quadratic of Ht and a cubic of H2 in
-// v - c.  The difference is exact and takes one operation where the scaled u
-// takes two, and Ht one product less: 27.5 operations per pair against 29.5.
-// Formed from the table in HBM in FP64 when a system starts (with the low parts
-// of the constant terms, so that these are rounded once): the cubics moved to
-// the new centres, Ht's cubic term economized (Chebyshev: y^3 ~ 3/4 s^2 y for
-// |y| <= s, at most 4e-8 of ln v's scale).  Mean relative errors against FP64 at
-// alpha 0.05..10, N 64..512: Ht 2.9e-8 (cubics 2.9e-8), H2 4.4e-8..8.6e-8
-// (4.5e-8..8.7e-8); largest, Ht where it is small, 1.7e-7 (1.3e-7), H2 1.1e-6
-// (1.1e-6); the runs' own errors against FP64 are unchanged.  An interval's
-// halves lie at byte (bits >> 13) & 0x7FF0 of each; v from 2^32 on would
-// alias, so its user keeps all points within TAB_QUAD_REACH scaled units.  The
-// two halves of an entry lie apart: a read of 16-byte pieces spreads over all
-// banks, with 32-byte entries over half of them (bank conflicts 1.05e6 against
-// 0.49e6 cycles, and no gain: 48 runs 1292 us).  4096 runs of 128 points, 400
-// steps: 10.27 ms against 10.45 on the cubics' window; 1024 runs of 64..512
-// points: 24.7 ms against 26.9 on the whole table.
-struct alignas(16) TabQ {
-    float c, h[3];  // at its offset
-};
-struct alignas(16) TabQ2 {
-    float g[4];     // TAB_QUAD_G bytes on
-};
-constexpr uint32_t TAB_QUAD_G = 32768;
-static_assert(sizeof(TabQ) == 16 && sizeof(TabQ2) == 16 && TAB_M == 4 && TAB_OCT >= 32,
-              "four pieces per interval of the table");
-constexpr float TAB_QUAD_REACH = 23000.0f;  // 1 + 2 (2 * 23000)^2 < 2^32
-__device__ __forceinline__ uint32_t tab_quad_off(uint32_t bits) { return (bits >> 13) & 0x7FF0u; }
-
-__device__ inline void tab_load_quads(const TabSys* g, const float* g0lo, unsigned char* win, int tid, int nthreads)
-{
-    TabQ* dst = reinterpret_cast<TabQ*>(win);
-    TabQ2* dst2 = reinterpret_cast<TabQ2*>(win + TAB_QUAD_G);
-    for (int k = tid; k < (int)(TAB_QUAD_G / sizeof(TabQ)); k += nthreads) {
-        const int e = ((k >> 6) + 1) & 31, j = k & 63, i = (e << TAB_M) + (j >> 2);
-        const TabE t = g->e[i];
-        const double K = ldexp(1.0, TAB_SHIFT + TAB_M - e);            // du / dv
-        const double u = (double)((2 * (j & 3) + 1) << (TAB_SHIFT - 3));  // u of the centre
-        const double s2 = ldexp(1.0, 2 * (e - 7));                     // half width, squared
-        auto moved = [&](const float (&p)[4], double p0lo, double (&o)[4]) {
-            const double a = p[0] + p0lo, b = p[1], c = p[2], d = p[3];
-            o[0] = fma(fma(fma(d, u, c), u, b), u, a);
-            o[1] = fma(fma(3.0 * d, u, 2.0 * c), u, b) * K;
-            o[2] = fma(3.0 * d, u, c) * K * K;
-            o[3] = d * K * K * K;
-        };
-        double h[4], q[4];
-        moved(t.h, (double)g->h0lo[i], h);
-        moved(t.g, (double)g0lo[i], q);
-        TabQ o;
-        o.c = ldexpf(1.0f + (float)(2 * j + 1) * (1.0f / 128.0f), e);
-        o.h[0] = (float)h[0];
-        o.h[1] = (float)fma(0.75 * s2, h[3], h[1]);
-        o.h[2] = (float)h[2];
-        dst[k] = o;
-        dst2[k] = TabQ2{{(float)q[0], (float)q[1], (float)q[2], (float)q[3]}};
+    constexpr int HV = (int)(TAB_WIN_G / sizeof(float4)), EV = (int)(sizeof(TabE) / sizeof(float4));
+    static_assert(EV == 2, "an entry is two pieces");
+    for (int i = tid; i < EV * HV; i += nthreads) {
+        // slot id mod 2048 holds entry id - TAB_BIAS; pieces in the table's order
+        const int slot = i / EV, half = i % EV, ent = (slot - (int)TAB_BIAS) & 2047;
+        dst[half * HV + slot] = ent < TAB_N ? src[ent * EV + half] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
@@ -342,29 +285,31 @@ __device__ __forceinline__ void reads_stay()
 #endif
 }
 
-// One pair's entry of the finer pieces (at LDS address 0) on its way: the loads
+// One pair's entry of the index window (at LDS address 0) on its way: the loads
 // are issued where it is looked up, the kernel functions formed where they are
 // needed
-struct QuadLook {
-    float v;
-    TabQ h;
-    TabQ2 g;
+struct WinLook {
+    uint32_t bits;
+    TabE e;
     __device__ __forceinline__ void fetch(float dx, float dy)
     {
-        v = fmaf(dx, dx, fmaf(dy, dy, 1.0f));
+        bits = __builtin_bit_cast(uint32_t, fmaf(dx, dx, fmaf(dy, dy, 1.0f)));
 #if defined(__HIP_DEVICE_COMPILE__)
         // (LDS addresses, which only the device pass compiles)
-        const uint32_t at = tab_quad_off(__builtin_bit_cast(uint32_t, v));
-        h = *(const __attribute__((address_space(3))) TabQ*)(uintptr_t)at;
-        g = *(const __attribute__((address_space(3))) TabQ2*)(uintptr_t)(at + TAB_QUAD_G);
+        struct alignas(16) Half {
+            float c[4];
+        };
+        typedef const __attribute__((address_space(3))) Half* LdsHalf;
+        const uint32_t at = tab_win_off(bits);
+        const Half h = *(LdsHalf)(uintptr_t)at, g = *(LdsHalf)(uintptr_t)(at + TAB_WIN_G);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            e.h[k] = h.c[k];
+            e.g[k] = g.c[k];
+        }
 #endif
     }
-    __device__ __forceinline__ void values(float& Ht, float& H2) const
-    {
-        const float u = v - h.c;
-        Ht = fmaf(fmaf(h.h[2], u, h.h[1]), u, h.h[0]);
-        H2 = fmaf(fmaf(fmaf(g.g[3], u, g.g[2]), u, g.g[1]), u, g.g[0]);
-    }
+    __device__ __forceinline__ void values(float& Ht, float& H2) const { tab_eval(e, tab_u(bits), Ht, H2); }
 };
 
 // kernel functions of one pair at offset (dx, dy) (FP32: positions scaled by
@@ -400,19 +345,10 @@ __device__ __forceinline__ void pair_kernel(const SysConst<T>& C, const Tab& et,
         const uint32_t id = bits >> TAB_SHIFT;
         if constexpr (!FAR) {
             if constexpr (CHECK) far = far || id >= tab_end(et);
-            if constexpr (WRAP >= 2) {
-                QuadLook e;
+            if constexpr (WRAP != 0) {
+                WinLook e;
                 e.fetch(dx, dy);
                 e.values(Ht, H2);
-            } else if constexpr (WRAP == 1) {
-                // the index window at LDS address 0 (tab_load_window): the
-                // entry's address is its offset in the window (an LDS
-                // address, which only the device pass compiles)
-#if defined(__HIP_DEVICE_COMPILE__)
-                typedef const __attribute__((address_space(3))) TabE* LdsTabE;
-                const TabE e = *(LdsTabE)(uintptr_t)tab_win_off(bits);
-                tab_eval(e, tab_u(bits), Ht, H2);
-#endif
             } else {
                 tab_eval(*reinterpret_cast<const TabE*>(tab_at(et) + (min(id, tab_end(et)) << 5)), tab_u(bits), Ht, H2);
             }
@@ -461,17 +397,16 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
         apply(q, dx, dy, Ht, H2);
     };
     int s = __builtin_amdgcn_readfirstlane(s_lo);
-    if constexpr (WRAP == 3) {
+    if constexpr (WRAP == 2) {
         // one offset ahead with the table entry and two with the point, so that
         // neither LDS read is waited for where it is issued (the last ones lie
         // past the range, within the workgroup's LDS, and are dropped).  Pays
-        // where a SIMD has two waves, for its eight register moves do not where
-        // it has four: 48 runs of 128 points 1230 us against 1272, 4096 of them
-        // 10.5 ms against 10.25
+        // where a SIMD has two waves; its eight register moves do not where it
+        // has four
         struct Stage {
             Src4<T> q;
             T dx, dy;
-            QuadLook e;
+            WinLook e;
         };
         auto look = [&](Stage& g) {
             g.dx = ti.x - g.q.x;
@@ -549,9 +484,8 @@ __device__ __forceinline__ bool sym_offsets(const SysConst<T>& C, const Tab& et,
 // the partial velocity of point 64c + lane.  CHECK = false: the caller
 // guarantees that no FP32 pair lies beyond the table, which then is read
 // without the per-pair test (an index beyond it reads a zero entry).
-// WRAP: tab points at the table's LDS index window (1: tab_load_window,
-// 2: tab_load_quads; 3: the same, read ahead; 4: FP64, the table at LDS address
-// 0)
+// WRAP: the table at LDS address 0: 1: FP32, its index window (tab_load_window);
+// 2: the same, read ahead; 4: FP64
 template <typename T, int TPL, int WPS, bool CHECK = true, int WRAP = 0, typename Tab>
 __device__ __forceinline__ void pair_phase_sym(const SysConst<T>& C, const Tab& tab, const Src4<T>* src2, int n,
                                                int wave, int lane, T (&accx)[TPL], T (&accy)[TPL])
