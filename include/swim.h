@@ -203,6 +203,8 @@ int swim_tune_load(swim_ctx *ctx, const char *path);
  *          alpha*eps <= 1 (Brinkman length longer than the blob).
  * x,y,fx,fy device dtype[sys_off[n_sys]]: positions and point forces (SoA).
  * ux,uy    device dtype[sys_off[n_sys]]: velocities (written).
+ * A system's result, to the bit, depends on its own points, alpha and eps
+ * alone, not on the other systems of the call.
  * Errors: SWIM_EINVAL for a bad layout or parameter.  Asynchronous. */
 int swim_pair_velocity(swim_ctx *ctx, int32_t dtype, int64_t n_sys, const int64_t *sys_off,
                        const double *alpha, const double *eps, const void *x, const void *y,
@@ -210,15 +212,18 @@ int swim_pair_velocity(swim_ctx *ctx, int32_t dtype, int64_t n_sys, const int64_
 
 /* swim_pair_velocity for callers that cannot allocate memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same arguments, kernels and results, with the call's
- * workspace (system offsets, alpha, eps, block list, per-system constants
- * and FP32 kernel tables) in a fixed device array of the library instead of
+ * hipMalloc): the same arguments and, to the bit, the same results, with the
+ * call's workspace (system offsets, alpha, eps, per-system constants and
+ * kernel tables) in a fixed device array of the library instead of
  * context allocations, and its few host values copied from the stack by one
- * synchronous copy on the stream (no pinned staging).  It calls no
+ * synchronous copy on the stream (no pinned staging).  FP32 systems of 512
+ * points and more are summed one-sided, without the partial-sum buffer that
+ * lets swim_pair_velocity evaluate their pairs once for both ends.  It calls no
  * hipMalloc, hipFree or other allocating routine.
- * Limits: n_sys <= 64 systems and at most 4160 pair-kernel blocks (256
- * targets each: about 1M points in all); beyond either, SWIM_EINVAL with a
- * message and nothing launched.  Each GPU holds one copy of the array
+ * Limits: n_sys <= 64 systems and at most 4160 blocks of 256 targets (of 512
+ * where a system has 2048 points or more), counted per system: about 1M
+ * points in all; beyond either, SWIM_EINVAL with a message and nothing
+ * launched.  Each GPU holds one copy of the array
  * (about 6.6 MB, kept until the process ends; its address is taken by
  * swim_create for the context's device, else SWIM_ESTATE).  Every call on
  * a GPU uses that GPU's one array: calls that overlap on one GPU (several

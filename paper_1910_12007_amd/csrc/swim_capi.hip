@@ -84,18 +84,19 @@ int64_t mlp_offb(int l) { return mlp_offW(l) + (int64_t)MLP_W[l] * MLP_W[l + 1];
 
 // Workspace of swim_pair_velocity_noalloc: a fixed device array in place of
 // the context's allocations.  Sections (256-byte aligned): system offsets,
-// alpha, eps, the first workgroup of each system, the
+// alpha, eps, the first workgroup of each system in either kernel, the
 // per-system constants (in the working type and in FP64) and the kernel
 // tables.  Every section is written by the call before its kernels read it,
 // so nothing needs clearing between calls.
 constexpr int64_t NOALLOC_MAX_SYS = 64;      // systems per call
-constexpr int64_t NOALLOC_MAX_BLOCKS = 4160; // blocks of 256 targets per call
+constexpr int64_t NOALLOC_MAX_BLOCKS = 4160; // blocks of 256 or 512 targets per call
 constexpr size_t na_align(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t NA_OFF = 0;
 constexpr size_t NA_ALPHA = na_align(NA_OFF + (NOALLOC_MAX_SYS + 1) * 8);
 constexpr size_t NA_EPS = na_align(NA_ALPHA + NOALLOC_MAX_SYS * 8);
-constexpr size_t NA_BLK = na_align(NA_EPS + NOALLOC_MAX_SYS * 8);
-constexpr size_t NA_SYSC = na_align(NA_BLK + (NOALLOC_MAX_SYS + 1) * 8);  // end of the staged host data
+constexpr size_t NA_BLK0 = na_align(NA_EPS + NOALLOC_MAX_SYS * 8);
+constexpr size_t NA_BLK1 = na_align(NA_BLK0 + (NOALLOC_MAX_SYS + 1) * 8);
+constexpr size_t NA_SYSC = na_align(NA_BLK1 + (NOALLOC_MAX_SYS + 1) * 8);  // end of the staged host data
 constexpr size_t NA_SYSC64 = na_align(NA_SYSC + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
 constexpr size_t NA_TAB = na_align(NA_SYSC64 + NOALLOC_MAX_SYS * sizeof(SysConst<double>));
 constexpr size_t NA_BYTES = na_align(NA_TAB + NOALLOC_MAX_SYS * sizeof(TabSys64));  // ~6.6 MB (FP32 tables share it)
@@ -420,6 +421,8 @@ hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, v
     return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, c->opt_blob, st);
 }
 
+// FP32 calls run in chunks of this many systems (6.5 GB of tables)
+constexpr int64_t FWD_CHUNK = 262144;
 // FP64 calls keep one kernel table of 99 KB per system in HBM: larger
 // batches run in chunks of this many systems (1.6 GB), fewer when the
 // allocation fails, so that tables never decide whether a call fits
@@ -433,6 +436,17 @@ int64_t tab64_chunk(swim_ctx* c, int64_t n_sys)
     }
     return m;
 }
+
+// first 64-target workgroup of each system whose kernel takes it (a prefix)
+template <typename F> void block_prefix(int64_t n_sys, const int64_t* sys_off, int64_t* blk0, F takes)
+{
+    blk0[0] = 0;
+    for (int64_t s = 0; s < n_sys; ++s)
+        blk0[s + 1] = blk0[s] + (takes(s) ? (sys_off[s + 1] - sys_off[s] + 63) / 64 : 0);
+}
+// systems that sum in the tile pairs' order (whichever kernel takes them): by
+// their own size alone, so that a system's bits depend on nothing else
+bool ordered_sum(int32_t dtype, int64_t n) { return dtype == SWIM_F32 && n >= ORDERED_MIN; }
 
 // The tile-pair path's layout of the systems added to it (host), and its upload
 struct TilePlan {
@@ -831,7 +845,6 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
 // so very large batches run in chunks of FWD_CHUNK (FP64: tab64_chunk)
 // systems; the systems are independent and their order within a batch does
 // not change any result.
-constexpr int64_t FWD_CHUNK = 262144;
 
 int forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim,
                  const double* params_dev, const Run& run, void* obs, void* speed, int32_t* status,
@@ -1061,11 +1074,13 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
 {
     // FP32 systems take the tile-pair path (every pair once, two launches)
     // from 1024 points on, and from 512 on in calls of 2^24 pairs and more;
-    // below, the one-sided kernel's single launch is as short or shorter.
-    // Whole calls, one-sided against tile pairs: 1 x 256 points 49 and 56 us,
+    // other systems from 512 points on the same sums one-sided, bit for bit
+    // (k_ordered_velocity), smaller ones the plain one-sided kernel, whose single
+    // launch is as short or shorter.
+    // Whole calls, plain one-sided against tile pairs: 1 x 256 points 49 and 56 us,
     // 1 x 512 55 and 58, 64 x 512 69 and 70, 512 x 512 240 and 192, 1 x 1024
     // 65 and 58, 1 x 4096 128 and 72, 16 x 4096 330 and 222.  Systems whose
-    // partial sums would pass 1 GiB in all stay one-sided.
+    // partial sums would pass 1 GiB in all, or find no memory, stay one-sided.
     double pairs = 0.0;
     for (int64_t s = 0; s < n_sys; ++s) pairs += (double)(sys_off[s + 1] - sys_off[s]) * (double)(sys_off[s + 1] - sys_off[s]);
     TilePlan plan;
@@ -1074,29 +1089,42 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
         for (int64_t s = 0; s < n_sys; ++s) {
             const int64_t n = sys_off[s + 1] - sys_off[s];
             const double nt = std::ceil((double)n / BIG_TILE_POINTS), bytes = nt * nt * BIG_TILE_POINTS * 16.0;
-            if (n < (pairs >= 16777216.0 ? 512 : 1024) || part + bytes > 1073741824.0) continue;
+            if (n < (pairs >= 16777216.0 ? ORDERED_MIN : 1024) || part + bytes > 1073741824.0) continue;
             part += bytes;
             plan.add(s, sys_off[s], (int32_t)n);
         }
     }
     plan.finish();
-    if (plan.slots && ensure(c, B_BT_PART, plan.bytes()) == SWIM_ENOMEM) {
-        (void)hipGetLastError();
-        plan = TilePlan();
+    if (plan.slots) {
+        const int rc = ensure(c, B_BT_PART, plan.bytes());
+        if (rc == SWIM_ENOMEM) {
+            (void)hipGetLastError();
+            plan = TilePlan();
+        } else if (rc != SWIM_OK) {
+            return rc;
+        }
     }
-    std::vector<int64_t> blk0(n_sys + 1, 0);
-    size_t q = 0;  // next system of the plan
-    for (int64_t s = 0; s < n_sys; ++s) {
-        const bool tiled = q < plan.list.size() && plan.list[q] == s;
-        q += tiled ? 1 : 0;
-        blk0[s + 1] = blk0[s] + (tiled ? 0 : (sys_off[s + 1] - sys_off[s] + 63) / 64);
+    auto size = [&](int64_t s) { return sys_off[s + 1] - sys_off[s]; };
+    std::vector<int64_t> blk0(n_sys + 1), blk1;
+    block_prefix(n_sys, sys_off, blk0.data(), [&](int64_t s) { return !ordered_sum(dtype, size(s)); });
+    int64_t n_ordered = 0;
+    for (int64_t s = 0; s < n_sys; ++s) n_ordered += ordered_sum(dtype, size(s)) ? 1 : 0;
+    if (n_ordered > (int64_t)plan.list.size()) {  // some of them without tile pairs
+        blk1.resize(n_sys + 1);
+        size_t q = 0;  // next system of the plan
+        block_prefix(n_sys, sys_off, blk1.data(), [&](int64_t s) {
+            const bool tiled = q < plan.list.size() && plan.list[q] == s;
+            q += tiled ? 1 : 0;
+            return ordered_sum(dtype, size(s)) && !tiled;
+        });
     }
-    TRY(begin_uploads(c, 4 * (n_sys + 1) * 8 + plan.upload_bytes()));
-    const int64_t *off_dev, *blk_dev;
+    TRY(begin_uploads(c, 5 * (n_sys + 1) * 8 + plan.upload_bytes()));
+    const int64_t *off_dev, *blk0_dev, *blk1_dev;
     const double *alpha_dev, *eps_dev;
     BigTiles bt{};
     TRY(put(c, sys_off, n_sys + 1, &off_dev));
-    TRY(put(c, blk0.data(), n_sys + 1, &blk_dev));
+    TRY(put(c, blk0.data(), n_sys + 1, &blk0_dev));
+    TRY(put(c, blk1.data(), blk1.size(), &blk1_dev));
     TRY(put(c, alpha, n_sys, &alpha_dev));
     TRY(put(c, eps, n_sys, &eps_dev));
     TRY(plan.upload(c, &bt));
@@ -1108,7 +1136,8 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
     void* tab = c->buf[B_TAB].p;
     HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
-    HIPCHK(launch_pair_velocity(dtype, n_sys, blk0[n_sys], blk_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
+    HIPCHK(launch_pair_velocity(dtype, n_sys, blk0[n_sys], blk0_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
+    HIPCHK(launch_ordered_velocity(n_sys, blk1.empty() ? 0 : blk1[n_sys], blk1_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
     HIPCHK(launch_tile_velocity(bt, sysc, tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
 }
@@ -1132,13 +1161,14 @@ int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t*
     const int64_t npts = sys_off[n_sys];
     if (npts > 0 && (!x || !y || !fx || !fy || !ux || !uy)) return fail(SWIM_EINVAL, "null data pointer");
     hipStream_t st = pick(c, stream);
-    const int64_t chunk = dtype == SWIM_F32 ? n_sys : tab64_chunk(c, n_sys);
+    // (chunks: the tables' memory, and the launches' limit of 2^32 threads)
+    const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
     if (n_sys <= chunk) return pair_velocity_chunk(c, dtype, n_sys, sys_off, alpha, eps, x, y, fx, fy, ux, uy, st);
     std::vector<int64_t> off(chunk + 1);
     for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
         const int64_t m = std::min(chunk, n_sys - s0);
         for (int64_t s = 0; s <= m; ++s) off[s] = sys_off[s0 + s] - sys_off[s0];
-        const size_t o = (size_t)sys_off[s0] * 8;
+        const size_t o = (size_t)sys_off[s0] * (dtype == SWIM_F32 ? 4 : 8);
         TRY(pair_velocity_chunk(c, dtype, m, off.data(), alpha + s0, eps + s0, (const char*)x + o, (const char*)y + o,
                                 (const char*)fx + o, (const char*)fy + o, (char*)ux + o, (char*)uy + o, st));
     }
@@ -1169,13 +1199,14 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     if (c->device >= NOALLOC_MAX_DEV || !g_scratch_dev[c->device])
         return fail(SWIM_ESTATE, "no workspace address for device %d", c->device);
     char* ws = (char*)g_scratch_dev[c->device];
+    // the size limit of the interface, in blocks of 256 (512) targets
     int64_t maxn = 0;
     for (int64_t s = 0; s < n_sys; ++s) maxn = std::max(maxn, sys_off[s + 1] - sys_off[s]);
     const int tpl = maxn >= 2048 ? 2 : 1;
     int64_t nb = 0;
     for (int64_t s = 0; s < n_sys; ++s) nb += (sys_off[s + 1] - sys_off[s] + 256 * tpl - 1) / (256 * tpl);
     if (nb > NOALLOC_MAX_BLOCKS)
-        return fail(SWIM_EINVAL, "%lld pair-kernel blocks exceed the no-allocation workspace (%lld)", (long long)nb,
+        return fail(SWIM_EINVAL, "%lld blocks of targets exceed the no-allocation workspace's limit (%lld)", (long long)nb,
                     (long long)NOALLOC_MAX_BLOCKS);
     // the host data of the call, laid out as in the workspace, on the stack;
     // one synchronous copy on the stream (no pinned staging buffer)
@@ -1183,10 +1214,12 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     memcpy(host + NA_OFF, sys_off, (size_t)(n_sys + 1) * 8);
     memcpy(host + NA_ALPHA, alpha, (size_t)n_sys * 8);
     memcpy(host + NA_EPS, eps, (size_t)n_sys * 8);
-    int64_t* blk0 = (int64_t*)(host + NA_BLK);
-    blk0[0] = 0;
-    for (int64_t s = 0; s < n_sys; ++s) blk0[s + 1] = blk0[s] + (sys_off[s + 1] - sys_off[s] + 63) / 64;
-    const int64_t n_wg = blk0[n_sys];
+    // the sums of swim_pair_velocity, bit for bit, by kernels without scratch memory
+    auto size = [&](int64_t s) { return sys_off[s + 1] - sys_off[s]; };
+    int64_t *blk0 = (int64_t*)(host + NA_BLK0), *blk1 = (int64_t*)(host + NA_BLK1);
+    block_prefix(n_sys, sys_off, blk0, [&](int64_t s) { return !ordered_sum(dtype, size(s)); });
+    block_prefix(n_sys, sys_off, blk1, [&](int64_t s) { return ordered_sum(dtype, size(s)); });
+    const int64_t n_plain = blk0[n_sys], n_ordered = blk1[n_sys];
     hipStream_t st = pick(c, stream);
     HIPCHK(hipMemcpyWithStream(ws, host, NA_SYSC, hipMemcpyHostToDevice, st));
     void* sysc = ws + NA_SYSC;
@@ -1195,8 +1228,11 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
                            c->opt_blob, st));
     void* tab = ws + NA_TAB;
     HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
-    HIPCHK(launch_pair_velocity(dtype, n_sys, n_wg, (const int64_t*)(ws + NA_BLK), (const int64_t*)(ws + NA_OFF), sysc,
-                                tab, x, y, fx, fy, ux, uy, st));
+    const int64_t* off = (const int64_t*)(ws + NA_OFF);
+    HIPCHK(launch_pair_velocity(dtype, n_sys, n_plain, (const int64_t*)(ws + NA_BLK0), off, sysc, tab, x, y, fx, fy, ux,
+                                uy, st));
+    HIPCHK(launch_ordered_velocity(n_sys, n_ordered, (const int64_t*)(ws + NA_BLK1), off, sysc, tab, x, y, fx, fy, ux,
+                                   uy, st));
     return SWIM_OK;
 }
 

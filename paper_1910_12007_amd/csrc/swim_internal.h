@@ -55,6 +55,12 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
 hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* pt_off,
                                 const void* sysc, const void* tab, const void* x, const void* y, const void* fx,
                                 const void* fy, void* ux, void* uy, hipStream_t st);
+// FP32 systems of ORDERED_MIN points and more, one-sided, with the bits of the
+// tile pairs (launch_tile_velocity)
+constexpr int ORDERED_MIN = 512;
+hipError_t launch_ordered_velocity(int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* pt_off,
+                                   const void* sysc, const void* tab, const void* x, const void* y, const void* fx,
+                                   const void* fy, void* ux, void* uy, hipStream_t st);
 // bytes of one system's kernel table (TabSys, TabSys64)
 size_t table_bytes(int dtype);
 // kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s]

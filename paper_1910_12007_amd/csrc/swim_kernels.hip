@@ -1544,6 +1544,128 @@ __global__ __launch_bounds__(256) void k_tile_velocity(BigTiles bt, const SysCon
     uy[p0 + i] = (float)fma(h1c, red[1][0] + red[1][1] + red[1][2] + red[1][3], v);
 }
 
+// The tile-pair path's sums without its partial-sum buffer, bit for bit: for
+// callers that cannot allocate it (swim_pair_velocity_noalloc) and systems below
+// its size.  One-sided: a workgroup takes a block of 64 targets, one per lane,
+// and its eight waves each a block of sources at a time, in the lane schedule and
+// with the code of the block pair it is there, target block (of the lower tile)
+// or moving one; the blocks' sums join by tile in k_tile_pairs' order, the tiles
+// in k_tile_velocity's.  Bound by VALU issue; every pair is evaluated for each of
+// its ends: 4 x 4096 points 141 us a call against 105 with the buffer.
+// blk0[s]: first workgroup of system s.
+struct OrderedLds {
+    TabSys tab;
+    Src4<float> own[128], src[VEL_WAVES][128];  // each block twice
+    V2<double> part[VEL_WAVES][64], diag[64];
+    double red[2][4];
+};
+__global__ __launch_bounds__(64 * VEL_WAVES) void k_ordered_velocity(int64_t n_sys, const int64_t* blk0,
+                                                                     const int64_t* pt_off,
+                                                                     const SysConst<float>* sysc, const TabSys* tabs,
+                                                                     const float* x, const float* y, const float* fx,
+                                                                     const float* fy, float* ux, float* uy)
+{
+    __shared__ __align__(16) unsigned char smem[sizeof(OrderedLds)];
+    OrderedLds& L = *reinterpret_cast<OrderedLds*>(smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s = prefix_item(blk0, n_sys, blockIdx.x);
+    const int64_t p0 = pt_off[s];
+    const int n = (int)(pt_off[s + 1] - p0), nt = (n + BT - 1) / BT;
+    const int A = (int)((int64_t)blockIdx.x - blk0[s]), tA = A >> 1;  // this workgroup's block, its tile
+    const SysConst<float>& C = sysc[s];
+    tab_load(tabs + s, &L.tab, tid, 64 * VEL_WAVES);
+    // point 64 k + lane; beyond n: at point n - 1, no force
+    auto point = [&](int k) {
+        const int i = 64 * k + lane;
+        const int64_t j = p0 + min(i, n - 1);
+        Src4<float> v;
+        v.x = x[j];
+        v.y = y[j];
+        v.fx = i < n ? fx[j] : 0.0f;
+        v.fy = i < n ? fy[j] : 0.0f;
+        return v;
+    };
+    const Src4<float> own = point(A);
+    if (w == 0) L.own[lane] = L.own[lane + 64] = own;
+    if (w < 4) {  // the forces' sum as in k_tile_velocity
+        double sfx = 0.0, sfy = 0.0;
+        for (int j = tid; j < n; j += 256) {
+            sfx += fx[p0 + j];
+            sfy += fy[p0 + j];
+        }
+        sfx = wave_sum(sfx);
+        sfy = wave_sum(sfy);
+        if (lane == 0) {
+            L.red[0][w] = sfx;
+            L.red[1][w] = sfy;
+        }
+    }
+    double u = 0.0, v = 0.0;
+    for (int k0 = 0; k0 < 2 * nt; k0 += VEL_WAVES) {
+        const int k = k0 + w;
+        Src4<float> q{};
+        if (k < 2 * nt) {
+            q = point(k);
+            L.src[w][lane] = L.src[w][lane + 64] = q;
+        }
+        __syncthreads();
+        V2<double> P{0.0, 0.0};
+        if (k < 2 * nt) {
+            // as the target block, or as the moving one
+            auto target = [&](int s_lo, int s_full, int s_hi, V2<double>& a, V2<double>* m) {
+                double bx, by, cx, cy;
+                const bool far = big_sym_block<false>(C, &L.tab, own, own.fx, own.fy, L.src[w], s_lo, s_full, s_hi,
+                                                      lane, a.x, a.y, bx, by);
+                if (__any(far)) {
+                    big_sym_block<true>(C, &L.tab, own, own.fx, own.fy, L.src[w], s_lo, s_full, s_hi, lane, a.x, a.y,
+                                        cx, cy);
+                    bx += cx;
+                    by += cy;
+                }
+                if (m) *m = V2<double>{bx, by};
+            };
+            if (k == A) {
+                // the diagonal block: offsets 1..32, offset 32 for lanes 0..31
+                V2<double> t{0.0, 0.0};
+                target(1, 32, 33, t, &P);
+                L.diag[lane] = t;
+            } else if (k > A) {
+                target(0, 64, 64, P, nullptr);
+            } else {
+                double ax = 0.0, ay = 0.0, cx, cy;
+                const bool far = big_sym_block<false>(C, &L.tab, q, q.fx, q.fy, L.own, 0, 64, 64, lane, ax, ay, P.x, P.y);
+                if (__any(far)) {
+                    big_sym_block<true>(C, &L.tab, q, q.fx, q.fy, L.own, 0, 64, 64, lane, ax, ay, cx, cy);
+                    P.x += cx;
+                    P.y += cy;
+                }
+            }
+        }
+        L.part[w][lane] = P;
+        __syncthreads();
+        if (w == 0) {
+            for (int j = 0; j < VEL_WAVES && k0 + j < 2 * nt; j += 2) {
+                const V2<double> e = L.part[j][lane], f = L.part[j + 1][lane];
+                if (k0 + j != 2 * tA) {
+                    u += e.x + f.x;
+                    v += e.y + f.y;
+                } else {
+                    // the own tile: moving sums by block, then target sums
+                    const V2<double> t = L.diag[lane];
+                    u += A & 1 ? (e.x + f.x) + t.x : e.x + (t.x + f.x);
+                    v += A & 1 ? (e.y + f.y) + t.y : e.y + (t.y + f.y);
+                }
+            }
+        }
+    }
+    const int i = 64 * A + lane;
+    if (w != 0 || i >= n) return;
+    const double h1c = C.h1c;
+    ux[p0 + i] = (float)fma(h1c, L.red[0][0] + L.red[0][1] + L.red[0][2] + L.red[0][3], u);
+    uy[p0 + i] = (float)fma(h1c, L.red[1][0] + L.red[1][1] + L.red[1][2] + L.red[1][3], v);
+}
+
 // sources (position, force at t = 0) of the large systems' first step
 __global__ __launch_bounds__(256) void k_big_sources(BigTiles bt, Batch b, BigState S)
 {
@@ -1844,6 +1966,17 @@ hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int6
         hipLaunchKernelGGL(k_pair_velocity<double>, grid, block, 0, st, n_sys, blk0, off,
                            (const SysConst<double>*)sysc, tab, (const double*)x, (const double*)y, (const double*)fx,
                            (const double*)fy, (double*)ux, (double*)uy);
+    return hipGetLastError();
+}
+
+hipError_t launch_ordered_velocity(int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* off, const void* sysc,
+                                   const void* tab, const void* x, const void* y, const void* fx, const void* fy,
+                                   void* ux, void* uy, hipStream_t st)
+{
+    if (nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_ordered_velocity, dim3((unsigned)nb), dim3(64 * VEL_WAVES), 0, st, n_sys, blk0, off,
+                       (const SysConst<float>*)sysc, (const TabSys*)tab, (const float*)x, (const float*)y,
+                       (const float*)fx, (const float*)fy, (float*)ux, (float*)uy);
     return hipGetLastError();
 }
 
