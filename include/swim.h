@@ -245,10 +245,13 @@ int swim_pair_velocity_noalloc(swim_ctx *ctx, int32_t dtype, int64_t n_sys, cons
  * (with SWIM_BLOB_PAPER: m = 1 - eps^3/R^3 for every alpha).
  * x, y, fx, fy device dtype[n]; tx, ty device dtype[nt]; u, v, p device
  * dtype[nt] (written).  alpha >= 0, eps > 0, alpha*eps <= 1.  Sums are
- *accumulated in FP64.  The pair kernel is read from the system's table (as
+ * accumulated in FP64.  FP32 reads the pair kernel from the system's table (as
  * in the forward runs; built on the device at each call), with the direct
- * evaluation beyond it.  The pressure weight m/(2 pi r^2):
- * FP32 from a second per-call table on the same intervals, FP64 directly.
+ * evaluation beyond it, and the pressure weight m/(2 pi r^2) from a second
+ * per-call table on the same intervals.  FP64 evaluates the weight directly,
+ * and the pair kernel too where it has closed forms that cost less than a table
+ * (alpha = 0; the reading's blob for fewer than 32 forces); else it reads the
+ * kernel from the system's FP64 table.
  * Asynchronous. */
 int swim_flow_field(swim_ctx *ctx, int32_t dtype, int64_t n, const void *x, const void *y, const void *fx,
                     const void *fy, double alpha, double eps, int64_t nt, const void *tx, const void *ty,

@@ -1279,6 +1279,10 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
             fc.ser[k] = fc.inv_e2 * (2.0 * (k + 1) * gam[k + 1] - 0.5 * z0 * z0 * gam[k] / (k + 1));
     }
     hipStream_t st = pick(c, stream);
+    if (dtype == SWIM_F64 && field_direct64(fc, n)) {
+        HIPCHK(launch_flow_field(dtype, n, x, y, fx, fy, fc, nullptr, nt, tx, ty, u, v, p, nullptr, nullptr, st));
+        return SWIM_OK;
+    }
     // the pair kernel from the system's table, as in the forward runs (built
     // on the device from the FP64 kernel functions)
     TRY(begin_uploads(c, 16 + sizeof(fc)));
@@ -1300,7 +1304,7 @@ int swim_flow_field(swim_ctx* c, int32_t dtype, int64_t n, const void* x, const 
         TRY(ensure(c, B_WTAB, (size_t)(TAB_N + 1) * 16));
         wtab = c->buf[B_WTAB].p;
     }
-    HIPCHK(launch_flow_field(dtype, n, x, y, fx, fy, fc_dev, nt, tx, ty, u, v, p, tab, wtab, st));
+    HIPCHK(launch_flow_field(dtype, n, x, y, fx, fy, fc, fc_dev, nt, tx, ty, u, v, p, tab, wtab, st));
     return SWIM_OK;
 }
 

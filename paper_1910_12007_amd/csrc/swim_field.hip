@@ -204,16 +204,15 @@ __global__ __launch_bounds__(FIELD_TILE) void k_flow_field32(int64_t n, const fl
     }
 }
 
-// FP64 fields: the kernel from the system's FP64 table (direct beyond it),
-// the pressure weight directly
+// FP64 fields: the kernel from the system's FP64 table (direct beyond it), or
+// DIRECT evaluated throughout; the pressure weight directly
+template <bool DIRECT>
 __global__ __launch_bounds__(FIELD_TILE) void k_flow_field64(int64_t n, const double* x, const double* y,
-                                                             const double* fx, const double* fy,
-                                                             const FieldConst* fcp,
+                                                             const double* fx, const double* fy, FieldConst fc,
                                                              int64_t nt, const double* tx, const double* ty, double* u,
                                                              double* v, double* p, const TabSys64* tab)
 {
     __shared__ Src4<double> tile[FIELD_TILE];
-    const FieldConst& fc = *fcp;
     const int tid = threadIdx.x;
     const int64_t a = (int64_t)blockIdx.x * FIELD_TILE + tid;
     const bool live = a < nt;
@@ -230,7 +229,9 @@ __global__ __launch_bounds__(FIELD_TILE) void k_flow_field64(int64_t n, const do
             sfy += s.fy;
             const double dx = X - s.x, dy = Y - s.y, t = fma(dx, dx, dy * dy), fd = fma(s.fx, dx, s.fy * dy);
             double Ht, H2;
-            if (tab64_lookup(tab, t, fc.c64.ts, Ht, H2)) {
+            if constexpr (DIRECT) {
+                kernel_eval_closed<double>(fc.c64, t, Ht, H2);
+            } else if (tab64_lookup(tab, t, fc.c64.ts, Ht, H2)) {
                 const V2<double> d = kernel_far64(fc.c64, t);
                 Ht = d.x;
                 H2 = d.y;
@@ -249,28 +250,47 @@ __global__ __launch_bounds__(FIELD_TILE) void k_flow_field64(int64_t n, const do
 
 }  // namespace
 
+// A table costs an upload, the constants' launch and 704 intervals' set-up, 25 us.
+// The Stokes limits' closed forms are a logarithm and a few products, less than
+// a pair's nine table reads (512 sources, 3e5 targets: 1.34 ms direct, 2.17 from
+// the table); the reading's Bessel functions are more (5.97 ms, 3.56 from the
+// table), but not for few sources, whose chain of pairs is short (64 sources, 100
+// targets 156 us against 126; one source and target 13 against 37).  The paper's
+// blob at alpha > 0 has no closed form.  The number of targets has no say, so that
+// a target's bits do not depend on the others.
+bool field_direct64(const FieldConst& fc, int64_t n)
+{
+    return fc.c64.paper != 2.0 && (fc.stokes || n < 32);
+}
+
 hipError_t launch_flow_field(int dtype, int64_t n, const void* x, const void* y, const void* fx, const void* fy,
-                             const FieldConst* fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,
-                             void* p, const void* tab, void* wtab, hipStream_t st)
+                             const FieldConst& fc, const FieldConst* fc_dev, int64_t nt, const void* tx, const void* ty,
+                             void* u, void* v, void* p, const void* tab, void* wtab, hipStream_t st)
 {
     if (nt == 0) return hipSuccess;
     if (dtype == 0) {
-        hipLaunchKernelGGL(k_weight_table, dim3(TAB_N / 256 + 1), dim3(256), 0, st, fc, (float4*)wtab);
+        hipLaunchKernelGGL(k_weight_table, dim3(TAB_N / 256 + 1), dim3(256), 0, st, fc_dev, (float4*)wtab);
         const float *X = (const float*)x, *Y = (const float*)y, *FX = (const float*)fx, *FY = (const float*)fy;
         // two targets per thread from 2^18 targets on (four workgroups per CU)
         if (nt >= (1 << 18))
             hipLaunchKernelGGL(k_flow_field32<2>, dim3((unsigned)((nt + 2 * FIELD_TILE - 1) / (2 * FIELD_TILE))),
-                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc, nt, (const float*)tx, (const float*)ty,
+                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc_dev, nt, (const float*)tx, (const float*)ty,
                                (float*)u, (float*)v, (float*)p, (const TabSys*)tab, (const float4*)wtab);
         else
             hipLaunchKernelGGL(k_flow_field32<1>, dim3((unsigned)((nt + FIELD_TILE - 1) / FIELD_TILE)),
-                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc, nt, (const float*)tx, (const float*)ty,
+                               dim3(FIELD_TILE), 0, st, n, X, Y, FX, FY, fc_dev, nt, (const float*)tx, (const float*)ty,
                                (float*)u, (float*)v, (float*)p, (const TabSys*)tab, (const float4*)wtab);
     } else {
-        hipLaunchKernelGGL(k_flow_field64, dim3((unsigned)((nt + FIELD_TILE - 1) / FIELD_TILE)), dim3(FIELD_TILE), 0, st,
-                           n, (const double*)x, (const double*)y, (const double*)fx, (const double*)fy, fc, nt,
-                           (const double*)tx, (const double*)ty, (double*)u, (double*)v, (double*)p,
-                           (const TabSys64*)tab);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((nt + FIELD_TILE - 1) / FIELD_TILE)), dim3(FIELD_TILE), 0, st, n,
+                               (const double*)x, (const double*)y, (const double*)fx, (const double*)fy, fc, nt,
+                               (const double*)tx, (const double*)ty, (double*)u, (double*)v, (double*)p,
+                               (const TabSys64*)tab);
+        };
+        if (tab)
+            launch(k_flow_field64<false>);
+        else
+            launch(k_flow_field64<true>);
     }
     return hipGetLastError();
 }

@@ -255,8 +255,11 @@ struct FieldConst {
     int32_t stokes, paper;  // paper: the paper's blob (mass 1 - eps^3/R^3)
     double ser[FIELD_NSER];
 };
+// whether an FP64 field evaluates its pairs directly instead of from a table
+bool field_direct64(const FieldConst& fc, int64_t n);
+// FP32: fc_dev (fc in device memory), tab and wtab; FP64: tab, or null for direct evaluation
 hipError_t launch_flow_field(int dtype, int64_t n, const void* x, const void* y, const void* fx, const void* fy,
-                             const FieldConst* fc, int64_t nt, const void* tx, const void* ty, void* u, void* v,  // fc: device
-                             void* p, const void* tab, void* wtab, hipStream_t st);
+                             const FieldConst& fc, const FieldConst* fc_dev, int64_t nt, const void* tx, const void* ty,
+                             void* u, void* v, void* p, const void* tab, void* wtab, hipStream_t st);
 
 }  // namespace swim
