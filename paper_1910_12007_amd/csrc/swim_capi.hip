@@ -416,9 +416,10 @@ int sysconst_buffers(swim_ctx* c, int32_t dtype, int64_t n_sys, void** sysc, voi
 }
 
 // the systems' kernel tables from their FP64 constants (an FP64 run's own)
-hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, void* sysc64, void* tab, hipStream_t st)
+hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, void* sysc64, void* tab, hipStream_t st,
+                        const int64_t* pt_off = nullptr)
 {
-    return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, c->opt_blob, st);
+    return launch_table_build(dtype, 0, n_sys, dtype == SWIM_F32 ? sysc64 : sysc, tab, c->opt_blob, st, pt_off);
 }
 
 // FP32 calls run in chunks of this many systems (6.5 GB of tables)
@@ -443,6 +444,18 @@ template <typename F> void block_prefix(int64_t n_sys, const int64_t* sys_off, i
     blk0[0] = 0;
     for (int64_t s = 0; s < n_sys; ++s)
         blk0[s + 1] = blk0[s] + (takes(s) ? (sys_off[s + 1] - sys_off[s] + 63) / 64 : 0);
+}
+// FP64 systems that are evaluated directly, without a table (direct64 on the device)
+bool direct_sum(const swim_ctx* c, int32_t dtype, int64_t n, double alpha)
+{
+    return dtype == SWIM_F64 && n <= DIRECT64_MAX && !(c->opt_blob == SWIM_BLOB_PAPER && alpha > 0.0);
+}
+// a call of such systems alone
+bool all_direct(const swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t* sys_off, const double* alpha)
+{
+    for (int64_t s = 0; s < n_sys; ++s)
+        if (!direct_sum(c, dtype, sys_off[s + 1] - sys_off[s], alpha[s])) return false;
+    return true;
 }
 // systems that sum in the tile pairs' order (whichever kernel takes them): by
 // their own size alone, so that a system's bits depend on nothing else
@@ -1106,10 +1119,19 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     }
     auto size = [&](int64_t s) { return sys_off[s + 1] - sys_off[s]; };
     std::vector<int64_t> blk0(n_sys + 1), blk1;
-    block_prefix(n_sys, sys_off, blk0.data(), [&](int64_t s) { return !ordered_sum(dtype, size(s)); });
-    int64_t n_ordered = 0;
-    for (int64_t s = 0; s < n_sys; ++s) n_ordered += ordered_sum(dtype, size(s)) ? 1 : 0;
-    if (n_ordered > (int64_t)plan.list.size()) {  // some of them without tile pairs
+    auto direct = [&](int64_t s) { return direct_sum(c, dtype, size(s), alpha[s]); };
+    block_prefix(n_sys, sys_off, blk0.data(), [&](int64_t s) { return !ordered_sum(dtype, size(s)) && !direct(s); });
+    int64_t n_ordered = 0, n_direct = 0;
+    for (int64_t s = 0; s < n_sys; ++s) {
+        n_ordered += ordered_sum(dtype, size(s)) ? 1 : 0;
+        n_direct += direct(s) ? 1 : 0;
+    }
+    // a second list: FP64 systems evaluated directly, or FP32 ones in the tile
+    // pairs' order without tile pairs
+    if (n_direct) {
+        blk1.resize(n_sys + 1);
+        block_prefix(n_sys, sys_off, blk1.data(), direct);
+    } else if (n_ordered > (int64_t)plan.list.size()) {
         blk1.resize(n_sys + 1);
         size_t q = 0;  // next system of the plan
         block_prefix(n_sys, sys_off, blk1.data(), [&](int64_t s) {
@@ -1133,11 +1155,19 @@ static int pair_velocity_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     void *sysc, *sysc64;
     TRY(sysconst_buffers(c, dtype, n_sys, &sysc, &sysc64));
     HIPCHK(launch_sysconst(dtype, n_sys, alpha_dev, eps_dev, sysc, sysc64, c->opt_blob, st));
-    TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
-    void* tab = c->buf[B_TAB].p;
-    HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
+    void* tab = nullptr;
+    if (n_direct < n_sys) {
+        TRY(ensure(c, B_TAB, (size_t)n_sys * table_bytes(dtype)));
+        tab = c->buf[B_TAB].p;
+        HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st, dtype == SWIM_F64 ? off_dev : nullptr));
+    }
     HIPCHK(launch_pair_velocity(dtype, n_sys, blk0[n_sys], blk0_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
-    HIPCHK(launch_ordered_velocity(n_sys, blk1.empty() ? 0 : blk1[n_sys], blk1_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
+    if (!blk1.empty()) {
+        if (dtype == SWIM_F64)
+            HIPCHK(launch_direct_velocity(n_sys, blk1[n_sys], blk1_dev, off_dev, sysc, x, y, fx, fy, ux, uy, st));
+        else
+            HIPCHK(launch_ordered_velocity(n_sys, blk1[n_sys], blk1_dev, off_dev, sysc, tab, x, y, fx, fy, ux, uy, st));
+    }
     HIPCHK(launch_tile_velocity(bt, sysc, tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
 }
@@ -1162,7 +1192,8 @@ int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t*
     if (npts > 0 && (!x || !y || !fx || !fy || !ux || !uy)) return fail(SWIM_EINVAL, "null data pointer");
     hipStream_t st = pick(c, stream);
     // (chunks: the tables' memory, and the launches' limit of 2^32 threads)
-    const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
+    const int64_t chunk =
+        dtype == SWIM_F32 || all_direct(c, dtype, n_sys, sys_off, alpha) ? FWD_CHUNK : tab64_chunk(c, n_sys);
     if (n_sys <= chunk) return pair_velocity_chunk(c, dtype, n_sys, sys_off, alpha, eps, x, y, fx, fy, ux, uy, st);
     std::vector<int64_t> off(chunk + 1);
     for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
@@ -1217,9 +1248,10 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     // the sums of swim_pair_velocity, bit for bit, by kernels without scratch memory
     auto size = [&](int64_t s) { return sys_off[s + 1] - sys_off[s]; };
     int64_t *blk0 = (int64_t*)(host + NA_BLK0), *blk1 = (int64_t*)(host + NA_BLK1);
-    block_prefix(n_sys, sys_off, blk0, [&](int64_t s) { return !ordered_sum(dtype, size(s)); });
-    block_prefix(n_sys, sys_off, blk1, [&](int64_t s) { return ordered_sum(dtype, size(s)); });
-    const int64_t n_plain = blk0[n_sys], n_ordered = blk1[n_sys];
+    auto second = [&](int64_t s) { return ordered_sum(dtype, size(s)) || direct_sum(c, dtype, size(s), alpha[s]); };
+    block_prefix(n_sys, sys_off, blk0, [&](int64_t s) { return !second(s); });
+    block_prefix(n_sys, sys_off, blk1, second);
+    const int64_t n_plain = blk0[n_sys], n_second = blk1[n_sys];
     hipStream_t st = pick(c, stream);
     HIPCHK(hipMemcpyWithStream(ws, host, NA_SYSC, hipMemcpyHostToDevice, st));
     void* sysc = ws + NA_SYSC;
@@ -1227,12 +1259,16 @@ int swim_pair_velocity_noalloc(swim_ctx* c, int32_t dtype, int64_t n_sys, const 
     HIPCHK(launch_sysconst(dtype, n_sys, (const double*)(ws + NA_ALPHA), (const double*)(ws + NA_EPS), sysc, sysc64,
                            c->opt_blob, st));
     void* tab = ws + NA_TAB;
-    HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st));
     const int64_t* off = (const int64_t*)(ws + NA_OFF);
+    if (!all_direct(c, dtype, n_sys, sys_off, alpha))
+        HIPCHK(build_tables(c, dtype, n_sys, sysc, sysc64, tab, st, dtype == SWIM_F64 ? off : nullptr));
     HIPCHK(launch_pair_velocity(dtype, n_sys, n_plain, (const int64_t*)(ws + NA_BLK0), off, sysc, tab, x, y, fx, fy, ux,
                                 uy, st));
-    HIPCHK(launch_ordered_velocity(n_sys, n_ordered, (const int64_t*)(ws + NA_BLK1), off, sysc, tab, x, y, fx, fy, ux,
-                                   uy, st));
+    const int64_t* blk1_dev = (const int64_t*)(ws + NA_BLK1);
+    if (dtype == SWIM_F64)
+        HIPCHK(launch_direct_velocity(n_sys, n_second, blk1_dev, off, sysc, x, y, fx, fy, ux, uy, st));
+    else
+        HIPCHK(launch_ordered_velocity(n_sys, n_second, blk1_dev, off, sysc, tab, x, y, fx, fy, ux, uy, st));
     return SWIM_OK;
 }
 

@@ -63,8 +63,17 @@ hipError_t launch_ordered_velocity(int64_t n_sys, int64_t nb, const int64_t* blk
                                    const void* fy, void* ux, void* uy, hipStream_t st);
 // bytes of one system's kernel table (TabSys, TabSys64)
 size_t table_bytes(int dtype);
-// kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s]
-hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st);
+// FP64 velocity sums evaluate systems of at most this many points directly where
+// the kernel functions are closed forms (all but the paper's blob at alpha > 0)
+constexpr int DIRECT64_MAX = 24;
+static_assert(DIRECT64_MAX <= 64, "one workgroup of 64 targets per system");
+hipError_t launch_direct_velocity(int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* pt_off,
+                                  const void* sysc, const void* x, const void* y, const void* fx, const void* fy,
+                                  void* ux, void* uy, hipStream_t st);
+// kernel tables of systems [s0, s0 + n) (FP64 constants sysc64) into tab[s];
+// pt_off, if not null: FP64, without those of the systems evaluated directly
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st,
+                              const int64_t* pt_off = nullptr);
 hipError_t launch_forces(int dtype, int64_t n_fil, const int64_t* fil_off, const int32_t* npt,
                          const double* params, double t, const void* x, const void* y, void* fx,
                          void* fy, hipStream_t st);

@@ -314,6 +314,17 @@ __global__ __launch_bounds__(64) void k_table_build(int64_t s0, int64_t n, const
     tab[s].e[i] = e;
 }
 
+// FP64 velocity sums: systems without a table (k_direct_velocity).  A table takes
+// 6336 evaluations and 99 KB, the pairs of a few points less: 10000 systems of 10
+// points at alpha = 0 88 us a call against 850, of 24 137 against 908; one system
+// of 24 points, the reading's blob, 34 against 36, where the chain of its pairs
+// catches up with the table's set-up.  By the system's own size, so that its bits do
+// not depend on the call.
+__device__ __forceinline__ bool direct64(const SysConst<double>& C, int64_t n)
+{
+    return C.paper != 2.0 && n <= DIRECT64_MAX;
+}
+
 // Kernel tables by the interval sweep (pb_iv_*), one workgroup of TAB_N
 // threads per system, one interval per thread: FP32 tables with the paper's
 // blob (K = 7 nodes), and FP64 tables of any blob (K = 9).  A system at
@@ -363,7 +374,7 @@ template <bool REVB> __device__ void pb_block_scan2(double& a, double& b, double
 
 template <int K>
 __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const SysConst<double>* __restrict__ sysc64,
-                                                             void* __restrict__ tab)
+                                                             void* __restrict__ tab, const int64_t* pt_off)
 {
     __shared__ double s_red[2 * PB_BLOCK / 64];
     __shared__ double s_sh[PB_NSER - 1], s_sg[PB_NSER - 1];
@@ -371,6 +382,7 @@ __global__ __launch_bounds__(PB_BLOCK) void k_table_build_pb(int64_t s0, const S
     const int64_t s = s0 + blockIdx.x;
     // read in place (uniform loads), not copied into per-lane registers
     const SysConst<double>& C = sysc64[s];
+    if (pt_off && direct64(C, pt_off[s + 1] - pt_off[s])) return;
     const bool sweep = C.paper == 2.0;
     double fh[K], fg[K];
     int iS = TAB_N;
@@ -519,6 +531,39 @@ __global__ __launch_bounds__(64 * VEL_WAVES) void k_pair_velocity(int64_t n_sys,
     }
     ux[p0 + i] = (T)fma((double)C.h1c, SFx, u);
     uy[p0 + i] = (T)fma((double)C.h1c, SFy, v);
+}
+
+// FP64 systems of at most DIRECT64_MAX points with closed forms (direct64), a wave
+// each: a target per lane, all sources in LDS.  blk0 as for the other sums.
+__global__ __launch_bounds__(64) void k_direct_velocity(int64_t n_sys, const int64_t* blk0, const int64_t* pt_off,
+                                                        const SysConst<double>* sysc, const double* x, const double* y,
+                                                        const double* fx, const double* fy, double* ux, double* uy)
+{
+    __shared__ Src4<double> src[DIRECT64_MAX];
+    const int lane = threadIdx.x;
+    const int64_t s = prefix_item(blk0, n_sys, blockIdx.x);
+    const int64_t p0 = pt_off[s];
+    const int n = (int)(pt_off[s + 1] - p0);
+    const SysConst<double>& C = sysc[s];
+    Src4<double> own{};
+    if (lane < n) src[lane] = own = Src4<double>{x[p0 + lane], y[p0 + lane], fx[p0 + lane], fy[p0 + lane]};
+    __syncthreads();
+    double u = 0.0, v = 0.0, sfx = 0.0, sfy = 0.0;
+    for (int j = 0; j < n; ++j) {
+        const Src4<double> q = src[j];
+        const double dx = own.x - q.x, dy = own.y - q.y;
+        double Ht, H2;
+        kernel_eval_closed<double>(C, fma(dx, dx, dy * dy), Ht, H2);
+        const double h2fd = H2 * fma(q.fx, dx, q.fy * dy);
+        u = fma(Ht, q.fx, fma(h2fd, dx, u));
+        v = fma(Ht, q.fy, fma(h2fd, dy, v));
+        sfx += q.fx;
+        sfy += q.fy;
+    }
+    if (lane < n) {
+        ux[p0 + lane] = fma(C.h1c, sfx, u);
+        uy[p0 + lane] = fma(C.h1c, sfy, v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1930,15 +1975,16 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
 
 size_t table_bytes(int dtype) { return dtype == 0 ? sizeof(TabSys) : sizeof(TabSys64); }
 
-hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st)
+hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc64, void* tab, int blob, hipStream_t st,
+                              const int64_t* pt_off)
 {
     if (n <= 0) return hipSuccess;
     if (dtype == 1)
         hipLaunchKernelGGL(k_table_build_pb<9>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab);
+                           (const SysConst<double>*)sysc64, tab, pt_off);
     else if (blob == 1)
         hipLaunchKernelGGL(k_table_build_pb<7>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
-                           (const SysConst<double>*)sysc64, tab);
+                           (const SysConst<double>*)sysc64, tab, (const int64_t*)nullptr);
     else
         hipLaunchKernelGGL(k_table_build, dim3((unsigned)(n * TAB_WAVES)), dim3(64), 0, st, s0, n,
                            (const SysConst<double>*)sysc64, (TabSys*)tab);
@@ -1966,6 +2012,17 @@ hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int6
         hipLaunchKernelGGL(k_pair_velocity<double>, grid, block, 0, st, n_sys, blk0, off,
                            (const SysConst<double>*)sysc, tab, (const double*)x, (const double*)y, (const double*)fx,
                            (const double*)fy, (double*)ux, (double*)uy);
+    return hipGetLastError();
+}
+
+hipError_t launch_direct_velocity(int64_t n_sys, int64_t nb, const int64_t* blk0, const int64_t* off, const void* sysc,
+                                  const void* x, const void* y, const void* fx, const void* fy, void* ux, void* uy,
+                                  hipStream_t st)
+{
+    if (nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_direct_velocity, dim3((unsigned)nb), dim3(64), 0, st, n_sys, blk0, off,
+                       (const SysConst<double>*)sysc, (const double*)x, (const double*)y, (const double*)fx,
+                       (const double*)fy, (double*)ux, (double*)uy);
     return hipGetLastError();
 }
 
