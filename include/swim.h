@@ -97,6 +97,12 @@ int swim_version(void);
  *                    in calls of more than one system per compute unit, if
  *                    the call's systems lie in one size class), 1, 2, 4, 8,
  *                    16 (reduced when the partial sums would not fit LDS).
+ *                    The waves split a system's sums, so the last bits of
+ *                    FP32 results follow their number: at 0, the sizes and
+ *                    the number of systems of the whole call (of n_prop
+ *                    systems for abc_prescreened's re-runs); set it for
+ *                    results that are the same, to the bit, in calls of any
+ *                    size.
  *                    Systems above 256 points need at least 2: a
  *                    forward call with 1 and such a system fails with
  *                    SWIM_EINVAL (the automatic choice never takes 1 there);

@@ -502,9 +502,40 @@ struct TilePlan {
 // ------------------------------------------------------------------------
 // forward run (shared by swim_forward and abc_step)
 // ------------------------------------------------------------------------
+// What a whole call fixes for all its chunks, so that a system's launch shape, and
+// with it the order of its FP32 sums, does not follow its place in the batch
+struct FwdCall {
+    int launch_tpl[9];       // bucket that each size bucket launches in (merge_buckets)
+    int64_t persistent = 0;  // systems of the persistent kernel
+    bool one_class = false;  // they lie in one launch bucket
+};
+FwdCall forward_call(int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim, double eps_over_ds)
+{
+    FwdCall f;
+    bool present[9] = {}, any_big = false;
+    for (int64_t s = 0; s < n_sys; ++s) {
+        const int t = forward_tpl(dtype, N[s], N[s] * (nswim ? nswim[s] : 1), eps_over_ds);
+        if (t > 0) {
+            present[t] = true;
+            ++f.persistent;
+        } else {
+            any_big = true;
+        }
+    }
+    merge_buckets(present, any_big, 1 + swim_ctx::N_AUX, f.launch_tpl);
+    int first = 0, classes = 0;
+    for (int t : f.launch_tpl)
+        if (t && t != first) {
+            first = t;
+            ++classes;
+        }
+    f.one_class = classes == 1;
+    return f;
+}
+
 int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim,
-                  const double* params_dev, const Run& run, void* obs, void* speed, int32_t* status,
-                  int32_t* steps_done, hipStream_t st)
+                  const double* params_dev, const Run& run, const FwdCall& call, void* obs, void* speed,
+                  int32_t* status, int32_t* steps_done, hipStream_t st)
 {
     if (n_sys == 0) return SWIM_OK;
     std::vector<int64_t> sw_off(n_sys + 1, 0), big_off(n_sys, 0);
@@ -515,17 +546,9 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
     std::vector<std::vector<int32_t>> bucket(8);
     std::vector<int64_t> big_list;
     std::vector<int8_t> tpl_of(n_sys);
-    bool present[9] = {}, any_big = false;
-    for (int64_t s = 0; s < n_sys; ++s) {
-        const int p = N[s] * (nswim ? nswim[s] : 1);
-        tpl_of[s] = (int8_t)forward_tpl(dtype, N[s], p, run.eps_over_ds);
-        if (tpl_of[s] > 0) present[tpl_of[s]] = true;
-        else any_big = true;
-    }
-    int launch_tpl[9];
-    merge_buckets(present, any_big, 1 + swim_ctx::N_AUX, launch_tpl);
-    if (c->forced_launch)
-        for (int t = 0; t <= 8; ++t) launch_tpl[t] = c->force_launch_tpl[t];
+    for (int64_t s = 0; s < n_sys; ++s)
+        tpl_of[s] = (int8_t)forward_tpl(dtype, N[s], N[s] * (nswim ? nswim[s] : 1), run.eps_over_ds);
+    const int(&launch_tpl)[9] = c->forced_launch ? c->force_launch_tpl : call.launch_tpl;
     for (int64_t s = 0; s < n_sys; ++s) {
         nsw[s] = nswim ? nswim[s] : 1;
         sw_off[s + 1] = sw_off[s] + nsw[s];
@@ -622,10 +645,10 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         // 30.0 ms with the few-systems choice throughout, 32.1 with the
         // many-systems one).  FP64 takes 8 (222 VGPRs; 16 waves have 128 and
         // spill 239 of them: 7.3 against 3.8 us per step at N = 64).
-        const bool many = (int64_t)order.size() > c->num_cu && bucket_span.size() == 1;
+        const bool many = call.persistent > c->num_cu && call.one_class;
         int wps_default = 8;
         if (dtype == SWIM_F32) {
-            if (q.tpl == 1) wps_default = many && (int64_t)order.size() > 2 * c->num_cu ? 4 : 8;
+            if (q.tpl == 1) wps_default = many && call.persistent > 2 * c->num_cu ? 4 : 8;
             else if (q.tpl >= 3) wps_default = many && q.tpl != 8 ? 8 : 16;
         }
         q.wps = c->opt_wps ? c->opt_wps : (c->tuned_wps[dtype][q.tpl] ? c->tuned_wps[dtype][q.tpl] : wps_default);
@@ -856,23 +879,26 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
 
 // Runs keep one kernel table per system in HBM (FP32 24.8 KB, FP64 99 KB),
 // so very large batches run in chunks of FWD_CHUNK (FP64: tab64_chunk)
-// systems; the systems are independent and their order within a batch does
-// not change any result.
+// systems; the systems are independent, and the launch shapes are the whole
+// call's, so that the order within a batch does not change any result.  as_n:
+// the shapes of a call of that many such systems (0: of this call).
 
 int forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim,
                  const double* params_dev, const Run& run, void* obs, void* speed, int32_t* status,
-                 int32_t* steps_done, hipStream_t st)
+                 int32_t* steps_done, hipStream_t st, int64_t as_n = 0)
 {
     const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
+    FwdCall call = forward_call(dtype, n_sys, N, nswim, run.eps_over_ds);
+    if (as_n) call.persistent = as_n;
     if (n_sys <= chunk)
-        return forward_chunk(c, dtype, n_sys, N, nswim, params_dev, run, obs, speed, status, steps_done, st);
+        return forward_chunk(c, dtype, n_sys, N, nswim, params_dev, run, call, obs, speed, status, steps_done, st);
     const size_t es = dtype == SWIM_F32 ? 4 : 8;
     int64_t f0 = 0;  // first filament of the chunk
     for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
         const int64_t m = std::min(chunk, n_sys - s0);
         int64_t nf = 0;
         for (int64_t s = s0; s < s0 + m; ++s) nf += nswim ? nswim[s] : 1;
-        TRY(forward_chunk(c, dtype, m, N + s0, nswim ? nswim + s0 : nullptr, params_dev + f0 * SWIM_NPARAM, run,
+        TRY(forward_chunk(c, dtype, m, N + s0, nswim ? nswim + s0 : nullptr, params_dev + f0 * SWIM_NPARAM, run, call,
                           (char*)obs + (size_t)f0 * run.n_obs * 2 * es, (char*)speed + (size_t)f0 * es, status + s0,
                           steps_done ? steps_done + s0 : nullptr, st));
         f0 += nf;
@@ -2242,8 +2268,9 @@ int abc_prescreened(swim_ctx* c, const abc_model* m, int32_t N, const float* par
             r.stop_data = (const double*)c->buf[B_DATA].p;
             r.stop_ssq = 2.0 * n_obs * tol * tol * (1.0 + 1e-6);
         }
+        // (the launch shape of the plain run of all n_prop draws: the same bits)
         TRY(forward_impl(c, m->dtype, n, Nv.data(), nullptr, rows, r, c->buf[B_OBS].p, c->buf[B_SPEED].p,
-                         (int32_t*)c->buf[B_STATUS].p, nullptr, st));
+                         (int32_t*)c->buf[B_STATUS].p, nullptr, st, n_prop));
         HIPCHK(launch_abc_distance(m->dtype, n, n_obs, c->buf[B_OBS].p, (const double*)c->buf[B_DATA].p,
                                    (const int32_t*)c->buf[B_STATUS].p, (double*)c->buf[B_DIST].p, st));
         HIPCHK(launch_accept(n, (const double*)c->buf[B_DIST].p, (const double*)c->buf[B_TOL].p,
