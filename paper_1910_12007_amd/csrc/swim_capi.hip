@@ -181,14 +181,14 @@ int ensure(swim_ctx* c, BufId id, size_t bytes)
 // the previous call's copies; put() then appends to the call's upload buffer
 // (one copy, by end_uploads), stage() copies into a buffer of its own that
 // outlives the call's own uploads (an ABC or TMCMC step's rows and data,
-// which the forward runs inside it read).
-int begin_uploads(swim_ctx* c, size_t total)
+// which the forward runs inside it read).  A call that only stages needs no
+// upload buffer (begin_staging).
+int begin_staging(swim_ctx* c, size_t total)
 {
     HIPCHK(hipEventSynchronize(c->up_ev));
     c->pin_off = 0;
     c->put_end = 0;
     total += 64 * 32;
-    TRY(ensure(c, B_UP, total));
     if (total > c->pinned_cap) {
         if (c->pinned) HIPCHK(hipHostFree(c->pinned));
         c->pinned = nullptr;
@@ -199,6 +199,12 @@ int begin_uploads(swim_ctx* c, size_t total)
         c->pinned_cap = cap;
     }
     return SWIM_OK;
+}
+
+int begin_uploads(swim_ctx* c, size_t total)
+{
+    TRY(begin_staging(c, total));
+    return ensure(c, B_UP, total + 64 * 32);
 }
 
 int stage(swim_ctx* c, const void* src, size_t bytes, BufId dst, hipStream_t st)
@@ -1764,7 +1770,7 @@ int abc_step(swim_ctx* c, const abc_model* m, const double* data, int32_t n_obs,
     TRY(ensure(c, B_DIST, (size_t)n * 8));
     TRY(ensure(c, B_TOL, 8));
     TRY(ensure(c, B_ACC, (size_t)n));
-    TRY(begin_uploads(c, rows.size() * 8 + (size_t)n_obs * 16));
+    TRY(begin_staging(c, rows.size() * 8 + (size_t)n_obs * 16));
     TRY(stage(c, rows.data(), rows.size() * 8, B_PARAMS, st));
     TRY(stage(c, data, (size_t)n_obs * 16, B_DATA, st));
     TRY(end_uploads(c, st));
@@ -2031,7 +2037,7 @@ int surrogate_targets(swim_ctx* c, int32_t dtype, int64_t n, int32_t n_obs, cons
     for (int j = 0; j < n_sum; ++j)
         if (sum_idx[j] < 0 || sum_idx[j] >= n_obs) return fail(SWIM_EINVAL, "summary index %d out of range", sum_idx[j]);
     hipStream_t st = pick(c, stream);
-    TRY(begin_uploads(c, (size_t)n_sum * 4));
+    TRY(begin_staging(c, (size_t)n_sum * 4));
     TRY(stage(c, sum_idx, (size_t)n_sum * 4, B_MLP_IDX, st));
     TRY(end_uploads(c, st));
     HIPCHK(launch_targets(dtype, n, n_obs, obs, speed, x0, y0, (const int32_t*)c->buf[B_MLP_IDX].p, n_sum, T, st));
@@ -2147,7 +2153,7 @@ int surrogate_dataset(swim_ctx* c, const abc_model* m, int32_t N, int64_t n_runs
     float* Xall = (float*)c->buf[B_PS_X].p;
     float* Tall = (float*)c->buf[B_DS_T].p;
     HIPCHK(launch_features(n_runs, theta, m->b, m->omega, nullptr, nullptr, Xall, st));
-    TRY(begin_uploads(c, (size_t)n_sum * 4));
+    TRY(begin_staging(c, (size_t)n_sum * 4));
     TRY(stage(c, sum_idx, (size_t)n_sum * 4, B_MLP_IDX, st));
     TRY(end_uploads(c, st));
     // the head starts at (L, 0) = (1, 0): parameter rows carry a zero offset
@@ -2214,7 +2220,7 @@ int abc_prescreened(swim_ctx* c, const abc_model* m, int32_t N, const float* par
     TRY(ensure(c, B_PS_KEEP, (size_t)n_prop));
     TRY(ensure(c, B_PS_IDX, (size_t)n_prop * 8));
     TRY(ensure(c, B_PS_NK, 8));
-    TRY(begin_uploads(c, osum.size() * 4 + (size_t)n_obs * 16 + 8));
+    TRY(begin_staging(c, osum.size() * 4 + (size_t)n_obs * 16 + 8));
     TRY(stage(c, osum.data(), osum.size() * 4, B_PS_SUM, st));
     TRY(stage(c, data, (size_t)n_obs * 16, B_DATA, st));
     TRY(stage(c, &tol, 8, B_TOL, st));
@@ -2767,7 +2773,7 @@ int tmcmc_run(swim_ctx* c, const abc_model* m, const tmcmc_opts* o, const double
         TRY(ensure(c, B_STATUS, (size_t)k * 4));
         TRY(ensure(c, B_SIGMA, (size_t)k * 8));
         TRY(ensure(c, B_LOGL, (size_t)k * 8));
-        TRY(begin_uploads(c, rows.size() * 8 + sig.size() * 8 + (size_t)n_obs * 16));
+        TRY(begin_staging(c, rows.size() * 8 + sig.size() * 8 + (size_t)n_obs * 16));
         TRY(stage(c, rows.data(), rows.size() * 8, B_PARAMS, st));
         TRY(stage(c, sig.data(), sig.size() * 8, B_SIGMA, st));
         TRY(stage(c, data, (size_t)n_obs * 16, B_DATA, st));
@@ -2855,7 +2861,7 @@ int tmcmc_sperm_run(swim_ctx* c, const sperm_tmcmc_model* m, const double* swim_
         TRY(ensure(c, B_SP_G, (size_t)k * n_obs * 2 * 8));
         TRY(ensure(c, B_STATUS, (size_t)k * 4));
         TRY(ensure(c, B_LOGL, (size_t)k * 8));
-        TRY(begin_uploads(c, rows.size() * 8 + sw.size() * 8 + sig.size() * 8 + (size_t)n_obs * 16));
+        TRY(begin_staging(c, rows.size() * 8 + sw.size() * 8 + sig.size() * 8 + (size_t)n_obs * 16));
         TRY(stage(c, rows.data(), rows.size() * 8, B_PARAMS, st));
         TRY(stage(c, sw.data(), sw.size() * 8, B_SP_SW, st));
         TRY(stage(c, sig.data(), sig.size() * 8, B_SP_SIG, st));
