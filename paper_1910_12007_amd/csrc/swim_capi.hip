@@ -581,7 +581,7 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         order.insert(order.end(), v.begin(), v.end());
     }
     // large systems: FP32 at the automatic choice takes the symmetric step
-    // (tile pairs, then tiles, of 256 points); otherwise target blocks of
+    // (tile pairs, then tiles, of BIG_TILE_POINTS points); otherwise target blocks of
     // 256 * tpl_big points of the one-sided step
     const bool big_sym = dtype == SWIM_F32 && c->opt_big_tpl == 0;
     const int tpl_big = c->opt_big_tpl ? c->opt_big_tpl : 1;
@@ -649,8 +649,9 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
         // batch's blow-ups are twice as fast as with 4.)  Beside other buckets
         // the longest runs' own speed counts (1024 systems of 64..512 points:
         // 30.0 ms with the few-systems choice throughout, 32.1 with the
-        // many-systems one).  FP64 takes 8 (222 VGPRs; 16 waves have 128 and
-        // spill 239 of them: 7.3 against 3.8 us per step at N = 64).
+        // many-systems one).  FP64 takes 8 (214..252 VGPRs, one workgroup
+        // per CU; 16 waves have 128 and spill 239 of them: 7.3 against 3.8 us per
+        // step at N = 64).
         const bool many = call.persistent > c->num_cu && call.one_class;
         int wps_default = 8;
         if (dtype == SWIM_F32) {

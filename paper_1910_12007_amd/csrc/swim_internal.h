@@ -24,7 +24,7 @@ struct Batch {
     const void* sysc;        // SysConst<T>[n_sys]
     const void* sysc64;      // SysConst<double>[n_sys] (FP32 runs: builds the kernel tables)
     const void* tab;         // kernel tables: TabSys[n_sys] (FP32), TabSys64[n_sys] (FP64)
-    int32_t alone;           // persistent runs: no more workgroups than compute units
+    int32_t alone;           // FP32 persistent runs: no more workgroups than compute units
 };
 
 struct Run {

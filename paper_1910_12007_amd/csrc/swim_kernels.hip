@@ -662,10 +662,13 @@ struct FwdLdsLayout {
 };
 __host__ __device__ constexpr size_t fwd_align16(size_t x) { return (x + 15) & ~(size_t)15; }
 // FP64 launch shapes that have a second build with the table in LDS (99 KB of
-// it, so one workgroup per CU), for launches whose workgroups share no CU: from
-// the caches, a pair's nine 16-byte reads are bound by the L1's 64 bytes a clock.
-// 2 runs of 64 points 3.4 -> 2.5 us a step, 4 of 200 points 36 -> 18; the copy
-// is under 2 us, so runs of a few steps keep the caches.
+// it, so one workgroup per CU, as the registers of eight waves allow anyway: 214..246
+// of 512 a lane).  Every launch of these shapes takes it from FWD_LDS64_STEPS steps
+// on, however many systems or other launches there are: from the caches, a pair's
+// nine 16-byte reads are bound by the L1's 64 bytes a clock.  2 runs of 64 points
+// 3.4 -> 2.5 us a step, 4 of 200 points 36 -> 18, 300 of 200 points 8 steps 602
+// -> 396 us; the copy is under 2 us per system, so runs of a few steps keep the
+// caches.
 __host__ __device__ constexpr bool fwd_lds64(int dtype, int tpl, int wps) { return dtype == 1 && tpl <= 4 && wps == 8; }
 constexpr int FWD_LDS64_STEPS = 8;
 __host__ __device__ constexpr FwdLdsLayout fwd_lds_layout(int dtype, int tpl, int wps, bool lds64 = false)
@@ -991,7 +994,7 @@ __device__ void run_system(const Batch& b, const Run& r, int s, const FwdLds<T>&
             // 1 + (r/eps)^2 < 2^44, inside the table (the initial positions
             // are the caller's: a run placed beyond the bound reads zeros
             // for its far pairs in its first step and stops)
-            // (FP64 reads its table from HBM and tests every pair)
+            // (FP64 reads its table from LDS or HBM and tests every pair)
             T ax[TPL], ay[TPL];
             const void* tab = COMP ? (const void*)L.tab : (const void*)((const TabSys64*)b.tab + s);
             constexpr int W = WIN ? (AHEAD ? 2 : 1) : LDS64 ? 4 : 0;
@@ -2126,7 +2129,7 @@ static hipError_t fwd_launch(int nblocks, const Batch& b, const Run& r, const in
     hipError_t e = fwd_prepare<T, TPL, WPS>();
     if (e != hipSuccess) return e;
     if constexpr (fwd_second_build<T>(TPL, WPS)) {
-        if (b.alone && (sizeof(T) == 4 || r.steps >= FWD_LDS64_STEPS)) {
+        if (sizeof(T) == 4 ? b.alone != 0 : r.steps >= FWD_LDS64_STEPS) {
             const size_t own = fwd_lds_layout(sizeof(T) == 4 ? 0 : 1, TPL, WPS, sizeof(T) == 8).total;
             hipLaunchKernelGGL((k_forward<T, TPL, WPS, true>), dim3(nblocks), dim3(64 * WPS), own, st, b, r, order, q,
                                (T*)obs, (T*)speed, status, done);
