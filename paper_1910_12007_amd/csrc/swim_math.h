@@ -409,25 +409,6 @@ SWIM_HD double pb_outer(double alpha, double eps, double r, double u0)
     return b;
 }
 
-// g(0) = -int_0^inf phi K0(alpha s) s ds; panels [2^-(j+2), 2^-(j+1)] in u
-// towards the logarithm of K0 at s = 0, then pb_outer from u = 1/2
-SWIM_HD double pb_g0(double alpha, double eps)
-{
-    double b = 0.0;
-    for (int j = 52; j >= 0; --j) {
-        const double ul = ldexp(1.0, -(j + 2)), uh = 2.0 * ul;
-        const double hm = 0.5 * (uh - ul), ct = 0.5 * (uh + ul);
-        for (int i = 0; i < 10; ++i) {
-            const double u = i < 5 ? ct - hm * GL10_X[4 - i] : ct + hm * GL10_X[i - 5];
-            const double w = i < 5 ? GL10_W[4 - i] : GL10_W[i - 5];
-            double sh, dens;
-            pb_point(u, &sh, &dens);
-            b += hm * w * dens * pb_k0x(alpha * eps * sh, 0.0, 1.0);
-        }
-    }
-    return -(b + pb_outer(alpha, eps, 0.0, 0.5));
-}
-
 // g(0) of the paper's blob in closed form.  The blob's Hankel transform is
 // (1 + k eps) exp(-k eps) and (Delta - alpha^2) g = phi, so with a = alpha eps
 //   g(0) = -(1/2pi) int_0^inf (1 + x) exp(-x) x / (x^2 + a^2) dx
