@@ -37,36 +37,33 @@ sys.path.insert(0, ROOT)
 # FLOP against the FP32 vector peak of 157.3 TFLOP/s.  Algorithmic work per
 # ordered pair evaluation of eq. (BrV) in its FP32 form: per distinct pair
 # (one evaluation serves both ends, symmetric schedule) the difference
-# vector (2), v = |d|^2 + 1 (2 FMA), the two functions by cubics (6 FMA; the
-# kernel's finer table pieces take a quadratic for one of them),
+# vector (2), v = |d|^2 + 1 (2 FMA), the two functions by cubics (6 FMA),
 # and for each end F.d times H2 (MUL, FMA, MUL) and the two accumulations
-# (4 FMA): 42 FLOP (FMA = 2) per distinct pair, 21 per ordered pair.  The
-# kernel is bound by VALU instruction issue, not FLOP: integer and float
-# operations share the issue slots.  rocprofv3's SQ_INSTS_VALU over the
-# launch gives 16.6 VALU lane-operations per ordered pair evaluation, all
-# work of the step included (the symmetric pair loop alone is 13.75 in the
-# ISA); the issue peak without packed FP32 is 256 CUs x 4 SIMDs x 16 lanes
-# per clock x 2.4 GHz = 39.3e12 lane-operations/s, i.e. 78.6 TFLOP/s of FMA
-# (the build keeps packed FP32 off).
+# (4 FMA): 42 FLOP (FMA = 2) per distinct pair, 21 per ordered pair.  Integer
+# and float operations share the vector units' issue: rocprofv3's SQ_INSTS_VALU
+# over the launch gives 17.6 VALU lane-operations per ordered pair evaluation,
+# all work of the step included (the symmetric pair loop alone is 14.75 in the
+# ISA; the build keeps packed FP32 off).  The rate is given per SIMD and clock
+# (256 CUs x 4 SIMDs, 2.4 GHz).  Sixteen lanes per clock, a wavefront every four
+# clocks, is no ceiling of it: the large-system step runs above.
 # (profiles/kernel_counters_and_times.md)
-VALU_OPS_PER_PAIR = 16.6
+VALU_OPS_PER_PAIR = 17.6
 PAIR_LOOP_VALU_OPS = 15.75  # the sperm kernel's symmetric pair loop alone (ISA, per ordered pair)
 FP32_FLOP_PER_PAIR = 21
-NONPACKED_FP32_PEAK_TFLOPS = 78.6
 # the FP32 large-system step, k_tile_pairs (every pair once for both points,
 # FP64 accumulation) and k_big_update: 25.0 VALU lane-operations per ordered
 # pair evaluation from SQ_INSTS_VALU (profiles/kernel_counters_and_times.md;
 # the one-sided k_big_step<float, 1> it replaced took 39.9)
 VALU_OPS_PER_PAIR_BIG = 25.0
-VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+SIMD_CLOCKS_PER_S = 256 * 4 * 2.4e9
 FP32_PEAK_TFLOPS = 157.3
 # HBM bytes of one launch of that kernel on this workload, from rocprofv3
-# FETCH_SIZE and WRITE_SIZE (KiB per dispatch: 48827.0 and 2231.8) scaled by
+# FETCH_SIZE and WRITE_SIZE (KiB per dispatch: 46317.0 and 2225.0) scaled by
 # the same counters over a 256 MiB device copy (x2.0 and x1.0), for the
 # kernel as it stands (profiles/kernel_counters_and_times.md): almost all of it
-# the first 32 octaves of the 4096 kernel tables read once into LDS; set
+# the 4096 kernel tables read once into LDS; set
 # it to None whenever the kernel changes until the counters are taken again
-TRAFFIC_BYTES = (48827.0 * 2.00 + 2231.8 * 1.00) * 1024
+TRAFFIC_BYTES = (46317.0 * 2.00 + 2225.0 * 1.00) * 1024
 
 
 def load_data():
@@ -229,8 +226,8 @@ def dense_leg(ctx, stream, samples=64, steps=1000, dt_div=64):
            "runs_stopped": int(np.sum(status.cpu().numpy() != 0)),
            "fp32_tflops": FP32_FLOP_PER_PAIR * pairs / (ms * 1e-3) / 1e12,
            "fp32_frac": FP32_FLOP_PER_PAIR * pairs / (ms * 1e-3) / 1e12 / FP32_PEAK_TFLOPS,
-           "valu_tops": VALU_OPS_PER_PAIR_BIG * pairs / (ms * 1e-3) / 1e12, "valu_peak_tops": VALU_PEAK_TOPS,
-           "valu_issue_frac": VALU_OPS_PER_PAIR_BIG * pairs / (ms * 1e-3) / 1e12 / VALU_PEAK_TOPS,
+           "valu_tops": VALU_OPS_PER_PAIR_BIG * pairs / (ms * 1e-3) / 1e12,
+           "valu_lanes_per_simd_clock": VALU_OPS_PER_PAIR_BIG * pairs / (ms * 1e-3) / SIMD_CLOCKS_PER_S,
            "valu_ops_per_pair": VALU_OPS_PER_PAIR_BIG}
     return out
 
@@ -347,7 +344,7 @@ def sperm_leg(ctx, stream, n=2000, steps=20000, dt=1e-5):
     extrapolation to a whole stage.  Configurations: one swimmer (74 points)
     and two swimmers with head centres 0.5 apart (148 points).
 
-    Roofline: VALU issue bound.  Algorithmic work is n_pts^2 ordered pairs
+    Roofline: bound by the vector units.  Algorithmic work is n_pts^2 ordered pairs
     per system step at PAIR_LOOP_VALU_OPS lane-operations each (the
     symmetric pair loop's cost per ordered pair; the point phase of the
     step, with its head and neck terms, comes on top)."""
@@ -374,7 +371,7 @@ def sperm_leg(ctx, stream, n=2000, steps=20000, dt=1e-5):
         npts = n_swim * 74
         st = status.cpu().numpy()
         pairs = float(n) * npts * npts * steps
-        tops = PAIR_LOOP_VALU_OPS * pairs / (ms * 1e-3) / 1e12
+        lanes = PAIR_LOOP_VALU_OPS * pairs / (ms * 1e-3) / SIMD_CLOCKS_PER_S
         tflops = FP32_FLOP_PER_PAIR * pairs / (ms * 1e-3) / 1e12
         out[f"{n_swim}_swimmer" + ("s" if n_swim > 1 else "")] = {
             "points_per_system": npts, "ms": ms, "us_per_step": 1e3 * ms / steps,
@@ -385,7 +382,7 @@ def sperm_leg(ctx, stream, n=2000, steps=20000, dt=1e-5):
                          "frac": tflops / FP32_PEAK_TFLOPS,
                          "kernel": "k_sperm_forward<float,%d,2>" % (1 if npts <= 64 else 2 if npts <= 128 else 3),
                          "fp32_flop_per_pair": FP32_FLOP_PER_PAIR, "pair_loop_valu_ops": PAIR_LOOP_VALU_OPS,
-                         "pair_loop_valu_issue_frac": tops / VALU_PEAK_TOPS}}
+                         "pair_loop_valu_lanes_per_simd_clock": lanes}}
     return out
 
 
@@ -470,8 +467,7 @@ def reading_blob_leg(ctx, stream, Ns, P, steps, dt, obs_every, paper_ms):
     prior draws, for comparison with the default (the paper's blob, eq.
     eqnblob).  Both read per-system FP32 tables, so a run step costs the
     same; the difference is the per-system set-up: a one-step run with each
-    blob.  Also the FP64 direct evaluation with each blob (the paper's
-    integrates every pair: a reference mode)."""
+    blob.  Also an FP64 velocity sum with each blob (from FP64 tables)."""
     import torch
     from paper_1910_12007_amd import swim
     n = len(Ns)
@@ -522,7 +518,7 @@ def reading_blob_leg(ctx, stream, Ns, P, steps, dt, obs_every, paper_ms):
             "ms": ms, "paper_blob_ms": paper_ms, "one_step_ms": one_reading, "one_step_paper_ms": one_paper,
             "paper_setup_extra_ms": one_paper - one_reading,
             "pair_evals_per_s": pairs / (ms * 1e-3), "runs_stopped": int((status != 0).sum().item()),
-            "fp64_direct": {"workload": f"one FP64 velocity sum of {m} points, alpha = 1, eps = 0.02",
+            "fp64_velocity": {"workload": f"one FP64 velocity sum of {m} points, alpha = 1, eps = 0.02",
                             "paper_ms": f64_paper, "reading_ms": f64_reading,
                             "paper_pair_evals_per_s": m * m / (f64_paper * 1e-3),
                             "reading_pair_evals_per_s": m * m / (f64_reading * 1e-3)}}
@@ -676,7 +672,7 @@ def main():
     kernel_ms = float(np.mean(kus)) * 1e-3
     setup_ms = float(np.mean([a.elapsed_time(b) for a, b in calls])) - kernel_ms
     tflops = FP32_FLOP_PER_PAIR * pairs / (kernel_ms * 1e-3) / 1e12
-    issue = VALU_OPS_PER_PAIR * pairs / (kernel_ms * 1e-3) / 1e12
+    valu_tops = VALU_OPS_PER_PAIR * pairs / (kernel_ms * 1e-3) / 1e12
     out = {
         "metric": "swimmer steps/s & Brinkmanlet pair-evals/s; ABC accepts/s surrogate vs plain",
         "value": pairs * args.steps / wall,
@@ -706,10 +702,8 @@ def main():
                      "kernel_ms_source": "HIP events around the persistent launch (SWIM_OPT_TIME_KERNEL), "
                                          f"mean of {len(kus)} calls",
                      "fp32_flop_per_pair": FP32_FLOP_PER_PAIR, "pair_evals_per_launch": pairs,
-                     "nonpacked_fp32_peak_tflops": NONPACKED_FP32_PEAK_TFLOPS,
-                     "frac_of_nonpacked": tflops / NONPACKED_FP32_PEAK_TFLOPS,
-                     "valu_ops_per_pair": VALU_OPS_PER_PAIR, "valu_issue_tops": issue,
-                     "valu_issue_peak_tops": VALU_PEAK_TOPS, "valu_issue_frac": issue / VALU_PEAK_TOPS},
+                     "valu_ops_per_pair": VALU_OPS_PER_PAIR, "valu_tops": valu_tops,
+                     "valu_lanes_per_simd_clock": valu_tops * 1e12 / SIMD_CLOCKS_PER_S},
     }
     out["reading_blob"] = reading_blob_leg(ctx, stream, Ns, P, steps, dt, obs_every, fwd_ms)
     out["surrogate_mfma"] = mlp_leg(ctx, stream)
