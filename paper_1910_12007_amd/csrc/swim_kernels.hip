@@ -606,9 +606,9 @@ __host__ __device__ constexpr bool fwd_window(int dtype, int tpl, int wps)
 // alone ends with the smallest systems, but where most draws blow up within a
 // few hundred steps the few long runs, small ones, start last (a generation of
 // 16384 draws: 0.25 s against 0.20 with the smaller systems first); smaller
-// first ends with the largest where all complete (1024 systems of 64..512
-// points, 500 steps: 31.4 ms, with this order 26.8; the draws' generations stay
-// at 0.118 and 0.177 s).  The forecast is forward Euler's bound on the bending
+// first ends with the largest where all complete (1024 systems of 64..512 points,
+// 500 steps: 31.4 ms, with this order 26.8; the draws' generations, 0.11..0.12 and
+// 0.18..0.24 s from run to run, stay within that).  The forecast is forward Euler's bound on the bending
 // modes, dt rho < 2 with rho = 5.5e4 (S_b / 0.1) (127 ds)^-3 (the paper's blob
 // at eps = 1.5 ds; a margin of 10 %): it decides the order of independent runs,
 // nothing else.  One workgroup per bucket, 4 us.

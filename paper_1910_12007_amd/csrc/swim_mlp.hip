@@ -398,7 +398,7 @@ hipError_t launch_flag_bounded(int64_t n, const float* T, int nt, int n_disp, fl
 // quarter of the rate, are 0.55 ms for 1M rows; the MFMAs' 0.18 and the weights'
 // way out of LDS, 0.35, hide behind them only in other waves, so the count of
 // waves decides: 126 VGPRs and 32 KB, four per SIMD.  One prescreen of 1M rows
-// takes 714 us; with the chunks through registers and padded rows (166 VGPRs,
+// takes 700..754 us by the box (714 on the one of the next figures); with the chunks through registers and padded rows (166 VGPRs,
 // three waves) 981; with 64-bit addresses per lane for the loads 756 at three
 // waves, 855 at four, with spills.
 // ---------------------------------------------------------------------------

@@ -601,11 +601,12 @@ __device__ void sperm_system(const SpermShape& g, const SpermRun& r, int64_t s, 
 // points, 1350 of them the pairs'), by the chain of one step in small ones.
 // Large batches therefore want the waves that hide a step's four barriers and
 // table reads: 128 VGPRs (the far-field evaluation and the trigonometry called,
-// not inlined) and 20 KB of LDS (24 octaves of the table) let eight systems of
-// two waves share a CU, where 202 VGPRs allowed four.  With the forces in two
+// not inlined; 25..34 step-invariant values spilled to scratch) and 20 KB of LDS
+// (24 octaves of the table) let eight systems of two waves share a CU, where 202
+// VGPRs allowed four.  With the forces in two
 // passes and the tail sums in registers, 2000 one-swimmer systems take 8.2 us
 // per step against 14.7, 1024 5.6 against 7.8, one system 3.3 against 4.6; 1000
-// of two swimmers 15.7 against 19.1 (above 128 points 128 VGPRs spill, and 168
+// of two swimmers 15.7 against 19.1 (above 128 points 128 VGPRs spill more, and 168
 // measure 18.8).
 // L64: FP64 with the table in LDS, for launches whose workgroups share no CU
 // (from the caches a pair's nine 16-byte reads are bound by the L1): one system
