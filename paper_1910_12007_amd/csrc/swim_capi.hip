@@ -430,6 +430,12 @@ hipError_t build_tables(swim_ctx* c, int32_t dtype, int64_t n_sys, void* sysc, v
 
 // FP32 calls run in chunks of this many systems (6.5 GB of tables)
 constexpr int64_t FWD_CHUNK = 262144;
+// and of as many large systems as have this many bytes of partial sums (2 MB for
+// 4096 points: 8192 of them, 4.3e6 tile pairs)
+constexpr int64_t FWD_PART_BYTES = (int64_t)16 << 30;
+// Velocity sums, whose launches take 512 threads per 64 points, in chunks of this
+// many such blocks
+constexpr int64_t VEL_BLOCKS = (int64_t)1 << 22;
 // FP64 calls keep one kernel table of 99 KB per system in HBM: larger
 // batches run in chunks of this many systems (1.6 GB), fewer when the
 // allocation fails, so that tables never decide whether a call fits
@@ -490,6 +496,11 @@ struct TilePlan {
         }
     }
     size_t bytes() const { return (size_t)slots * BIG_TILE_POINTS * 2 * sizeof(double); }
+    static int64_t part_bytes(int64_t n)  // of a system of n points
+    {
+        const int64_t nt = (n + BIG_TILE_POINTS - 1) / BIG_TILE_POINTS;
+        return nt * nt * BIG_TILE_POINTS * 2 * (int64_t)sizeof(double);
+    }
     size_t upload_bytes() const { return (list.size() * 6 + 2) * 8; }
     int upload(swim_ctx* c, BigTiles* t) const
     {
@@ -514,21 +525,24 @@ struct FwdCall {
     int launch_tpl[9];       // bucket that each size bucket launches in (merge_buckets)
     int64_t persistent = 0;  // systems of the persistent kernel
     bool one_class = false;  // they lie in one launch bucket
+    bool any_big = false;    // some system takes the large-system step
 };
 FwdCall forward_call(int32_t dtype, int64_t n_sys, const int32_t* N, const int32_t* nswim, double eps_over_ds)
 {
     FwdCall f;
-    bool present[9] = {}, any_big = false;
+    bool present[9] = {};
+    int t = 0, lastN = 0, last_pts = 0;  // (runs of equal systems are the rule)
     for (int64_t s = 0; s < n_sys; ++s) {
-        const int t = forward_tpl(dtype, N[s], N[s] * (nswim ? nswim[s] : 1), eps_over_ds);
+        const int pts = N[s] * (nswim ? nswim[s] : 1);
+        if (N[s] != lastN || pts != last_pts) t = forward_tpl(dtype, lastN = N[s], last_pts = pts, eps_over_ds);
         if (t > 0) {
             present[t] = true;
             ++f.persistent;
         } else {
-            any_big = true;
+            f.any_big = true;
         }
     }
-    merge_buckets(present, any_big, 1 + swim_ctx::N_AUX, f.launch_tpl);
+    merge_buckets(present, f.any_big, 1 + swim_ctx::N_AUX, f.launch_tpl);
     int first = 0, classes = 0;
     for (int t : f.launch_tpl)
         if (t && t != first) {
@@ -885,7 +899,8 @@ int forward_chunk(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, c
 
 
 // Runs keep one kernel table per system in HBM (FP32 24.8 KB, FP64 99 KB),
-// so very large batches run in chunks of FWD_CHUNK (FP64: tab64_chunk)
+// so very large batches run in chunks of FWD_CHUNK (FP64: tab64_chunk; FP32
+// also by the large systems' partial sums, which bounds their launches, too)
 // systems; the systems are independent, and the launch shapes are the whole
 // call's, so that the order within a batch does not change any result.  as_n:
 // the shapes of a call of that many such systems (0: of this call).
@@ -897,14 +912,19 @@ int forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const int32_t* N, co
     const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
     FwdCall call = forward_call(dtype, n_sys, N, nswim, run.eps_over_ds);
     if (as_n) call.persistent = as_n;
-    if (n_sys <= chunk)
-        return forward_chunk(c, dtype, n_sys, N, nswim, params_dev, run, call, obs, speed, status, steps_done, st);
+    const bool tiles = call.any_big && dtype == SWIM_F32 && c->opt_big_tpl == 0;
     const size_t es = dtype == SWIM_F32 ? 4 : 8;
     int64_t f0 = 0;  // first filament of the chunk
-    for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
-        const int64_t m = std::min(chunk, n_sys - s0);
-        int64_t nf = 0;
-        for (int64_t s = s0; s < s0 + m; ++s) nf += nswim ? nswim[s] : 1;
+    for (int64_t s0 = 0, m; s0 < n_sys; s0 += m) {
+        int64_t nf = 0, part = 0;
+        for (m = 0; m < chunk && s0 + m < n_sys; ++m) {
+            const int64_t s = s0 + m, nsw = nswim ? nswim[s] : 1;
+            if (tiles && forward_tpl(dtype, N[s], (int)(N[s] * nsw), run.eps_over_ds) < 0) {
+                part += TilePlan::part_bytes(N[s] * nsw);
+                if (m > 0 && part > FWD_PART_BYTES) break;
+            }
+            nf += nsw;
+        }
         TRY(forward_chunk(c, dtype, m, N + s0, nswim ? nswim + s0 : nullptr, params_dev + f0 * SWIM_NPARAM, run, call,
                           (char*)obs + (size_t)f0 * run.n_obs * 2 * es, (char*)speed + (size_t)f0 * es, status + s0,
                           steps_done ? steps_done + s0 : nullptr, st));
@@ -1227,10 +1247,15 @@ int swim_pair_velocity(swim_ctx* c, int32_t dtype, int64_t n_sys, const int64_t*
     // (chunks: the tables' memory, and the launches' limit of 2^32 threads)
     const int64_t chunk =
         dtype == SWIM_F32 || all_direct(c, dtype, n_sys, sys_off, alpha) ? FWD_CHUNK : tab64_chunk(c, n_sys);
-    if (n_sys <= chunk) return pair_velocity_chunk(c, dtype, n_sys, sys_off, alpha, eps, x, y, fx, fy, ux, uy, st);
-    std::vector<int64_t> off(chunk + 1);
-    for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
-        const int64_t m = std::min(chunk, n_sys - s0);
+    std::vector<int64_t> off;
+    for (int64_t s0 = 0, m; s0 < n_sys; s0 += m) {
+        int64_t blocks = 0;
+        for (m = 0; m < chunk && s0 + m < n_sys; ++m) {
+            blocks += (sys_off[s0 + m + 1] - sys_off[s0 + m] + 63) / 64;
+            if (m > 0 && blocks > VEL_BLOCKS) break;
+        }
+        if (m == n_sys) return pair_velocity_chunk(c, dtype, n_sys, sys_off, alpha, eps, x, y, fx, fy, ux, uy, st);
+        off.resize(m + 1);
         for (int64_t s = 0; s <= m; ++s) off[s] = sys_off[s0 + s] - sys_off[s0];
         const size_t o = (size_t)sys_off[s0] * (dtype == SWIM_F32 ? 4 : 8);
         TRY(pair_velocity_chunk(c, dtype, m, off.data(), alpha + s0, eps + s0, (const char*)x + o, (const char*)y + o,
@@ -1496,21 +1521,20 @@ SpermShape sperm_geometry(const swim_sperm_shape& sh)
 // the launch sequence of a (checked) sperm run on stream st
 int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_sperm_shape& sh,
                        const double* sys_params, const double* swim_params, int32_t steps, double dt,
-                       int32_t obs_every, void* head, void* tail, int32_t* status, hipStream_t st)
+                       int32_t obs_every, void* head, void* tail, int32_t* status, hipStream_t st, int64_t as_n = 0)
 {
     if (n_sys == 0) return SWIM_OK;
-    if (dtype == SWIM_F64) {
-        const int64_t chunk = tab64_chunk(c, n_sys);
+    if (!as_n) {
+        // chunks as in forward runs, with the whole call's waves per system (as_n)
+        const int64_t chunk = dtype == SWIM_F32 ? FWD_CHUNK : tab64_chunk(c, n_sys);
         const int64_t nobs1 = (obs_every > 0 ? steps / obs_every : 0) + 1;
-        if (chunk < n_sys) {
-            for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
-                const size_t o = (size_t)s0 * sh.n_swim * nobs1 * 2 * 8;
-                TRY(sperm_forward_impl(c, dtype, std::min(chunk, n_sys - s0), sh, sys_params + SWIM_SP_NPARAM * s0,
-                                       swim_params + (size_t)3 * sh.n_swim * s0, steps, dt, obs_every,
-                                       (char*)head + o, (char*)tail + o, status + s0, st));
-            }
-            return SWIM_OK;
+        for (int64_t s0 = 0; s0 < n_sys; s0 += chunk) {
+            const size_t o = (size_t)s0 * sh.n_swim * nobs1 * 2 * (dtype == SWIM_F32 ? 4 : 8);
+            TRY(sperm_forward_impl(c, dtype, std::min(chunk, n_sys - s0), sh, sys_params + SWIM_SP_NPARAM * s0,
+                                   swim_params + (size_t)3 * sh.n_swim * s0, steps, dt, obs_every,
+                                   (char*)head + o, (char*)tail + o, status + s0, st, n_sys));
         }
+        return SWIM_OK;
     }
     const SpermShape g = sperm_geometry(sh);
     SpermRun r{};
@@ -1532,7 +1556,7 @@ int sperm_forward_impl(swim_ctx* c, int32_t dtype, int64_t n_sys, const swim_spe
     int wps = 8;
     if (dtype == SWIM_F32) {
         const int64_t waves = (tpl <= 2 ? 16 : 8) * (int64_t)c->num_cu;
-        wps = n_sys * 8 <= waves ? 8 : n_sys * 4 <= waves ? 4 : 2;
+        wps = as_n * 8 <= waves ? 8 : as_n * 4 <= waves ? 4 : 2;
     }
     if (c->opt_wps == 2 || c->opt_wps == 4 || c->opt_wps == 8) wps = c->opt_wps;
     void *sysc, *sysc64;

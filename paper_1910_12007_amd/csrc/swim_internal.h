@@ -46,6 +46,12 @@ struct Run {
 // (dtype 0 also writes the FP64 constants into sysc64, for the kernel tables)
 // blob: 0 the kernel reading's blob, 1 the paper's blob (closed forms at
 // alpha = 0, quadrature for alpha > 0)
+// whether a launch fits: a grid of 2^32 threads and more is cut short without an
+// error
+inline bool grid_fits(int64_t blocks, int threads)
+{
+    return blocks <= 0x7FFFFFFF && blocks * threads < ((int64_t)1 << 32);
+}
 hipError_t launch_sysconst_batch(int dtype, int64_t n_sys, const int64_t* sw_off, const int32_t* npt,
                                  const double* params, double eps_over_ds, void* sysc, void* sysc64,
                                  int32_t* status, int blob, hipStream_t st);

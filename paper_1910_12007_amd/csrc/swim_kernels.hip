@@ -1954,6 +1954,7 @@ hipError_t launch_sysconst_batch(int dtype, int64_t n_sys, const int64_t* sw_off
                                  int32_t* status, int blob, hipStream_t st)
 {
     if (n_sys <= 0) return hipSuccess;
+    if (!grid_fits(n_sys, 64)) return hipErrorInvalidConfiguration;
     if (dtype == 0)
         hipLaunchKernelGGL(k_sysconst_batch<float>, dim3((unsigned)n_sys), dim3(64), 0, st, sw_off, npt, params,
                            eps_over_ds, (SysConst<float>*)sysc, (SysConst<double>*)sysc64, status, blob);
@@ -1967,6 +1968,7 @@ hipError_t launch_sysconst(int dtype, int64_t n_sys, const double* alpha, const 
                            void* sysc64, int blob, hipStream_t st)
 {
     if (n_sys <= 0) return hipSuccess;
+    if (!grid_fits(n_sys, 64)) return hipErrorInvalidConfiguration;
     if (dtype == 0)
         hipLaunchKernelGGL(k_sysconst<float>, dim3((unsigned)n_sys), dim3(64), 0, st, alpha, eps,
                            (SysConst<float>*)sysc, (SysConst<double>*)sysc64, blob);
@@ -1982,6 +1984,7 @@ hipError_t launch_table_build(int dtype, int64_t s0, int64_t n, const void* sysc
                               const int64_t* pt_off)
 {
     if (n <= 0) return hipSuccess;
+    if (!grid_fits(n, PB_BLOCK) || !grid_fits(n * TAB_WAVES, 64)) return hipErrorInvalidConfiguration;
     if (dtype == 1)
         hipLaunchKernelGGL(k_table_build_pb<9>, dim3((unsigned)n), dim3(PB_BLOCK), 0, st, s0,
                            (const SysConst<double>*)sysc64, tab, pt_off);
@@ -2006,6 +2009,7 @@ hipError_t launch_pair_velocity(int dtype, int64_t n_sys, int64_t nb, const int6
                                 const void* fy, void* ux, void* uy, hipStream_t st)
 {
     if (nb <= 0) return hipSuccess;
+    if (!grid_fits(nb, 64 * VEL_WAVES)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)nb), block(64 * VEL_WAVES);
     if (dtype == 0)
         hipLaunchKernelGGL(k_pair_velocity<float>, grid, block, 0, st, n_sys, blk0, off, (const SysConst<float>*)sysc,
@@ -2023,6 +2027,7 @@ hipError_t launch_direct_velocity(int64_t n_sys, int64_t nb, const int64_t* blk0
                                   hipStream_t st)
 {
     if (nb <= 0) return hipSuccess;
+    if (!grid_fits(nb, 64)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_direct_velocity, dim3((unsigned)nb), dim3(64), 0, st, n_sys, blk0, off,
                        (const SysConst<double>*)sysc, (const double*)x, (const double*)y, (const double*)fx,
                        (const double*)fy, (double*)ux, (double*)uy);
@@ -2034,6 +2039,7 @@ hipError_t launch_ordered_velocity(int64_t n_sys, int64_t nb, const int64_t* blk
                                    void* ux, void* uy, hipStream_t st)
 {
     if (nb <= 0) return hipSuccess;
+    if (!grid_fits(nb, 64 * VEL_WAVES)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_ordered_velocity, dim3((unsigned)nb), dim3(64 * VEL_WAVES), 0, st, n_sys, blk0, off,
                        (const SysConst<float>*)sysc, (const TabSys*)tab, (const float*)x, (const float*)y,
                        (const float*)fx, (const float*)fy, (float*)ux, (float*)uy);
@@ -2057,6 +2063,7 @@ hipError_t launch_tile_velocity(const BigTiles& bt, const void* sysc, const void
                                 const void* fx, const void* fy, void* ux, void* uy, hipStream_t st)
 {
     if (bt.n_big <= 0) return hipSuccess;
+    if (!grid_fits(bt.n_pairs, 256) || !grid_fits(bt.n_tiles, 256)) return hipErrorInvalidConfiguration;
     hipError_t e = tile_prepare<true>();
     if (e != hipSuccess) return e;
     const SysConst<float>* C = (const SysConst<float>*)sysc;
@@ -2299,6 +2306,7 @@ hipError_t launch_big_sym_step(const BigTiles& bt, const Batch& b, const BigStat
                                int32_t* status, int32_t* steps_done, hipStream_t st)
 {
     if (bt.n_big <= 0) return hipSuccess;
+    if (!grid_fits(bt.n_pairs, 256) || !grid_fits(bt.n_tiles, UPD_PT * UPD_SG)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_tile_pairs<false>, dim3((unsigned)bt.n_pairs), dim3(256), TileLds::total, st, bt,
                        (const SysConst<float>*)b.sysc, (const TabSys*)b.tab, (const float*)nullptr,
                        (const float*)nullptr, (const float*)nullptr, (const float*)nullptr, (const int32_t*)status);

@@ -774,6 +774,7 @@ hipError_t launch_sperm_setup(int dtype, int64_t n_sys, int32_t nsw, double eps,
                               hipStream_t st)
 {
     if (n_sys == 0) return hipSuccess;
+    if (!grid_fits(n_sys, 64)) return hipErrorInvalidConfiguration;
     const unsigned nb = (unsigned)n_sys;
     if (dtype == 0)
         hipLaunchKernelGGL(k_sperm_setup<float>, dim3(nb), dim3(64), 0, st, nsw, eps, sysp, swp,
