@@ -1,7 +1,7 @@
 """FP64 velocity sums in units 2^e times as long (positions and eps scaled, alpha
-by the inverse): u = sum H1 F + H2 (F.d) d is the same in every unit.  Powers of
-two scale exactly, so only the order-independent rounding of the far pairs' direct
-evaluation could differ: 1e-14 of the velocities' norm, 2^6 roundings."""
+by the inverse): u = sum H1 F + H2 (F.d) d is the same in every unit, and powers of
+two scale exactly.  1e-14 of the velocities' norm, 2^6 roundings, is left to the
+hardware's reciprocal estimates."""
 import numpy as np
 import pytest
 
